@@ -90,7 +90,8 @@ struct LoadInfo {
   unsigned long long total_vertex_weight;
   unsigned long long total_net_weight;
   int big_rows;       // incidence rows longer than kSmallRow
-  int pad[5];
+  unsigned max_bucket;  // most pins in one vertex range of the transpose (LoadSplit)
+  int pad[4];
 };
 
 // One load workgroup's share of the LoadInfo maxima and sums; the load folds
@@ -208,12 +209,29 @@ inline Launch single_launch(const InstDesc& d) {
   return L;
 }
 
+// The transpose by vertex ranges (hg_load.hip): the pins are split into
+// `coarse` ranges of 64 buckets, these into buckets of 2^shift vertices, and
+// one workgroup turns a bucket into finished incidence rows in LDS.
+constexpr int kPartTile = 8192;      // pins per tile of the two splits
+constexpr int kPartGrid = 512;       // persistent workgroups of the first split
+constexpr int kMaxBuckets = 8192;
+constexpr int kFinePer = 64;         // buckets per coarse range
+constexpr int kMaxCoarse = kMaxBuckets / kFinePer;
+constexpr int kMaxShift = 10;        // a bucket holds at most 2^10 vertices
+constexpr int kBucketCap = 10240;    // pins that a bucket's LDS rows hold
+struct LoadSplit {
+  int shift;      // vertices per bucket = 1 << shift; -1: sort by radix passes
+  int buckets, coarse, tiles, grid;
+};
+LoadSplit load_split(int n, long long P);
+
 struct WsLayout {
   size_t cand, touched, heavy, big, hist, overflow, thr, tilesum, ctr, info, scan, flags;
   size_t red;   // kSlots partial sums for whole-array reductions (km1)
   size_t bw_slots;   // kSlots x k_max block-weight deltas (apply), folded in by the round record
   size_t part8;      // n bytes: the partition as block ids of one byte (pin-count gathers)
   size_t lkey[2], lval, lhist, ldtot;   // load only: radix-sort buffers of the transpose
+  size_t lbase;      // load only: bucket starts and write cursors (LoadSplit)
   size_t lpart;      // load only: per-workgroup partial facts (LoadPart[kLoadGrid])
   size_t total;
   int num_tiles;

@@ -3,9 +3,10 @@
 //
 // The paper stores a hypergraph as two adjacency arrays, the pins of each net
 // and the incident nets of each vertex (section "Coarsening", subsection
-// "Contraction").  Here the second array is built on the device by a stable
-// radix sort of the (pin, net) pairs by pin, so that I(v) lists nets in
-// increasing id.
+// "Contraction").  Here the second array is built on the device, I(v) listing
+// nets in increasing id: the (pin, net) pairs are split by vertex range in two
+// passes and finished in LDS, or, where a range would not fit, stably
+// radix-sorted by pin.
 #include "hg_device.h"
 #include "hg_internal.h"
 #include "hg_sort.h"
@@ -104,9 +105,12 @@ __device__ __forceinline__ int block_max_int(int v, int* s_tmp) {
 }
 
 // Nets: increasing offsets with fixed ends (no empty net), positive weights.
+// With tile_first set, the net holding the first pin of every tile of
+// kPartTile pins is written there (tile_first[tiles] = m - 1).
 __global__ __launch_bounds__(kBlock) void k_check_nets(int m, long long P,
                                                        const long long* eptr, const int* ewgt,
-                                                       LoadInfo* info, LoadPart* part) {
+                                                       LoadInfo* info, LoadPart* part,
+                                                       int* tile_first, int tiles) {
   __shared__ long long s_tmp[kBlock / kWave];
   __shared__ int s_imax[kBlock / kWave];
   int err = 0, size = 0;
@@ -117,7 +121,15 @@ __global__ __launch_bounds__(kBlock) void k_check_nets(int m, long long P,
     if (e == 0 && s != 0) err |= kErrCsr;
     if (e == m - 1 && t != P) err |= kErrCsr;
     if (t <= s || s < 0 || t > P) err |= kErrCsr;
-    else if (t - s > size) size = (int)((t - s) > 0x7fffffffLL ? 0x7fffffff : (t - s));
+    else {
+      if (t - s > size) size = (int)((t - s) > 0x7fffffffLL ? 0x7fffffff : (t - s));
+      if (tile_first) {
+        // tiles whose first pin lies in [s, t), all below `tiles` as t <= P
+        for (long long x = (s + kPartTile - 1) / kPartTile; x * kPartTile < t; ++x)
+          tile_first[x] = (int)e;
+        if (e == m - 1) tile_first[tiles] = m - 1;
+      }
+    }
     const long long w = ewgt ? ewgt[e] : 1;
     if (w <= 0) err |= kErrWeight;
     else wsum += w;
@@ -156,8 +168,13 @@ __global__ __launch_bounds__(kBlock) void k_check_vertices(int n, const int* vwg
   }
 }
 
-// LoadInfo's maxima and sums from the workgroups' parts (one workgroup).
-__global__ __launch_bounds__(kBlock) void k_fold_load(const LoadPart* part, LoadInfo* info) {
+// LoadInfo's maxima and sums from the workgroups' parts (one workgroup).  With
+// `cbase` set it holds the pin count of every coarse range of the split and
+// `cmost` their fullest buckets': the counts become the ranges' starts
+// (cbase[coarse] = their sum) and the fullest bucket goes to LoadInfo.
+__global__ __launch_bounds__(kBlock) void k_fold_load(const LoadPart* part, LoadInfo* info,
+                                                      unsigned* cbase, const unsigned* cmost,
+                                                      int coarse) {
   __shared__ long long s_tmp[kBlock / kWave];
   __shared__ int s_imax[kBlock / kWave];
   unsigned long long tnw = 0, tvw = 0;
@@ -177,6 +194,15 @@ __global__ __launch_bounds__(kBlock) void k_fold_load(const LoadPart* part, Load
   mvw = block_max_int(mvw, s_imax);
   md = block_max_int(md, s_imax);
   miw = block_max_int(miw, s_imax);
+  if (cbase) {
+    const int c = threadIdx.x;                          // coarse <= kMaxCoarse < kBlock
+    const long long mine = c < coarse ? cbase[c] : 0;
+    long long tot;
+    const long long at = block_excl_scan64(mine, s_tmp, &tot);
+    if (c <= coarse) cbase[c] = (unsigned)at;
+    const int most = block_max_int(c < coarse ? (int)cmost[c] : 0, s_imax);
+    if (c == 0) info->max_bucket = (unsigned)most;
+  }
   if (threadIdx.x == 0) {
     info->total_net_weight = tnw;
     info->total_vertex_weight = tvw;
@@ -211,6 +237,613 @@ static SortPass first_load_pass(hg_graph_s* g) {
   return SP;
 }
 
+// ------------------------------------------------------------------ vertex ranges
+// The transpose by vertex ranges.  A pass of the radix sort moves 8-byte pairs
+// in runs of about 32 and needs its own digit count; three of them, the pair
+// expansion and the row starts took 1.36 ms on a netlist of 4M cells and 56.5M
+// pins, for the 0.5 GB that the transpose has to read and write.  Here
+//   1. one count of the pins per bucket (a range of 2^shift vertices) and
+//      workgroup, which is also the pins' range check,
+//   2. a split into coarse ranges of 64 buckets, the nets found on the way,
+//   3. a split of every coarse range into its buckets; what is left of a pin
+//      fits 16 bits,
+//   4. per bucket one workgroup that places the nets in their rows in LDS,
+//      sorts every row and writes row starts and rows.
+// The splits need not be stable (rows are sorted last), so a pin's place in
+// its tile is one LDS atomic, and the workgroups of the second split reserve
+// their output by one global atomic per bucket and tile.  Rows are sets
+// sorted by net id, so nothing depends on the order of arrival.
+// Measured (kernels of one load): netlist 4M cells, 56.5M pins 1420 -> 690 us
+// (count 64, coarse split 198, fine split 209, rows 142; the 2.1 GB they move
+// take 410 us at a large copy's 5.1 TB/s), matrix 1M x 1M, 10M pins 287 ->
+// 158 us.
+
+constexpr int kPartBlock = 1024;                       // threads of the split kernels
+constexpr int kPartPer = kPartTile / kPartBlock;       // pins per thread and tile
+constexpr int kRowsBlock = 512;                        // threads of a bucket's workgroup
+constexpr int kRowsWaves = kRowsBlock / kWave;
+
+// Buckets of at most 8192 pins on average (the LDS rows take kBucketCap, so
+// even ranges fit; the count decides), as long as the ranges stay few enough
+// for the tables: n > 8192 * 1024, or more than 8192 pins on average in the
+// smallest allowed range, go to the radix sort, and so do hypergraphs whose
+// count table would not fit the scratch of one word per pin (far fewer pins
+// than vertices).
+LoadSplit load_split(int n, long long P) {
+  LoadSplit L;
+  L.shift = -1;
+  L.buckets = L.coarse = L.tiles = L.grid = 0;
+  int shift = 0;
+  while (shift < kMaxShift && (((long long)n - 1) >> shift) + 1 > kMaxBuckets) ++shift;
+  if ((((long long)n - 1) >> shift) + 1 > kMaxBuckets) return L;
+  if ((P << shift) / n > kPartTile) return L;
+  // wider ranges while they stay light and either leave two workgroups per
+  // compute unit or are not worth a workgroup yet
+  while (shift < 9 && (P << (shift + 1)) / n <= kPartTile &&
+         ((n >> (shift + 1)) >= 512 || (P << shift) / n < 512))
+    ++shift;
+  const int buckets = ((n - 1) >> shift) + 1;
+  const int tiles = (int)((P + kPartTile - 1) / kPartTile);
+  const int grid = tiles < kPartGrid ? tiles : kPartGrid;
+  if ((long long)grid * buckets > P) return L;
+  L.shift = shift;
+  L.buckets = buckets;
+  L.coarse = (buckets + kFinePer - 1) / kFinePer;
+  L.tiles = tiles;
+  L.grid = grid;
+  return L;
+}
+
+struct Split {
+  int n, m, P;
+  LoadSplit L;
+  const int* pins;
+  const long long* eptr;
+  int* tile_first;        // [tiles + 1]
+  unsigned* counts;       // [grid][buckets]
+  unsigned* ccounts;      // [grid][coarse]: pins per range; then, of the workgroups before
+  unsigned* cbase;        // [coarse + 1]: first pin of every range
+  unsigned* cmost;        // [coarse]: pins of the range's fullest bucket
+  unsigned* rel;          // [buckets]: first pin of every bucket in its range
+  unsigned* cursor;       // [buckets]: write positions of the second split, likewise
+  unsigned* cpin;         // [P]: pins by coarse range
+  int* cnet;              // [P]
+  unsigned short* low;    // [P]: pin & (2^shift - 1) by bucket
+  int* val;               // [P]: the nets, by bucket (in the rows' own array)
+  LoadInfo* info;
+  long long* vptr;
+};
+
+// Tiles [first, last) of persistent workgroup w.
+__device__ __forceinline__ void split_tiles(const Split& S, int w, int& first, int& last) {
+  const int per = S.L.tiles / S.L.grid, rem = S.L.tiles % S.L.grid;
+  first = w * per + (w < rem ? w : rem);
+  last = first + per + (w < rem ? 1 : 0);
+}
+
+// Pins per bucket of this workgroup's tiles, and the range check.
+__global__ __launch_bounds__(kPartBlock) void k_split_count(Split S) {
+  __shared__ unsigned s_cnt[kMaxBuckets];
+  for (int i = threadIdx.x; i < S.L.buckets; i += kPartBlock) s_cnt[i] = 0;
+  __syncthreads();
+  int first, last;
+  split_tiles(S, blockIdx.x, first, last);
+  bool bad = false;
+  for (int t = first; t < last; ++t) {
+    const long long base = (long long)t * kPartTile;
+    unsigned v[kPartPer];
+#pragma unroll
+    for (int r = 0; r < kPartPer; ++r) {
+      const long long i = base + r * kPartBlock + threadIdx.x;
+      v[r] = i < S.P ? (unsigned)S.pins[i] : 0xffffffffu;
+    }
+#pragma unroll
+    for (int r = 0; r < kPartPer; ++r) {
+      if (v[r] < (unsigned)S.n)
+        atomicAdd(&s_cnt[v[r] >> S.L.shift], 1u);
+      else
+        bad |= base + r * kPartBlock + threadIdx.x < S.P;
+    }
+  }
+  if (bad) atomicOr(&S.info->err, kErrPin);
+  __syncthreads();
+  unsigned* row = S.counts + (size_t)blockIdx.x * S.L.buckets;
+  for (int i = threadIdx.x; i < S.L.buckets; i += kPartBlock) row[i] = s_cnt[i];
+  const int lane = lane_id();
+  for (int c = threadIdx.x / kWave; c < S.L.coarse; c += kPartBlock / kWave) {
+    const int i = c * kFinePer + lane;                 // kFinePer == kWave
+    const unsigned all = wave_sum(i < S.L.buckets ? s_cnt[i] : 0u);
+    if (lane == 0) S.ccounts[(size_t)blockIdx.x * S.L.coarse + c] = all;
+  }
+}
+static_assert(kFinePer == kWave, "a wavefront sums a range's buckets");
+
+// One workgroup per coarse range: its buckets' starts, the range's total (to
+// cbase, which k_fold_load turns into starts), and for every counting
+// workgroup the pins of the range that the ones before it hold.
+constexpr int kSplitScanBlock = 1024;
+
+__global__ __launch_bounds__(kSplitScanBlock) void k_split_scan(Split S) {
+  constexpr int kRowsAt = kSplitScanBlock / kWave;     // table rows read at a time
+  constexpr int kRows = kPartGrid / kRowsAt;
+  __shared__ unsigned s_col[kRowsAt][kWave];
+  const int wv = threadIdx.x / kWave, lane = lane_id();
+  const int col = blockIdx.x * kFinePer + lane;
+  const bool in = col < S.L.buckets;
+  unsigned c[kRows];                                   // every row requested before the first wait
+#pragma unroll
+  for (int q = 0; q < kRows; ++q) {
+    const int w = wv + q * kRowsAt;
+    c[q] = in && w < S.L.grid ? S.counts[(size_t)w * S.L.buckets + col] : 0u;
+  }
+  unsigned sum = 0;
+#pragma unroll
+  for (int q = 0; q < kRows; ++q) sum += c[q];
+  s_col[wv][lane] = sum;
+  __syncthreads();
+  if (wv == 0) {
+    unsigned tot = 0;
+    for (int q = 0; q < kRowsAt; ++q) tot += s_col[q][lane];
+    const unsigned before = (unsigned)wave_incl_scan((int)tot) - tot;
+    if (in) S.rel[col] = S.cursor[col] = before;
+    const unsigned most = (unsigned)wave_max((int)tot);
+    if (lane == kWave - 1) {
+      S.cbase[blockIdx.x] = before + tot;
+      S.cmost[blockIdx.x] = most;
+    }
+  } else if (wv == 1) {
+    unsigned x[kPartGrid / kWave];
+#pragma unroll
+    for (int q = 0; q < kPartGrid / kWave; ++q) {
+      const int w = q * kWave + lane;
+      x[q] = w < S.L.grid ? S.ccounts[(size_t)w * S.L.coarse + blockIdx.x] : 0u;
+    }
+    unsigned carry = 0;
+#pragma unroll
+    for (int q = 0; q < kPartGrid / kWave; ++q) {
+      const int w = q * kWave + lane;
+      const unsigned incl = (unsigned)wave_incl_scan((int)x[q]);
+      if (w < S.L.grid) S.ccounts[(size_t)w * S.L.coarse + blockIdx.x] = carry + incl - x[q];
+      carry += (unsigned)__shfl((int)incl, kWave - 1);
+    }
+  }
+}
+
+// First pin of bucket b, and of the one after it.
+__device__ __forceinline__ unsigned bucket_start(const Split& S, int b) {
+  return S.cbase[b / kFinePer] + S.rel[b];
+}
+__device__ __forceinline__ unsigned bucket_end(const Split& S, int b) {
+  return b + 1 == S.L.buckets || (b + 1) % kFinePer == 0 ? S.cbase[b / kFinePer + 1]
+                                                        : bucket_start(S, b + 1);
+}
+
+// Exclusive prefix of cnt[0 .. 128) into off, by the first wave (two entries
+// per lane); returns nothing, the caller synchronizes.
+__device__ __forceinline__ void scan_counts(const unsigned* cnt, unsigned* off, int count) {
+  if (threadIdx.x < kWave) {
+    const int i0 = 2 * threadIdx.x;
+    const int a = i0 < count ? (int)cnt[i0] : 0, b = i0 + 1 < count ? (int)cnt[i0 + 1] : 0;
+    const int incl = wave_incl_scan(a + b);
+    if (i0 < count) off[i0] = (unsigned)(incl - a - b);
+    if (i0 + 1 < count) off[i0 + 1] = (unsigned)(incl - b);
+  }
+}
+
+// Place of this lane's item among the items of its key: one LDS atomic per
+// run of equal keys in neighbouring lanes (the pins of a net, listed in
+// order, mostly fall in one range: with one atomic per lane a wavefront's
+// adds to that range's word took 64 turns).  Every lane of the wave calls.
+__device__ __forceinline__ unsigned run_rank(unsigned* cnt, unsigned key, bool live) {
+  const int lane = lane_id();
+  const unsigned k = live ? key : 0xffffffffu;
+  const unsigned prev = (unsigned)__shfl_up((int)k, 1);
+  const unsigned long long heads = __ballot(lane == 0 || k != prev);
+  const unsigned long long upto = ~0ull >> (kWave - 1 - lane);
+  const int head = kWave - 1 - __clzll((long long)(heads & upto));
+  const unsigned long long later = heads & ~upto;
+  unsigned at = 0;      // netlist: coarse split 335 -> 307, fine split 256 -> 197 us
+  if (live && head == lane) {
+    const int end = later ? __ffsll((long long)later) - 1 : kWave;
+    at = atomicAdd(&cnt[k], (unsigned)(end - lane));
+  }
+  return (unsigned)__shfl((int)at, head) + (unsigned)(lane - head);
+}
+
+// First split: (pin, net) pairs by coarse range.  The pairs are staged in LDS
+// in range order (pins, then nets in the same words) so that a tile's run of
+// a range leaves as consecutive addresses.
+struct CoarseLds {
+  unsigned stage[kPartTile];
+  unsigned long long start[kPartTile / 64];   // one bit per net start
+  unsigned before[kPartTile / 64];            // net starts before the word
+  unsigned cur[kMaxCoarse], cnt[kMaxCoarse], off[kMaxCoarse];
+};
+
+// One tile of `here` pins (FULL: kPartTile; without the bounds tests the
+// registers of eight pins fit and the netlist's split takes 198, not 307 us).
+template <bool FULL>
+__device__ __forceinline__ void split_coarse_tile(const Split& S, CoarseLds& M, int t, int here) {
+  const int C = S.L.coarse, shift = S.L.shift + 6;         // 64 = kFinePer buckets a range
+  const long long base = (long long)t * kPartTile;
+  const int* pins = S.pins + base;
+  const int wv = threadIdx.x / kWave, lane = lane_id();
+  unsigned pin[kPartPer];
+#pragma unroll
+  for (int r = 0; r < kPartPer; ++r) {
+    const int i = r * kPartBlock + threadIdx.x;
+    pin[r] = FULL || i < here ? (unsigned)pins[i] : 0u;
+  }
+  const int net0 = S.tile_first[t], net1 = S.tile_first[t + 1];
+  for (int c = threadIdx.x; c < C; c += kPartBlock) M.cnt[c] = 0;
+  if (threadIdx.x < kPartTile / 64) M.start[threadIdx.x] = 0;
+  __syncthreads();
+  // nets (net0, net1] are the ones that can start inside the tile
+  for (int e = net0 + 1 + (int)threadIdx.x; e <= net1; e += kPartBlock) {
+    const long long at = S.eptr[e] - base;                 // > 0; past the tile for net1 only
+    if (at < here) atomicOr(&M.start[at >> 6], 1ull << (at & 63));
+  }
+  unsigned slot[kPartPer];
+#pragma unroll
+  for (int r = 0; r < kPartPer; ++r)
+    slot[r] = run_rank(M.cnt, pin[r] >> shift, FULL || r * kPartBlock + (int)threadIdx.x < here);
+  __syncthreads();
+  scan_counts(M.cnt, M.off, C);
+  if (wv == 1) {
+    const int c0 = __popcll(M.start[2 * lane]), c1 = __popcll(M.start[2 * lane + 1]);
+    const int incl = wave_incl_scan(c0 + c1);
+    M.before[2 * lane] = (unsigned)(incl - c0 - c1);
+    M.before[2 * lane + 1] = (unsigned)(incl - c1);
+  }
+  __syncthreads();
+#pragma unroll
+  for (int r = 0; r < kPartPer; ++r) {
+    if (FULL || r * kPartBlock + (int)threadIdx.x < here) {
+      slot[r] += M.off[pin[r] >> shift];
+      M.stage[slot[r]] = pin[r];
+    }
+  }
+  __syncthreads();
+  unsigned dst[kPartPer];
+#pragma unroll
+  for (int r = 0; r < kPartPer; ++r) {
+    const int j = r * kPartBlock + threadIdx.x;
+    dst[r] = 0;
+    if (FULL || j < here) {
+      const unsigned v = M.stage[j], c = v >> shift;
+      dst[r] = M.cur[c] + ((unsigned)j - M.off[c]);
+      S.cpin[dst[r]] = v;
+    }
+  }
+  __syncthreads();
+  const unsigned long long upto = ~0ull >> (kWave - 1 - lane);
+#pragma unroll
+  for (int r = 0; r < kPartPer; ++r) {
+    if (FULL || r * kPartBlock + (int)threadIdx.x < here) {
+      const int word = r * (kPartBlock / kWave) + wv;      // this item's bit is the lane's
+      M.stage[slot[r]] = (unsigned)net0 + M.before[word] + (unsigned)__popcll(M.start[word] & upto);
+    }
+  }
+  __syncthreads();
+#pragma unroll
+  for (int r = 0; r < kPartPer; ++r) {
+    const int j = r * kPartBlock + threadIdx.x;
+    if (FULL || j < here) S.cnet[dst[r]] = (int)M.stage[j];
+  }
+  for (int c = threadIdx.x; c < C; c += kPartBlock) M.cur[c] += M.cnt[c];
+  __syncthreads();
+}
+
+__global__ __launch_bounds__(kPartBlock, 8) void k_split_coarse(Split S) {
+  __shared__ CoarseLds M;
+  for (int c = threadIdx.x; c < S.L.coarse; c += kPartBlock)
+    M.cur[c] = S.cbase[c] + S.ccounts[(size_t)blockIdx.x * S.L.coarse + c];
+  int first, last;
+  split_tiles(S, blockIdx.x, first, last);
+  for (int t = first; t < last; ++t) {
+    const long long left = S.P - (long long)t * kPartTile;
+    if (left >= kPartTile)
+      split_coarse_tile<true>(S, M, t, kPartTile);
+    else
+      split_coarse_tile<false>(S, M, t, (int)left);
+  }
+}
+
+// A tile of `here` pairs (FULL: kPartTile, no bounds tests) from `from` on
+// into the buckets of coarse range c, whose pins begin at `start`.
+struct FineLds {
+  unsigned stage[kPartTile];
+  unsigned tiles[kMaxCoarse], first[kMaxCoarse];
+  unsigned cnt[kFinePer], off[kFinePer], out[kFinePer];
+};
+
+template <bool FULL>
+__device__ __forceinline__ void split_fine_tile(const Split& S, FineLds& M, int c, unsigned start,
+                                                unsigned from, int here) {
+  const int shift = S.L.shift;
+  const unsigned* cpin = S.cpin + from;
+  const int* cnet = S.cnet + from;
+  unsigned pin[kPartPer], slot[kPartPer];
+  int net[kPartPer];
+#pragma unroll
+  for (int r = 0; r < kPartPer; ++r) {
+    const int i = r * kPartBlock + threadIdx.x;
+    pin[r] = FULL || i < here ? cpin[i] : 0u;
+  }
+#pragma unroll
+  for (int r = 0; r < kPartPer; ++r) {
+    const int i = r * kPartBlock + threadIdx.x;
+    net[r] = FULL || i < here ? cnet[i] : 0;
+  }
+#pragma unroll
+  for (int r = 0; r < kPartPer; ++r) {
+    slot[r] = run_rank(M.cnt, (pin[r] >> shift) & (kFinePer - 1),
+                       FULL || r * kPartBlock + (int)threadIdx.x < here);
+  }
+  __syncthreads();
+  scan_counts(M.cnt, M.off, kFinePer);
+  if (threadIdx.x >= kWave && threadIdx.x < kWave + kFinePer) {
+    const int f = threadIdx.x - kWave;
+    const unsigned k = M.cnt[f];
+    M.out[f] = k ? start + atomicAdd(&S.cursor[c * kFinePer + f], k) : 0u;
+  }
+  __syncthreads();
+#pragma unroll
+  for (int r = 0; r < kPartPer; ++r) {
+    if (FULL || r * kPartBlock + (int)threadIdx.x < here) {
+      slot[r] += M.off[(pin[r] >> shift) & (kFinePer - 1)];
+      M.stage[slot[r]] = pin[r];
+    }
+  }
+  __syncthreads();
+  unsigned dst[kPartPer];
+  const unsigned mask = (1u << shift) - 1u;
+#pragma unroll
+  for (int r = 0; r < kPartPer; ++r) {
+    const int j = r * kPartBlock + threadIdx.x;
+    dst[r] = 0;
+    if (FULL || j < here) {
+      const unsigned v = M.stage[j], f = (v >> shift) & (kFinePer - 1);
+      dst[r] = M.out[f] + ((unsigned)j - M.off[f]);
+      S.low[dst[r]] = (unsigned short)(v & mask);
+    }
+  }
+  __syncthreads();
+#pragma unroll
+  for (int r = 0; r < kPartPer; ++r)
+    if (FULL || r * kPartBlock + (int)threadIdx.x < here) M.stage[slot[r]] = (unsigned)net[r];
+  __syncthreads();
+#pragma unroll
+  for (int r = 0; r < kPartPer; ++r) {
+    const int j = r * kPartBlock + threadIdx.x;
+    if (FULL || j < here) S.val[dst[r]] = (int)M.stage[j];
+  }
+}
+
+// Second split: a tile of one coarse range into the range's buckets.  The
+// grid covers the tiles of all ranges (each range's last tile may be short).
+__global__ __launch_bounds__(kPartBlock, 8) void k_split_fine(Split S) {
+  __shared__ FineLds M;
+  const int C = S.L.coarse;
+  for (int c = threadIdx.x; c < C; c += kPartBlock)
+    M.tiles[c] = (S.cbase[c + 1] - S.cbase[c] + kPartTile - 1) / kPartTile;
+  if (threadIdx.x < kFinePer) M.cnt[threadIdx.x] = 0;
+  __syncthreads();
+  scan_counts(M.tiles, M.first, C);
+  __syncthreads();
+  const unsigned tile = blockIdx.x;
+  if (tile >= M.first[C - 1] + M.tiles[C - 1]) return;     // whole workgroup
+  int lo = 0, hi = C - 1;                                  // the last range starting at or before
+  while (lo < hi) {
+    const int mid = (lo + hi + 1) >> 1;
+    if (M.first[mid] <= tile) lo = mid; else hi = mid - 1;
+  }
+  // ranges without a tile share their start with the next one, which the
+  // search prefers, so `lo` owns the tile
+  const unsigned start = S.cbase[lo], end = S.cbase[lo + 1];
+  const unsigned from = start + (tile - M.first[lo]) * kPartTile;
+  const int here = end - from < (unsigned)kPartTile ? (int)(end - from) : kPartTile;
+  if (here == kPartTile)
+    split_fine_tile<true>(S, M, lo, start, from, here);
+  else
+    split_fine_tile<false>(S, M, lo, start, from, here);
+}
+
+// Ascending sort of N (16 or 32) registers by Batcher's odd-even merge network.
+template <int N>
+__device__ __forceinline__ void sort_regs(int (&x)[N]) {
+#pragma unroll
+  for (int p = 1; p < N; p <<= 1) {
+#pragma unroll
+    for (int q = p; q >= 1; q >>= 1) {
+#pragma unroll
+      for (int j = q % p; j + q < N; j += 2 * q) {
+#pragma unroll
+        for (int i = 0; i < q; ++i) {
+          if (i + j + q < N && (i + j) / (2 * p) == (i + j + q) / (2 * p)) {
+            const int a = x[i + j], b = x[i + j + q];
+            x[i + j] = a < b ? a : b;
+            x[i + j + q] = a < b ? b : a;
+          }
+        }
+      }
+    }
+  }
+}
+
+// A row of d <= N nets in LDS sorted by one thread; true if a net repeats.
+template <int N>
+__device__ __forceinline__ bool sort_row(int* row, int d) {
+  int x[N];
+#pragma unroll
+  for (int i = 0; i < N; ++i) x[i] = i < d ? row[i] : 0x7fffffff;
+  sort_regs<N>(x);
+  bool dup = false;
+#pragma unroll
+  for (int i = 0; i < N; ++i) {
+    if (i < d) row[i] = x[i];
+    if (i > 0) dup |= i < d && x[i] == x[i - 1];
+  }
+  return dup;
+}
+
+// One workgroup per bucket: row starts from a count of its pins per vertex,
+// the nets placed in their rows in LDS in any order, then every row sorted
+// (rows of up to 16 and of up to 32 nets by one thread in registers, each
+// kind in wavefronts of its own; rows of up to 512 by one wavefront ranking
+// its entries; longer ones by the workgroup) and the bucket written out.  A
+// vertex twice in a net shows as two equal neighbours.
+__global__ __launch_bounds__(kRowsBlock) void k_bucket_rows(Split S) {
+  constexpr int kV = 1 << kMaxShift;
+  constexpr int kVPer = kV / kRowsBlock;                   // 2
+  constexpr int kPer = kBucketCap / kRowsBlock;            // pins per thread
+  constexpr int kWaveRow = 512;                            // longest row of one wavefront
+  __shared__ int s_row[kBucketCap];
+  __shared__ unsigned s_start[kV + 1];
+  __shared__ unsigned s_cur[kV];                           // counts, then write positions
+  __shared__ unsigned short s_short[kV];                   // rows of 2..16, and 17..32 from the back
+  __shared__ unsigned short s_long[kBucketCap / 33 + 1];
+  __shared__ unsigned s_wsum[kRowsWaves];
+  __shared__ unsigned s_n16, s_n32, s_nlong;
+  const int V = 1 << S.L.shift;
+  const int b = blockIdx.x;
+  const unsigned from = bucket_start(S, b);
+  const int N = (int)(bucket_end(S, b) - from);
+  const int v0 = b << S.L.shift;
+  const int nv = S.n - v0 < V ? S.n - v0 : V;
+  for (int i = threadIdx.x; i < kV; i += kRowsBlock) s_cur[i] = 0;
+  if (threadIdx.x == 0) s_n16 = s_n32 = s_nlong = 0;
+  __syncthreads();
+  // the whole bucket requested before the first wait
+  const unsigned short* low = S.low + from;
+  int* val = S.val + from;
+  unsigned lv[kPer];
+  int net[kPer];
+#pragma unroll
+  for (int q = 0; q < kPer; ++q) {
+    const int i = q * kRowsBlock + threadIdx.x;
+    lv[q] = i < N ? low[i] : 0u;
+  }
+#pragma unroll
+  for (int q = 0; q < kPer; ++q) {
+    const int i = q * kRowsBlock + threadIdx.x;
+    net[q] = i < N ? val[i] : 0;
+  }
+#pragma unroll
+  for (int q = 0; q < kPer; ++q)
+    if (q * kRowsBlock + (int)threadIdx.x < N) atomicAdd(&s_cur[lv[q]], 1u);
+  __syncthreads();
+  const int wv = threadIdx.x / kWave, lane = lane_id();
+  {
+    const int i0 = kVPer * threadIdx.x;
+    const unsigned a = s_cur[i0], c = s_cur[i0 + 1];
+    const int incl = wave_incl_scan((int)(a + c));
+    if (lane == kWave - 1) s_wsum[wv] = (unsigned)incl;
+    __syncthreads();
+    unsigned off = 0;
+    for (int w = 0; w < kRowsWaves; ++w) off += w < wv ? s_wsum[w] : 0u;
+    const unsigned st = off + (unsigned)incl - a - c;
+    s_start[i0] = s_cur[i0] = st;
+    s_start[i0 + 1] = s_cur[i0 + 1] = st + a;
+    if (threadIdx.x == kRowsBlock - 1) s_start[kV] = st + a + c;
+    if (i0 < nv) S.vptr[v0 + i0] = (long long)from + st;
+    if (i0 + 1 < nv) S.vptr[v0 + i0 + 1] = (long long)from + st + a;
+    if (v0 + nv == S.n && threadIdx.x == 0) S.vptr[S.n] = S.P;
+    // rows by length: one LDS slot each
+#pragma unroll
+    for (int q = 0; q < kVPer; ++q) {
+      const unsigned d = q ? c : a;
+      const int r = i0 + q;
+      if (d > 32) s_long[atomicAdd(&s_nlong, 1u)] = (unsigned short)r;
+      else if (d > 16) s_short[kV - 1 - atomicAdd(&s_n32, 1u)] = (unsigned short)r;
+      else if (d > 1) s_short[atomicAdd(&s_n16, 1u)] = (unsigned short)r;
+    }
+  }
+  __syncthreads();
+#pragma unroll
+  for (int q = 0; q < kPer; ++q)
+    if (q * kRowsBlock + (int)threadIdx.x < N) s_row[atomicAdd(&s_cur[lv[q]], 1u)] = net[q];
+  __syncthreads();
+  bool dup = false;
+  const int n16 = (int)s_n16, n32 = (int)s_n32, nlong = (int)s_nlong;
+  for (int i = threadIdx.x; i < n16; i += kRowsBlock) {
+    const int r = s_short[i];
+    dup |= sort_row<16>(s_row + s_start[r], (int)(s_start[r + 1] - s_start[r]));
+  }
+  for (int i = threadIdx.x; i < n32; i += kRowsBlock) {
+    const int r = s_short[kV - 1 - i];
+    dup |= sort_row<32>(s_row + s_start[r], (int)(s_start[r + 1] - s_start[r]));
+  }
+  for (int i = wv; i < nlong; i += kRowsWaves) {
+    const int r = s_long[i];
+    const int d = (int)(s_start[r + 1] - s_start[r]);
+    if (d > kWaveRow) continue;
+    int* row = s_row + s_start[r];
+    // every lane ranks its entries among the row's (equal entries by place)
+    int x[kWaveRow / kWave], rank[kWaveRow / kWave];
+#pragma unroll
+    for (int q = 0; q < kWaveRow / kWave; ++q) {
+      const int at = q * kWave + lane;
+      x[q] = at < d ? row[at] : 0x7fffffff;
+      rank[q] = 0;
+    }
+    for (int j = 0; j < d; ++j) {
+      const int y = row[j];
+#pragma unroll
+      for (int q = 0; q < kWaveRow / kWave; ++q) {
+        const int at = q * kWave + lane;
+        rank[q] += y < x[q] || (y == x[q] && j < at);
+        dup |= at < d && y == x[q] && j < at;
+      }
+    }
+    wave_lds_sync();
+#pragma unroll
+    for (int q = 0; q < kWaveRow / kWave; ++q)
+      if (q * kWave + lane < d) row[rank[q]] = x[q];
+    wave_lds_sync();
+  }
+  __syncthreads();
+  for (int i = 0; i < nlong; ++i) {                        // the same rows for every thread
+    const int r = s_long[i];
+    const int d = (int)(s_start[r + 1] - s_start[r]);
+    if (d <= kWaveRow) continue;
+    int* row = s_row + s_start[r];
+    int pow2 = 1;
+    while (pow2 < d) pow2 <<= 1;
+    bitonic_sort_block(d, pow2, [&](int j) { return row[j]; }, [&](int j, int x) { row[j] = x; });
+    for (int j = 1 + threadIdx.x; j < d; j += kRowsBlock) dup |= row[j] == row[j - 1];
+    __syncthreads();
+  }
+  if (dup) atomicOr(&S.info->err, kErrDuplicate);
+  for (int i = threadIdx.x; i < N; i += kRowsBlock) val[i] = s_row[i];
+}
+
+static Split make_split(hg_graph_s* g) {
+  Split S;
+  S.n = g->n;
+  S.m = g->m;
+  S.P = (int)g->P;
+  S.L = load_split(g->n, g->P);
+  S.pins = g->pins;
+  S.eptr = g->eptr;
+  // the radix sort's scratch: tile table and coarse offsets in its digit
+  // table, the counts where the second split later leaves the low pin bits
+  S.tile_first = (int*)(g->ws + g->lay.lhist);
+  S.ccounts = (unsigned*)(g->ws + g->lay.lhist) + S.L.tiles + 1;
+  S.counts = (unsigned*)(g->ws + g->lay.lkey[1]);
+  S.rel = (unsigned*)(g->ws + g->lay.lbase);
+  S.cursor = S.rel + S.L.buckets;
+  S.cbase = S.cursor + S.L.buckets;
+  S.cmost = S.cbase + S.L.coarse + 1;
+  S.cpin = (unsigned*)(g->ws + g->lay.lkey[0]);
+  S.cnet = (int*)(g->ws + g->lay.lval);
+  S.low = (unsigned short*)(g->ws + g->lay.lkey[1]);
+  S.val = g->vnets;
+  S.info = (LoadInfo*)(g->ws + g->lay.info);
+  S.vptr = g->vptr;
+  return S;
+}
+
 hipError_t load_check(hg_graph_s* g, hipStream_t s) {
   LoadInfo* info = (LoadInfo*)(g->ws + g->lay.info);
   LoadPart* part = (LoadPart*)(g->ws + g->lay.lpart);
@@ -219,29 +852,36 @@ hipError_t load_check(hg_graph_s* g, hipStream_t s) {
   Z.add(part, (long long)sizeof(LoadPart) * kLoadGrid);
   hipError_t e = zero_ranges(Z, s);
   if (e != hipSuccess) return e;
+  const Split S = make_split(g);
+  const bool split = S.L.shift >= 0;
   hipLaunchKernelGGL(k_check_nets, dim3(grid_cap_load(g->m)), dim3(kBlock), 0, s, g->m, g->P,
-                     g->eptr, g->ewgt, info, part);
-  // the pins' range check is the sort's first digit count, which reads every
-  // pin anyway (a pin outside [0, n) only lands in some digit's count; the
-  // build does not start unless the checks pass)
-  SortPass SP = first_load_pass(g);
-  SP.err = &info->err;
-  SP.err_bit = kErrPin;
-  SP.key_limit = (unsigned)g->n;
-  if (long_load_sort(g->P))
-    hipLaunchKernelGGL(k_sort_hist<kSortPerLong>, dim3(SP.tiles), dim3(kBlock), 0, s, SP);
-  else
-    hipLaunchKernelGGL(k_sort_hist<kSortPer>, dim3(SP.tiles), dim3(kBlock), 0, s, SP);
+                     g->eptr, g->ewgt, info, part, split ? S.tile_first : nullptr, S.L.tiles);
+  // the pins' range check rides on a count that reads every pin anyway: the
+  // buckets' or the sort's first digit count (a pin outside [0, n) only lands
+  // in some digit's count, and nothing is built unless the checks pass)
+  if (split) {
+    hipLaunchKernelGGL(k_split_count, dim3(S.L.grid), dim3(kPartBlock), 0, s, S);
+    hipLaunchKernelGGL(k_split_scan, dim3(S.L.coarse), dim3(kSplitScanBlock), 0, s, S);
+  } else {
+    SortPass SP = first_load_pass(g);
+    SP.err = &info->err;
+    SP.err_bit = kErrPin;
+    SP.key_limit = (unsigned)g->n;
+    if (long_load_sort(g->P))
+      hipLaunchKernelGGL(k_sort_hist<kSortPerLong>, dim3(SP.tiles), dim3(kBlock), 0, s, SP);
+    else
+      hipLaunchKernelGGL(k_sort_hist<kSortPer>, dim3(SP.tiles), dim3(kBlock), 0, s, SP);
+  }
   hipLaunchKernelGGL(k_check_vertices, dim3(grid_cap_load(g->n)), dim3(kBlock), 0, s, g->n,
                      g->vwgt, info, part);
-  hipLaunchKernelGGL(k_fold_load, dim3(1), dim3(kBlock), 0, s, (const LoadPart*)part, info);
+  hipLaunchKernelGGL(k_fold_load, dim3(1), dim3(kBlock), 0, s, (const LoadPart*)part, info,
+                     split ? S.cbase : nullptr, S.cmost, S.L.coarse);
   return hipGetLastError();
 }
-
 constexpr int kBigRowGrid = 256;   // workgroups striding over the long rows
 
 // ------------------------------------------------------------------ transpose
-// (pin, net) pairs in net order, stably radix-sorted by pin: the values are
+// The general path: (pin, net) pairs in net order, stably radix-sorted by pin: the values are
 // then the incidence rows, each listing its nets in increasing id, with no
 // atomics anywhere (so nothing depends on timing).  Row starts come from
 // where the sorted keys change.
@@ -419,12 +1059,10 @@ __global__ void k_big_row_facts(const long long* vptr, const int* vnets, const i
   }
 }
 
-// Builds vptr/vnets and the rows' facts (short rows one per thread, long
-// rows one per workgroup).
-hipError_t load_build(hg_graph_s* g, hipStream_t s) {
+// The transpose by radix passes over the (pin, net) pairs; `counted`: the
+// checks left the first pass's digit counts.
+static void build_by_sort(hg_graph_s* g, bool counted, hipStream_t s) {
   LoadInfo* info = (LoadInfo*)(g->ws + g->lay.info);
-  int* big = (int*)(g->ws + g->lay.big);
-  int* heavy = (int*)(g->ws + g->lay.heavy);
   const long long P = g->P;
   int passes = 0;
   for (int bits = 0; bits < 32 && (1ll << bits) < (long long)g->n; bits += 8) ++passes;
@@ -438,8 +1076,7 @@ hipError_t load_build(hg_graph_s* g, hipStream_t s) {
   const long long waves = ((long long)g->m + kWave - 1) / kWave;
   const unsigned blocks = (unsigned)((waves + kBlock / kWave - 1) / (kBlock / kWave));
   hipLaunchKernelGGL(k_pin_pairs, dim3(blocks), dim3(kBlock), 0, s, g->m, g->eptr, val[0]);
-  // the first pass reads the (validated, non-negative) pins as its keys; its
-  // digit counts were taken by the checks
+  // the first pass reads the (validated, non-negative) pins as its keys
   SortPass SP = first_load_pass(g);
   const bool long_sort = long_load_sort(P);
   for (int q = 0; q < passes; ++q) {
@@ -447,9 +1084,10 @@ hipError_t load_build(hg_graph_s* g, hipStream_t s) {
     SP.key_out = key[(q & 1) ^ 1];
     SP.val_out = val[(q & 1) ^ 1];
     SP.shift = 8 * q;
-    if (q == 0 && long_sort)
+    const bool has_counts = q == 0 && counted;
+    if (has_counts && long_sort)
       sort_pass_counted<kSortPerLong>(SP, s);
-    else if (q == 0)
+    else if (has_counts)
       sort_pass_counted(SP, s);
     else if (long_sort)
       sort_pass<kSortPerLong>(SP, s);
@@ -462,12 +1100,30 @@ hipError_t load_build(hg_graph_s* g, hipStream_t s) {
   const int vec = (((uintptr_t)skey | (uintptr_t)g->vnets) & 15) == 0;
   hipLaunchKernelGGL(k_row_starts, dim3((unsigned)((rs_threads + kBlock - 1) / kBlock)),
                      dim3(kBlock), 0, s, P, g->n, skey, (const int*)g->vnets, vec, g->vptr, info);
+}
+
+// Builds vptr/vnets (by vertex ranges when the checks counted buckets that
+// all fit a workgroup's LDS) and the rows' facts (short rows one per thread,
+// long rows one per workgroup).
+hipError_t load_build(hg_graph_s* g, hipStream_t s) {
+  LoadInfo* info = (LoadInfo*)(g->ws + g->lay.info);
+  int* big = (int*)(g->ws + g->lay.big);
+  int* heavy = (int*)(g->ws + g->lay.heavy);
+  const Split S = make_split(g);
+  if (S.L.shift >= 0 && g->info.max_bucket <= (unsigned)kBucketCap) {
+    hipLaunchKernelGGL(k_split_coarse, dim3(S.L.grid), dim3(kPartBlock), 0, s, S);
+    hipLaunchKernelGGL(k_split_fine, dim3(S.L.tiles + S.L.coarse), dim3(kPartBlock), 0, s, S);
+    hipLaunchKernelGGL(k_bucket_rows, dim3(S.L.buckets), dim3(kRowsBlock), 0, s, S);
+  } else {
+    build_by_sort(g, S.L.shift < 0, s);
+  }
   // all net weights 1 (the checks summed them to m): rows need no weights
   const int* ew = g->info.total_net_weight == (unsigned long long)g->m ? nullptr : g->ewgt;
   LoadPart* part = (LoadPart*)(g->ws + g->lay.lpart);
   hipLaunchKernelGGL(k_row_facts, dim3(grid_cap_load(g->n)), dim3(kBlock), 0, s, g->n, g->vptr,
                      g->vnets, ew, big, heavy, info, part);
-  hipLaunchKernelGGL(k_fold_load, dim3(1), dim3(kBlock), 0, s, (const LoadPart*)part, info);
+  hipLaunchKernelGGL(k_fold_load, dim3(1), dim3(kBlock), 0, s, (const LoadPart*)part, info,
+                     (unsigned*)nullptr, (const unsigned*)nullptr, 0);
   if (ew)
     hipLaunchKernelGGL(k_big_row_facts, dim3(kBigRowGrid), dim3(kBlock), 0, s, g->vptr, g->vnets,
                        ew, big, heavy, info);

@@ -1,0 +1,88 @@
+"""The incidence transpose at the edges of its tiles, ranges and row classes.
+
+Every row is compared with a stable sort of the (pin, net) pairs (exactly:
+whole numbers), through both paths: vertex ranges finished in LDS, and the
+radix sort that takes over where a range does not fit."""
+import numpy as np
+import pytest
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.fixture(scope="module")
+def H():
+    import torch
+    if not torch.cuda.is_available():
+        pytest.skip("needs a GPU")
+    from paper_2010_10272_amd import hgref
+    return hgref
+
+
+def rows_of_degrees(n, degrees, m, seed):
+    """Net CSR in which vertex v has degrees[v] pins (the rest about 3), every
+    net non-empty, no vertex twice in a net."""
+    rng = np.random.default_rng(seed)
+    deg = rng.integers(1, 6, n)
+    deg[:len(degrees)] = degrees
+    nets = np.concatenate([rng.choice(m, d, replace=False) for d in deg])
+    pins = np.repeat(np.arange(n), deg)
+    empty = np.setdiff1d(np.arange(m), nets)
+    nets, pins = np.concatenate([nets, empty]), np.concatenate([pins, rng.integers(0, n, empty.size)])
+    order = np.lexsort((rng.random(nets.size), nets))        # pins of a net in any order
+    eptr = np.concatenate(([0], np.cumsum(np.bincount(nets, minlength=m))))
+    return eptr.astype(np.int64), pins[order].astype(np.int32)
+
+
+def with_pins(P, n, seed):
+    """P pins in two-pin nets (the last has one when P is odd)."""
+    rng = np.random.default_rng(seed)
+    a = rng.integers(0, n, (P + 1) // 2)
+    pins = np.stack([a, (a + 1 + rng.integers(0, n - 1, a.size)) % n], 1).reshape(-1)[:P]
+    eptr = np.minimum(np.arange(0, P + 2, 2), P)
+    return eptr[:(P + 1) // 2 + 1].astype(np.int64), pins.astype(np.int32)
+
+
+CASES = {
+    # pins around one and two tiles of 8192, vertices around a bucket's width
+    "tile-1": lambda: (700, *with_pins(8191, 700, 1)),
+    "tile": lambda: (512, *with_pins(8192, 512, 2)),
+    "tile+1": lambda: (513, *with_pins(8193, 513, 3)),
+    "two-tiles": lambda: (70_001, *with_pins(2 * 8192 + 1, 70_001, 4)),
+    "one-net": lambda: (5, np.array([0, 5], np.int64), np.array([4, 0, 3, 1, 2], np.int32)),
+    "one-vertex": lambda: (1, np.arange(9, dtype=np.int64), np.zeros(8, np.int32)),
+    # rows on both sides of every class: 16, 32, 512
+    "row-classes": lambda: (3000, *rows_of_degrees(3000, [16, 17, 32, 33, 64, 65, 511, 512, 513,
+                                                          1500], 2000, 5)),
+    # a vertex in 30,000 nets: no bucket holds it, the radix sort takes over
+    "hub": lambda: (9000, *rows_of_degrees(9000, [30_000], 30_000, 6)),
+    # long nets across tiles, and more than one coarse range of 64 buckets
+    "wide": lambda: (200_003, *with_pins(900_001, 200_003, 7)),
+    "long-nets": lambda: (20_000, np.arange(0, 60_001, 20_000, dtype=np.int64),
+                          np.concatenate([np.random.default_rng(8 + i).permutation(20_000)
+                                          for i in range(3)]).astype(np.int32)),
+    # few pins for many vertices: most rows empty (radix sort)
+    "sparse-rows": lambda: (3_000_000, *with_pins(5000, 3_000_000, 9)),
+}
+
+
+@pytest.mark.parametrize("name", list(CASES))
+def test_incidence_rows(H, name):
+    n, eptr, pins = CASES[name]()
+    g = H.hg_load_csr(n, eptr, pins, k_max=2)
+    net = np.repeat(np.arange(eptr.size - 1), np.diff(eptr))
+    order = np.argsort(pins, kind="stable")
+    vptr = np.concatenate(([0], np.cumsum(np.bincount(pins, minlength=n))))
+    assert np.array_equal(g.vptr.cpu().numpy(), vptr)
+    assert np.array_equal(g.vnets.cpu().numpy(), net[order])
+    assert H.hg_get_info(g)["max_degree"] == int(np.diff(vptr).max())
+
+
+@pytest.mark.parametrize("degree", [2, 16, 20, 32, 40, 600])
+def test_repeated_pin_rejected(H, degree):
+    """A vertex twice in one net, its row in every row class."""
+    eptr, pins = rows_of_degrees(2000, [degree - 1], 1500, degree)
+    e = int(np.searchsorted(eptr, np.nonzero(pins == 0)[0][0], side="right") - 1)
+    pins = np.insert(pins, eptr[e], 0)
+    eptr = eptr + (np.arange(eptr.size) > e)
+    with pytest.raises(H.HgError, match="twice"):
+        H.hg_load_csr(2000, eptr, pins, k_max=2)
