@@ -26,40 +26,70 @@ __device__ __forceinline__ unsigned xcd_remap(unsigned bid, unsigned nblocks) {
   return xcd < rem ? xcd * (per + 1) + local : rem * (per + 1) + (xcd - rem) * per + local;
 }
 
-// ---- convergent wave reductions (every lane of the wave must call) ----
-template <typename T>
-__device__ __forceinline__ T wave_sum(T v) {
-#pragma unroll
-  for (int o = kWave / 2; o > 0; o >>= 1) v += __shfl_xor(v, o);
+// ---- convergent wave scans and reductions (every lane of the wave must call) ----
+// By data-parallel primitives: each step moves a register within the vector
+// unit (shifts by 1, 2, 4, 8 inside the rows of 16 lanes, then the last lane of
+// a row to the next rows), a few cycles each, where a shuffle goes through
+// LDS.  The small kernels between the sweeps are chains of such scans.
+template <int CTRL, int ROWS>
+__device__ __forceinline__ int dpp_move(int v) {
+  return __builtin_amdgcn_update_dpp(0, v, CTRL, ROWS, 0xf, false);   // 0 where nothing comes in
+}
+template <int CTRL, int ROWS>
+__device__ __forceinline__ unsigned dpp_move(unsigned v) {
+  return (unsigned)dpp_move<CTRL, ROWS>((int)v);
+}
+template <int CTRL, int ROWS>
+__device__ __forceinline__ long long dpp_move(long long v) {
+  const unsigned lo = dpp_move<CTRL, ROWS>((unsigned)v);
+  const unsigned hi = dpp_move<CTRL, ROWS>((unsigned)((unsigned long long)v >> 32));
+  return (long long)(((unsigned long long)hi << 32) | lo);
+}
+
+constexpr int kDppShr = 0x110, kDppBcast15 = 0x142, kDppBcast31 = 0x143;
+
+// Inclusive scan over the wave; 0 is the identity that empty lanes bring in.
+template <typename T, typename Op>
+__device__ __forceinline__ T wave_scan_op(T v, Op op) {
+  v = op(v, dpp_move<kDppShr | 1, 0xf>(v));
+  v = op(v, dpp_move<kDppShr | 2, 0xf>(v));
+  v = op(v, dpp_move<kDppShr | 4, 0xf>(v));
+  v = op(v, dpp_move<kDppShr | 8, 0xf>(v));
+  v = op(v, dpp_move<kDppBcast15, 0xa>(v));
+  v = op(v, dpp_move<kDppBcast31, 0xc>(v));
   return v;
 }
 
+__device__ __forceinline__ int last_lane(int v) {
+  return __builtin_amdgcn_readlane(v, kWave - 1);
+}
+__device__ __forceinline__ unsigned last_lane(unsigned v) {
+  return (unsigned)last_lane((int)v);
+}
+__device__ __forceinline__ long long last_lane(long long v) {
+  const unsigned lo = last_lane((unsigned)v);
+  const unsigned hi = last_lane((unsigned)((unsigned long long)v >> 32));
+  return (long long)(((unsigned long long)hi << 32) | lo);
+}
+
+__device__ __forceinline__ int wave_incl_scan(int v) {
+  return wave_scan_op(v, [](int a, int b) { return a + b; });
+}
+__device__ __forceinline__ long long wave_incl_scan64(long long v) {
+  return wave_scan_op(v, [](long long a, long long b) { return a + b; });
+}
+template <typename T>
+__device__ __forceinline__ T wave_sum(T v) {
+  return last_lane(wave_scan_op(v, [](T a, T b) { return a + b; }));
+}
+// Maximum over the wave, of values that may be negative: lanes that receive
+// nothing in a step keep their own.
 template <typename T>
 __device__ __forceinline__ T wave_max(T v) {
 #pragma unroll
   for (int o = kWave / 2; o > 0; o >>= 1) {
     T w = __shfl_xor(v, o);
     v = w > v ? w : v;
-  }
-  return v;
-}
-
-__device__ __forceinline__ int wave_incl_scan(int v) {
-  int lane = lane_id();
-#pragma unroll
-  for (int o = 1; o < kWave; o <<= 1) {
-    int w = __shfl_up(v, o);
-    if (lane >= o) v += w;
-  }
-  return v;
-}
-
-__device__ __forceinline__ long long wave_incl_scan64(long long v) {
-  int lane = lane_id();
-#pragma unroll
-  for (int o = 1; o < kWave; o <<= 1) {
-    long long w = __shfl_up(v, o);
-    if (lane >= o) v += w;
   }
   return v;
 }
@@ -133,5 +163,10 @@ typedef unsigned u32x2 __attribute__((ext_vector_type(2)));
 typedef unsigned u32x4 __attribute__((ext_vector_type(4)));
 typedef int i32x4 __attribute__((ext_vector_type(4)));
 typedef long long i64x2 __attribute__((ext_vector_type(2)));
+// Four ints at any 4-byte address (one 16-byte load; gfx950 takes it unaligned).
+typedef int i32x4u __attribute__((ext_vector_type(4), aligned(4)));
+__device__ __forceinline__ i32x4u load4_unaligned(const int* p) {
+  return *(const __attribute__((address_space(1))) i32x4u*)p;
+}
 
 }  // namespace hg
