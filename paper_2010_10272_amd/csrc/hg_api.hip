@@ -187,6 +187,7 @@ InstDesc make_desc(hg_graph_s* g, int k, long long lmax, int* part, int* phi,
   d.k = k;
   d.rw = net_words(k);
   d.view = net_view(k, g->unit_nets);
+  d.sweep = d.view;
   d.unit_nets = g->unit_nets ? 1 : 0;
   d.cmax = g->info.max_vertex_weight;
   d.lds_buckets = lds_buckets(k);
@@ -223,6 +224,16 @@ InstDesc make_desc(hg_graph_s* g, int k, long long lmax, int* part, int* phi,
   d.bw_slots = (long long*)(ws + g->lay.bw_slots);
   d.part8 = (unsigned char*)(ws + g->lay.part8);
   return d;
+}
+
+// The load's sort buffers are free once the graph is loaded; calls that count
+// the pins before their rounds keep the select's view there (at most 2 bytes a
+// net, and P >= m words).
+void keep_sweep_view(hg_graph_s* g, InstDesc& d) {
+  const int v = sweep_view(d.view, d.k);
+  if (v == d.view) return;
+  d.sweep = v;
+  d.sview = (unsigned char*)(g->ws + g->lay.lkey[0]);
 }
 
 }  // namespace hg
@@ -410,6 +421,7 @@ static hipError_t enqueue_refine(hg_graph g, int k, long long lmax, int rounds, 
                                  hipStream_t s) {
   hg::InstDesc d = hg::make_desc(g, k, lmax, part, phi, netstate, (long long*)block_w, eligible,
                                  nullptr, (long long*)km1, stats);
+  hg::keep_sweep_view(g, d);
   hg::CountPlan cplan;
   hg::single_count_plan(d, cplan);
   hipError_t e = hg::launch_counts(cplan, true, true, s);

@@ -80,11 +80,12 @@ __global__ __launch_bounds__(kBlock) void k_gains_light(Launch L, long long* __r
   // done: nothing to compute for this lane (out of range, invalid block, or
   // a block within L_max when only overloaded blocks are asked for);
   // have: this lane's row was computed here (a light vertex)
-  bool done = false, have = false;
-  int a = 0, tot = 0, ben = 0;
-  BitCounters<WK> C;
-  C.clear();
+  bool done = false;
+  int a = 0;
+  long long b0 = D.P, b1 = D.P;
   if (u < D.n) {
+    b0 = D.vptr[u];
+    b1 = D.vptr[u + 1];
     a = D.part[u];
     if ((unsigned)a >= (unsigned)k) {
       atomicOr(D.err_flags, kErrPart);
@@ -94,57 +95,19 @@ __global__ __launch_bounds__(kBlock) void k_gains_light(Launch L, long long* __r
         if (benefit) benefit[u] = 0;
       }
       done = true;
+      a = 0;
     } else if (only_over && D.block_w[a] <= D.lmax) {
       done = true;
     }
   } else {
     done = true;
   }
-  if (!done) {
-    const long long b0 = D.vptr[u], b1 = D.vptr[u + 1];
-    if (b1 - b0 <= kLightLimit) {                    // longer rows: the heavy kernel
-      const int aw = a >> 5;
-      const unsigned abit = 1u << (a & 31);
-      bool heavy = false;
-      for (long long j = b0; j < b1 && !heavy; j += kUnroll) {
-        unsigned w[kUnroll], S[kUnroll], Lb[kUnroll][WK];
-        bool cut[kUnroll];
-        int e[kUnroll];
-#pragma unroll
-        for (int q = 0; q < kUnroll; ++q) e[q] = global_ptr(D.vnets)[j + q < b1 ? j + q : j];
-#pragma unroll
-        for (int q = 0; q < kUnroll; ++q)
-          read_net<WK, VIEW>(D.netstate, D.rw, D.view_ptr, e[q], aw, w[q], cut[q], Lb[q], S[q]);
-#pragma unroll
-        for (int q = 0; q < kUnroll; ++q) {
-          if (j + q >= b1) {             // past the row end: a repeated slot, masked
-            w[q] = 0;
-            S[q] = 0;
-#pragma unroll
-            for (int x = 0; x < WK; ++x) Lb[q][x] = 0;
-          }
-        }
-#pragma unroll
-        for (int q = 0; q < kUnroll; ++q) {
-          tot += (int)w[q];
-          if (S[q] & abit) ben += (int)w[q];
-        }
-        if (tot > kLightLimit) {
-          heavy = true;                   // heavier rows: the heavy kernel
-          break;
-        }
-#pragma unroll
-        for (int q = 0; q < kUnroll; ++q) {
-          if constexpr (VIEW != kViewFull) {
-            C.add_one(Lb[q]);             // unit nets (masked slots add nothing)
-          } else if (w[q]) {
-            C.add(Lb[q], w[q]);
-          }
-        }
-      }
-      have = !heavy;
-    }
-  }
+  const bool mine = !done && b1 - b0 <= kLightLimit;   // longer rows: the heavy kernel
+  RowSums<WK, VIEW> R;
+  walk_row<WK, VIEW, 4>(D, D.view_ptr, b0, mine ? (int)(b1 - b0) : 0, mine ? a : 0, R);
+  const bool have = mine && !R.heavy;                  // heavier rows: the heavy kernel
+  const BitCounters<WK>& C = R.C;
+  const int tot = R.tot, ben = R.ben;
   if (have && cache) {
     const long long n = D.n;
     cache[u] = ben;
@@ -187,13 +150,13 @@ __global__ __launch_bounds__(kBlock) void k_gains_light(Launch L, long long* __r
   }
   // staged rows: every lane of the wavefront takes part, writing only the
   // rows whose lane computed them
-  const unsigned long long mine = __ballot(have);
+  const unsigned long long rows = __ballot(have);
   const long long row0 = u - lane_id();             // the wavefront's first vertex
   long long(*stage)[kStageMax + 1] = s_stage[threadIdx.x / kWave];
   if (k % 16 == 0)
-    write_rows_staged<16, WK>(stage, gains, k, row0, mine, have, a, base, C);
+    write_rows_staged<16, WK>(stage, gains, k, row0, rows, have, a, base, C);
   else
-    write_rows_staged<8, WK>(stage, gains, k, row0, mine, have, a, base, C);
+    write_rows_staged<8, WK>(stage, gains, k, row0, rows, have, a, base, C);
 }
 
 // Unit: 4 consecutive heavy-list entries (one per wavefront).
@@ -256,21 +219,21 @@ __global__ __launch_bounds__(kBlock) void k_gains_heavy(Launch L, long long* __r
 }
 
 GainsKernel gains_kernel(int k, int view) {
-  typedef void (*K)(Launch, long long*, long long*, int*, int);
-  K kern;
   switch (view) {
-    case kView16: kern = k_gains_light<1, kView16>; break;
-    case kView32: kern = k_gains_light<1, kView32>; break;
-    case kView64: kern = k_gains_light<2, kView64>; break;
-    default:
-      switch (bit_words(k)) {
-        case 1: kern = k_gains_light<1, kViewFull>; break;
-        case 2: kern = k_gains_light<2, kViewFull>; break;
-        case 4: kern = k_gains_light<4, kViewFull>; break;
-        default: kern = k_gains_light<8, kViewFull>; break;
-      }
+    case kView16: return (GainsKernel)(void*)k_gains_light<1, kView16>;
+    case kView32: return (GainsKernel)(void*)k_gains_light<1, kView32>;
+    case kView64: return (GainsKernel)(void*)k_gains_light<2, kView64>;
+    case kViewUnit:
+      return bit_words(k) == 4 ? (GainsKernel)(void*)k_gains_light<4, kViewUnit>
+                               : (GainsKernel)(void*)k_gains_light<8, kViewUnit>;
+    default: break;
   }
-  return (GainsKernel)(void*)kern;
+  switch (bit_words(k)) {
+    case 1: return (GainsKernel)(void*)k_gains_light<1, kViewFull>;
+    case 2: return (GainsKernel)(void*)k_gains_light<2, kViewFull>;
+    case 4: return (GainsKernel)(void*)k_gains_light<4, kViewFull>;
+    default: return (GainsKernel)(void*)k_gains_light<8, kViewFull>;
+  }
 }
 
 hipError_t launch_gains(hg_graph_s* g, const InstDesc& d, long long* gains, long long* benefit,

@@ -26,7 +26,6 @@ constexpr int kSmallRow = 64;          // incidence rows up to this length sort 
 constexpr int kNumXcd = 8;             // MI355X: 8 XCDs, each with its own L2
 constexpr int kLdsHistEntries = 2048;  // per-workgroup LDS gain histogram (k * buckets)
 constexpr int kSelectGrid = 2048;      // persistent workgroups of the select sweep
-constexpr int kUnroll = 4;             // record gathers in flight per thread in the gains sweep
 constexpr int kFinalizeGrid = 2048;    // persistent workgroups of the finalize sweep
 
 // Validation bits raised on the device.
@@ -113,8 +112,8 @@ struct InstDesc {
   int cmax, lds_buckets, heavy_count, num_tiles;
   int hist_stride;               // k_max * kBuckets: distance between histogram replicas
   int hist_reps;                 // histogram replicas in use (workgroup b adds to b % hist_reps)
+  int sweep;                     // NetView that the select reads: view, or sview's kind
   int round_base;                // round r's record goes to stats[r - round_base]
-  int pad1;
   long long P, lmax;
   const long long* eptr;
   const int* pins;
@@ -127,6 +126,7 @@ struct InstDesc {
   int* phi;
   unsigned* netstate;
   unsigned* view_ptr;            // compact Lambda/S copy (behind the records)
+  unsigned char* sview;          // narrower copy kept by refine calls in the workspace; null: none
   long long* block_w;
   unsigned char* eligible;
   unsigned char* moved;          // may be null
@@ -257,14 +257,25 @@ __host__ __device__ inline int bit_words(int k) {
 // 16 bytes (w(e) = 1 is implied and lambda(e) = popcount(Lambda)).  With k <=
 // 16 a million nets take 4 MB, one XCD's L2.  kViewFull means the sweeps read
 // the full net record instead.
-enum NetView : int { kViewFull = 0, kView16 = 1, kView32 = 2, kView64 = 3 };
+// kViewUnit: full records (k > 64), every net weight 1.  kView8 and kView4
+// (k <= 8 and k <= 4: 2 and 1 bytes a net) are never part of a net-state array:
+// a call that counts the pins itself and then runs rounds keeps them in the
+// workspace (see sweep_view).
+enum NetView : int {
+  kViewFull = 0, kView16 = 1, kView32 = 2, kView64 = 3, kViewUnit = 4, kView8 = 5, kView4 = 6
+};
 
 __host__ __device__ inline int net_view(int k, bool unit_nets) {
   if (!unit_nets) return kViewFull;
   if (k <= 16) return kView16;
   if (k <= 32) return kView32;
   if (k <= 64) return kView64;
-  return kViewFull;
+  return kViewUnit;
+}
+
+// The copy that a refine call keeps for its select sweeps, or `view` itself.
+inline int sweep_view(int view, int k) {
+  return view != kView16 ? view : k <= 4 ? kView4 : k <= 8 ? kView8 : kView16;
 }
 
 __host__ __device__ inline int view_bytes(int view) {
@@ -365,5 +376,6 @@ inline int lds_buckets(int k) {
 InstDesc make_desc(hg_graph_s* g, int k, long long lmax, int* part, int* phi,
                    unsigned* netstate, long long* block_w, unsigned char* eligible,
                    unsigned char* moved, long long* km1, hg_round_stats* stats);
+void keep_sweep_view(hg_graph_s* g, InstDesc& d);
 
 }  // namespace hg

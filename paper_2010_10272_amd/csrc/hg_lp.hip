@@ -91,12 +91,33 @@ __device__ __forceinline__ WorkItem single_unit(int unit) {
 // the final flush go to the histogram replica of this workgroup's XCD.
 constexpr int kDenseWave = 3 * kWave / 4;   // eligible lanes that make a wave's slice dense
 
+// The sweep's end: the workgroup's counts (each below 2^31, so two fit one
+// 64-bit sum) to its counter slots, and `flush` once every thread is done.
+template <typename F>
+__device__ __forceinline__ void add_select_counts(const InstDesc& D, unsigned long long* s_sums,
+                                                  int elig, int bnd, int cand, int apins,
+                                                  F flush) {
+  const long long eb = wave_sum((long long)elig | ((long long)bnd << 32));
+  const long long ca = wave_sum((long long)cand | ((long long)apins << 32));
+  if (lane_id() == 0) {
+    atomicAdd(&s_sums[0], (unsigned long long)eb);
+    atomicAdd(&s_sums[1], (unsigned long long)ca);
+  }
+  __syncthreads();
+  flush();
+  if (threadIdx.x < 4) {
+    const int which[4] = {kCtrEligible, kCtrBoundary, kCtrCandidates, kCtrActivePins};
+    const unsigned long long v = (s_sums[threadIdx.x / 2] >> (32 * (threadIdx.x % 2))) & 0xffffffffu;
+    if (v) atomicAdd(&D.ctr->slot[which[threadIdx.x]][blockIdx.x % kSlots], v);
+  }
+}
+
 template <int WK, int VIEW, int U>
 __global__ __launch_bounds__(kBlock) void k_select_light(Launch L) {
   __shared__ long long s_W[HG_MAX_K];
   __shared__ unsigned s_open[WK];
   __shared__ unsigned long long s_hist[kLdsHistEntries];
-  __shared__ long long s_tmp[kBlock / kWave];
+  __shared__ unsigned long long s_sums[2];
   __shared__ int s_q[kBlock / kWave][2 * kWave];   // per-wave queues of eligible vertices
   const InstDesc D0 = L.one;
   const WorkItem wi = work_item(L, xcd_sweep((D0.n + kBlock - 1) / kBlock));
@@ -105,6 +126,7 @@ __global__ __launch_bounds__(kBlock) void k_select_light(Launch L) {
   const int k = D.k, B = D.lds_buckets, n = D.n;
   const long long lmax = D.lmax;
   for (int i = threadIdx.x; i < WK; i += kBlock) s_open[i] = 0;
+  if (threadIdx.x < 2) s_sums[threadIdx.x] = 0;
   for (int i = threadIdx.x; i < k * B; i += kBlock) s_hist[i] = 0;
   __syncthreads();
   for (int i = threadIdx.x; i < k; i += kBlock) {
@@ -114,7 +136,8 @@ __global__ __launch_bounds__(kBlock) void k_select_light(Launch L) {
   }
   __syncthreads();
   unsigned long long* my_hist = D.hist + (size_t)(blockIdx.x % D.hist_reps) * D.hist_stride;
-  long long n_elig = 0, n_bnd = 0, n_cand = 0, n_apins = 0;
+  // per thread: at most n vertices and P pins, both below 2^31
+  int n_elig = 0, n_bnd = 0, n_cand = 0, n_apins = 0;
   // valid-block masks (only blocks < k; guards against stale caller state)
   unsigned valid[WK];
 #pragma unroll
@@ -122,11 +145,9 @@ __global__ __launch_bounds__(kBlock) void k_select_light(Launch L) {
     const int lo = w * 32;
     valid[w] = k >= lo + 32 ? ~0u : (k > lo ? (1u << (k - lo)) - 1u : 0u);
   }
-  const long long* __restrict__ vptr = D.vptr;
-  const int* __restrict__ vnets = D.vnets;
-  const unsigned* __restrict__ netstate = D.netstate;
-  const unsigned* __restrict__ view = D.view_ptr;
-  const int rw = D.rw;
+  const void* __restrict__ view =
+      VIEW == kView8 || VIEW == kView4 ? (const void*)D.sview : (const void*)D.view_ptr;
+  const int lane = lane_id(), wv = threadIdx.x / kWave;
   // Each wave queues the eligible vertices of its 64-vertex slices in LDS
   // and processes them 64 at a time, so that later rounds (few eligible
   // vertices) run full waves instead of mostly idle ones; slices that are
@@ -134,88 +155,50 @@ __global__ __launch_bounds__(kBlock) void k_select_light(Launch L) {
   // workgroup barrier is involved, so waves keep sweeping independently.
   // Every vertex gets its moved flag cleared, and the non-eligible ones
   // their "no candidate" word, when its slice is read.
-  auto one_vertex = [&](const long long u) {
-    const int a = D.part[u];
-    if ((unsigned)a >= (unsigned)k) {
-      atomicOr(D.err_flags, kErrPart);
-      D.cand[u] = -1;
-      D.eligible[u] = 0;
-      return;
-    }
-    const long long b0 = vptr[u], b1 = vptr[u + 1];
-    if (b1 - b0 > kLightLimit) return;        // heavy vertex: the wavefront kernel owns it
-    BitCounters<WK> C;
-    C.clear();
-    int tot = 0, ben = 0;
-    bool bnd = false, heavy = false;
-    const int aw = a >> 5;
-    const unsigned abit = 1u << (a & 31);
-    // Software-pipelined sweep: issue U independent record gathers before
-    // consuming any of them (U = 8 for average degrees of 12 and more, else
-    // 4).  Slots past the row end load the row's
-    // first entry again (always valid) and are masked afterwards, so no load
-    // sits in a branch of its own.  With unit nets w(I(u)) is the degree,
-    // which the row length already bounds, so only weighted nets are
-    // watched for the heavy limit.
-    const int deg = (int)(b1 - b0);
-    const auto row = global_ptr(vnets + b0);
-    for (int jj = 0; jj < deg; jj += U) {
-      unsigned w[U], S[U], Lb[U][WK];
-      bool cut[U];
-      int e[U];
-#pragma unroll
-      for (int q = 0; q < U; ++q) e[q] = row[jj + q < deg ? jj + q : jj];
-#pragma unroll
-      for (int q = 0; q < U; ++q)
-        read_net<WK, VIEW>(netstate, rw, view, e[q], aw, w[q], cut[q], Lb[q], S[q]);
-#pragma unroll
-      for (int q = 0; q < U; ++q) {
-        if (jj + q >= deg) {
-          w[q] = 0;
-          cut[q] = false;
-          S[q] = 0;
-#pragma unroll
-          for (int x = 0; x < WK; ++x) Lb[q][x] = 0;
-        }
-      }
-#pragma unroll
-      for (int q = 0; q < U; ++q) {
-        bnd |= cut[q];
-        if (S[q] & abit) ben += (int)w[q];
-      }
-      if constexpr (VIEW == kViewFull) {
-#pragma unroll
-        for (int q = 0; q < U; ++q) tot += (int)w[q];
-        if (tot > kLightLimit) {
-          heavy = true;
-          break;
-        }
-      }
-#pragma unroll
-      for (int q = 0; q < U; ++q) {
-        if constexpr (VIEW != kViewFull) {
-          C.add_one(Lb[q]);               // unit nets (masked slots add nothing)
-        } else if (w[q]) {
-          C.add(Lb[q], w[q]);
-        }
+  //
+  // One wavefront's vertices: lane's vertex u, if `act`.
+  auto wave_vertices = [&](const long long u, const bool act) {
+    int a = 0, deg = 0;
+    long long b0 = 0, cu = 1;
+    bool mine = false;
+    if (act) {
+      a = D.part[u];
+      b0 = D.vptr[u];
+      const long long len = D.vptr[u + 1] - b0;
+      if (D.vwgt) cu = D.vwgt[u];
+      if ((unsigned)a >= (unsigned)k) {
+        atomicOr(D.err_flags, kErrPart);
+        D.cand[u] = -1;
+        D.eligible[u] = 0;
+      } else if (len <= kLightLimit) {           // longer rows: the heavy kernel's
+        mine = true;
+        deg = (int)len;
       }
     }
-    if constexpr (VIEW != kViewFull) tot = deg;
-    if (heavy) return;
+    if (!mine) a = 0;
+    RowSums<WK, VIEW> R;
+    walk_row<WK, VIEW, U>(D, view, b0, deg, a, R);
+    if (!mine || R.heavy) return;
     D.eligible[u] = 0;
     n_elig += 1;
     long long out = -1;
-    if (bnd) {
+    const int aw = a >> 5;
+    const unsigned abit = 1u << (a & 31);
+    // blocks of u's nets beside its own: there is one iff u is on a cut net
+    unsigned T[WK], anyT = 0;
+    R.C.nonzero(T);
+#pragma unroll
+    for (int w = 0; w < WK; ++w) {
+      T[w] &= w == aw ? valid[w] & ~abit : valid[w];
+      anyT |= T[w];
+    }
+    if (anyT) {
       n_bnd += 1;
-      n_apins += b1 - b0;
-      const long long cu = D.vwgt ? D.vwgt[u] : 1;
-      unsigned T[WK], F[WK];
-      C.nonzero(T);
+      n_apins += deg;
+      unsigned F[WK];
       unsigned anyF = 0;
 #pragma unroll
       for (int w = 0; w < WK; ++w) {
-        T[w] &= valid[w];
-        if (w == aw) T[w] &= ~abit;
         F[w] = T[w] & s_open[w];
         unsigned rest = T[w] & ~s_open[w];
         while (rest) {
@@ -226,7 +209,7 @@ __global__ __launch_bounds__(kBlock) void k_select_light(Launch L) {
         anyF |= F[w];
       }
       if (anyF) {
-        const int conn = (int)C.narrow_to_max(F);
+        const int conn = (int)R.C.narrow_to_max(F);
         int t = -1;
         long long tw = 0;
 #pragma unroll
@@ -243,7 +226,7 @@ __global__ __launch_bounds__(kBlock) void k_select_light(Launch L) {
             }
           }
         }
-        const int g = ben - tot + conn;
+        const int g = R.ben - R.tot + conn;
         if (g > 0 || (g == 0 && tw + cu < s_W[a])) {
           out = pack_cand(g, t);
           n_cand += 1;
@@ -257,32 +240,40 @@ __global__ __launch_bounds__(kBlock) void k_select_light(Launch L) {
     }
     D.cand[u] = out;
   };
-  const int lane = lane_id();
-  int* my_q = s_q[threadIdx.x / kWave];
+  int* my_q = s_q[wv];
   int qn = 0;                                  // this wave's queue length (wave-uniform)
-  // one call site of one_vertex (the select body is large): the extra last
+  // the next slice's flags are on their way while a slice is processed
+  auto flag_of = [&](int it) {
+    const long long u = ((long long)wi.first + (long long)it * wi.stride) * kBlock + threadIdx.x;
+    return it < wi.count && u < n ? D.eligible[u] : (unsigned char)0;
+  };
+  unsigned char next_flag = flag_of(0);
+  // one call site of wave_vertices (the select body is large): the extra last
   // iteration flushes the queue
   for (int it = 0; it <= wi.count; ++it) {
-    long long todo = -1;
+    long long u = 0;
+    bool act = false, run = false;
     if (it < wi.count) {
       const long long c = (long long)wi.first + (long long)it * wi.stride;
-      const long long u = c * kBlock + threadIdx.x;
-      bool el = false;
+      u = c * kBlock + threadIdx.x;
+      const bool el = next_flag != 0;
+      next_flag = flag_of(it + 1);
       if (u < n) {
         if (D.moved) D.moved[u] = 0;
-        el = D.eligible[u] != 0;
         if (!el) D.cand[u] = -1;
       }
       const unsigned long long mask = __ballot(el);
       const int cnt = __popcll(mask);
       if (cnt >= kDenseWave) {                 // mostly eligible: in place
-        todo = el ? u : -1;
+        act = el;
+        run = true;
       } else {
         if (el) my_q[qn + __popcll(mask & ((1ull << lane) - 1))] = (int)u;
         qn += cnt;                             // < 2 * kWave
         wave_lds_sync();
         if (qn >= kWave) {
-          todo = my_q[lane];
+          u = my_q[lane];
+          act = run = true;
           const int rest = qn - kWave;
           const int keep = lane < rest ? my_q[kWave + lane] : 0;
           wave_lds_sync();
@@ -291,28 +282,19 @@ __global__ __launch_bounds__(kBlock) void k_select_light(Launch L) {
           wave_lds_sync();
         }
       }
-    } else if (lane < qn) {
-      todo = my_q[lane];
+    } else if (qn > 0) {
+      run = true;
+      act = lane < qn;
+      u = act ? my_q[lane] : 0;
     }
-    if (todo >= 0) one_vertex(todo);
+    if (run) wave_vertices(u, act);
   }
-  __syncthreads();
-  for (int i = threadIdx.x; i < k * B; i += kBlock) {
-    const unsigned long long v = s_hist[i];
-    if (v) atomicAdd(&my_hist[(i / B) * kBuckets + (i % B)], v);
-  }
-  n_elig = block_sum64(n_elig, s_tmp);
-  n_bnd = block_sum64(n_bnd, s_tmp);
-  n_cand = block_sum64(n_cand, s_tmp);
-  n_apins = block_sum64(n_apins, s_tmp);
-  if (threadIdx.x == 0) {
-    const int sl = blockIdx.x % kSlots;
-    RoundCounters* ctr = D.ctr;
-    if (n_apins) atomicAdd(&ctr->slot[kCtrActivePins][sl], (unsigned long long)n_apins);
-    if (n_elig) atomicAdd(&ctr->slot[kCtrEligible][sl], (unsigned long long)n_elig);
-    if (n_bnd) atomicAdd(&ctr->slot[kCtrBoundary][sl], (unsigned long long)n_bnd);
-    if (n_cand) atomicAdd(&ctr->slot[kCtrCandidates][sl], (unsigned long long)n_cand);
-  }
+  add_select_counts(D, s_sums, n_elig, n_bnd, n_cand, n_apins, [&] {
+    for (int i = threadIdx.x; i < k * B; i += kBlock) {
+      const unsigned long long v = s_hist[i];
+      if (v) atomicAdd(&my_hist[(i / B) * kBuckets + (i % B)], v);
+    }
+  });
 }
 
 // One wavefront per heavy vertex (w(I(u)) > 255): per-block connection
@@ -430,7 +412,7 @@ template <int G>
 __global__ __launch_bounds__(kBlock) void k_select_cached(Launch L) {
   __shared__ long long s_W[HG_MAX_K];
   __shared__ unsigned long long s_hist[kLdsHistEntries];
-  __shared__ long long s_tmp[kBlock / kWave];
+  __shared__ unsigned long long s_sums[2];
   const InstDesc D0 = L.one;
   const WorkItem wi = work_item(L, xcd_sweep((D0.n + kBlock - 1) / kBlock));
   if (wi.count == 0) return;
@@ -438,10 +420,11 @@ __global__ __launch_bounds__(kBlock) void k_select_cached(Launch L) {
   const int k = D.k, B = D.lds_buckets, n = D.n;
   const long long lmax = D.lmax;
   for (int i = threadIdx.x; i < k * B; i += kBlock) s_hist[i] = 0;
+  if (threadIdx.x < 2) s_sums[threadIdx.x] = 0;
   for (int i = threadIdx.x; i < k; i += kBlock) s_W[i] = D.block_w[i];
   __syncthreads();
   unsigned long long* my_hist = D.hist + (size_t)(blockIdx.x % D.hist_reps) * D.hist_stride;
-  long long n_elig = 0, n_bnd = 0, n_cand = 0, n_apins = 0;
+  int n_elig = 0, n_bnd = 0, n_cand = 0, n_apins = 0;   // as in the light sweep
   const int gl = threadIdx.x % G;
   constexpr int kPer = kBlock / G;
   const int Q = cache_stride(k) / 4;
@@ -511,7 +494,7 @@ __global__ __launch_bounds__(kBlock) void k_select_cached(Launch L) {
       long long out = -1;
       if (bnd) {
         n_bnd += 1;
-        n_apins += D.vptr[u + 1] - D.vptr[u];
+        n_apins += (int)(D.vptr[u + 1] - D.vptr[u]);
         if (bi >= 0) {
           const int g = ben - tot + bc;
           if (g > 0 || (g == 0 && bw + cu < s_W[a])) {
@@ -530,23 +513,12 @@ __global__ __launch_bounds__(kBlock) void k_select_cached(Launch L) {
       D.cand[u] = out;
     }
   }
-  __syncthreads();
-  for (int i = threadIdx.x; i < k * B; i += kBlock) {
-    const unsigned long long v = s_hist[i];
-    if (v) atomicAdd(&my_hist[(i / B) * kBuckets + (i % B)], v);
-  }
-  n_elig = block_sum64(n_elig, s_tmp);
-  n_bnd = block_sum64(n_bnd, s_tmp);
-  n_cand = block_sum64(n_cand, s_tmp);
-  n_apins = block_sum64(n_apins, s_tmp);
-  if (threadIdx.x == 0) {
-    const int sl = blockIdx.x % kSlots;
-    RoundCounters* ctr = D.ctr;
-    if (n_apins) atomicAdd(&ctr->slot[kCtrActivePins][sl], (unsigned long long)n_apins);
-    if (n_elig) atomicAdd(&ctr->slot[kCtrEligible][sl], (unsigned long long)n_elig);
-    if (n_bnd) atomicAdd(&ctr->slot[kCtrBoundary][sl], (unsigned long long)n_bnd);
-    if (n_cand) atomicAdd(&ctr->slot[kCtrCandidates][sl], (unsigned long long)n_cand);
-  }
+  add_select_counts(D, s_sums, n_elig, n_bnd, n_cand, n_apins, [&] {
+    for (int i = threadIdx.x; i < k * B; i += kBlock) {
+      const unsigned long long v = s_hist[i];
+      if (v) atomicAdd(&my_hist[(i / B) * kBuckets + (i % B)], v);
+    }
+  });
 }
 
 // b(u) of every vertex that moved this round, from the finalized net records
@@ -1163,7 +1135,7 @@ __global__ __launch_bounds__(kBlock) void k_finalize_cached(Launch L) {
       const unsigned old_word = gl >= 2 && gl < 2 + 2 * wk ? rec[gl] : 0u;
       NetBits nb = net_bits<G>(k, gl, [&](int i2) { return row[i2]; });
       if (gl >= 1 && gl < 2 + 2 * wk) rec[gl] = nb.word;
-      if (D.view != kViewFull) write_view(D.view_ptr, e, D.view, gl, nb);
+      if (D.view != kViewFull) write_views(D, e, gl, nb);
       if (gl == 1) dcheck += (long long)(lam_old - nb.lambda) * w;
       const long long b = D.eptr[e], t = D.eptr[e + 1];
       if (gl == 0) {
@@ -1250,7 +1222,7 @@ __global__ __launch_bounds__(kBlock) void k_finalize(Launch L) {
       const long long b = D.eptr[e], t = D.eptr[e + 1];
       NetBits nb = net_bits<G>(k, gl, [&](int i2) { return row[i2]; });
       if (gl >= 1 && gl < 2 + 2 * wk) rec[gl] = nb.word;
-      if (D.view != kViewFull) write_view(D.view_ptr, e, D.view, gl, nb);
+      if (D.view != kViewFull) write_views(D, e, gl, nb);
       if (gl == 1) dcheck += (long long)(lam_old - nb.lambda) * w;
       if (gl == 0) {
         D.touched[e] = 0;
@@ -1389,27 +1361,29 @@ __global__ __launch_bounds__(kBlock) void k_round_stats(Launch L) {
 int group_lanes(int k);
 
 // Kernel selection per instance shape (shared with the batch planner).
-// Record gathers in flight per vertex: eight where the average degree is
-// 12 or more (half the dependent load steps for the typical vertex), four
-// below (eight would mostly load padding slots).
-template <int U>
-SelectKernel select_kernel_u(int k, int view) {
+// Entries in flight per vertex: eight where the average degree is 12 or more
+// and an entry is at most two words (half the dependent load steps for the
+// typical vertex: netlist 162 -> 148 us), four elsewhere (eight would mostly
+// load padding slots: matrix 46.9 against 48.8 us; wider entries cost
+// registers).
+SelectKernel select_kernel(int k, int view, long long P, int n) {
+  const bool wide = P >= 12LL * n;
   switch (view) {
-    case kView16: return k_select_light<1, kView16, U>;
-    case kView32: return k_select_light<1, kView32, U>;
-    case kView64: return k_select_light<2, kView64, U>;
+    case kView16: return wide ? k_select_light<1, kView16, 8> : k_select_light<1, kView16, 4>;
+    case kView32: return wide ? k_select_light<1, kView32, 8> : k_select_light<1, kView32, 4>;
+    case kView8: return wide ? k_select_light<1, kView8, 8> : k_select_light<1, kView8, 4>;
+    case kView4: return wide ? k_select_light<1, kView4, 8> : k_select_light<1, kView4, 4>;
+    case kView64: return k_select_light<2, kView64, 4>;
+    case kViewUnit:
+      return bit_words(k) == 4 ? k_select_light<4, kViewUnit, 4> : k_select_light<8, kViewUnit, 4>;
     default: break;
   }
   switch (bit_words(k)) {
-    case 1: return k_select_light<1, kViewFull, U>;
-    case 2: return k_select_light<2, kViewFull, U>;
-    case 4: return k_select_light<4, kViewFull, U>;
-    default: return k_select_light<8, kViewFull, U>;
+    case 1: return k_select_light<1, kViewFull, 4>;
+    case 2: return k_select_light<2, kViewFull, 4>;
+    case 4: return k_select_light<4, kViewFull, 4>;
+    default: return k_select_light<8, kViewFull, 4>;
   }
-}
-
-SelectKernel select_kernel(int k, int view, long long P, int n) {
-  return P >= 12LL * n ? select_kernel_u<8>(k, view) : select_kernel_u<4>(k, view);
 }
 
 // The plain finalize reads one Phi row and writes one record per net: for
@@ -1488,7 +1462,7 @@ void single_round_plan(const InstDesc& d, RoundPlan& plan) {
   const Launch L = single_launch(d);
   const long long chunks = ((long long)d.n + kBlock - 1) / kBlock;
   PlanLaunch sel;
-  sel.kernel = (void*)select_kernel(d.k, d.view, d.P, d.n);
+  sel.kernel = (void*)select_kernel(d.k, d.sweep, d.P, d.n);
   sel.grid = (unsigned)(chunks < kSelectGrid ? chunks : kSelectGrid);
   sel.L = L;
   plan.select.push_back(sel);

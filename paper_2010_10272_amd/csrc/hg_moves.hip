@@ -1162,6 +1162,7 @@ hg_status hg_refine_exact(hg_graph g, int32_t k, double eps, int32_t rounds, int
   hipStream_t s = (hipStream_t)stream;
   hg::InstDesc d = hg::make_desc(g, k, lmax, part, phi, netstate, (long long*)block_w, eligible,
                                  nullptr, (long long*)km1_out, stats);
+  hg::keep_sweep_view(g, d);
   hg::CountPlan cplan;
   hg::single_count_plan(d, cplan);
   HG_TRY(hg::launch_counts(cplan, true, true, s), "pin counts");

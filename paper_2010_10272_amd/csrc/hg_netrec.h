@@ -93,18 +93,25 @@ __device__ __forceinline__ void write_netrec(unsigned* rec, int gl, int w, const
   }
 }
 
-// Write net e's entry of the compact Lambda/S view (NetView) from the record
-// words held by the group's lanes (lane 2.. holds Lambda, then S).  All lanes
-// of the group must call it.
-__device__ __forceinline__ void write_view(unsigned* view, long long e, int view_kind, int gl,
-                                           const NetBits& b) {
+// Write net e's entry of the compact Lambda/S views (NetView) from the record
+// words held by the group's lanes (lane 2.. holds Lambda, then S): the one
+// behind the records, and the refine call's own narrower one when there is
+// one.  All lanes of the group must call it.
+__device__ __forceinline__ void write_views(const InstDesc& D, long long e, int gl,
+                                            const NetBits& b) {
   const unsigned next = __shfl(b.word, lane_id() + 1);   // the word of lane gl + 1
-  if (view_kind == kView16) {
-    if (gl == 2) view[e] = (b.word & 0xffffu) | (next << 16);
-  } else if (view_kind == kView32) {
-    if (gl == 2 || gl == 3) view[e * 2 + (gl - 2)] = b.word;
-  } else if (view_kind == kView64) {
-    if (gl >= 2 && gl < 6) view[e * 4 + (gl - 2)] = b.word;
+  if (D.view == kView16) {
+    if (gl == 2) {
+      D.view_ptr[e] = (b.word & 0xffffu) | (next << 16);
+      if (D.sweep == kView8)
+        reinterpret_cast<unsigned short*>(D.sview)[e] = (unsigned short)(b.word | (next << 8));
+      else if (D.sweep == kView4)
+        D.sview[e] = (unsigned char)(b.word | (next << 4));
+    }
+  } else if (D.view == kView32) {
+    if (gl == 2 || gl == 3) D.view_ptr[e * 2 + (gl - 2)] = b.word;
+  } else if (D.view == kView64) {
+    if (gl >= 2 && gl < 6) D.view_ptr[e * 4 + (gl - 2)] = b.word;
   }
 }
 

@@ -107,7 +107,7 @@ __global__ __launch_bounds__(kBlock) void k_pincounts(Launch L) {
       const int w = D.ewgt ? D.ewgt[e] : 1;
       write_netrec(D.netstate + e * (long long)rw, gl, w, bits, k);
       if (D.view != kViewFull) {
-        write_view(D.view_ptr, e, D.view, gl, bits);
+        write_views(D, e, gl, bits);
       } else if (gl < view_words(k)) {
         // the compact copy is not used for weighted nets: keep it defined (zero)
         D.view_ptr[e * view_words(k) + gl] = 0u;
