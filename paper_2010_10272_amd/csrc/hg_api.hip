@@ -162,7 +162,7 @@ WsLayout ws_layout(int n, int m, long long P, int k_max) {
   L.flags = take(256);
   L.red = take(sizeof(unsigned long long) * kSlots);
   L.bw_slots = take(sizeof(long long) * kSlots * (size_t)k_max);
-  L.part8 = take((size_t)n);
+  L.part8 = take(((size_t)n + 7) / 8 * 8);   // whole groups of eight
   L.lkey[0] = take(sizeof(unsigned) * (size_t)P);
   L.lkey[1] = take(sizeof(unsigned) * (size_t)P);
   L.lval = take(sizeof(int) * (size_t)P);

@@ -169,9 +169,9 @@ size_t build_plans(const std::vector<BatchMember>& mem, const std::vector<int>& 
       for (int t = 0; t < k; ++t) approve.flat.push_back(WorkItem{i, t, -1, 1});
     }
     if (cp) {
-      KindItems* p = variant(pc, (void*)pincount_kernel_g(G));
-      add_split(*p, i, ceil_div(g->m, kBlock / G), S.count_chunks * G, home[i]);
-      p->lds = std::max(p->lds, pincount_lds(G, k));
+      KindItems* p = variant(pc, (void*)pincount_kernel(k));
+      add_split(*p, i, ceil_div(g->m, kBlock), S.count_chunks, home[i]);
+      p->lds = std::max(p->lds, pincount_lds(k));
       add_split(verts, i, ceil_div(g->n, kBwChunk), 1, home[i]);
     }
     inst.flat.push_back(WorkItem{i, 0, 1, 1});

@@ -82,6 +82,17 @@ template <typename T>
 __device__ __forceinline__ T wave_sum(T v) {
   return last_lane(wave_scan_op(v, [](T a, T b) { return a + b; }));
 }
+// The value of the lane before (0 in lane 0).
+__device__ __forceinline__ unsigned lane_before(unsigned v) {
+  return (unsigned)__builtin_amdgcn_update_dpp(0, (int)v, 0x138 /* wave_shr:1 */, 0xf, 0xf, false);
+}
+
+// add + the bits of `mask` below this lane.
+__device__ __forceinline__ int lanes_below(unsigned long long mask, int add) {
+  return (int)__builtin_amdgcn_mbcnt_hi((unsigned)(mask >> 32),
+                                        __builtin_amdgcn_mbcnt_lo((unsigned)mask, (unsigned)add));
+}
+
 // Maximum over the wave, of values that may be negative: lanes that receive
 // nothing in a step keep their own.
 template <typename T>

@@ -437,7 +437,7 @@ __device__ __forceinline__ void scan_counts(const unsigned* cnt, unsigned* off, 
 __device__ __forceinline__ unsigned run_rank(unsigned* cnt, unsigned key, bool live) {
   const int lane = lane_id();
   const unsigned k = live ? key : 0xffffffffu;
-  const unsigned prev = (unsigned)__shfl_up((int)k, 1);
+  const unsigned prev = lane_before(k);
   const unsigned long long heads = __ballot(lane == 0 || k != prev);
   const unsigned long long upto = ~0ull >> (kWave - 1 - lane);
   const int head = kWave - 1 - __clzll((long long)(heads & upto));

@@ -31,7 +31,7 @@ struct RoundPlan {
   bool any_heavy = false;
 };
 
-// Pin counts (one launch per group width), then the per-instance km1 slot
+// Pin counts (one launch per bitset width), then the per-instance km1 slot
 // sums, the block-weight reset and sweep.
 struct CountPlan {
   std::vector<PlanLaunch> pincounts;
@@ -46,9 +46,8 @@ SelectKernel select_kernel(int k, int view, long long P, int n);
 // gain-cache deltas (it must be used exactly when the descriptor has a cache)
 FinalizeKernel finalize_kernel(int k, bool cache);
 FinalizeKernel finalize_kernel_g(int G, bool cache);   // G lanes per net (4, 8, 16 or 32)
-GroupKernel pincount_kernel(int k);          // lanes per net: group_lanes(k)
-GroupKernel pincount_kernel_g(int G);        // G lanes per net (4, 8, 16 or 32)
-size_t pincount_lds(int G, int k);           // its dynamic LDS bytes
+GroupKernel pincount_kernel(int k);          // units of 256 nets
+size_t pincount_lds(int k);                  // its dynamic LDS bytes
 GainsKernel gains_kernel(int k, int view);
 int group_lanes(int k);
 

@@ -78,21 +78,6 @@ __device__ __forceinline__ NetBits net_bits(int k, int gl, Get get) {
   return net_bits_mc<G, 8>(k, gl, get);
 }
 
-// Write a whole record (w in word 0, zero padding); needs G >= record words,
-// which holds for the group sizes chosen per k (G >= 4 = words for k <= 32,
-// G = 64 >= 32 words otherwise).
-__device__ __forceinline__ void write_netrec(unsigned* rec, int gl, int w, const NetBits& b,
-                                             int k) {
-  const int wk = bit_words(k);
-  const int rw = net_words(k);
-  if (gl < rw) {
-    unsigned val = 0;
-    if (gl == 0) val = (unsigned)w;
-    else if (gl < 2 + 2 * wk) val = b.word;
-    rec[gl] = val;
-  }
-}
-
 // Write net e's entry of the compact Lambda/S views (NetView) from the record
 // words held by the group's lanes (lane 2.. holds Lambda, then S): the one
 // behind the records, and the refine call's own narrower one when there is
@@ -113,6 +98,56 @@ __device__ __forceinline__ void write_views(const InstDesc& D, long long e, int 
   } else if (D.view == kView64) {
     if (gl >= 2 && gl < 6) D.view_ptr[e * 4 + (gl - 2)] = b.word;
   }
+}
+
+// Net e's whole record (zero padding) and views, written by one lane.
+template <int WK>
+__device__ __forceinline__ void write_record(const InstDesc& D, long long e, int w, int lambda,
+                                             const unsigned (&lam)[WK],
+                                             const unsigned (&one)[WK]) {
+  constexpr int N = 2 + 2 * WK;
+  constexpr int RW = N <= 4 ? 4 : N <= 8 ? 8 : N <= 16 ? 16 : 32;   // net_words
+  unsigned r[RW];
+#pragma unroll
+  for (int i = 0; i < RW; ++i) r[i] = 0;
+  r[0] = (unsigned)w;
+  r[1] = (unsigned)lambda;
+#pragma unroll
+  for (int i = 0; i < WK; ++i) {
+    r[2 + i] = lam[i];
+    r[2 + WK + i] = one[i];
+  }
+  u32x4* rec = reinterpret_cast<u32x4*>(D.netstate + e * RW);
+#pragma unroll
+  for (int i = 0; i < RW / 4; ++i) {
+    const u32x4 q = {r[4 * i], r[4 * i + 1], r[4 * i + 2], r[4 * i + 3]};
+    rec[i] = q;
+  }
+  if constexpr (WK == 1) {
+    if (D.view == kView16) {
+      D.view_ptr[e] = (lam[0] & 0xffffu) | (one[0] << 16);
+      if (D.sweep == kView8)
+        reinterpret_cast<unsigned short*>(D.sview)[e] = (unsigned short)(lam[0] | (one[0] << 8));
+      else if (D.sweep == kView4)
+        D.sview[e] = (unsigned char)(lam[0] | (one[0] << 4));
+      return;
+    }
+    if (D.view == kView32) {
+      const u32x2 q = {lam[0], one[0]};
+      *reinterpret_cast<u32x2*>(D.view_ptr + 2 * e) = q;
+      return;
+    }
+  }
+  if constexpr (WK == 2) {
+    if (D.view == kView64) {
+      const u32x4 q = {lam[0], lam[1], one[0], one[1]};
+      *reinterpret_cast<u32x4*>(D.view_ptr + 4 * e) = q;
+      return;
+    }
+  }
+  // the compact copy is not used for weighted nets: keep it defined (zero)
+  const int vw = view_words(D.k);
+  for (int i = 0; i < vw; ++i) D.view_ptr[e * vw + i] = 0u;
 }
 
 }  // namespace hg

@@ -3,11 +3,11 @@
 //
 // Section "Preliminaries" defines Phi, Lambda, lambda and km1; subsection
 // "Data Structures for Gain Calculation" keeps Phi and a bitset Lambda per
-// net.  Here one group of G lanes owns one net at a time: it counts the net's
-// pins per block in LDS, writes the Phi row (16-byte streaming stores when
-// rows are aligned, coalesced 4-byte stores otherwise) and builds the bitsets
-// with wave ballots.  No global atomics touch Phi, so the result is
-// deterministic by construction.
+// net.  Here a wavefront owns 64 consecutive nets at a time: their pins are one
+// run of the pin array, counted 64 at a time into byte counters in LDS; then
+// each lane builds its net's bitsets from its counters, and the rows leave as
+// whole lines.  No global atomics touch Phi, so the result is deterministic by
+// construction.
 #include "hg_device.h"
 #include "hg_internal.h"
 #include "hg_lp.h"
@@ -15,7 +15,7 @@
 
 namespace hg {
 
-constexpr int kStateGrid = 8192;   // persistent workgroups of the single-instance net sweep
+constexpr int kStateGrid = 4096;   // persistent workgroups of the single-instance net sweep
 constexpr int kKm1Chunk = kBlock * 8;
 
 __device__ __forceinline__ WorkItem contiguous_units(long long units) {
@@ -31,94 +31,223 @@ __device__ __forceinline__ WorkItem contiguous_units(long long units) {
   return w;
 }
 
-// Pin slots per lane and pass: the pin loads of kCountSlots * G pins, then
-// their block-id loads, are in flight together (the sweep is bound by their
-// latency); slots past the net's end repeat its first pin and are masked.
-// Block ids are gathered from the byte copy part8 that the block-weight
-// sweep writes just before (a quarter of the bytes of part: on a 4M-vertex
-// netlist 4 MB, which an XCD's L2 mostly holds, instead of 16 MB).
-constexpr int kCountSlots = 4;
+// Block ids are gathered from a packed copy of the partition that the
+// block-weight sweep writes just before: four bits a vertex for k <= 16, a byte
+// beyond (2 and 4 MB on a 4M-vertex netlist, where an XCD's L2 has 4 MB, instead
+// of 16 MB).  If that sweep met an id outside [0, k), the ids come from the
+// partition itself, so that such vertices are skipped.
+constexpr int kCountUnit = kBlock;           // nets per unit: 64 per wavefront
+constexpr int kCountFlight = 4;              // pins in flight per lane
+constexpr int kByteNet = 255;                // longest net whose counts surely fit a byte
 
-// Unit: kBlock/G consecutive nets (one per group).  G lanes per net (G
-// divides 64, G >= the record words); LDS counters: (kBlock/G) groups x k
-// ints.
-template <int G>
+// Nets a wavefront takes at a time (the counters of 64 fill the LDS for k > 128).
+__host__ __device__ __forceinline__ int count_nets(int k) { return k > 128 ? 32 : 64; }
+// Words of a net's byte counters in LDS: odd, so that lanes reading their own
+// nets' word i use all banks.
+__host__ __device__ __forceinline__ int count_stride(int k) { return ((k + 3) / 4) | 1; }
+
+// Counters -> bits: bit i of `nz` / `one` for byte i of x non-zero / equal to one.
+__device__ __forceinline__ void byte_bits(unsigned x, unsigned& nz, unsigned& one) {
+  constexpr unsigned low7 = 0x7f7f7f7fu;
+  const unsigned a = (((x & low7) + low7) | x) & ~low7;               // bytes != 0
+  const unsigned y = x ^ 0x01010101u;
+  const unsigned b = ~((((y & low7) + low7) | y) | low7);             // bytes == 1
+  // the four top bits to bits 0..3
+  nz = ((a >> 7) * 0x10204080u) >> 28;
+  one = ((b >> 7) * 0x10204080u) >> 28;
+}
+
+// Counts of one net longer than kByteNet by the whole wavefront, in 32-bit
+// words (`cnt`, k of them): Phi row, and its bits into the lane that owns it.
+template <typename Block>
+__device__ void count_long_net(const InstDesc& D, long long e, long long b, long long t, int* cnt,
+                               Block block) {
+  const int lane = lane_id(), k = D.k;
+  for (int i = lane; i < k; i += kWave) cnt[i] = 0;
+  wave_lds_sync();
+  for (long long p = b + lane; p < t; p += kWave) {
+    const unsigned v = block(D.pins[p]);
+    if (v < (unsigned)k) atomicAdd(&cnt[v], 1);
+  }
+  wave_lds_sync();
+  for (int i = lane; i < k; i += kWave) D.phi[e * k + i] = cnt[i];
+}
+
+// Unit: kCountUnit consecutive nets.  What bounds it: the block ids' gathers
+// (lines outstanding per compute unit).  A lane group per net (8 lanes, four
+// slots each) left two thirds of the gather slots empty on nets of ten pins and
+// half the lanes idle; here every lane has a pin.  Pins of a net in one block
+// are often neighbours, so each run of equal (net, block) adds once.  (Four
+// consecutive pins per lane need a third fewer operations, but their gathers
+// touch more lines at a time: netlist 370 -> 404 us.)  Per call, before and
+// now: netlist 56.5M pins, k = 16 523 -> 367 us (gathers 135 of them, Phi
+// stores 65), matrix 10M pins k = 8 82 -> 48, k = 64 128 -> 95.
+template <int WK>
 __global__ __launch_bounds__(kBlock) void k_pincounts(Launch L) {
-  extern __shared__ int s_cnt[];   // [kBlock/G][k]
-  __shared__ long long s_tmp[kBlock / kWave];
-  constexpr int kGroups = kBlock / G;
-  const WorkItem wi = work_item(L, contiguous_units((L.one.m + kGroups - 1) / kGroups));
+  extern __shared__ unsigned s_count[];   // per wave: NW x stride byte counters, k words
+  __shared__ unsigned char s_flag[kBlock / kWave][kCountFlight * kWave];
+  __shared__ long long s_km1;
+  const WorkItem wi = work_item(L, contiguous_units((L.one.m + kCountUnit - 1) / kCountUnit));
   if (wi.count == 0) return;
   const InstDesc D = inst_desc(L, wi.inst);
-  const int grp = threadIdx.x / G;
-  const int gl = threadIdx.x % G;
-  const int k = D.k, m = D.m, rw = D.rw;
-  int* cnt = s_cnt + grp * k;
+  const int k = D.k, m = D.m;
+  const int NW = count_nets(k), stride = count_stride(k);
+  const int lane = lane_id(), wv = threadIdx.x / kWave;
+  unsigned* cnt = s_count + (size_t)wv * (NW * stride + k);
+  int* big = reinterpret_cast<int*>(cnt + NW * stride);
+  unsigned char* flag = s_flag[wv];
+  const bool checked = (*D.err_flags & kErrPart) == 0;
+  const bool nibbles = k <= 16;
+  auto block = [&](int v) -> unsigned {
+    if (!checked) return (unsigned)D.part[v];
+    if (!nibbles) return D.part8[v];
+    return (D.part8[(unsigned)v >> 1] >> (4 * (v & 1))) & 15u;
+  };
   // Phi rows leave as 16-byte streaming stores when rows are 16-byte aligned
   const bool vec_phi = (k & 3) == 0 && ((uintptr_t)D.phi & 15) == 0;
+  if (threadIdx.x == 0) s_km1 = 0;
+  __syncthreads();
+#pragma unroll
+  for (int q = 0; q < kCountFlight; ++q) flag[q * kWave + lane] = 0;
+  for (int i = lane; i < NW * stride; i += kWave) cnt[i] = 0;
   long long km1_local = 0;
-  // the next net's pin range is loaded while this net's pins are counted
-  // (one dependent load fewer per net)
+  const int per_wave = kCountUnit / (kBlock / kWave), turns = per_wave / NW;
+  // first net of turn `it`, and lane's pin range in it (the next turn's is
+  // loaded while this one's pins are counted)
+  auto first_net = [&](int it) {
+    const long long unit = (long long)wi.first + (long long)(it / turns) * wi.stride;
+    return it < wi.count * turns ? unit * kCountUnit + wv * per_wave + (it % turns) * NW
+                                 : (long long)m;
+  };
   long long nb = 0, nt = 0;
-  {
-    const long long e0 = (long long)wi.first * kGroups + grp;
-    if (e0 < m) {
-      nb = D.eptr[e0];
-      nt = D.eptr[e0 + 1];
+  auto load_range = [&](long long e0) {
+    nb = nt = 0;
+    if (lane < NW && e0 + lane < m) {
+      nb = D.eptr[e0 + lane];
+      nt = D.eptr[e0 + lane + 1];
     }
-  }
-  for (int it = 0; it < wi.count; ++it) {
-    const long long e = ((long long)wi.first + (long long)it * wi.stride) * kGroups + grp;
-    const long long b = nb, t = nt;
-    if (e < m)
-      for (int i = gl; i < k; i += G) cnt[i] = 0;
+  };
+  load_range(first_net(0));
+  for (int it = 0; it < wi.count * turns; ++it) {
+    const long long e0 = first_net(it);
+    const long long b = nb;
+    const int len = (int)(nt - nb);
+    load_range(first_net(it + 1));
+    if (e0 >= m) continue;                                  // the same for the whole wave
+    const int nets = m - e0 < NW ? (int)(m - e0) : NW;
+    const long long e = e0 + lane;
+    const unsigned long long is_long = __ballot(len > kByteNet);
+    const int incl = wave_incl_scan(len);
+    const int total = last_lane(incl), first = incl - len;  // this net's place in the run
+    const long long run = __shfl(b, 0);
+    const int* pins = D.pins + run;
     wave_lds_sync();
-    if (it + 1 < wi.count) {
-      const long long en = e + (long long)wi.stride * kGroups;
-      nb = nt = 0;
-      if (en < m) {
-        nb = D.eptr[en];
-        nt = D.eptr[en + 1];
+    int before = -1;                                        // last net starting before this step
+    for (int s = 0; s < total; s += kCountFlight * kWave) {
+      int v[kCountFlight];
+#pragma unroll
+      for (int q = 0; q < kCountFlight; ++q) {
+        const int p = s + q * kWave + lane;
+        v[q] = p < total ? pins[p] : -1;
       }
+      if (len > 0 && first >= s && first < s + kCountFlight * kWave) flag[first - s] = 1;
+      unsigned id[kCountFlight];
+#pragma unroll
+      for (int q = 0; q < kCountFlight; ++q) id[q] = v[q] >= 0 ? block(v[q]) : ~0u;
+      wave_lds_sync();
+#pragma unroll
+      for (int q = 0; q < kCountFlight; ++q) {
+        const unsigned here = flag[q * kWave + lane];
+        flag[q * kWave + lane] = 0;
+        const unsigned long long starts = __ballot(here != 0);
+        const int net = lanes_below(starts, before) + (int)here;
+        before += __popcll(starts);
+        bool live = id[q] < (unsigned)k;
+        if (is_long) live = live && !((is_long >> (net & 63)) & 1ull);
+        // one add per run of equal (net, block) in neighbouring lanes
+        const unsigned key = live ? ((unsigned)net << 8) | id[q] : ~0u;
+        const unsigned prev = lane_before(key);
+        const unsigned long long heads = __ballot(lane == 0 || key != prev);
+        if (live && ((heads >> lane) & 1ull)) {
+          const unsigned long long later = heads >> lane >> 1;
+          const int run_len = later ? __ffsll((long long)later) : kWave - lane;
+          atomicAdd(&cnt[net * stride + (id[q] >> 2)], (unsigned)run_len << (8 * (id[q] & 3)));
+        }
+      }
+      wave_lds_sync();
     }
-    for (long long p0 = b + gl; p0 < t; p0 += kCountSlots * G) {
-      int v[kCountSlots];
+    // lane's net: bitsets from its counters
+    unsigned lam[WK], one[WK];
+    int lambda = 0;
 #pragma unroll
-      for (int q = 0; q < kCountSlots; ++q) v[q] = D.pins[p0 + q * G < t ? p0 + q * G : p0];
-#pragma unroll
-      for (int q = 0; q < kCountSlots; ++q) v[q] = D.part8[v[q]];
-#pragma unroll
-      for (int q = 0; q < kCountSlots; ++q) {
-        // part itself was checked by the block-weight sweep
-        if (p0 + q * G < t && (unsigned)v[q] < (unsigned)k) atomicAdd(&cnt[v[q]], 1);
+    for (int w = 0; w < WK; ++w) {
+      lam[w] = one[w] = 0;
+      if (lane < nets) {
+        for (int j = 0; j < 8 && w * 32 + 4 * j < k; ++j) {
+          unsigned nz, on;
+          byte_bits(cnt[lane * stride + w * 8 + j], nz, on);
+          lam[w] |= nz << (4 * j);
+          one[w] |= on << (4 * j);
+        }
+      }
+      lambda += __popc(lam[w]);
+    }
+    // Phi rows: the run of rows, 16 bytes (or one count) per lane and step
+    if (vec_phi) {
+      const int words = k >> 2, all = nets * words;
+      int row = lane / words, col = lane % words;           // words <= 64
+      const int drow = kWave / words, dcol = kWave % words;
+      for (int i = lane; i < all; i += kWave) {
+        const unsigned x = cnt[row * stride + col];
+        const i32x4 o = {(int)(x & 255u), (int)((x >> 8) & 255u), (int)((x >> 16) & 255u),
+                         (int)(x >> 24)};
+        if (!((is_long >> row) & 1ull))
+          __builtin_nontemporal_store(o, reinterpret_cast<i32x4*>(D.phi + e0 * k) + i);
+        row += drow;
+        col += dcol;
+        if (col >= words) {
+          col -= words;
+          ++row;
+        }
+      }
+    } else {
+      for (int i = lane; i < nets * k; i += kWave) {
+        const int row = i / k, col = i % k;
+        if (!((is_long >> row) & 1ull))
+          D.phi[e0 * k + i] = (int)((cnt[row * stride + (col >> 2)] >> (8 * (col & 3))) & 255u);
       }
     }
     wave_lds_sync();
-    if (e < m) {
-      const NetBits bits = net_bits<G>(k, gl, [&](int i) { return cnt[i]; });
-      int* phi_row = D.phi + e * (long long)k;
-      if (vec_phi) {
-        for (int i = gl; i < (k >> 2); i += G)
-          __builtin_nontemporal_store(reinterpret_cast<const i32x4*>(cnt)[i],
-                                      reinterpret_cast<i32x4*>(phi_row) + i);
-      } else {
-        for (int i = gl; i < k; i += G) phi_row[i] = cnt[i];
+    for (int i = lane; i < nets * stride; i += kWave) cnt[i] = 0;   // for the next nets
+    for (unsigned long long left = is_long; left; left &= left - 1) {
+      const int j = __ffsll((long long)left) - 1;
+      const long long lb = __shfl(b, j);
+      count_long_net(D, e0 + j, lb, lb + __shfl(len, j), big, block);
+      if (lane == j) {
+        lambda = 0;
+#pragma unroll
+        for (int w = 0; w < WK; ++w) {
+          lam[w] = one[w] = 0;
+          for (int i = 0; i < 32 && w * 32 + i < k; ++i) {
+            lam[w] |= (big[w * 32 + i] > 0 ? 1u : 0u) << i;
+            one[w] |= (big[w * 32 + i] == 1 ? 1u : 0u) << i;
+          }
+          lambda += __popc(lam[w]);
+        }
       }
+      wave_lds_sync();
+    }
+    if (lane < nets) {
       const int w = D.ewgt ? D.ewgt[e] : 1;
-      write_netrec(D.netstate + e * (long long)rw, gl, w, bits, k);
-      if (D.view != kViewFull) {
-        write_views(D, e, gl, bits);
-      } else if (gl < view_words(k)) {
-        // the compact copy is not used for weighted nets: keep it defined (zero)
-        D.view_ptr[e * view_words(k) + gl] = 0u;
-      }
-      if (gl == 0) km1_local += (long long)(bits.lambda - 1) * w;
+      write_record<WK>(D, e, w, lambda, lam, one);
+      km1_local += (long long)(lambda - 1) * w;
     }
-    wave_lds_sync();
   }
-  const long long tot = block_sum64(km1_local, s_tmp);
-  if (threadIdx.x == 0 && tot)
-    atomicAdd(&D.red[blockIdx.x % kSlots], (unsigned long long)tot);
+  km1_local = wave_sum(km1_local);
+  if (lane == 0 && km1_local) atomicAdd((unsigned long long*)&s_km1, (unsigned long long)km1_local);
+  __syncthreads();
+  if (threadIdx.x == 0 && s_km1)
+    atomicAdd(&D.red[blockIdx.x % kSlots], (unsigned long long)s_km1);
 }
 
 // Unit: one instance.  Sum its km1 slots into *km1 (or just clear them) and
@@ -151,11 +280,11 @@ __global__ __launch_bounds__(kBlock) void k_count_epilogue(Launch L, int want_km
   }
 }
 
-// Unit: kBwChunk consecutive vertices.  LDS partial sums per workgroup, then
-// one atomic per block into the workgroup's slot row (the epilogue folds the
-// rows into block_w).  Every vertex's block also goes to part8 (one byte).
-// With mark_eligible every vertex is also made eligible (the start of a
-// refinement).
+// Unit: kBwChunk consecutive vertices, eight per thread and step.  LDS partial
+// sums per workgroup, then one atomic per block into the workgroup's slot row
+// (the epilogue folds the rows into block_w).  Every vertex's block also goes to
+// part8, packed as the pin counts read it.  With mark_eligible every vertex is
+// also made eligible (the start of a refinement).
 __global__ __launch_bounds__(kBlock) void k_block_weights(Launch L, int mark_eligible) {
   __shared__ unsigned long long s_w[HG_MAX_K];
   const WorkItem wi = work_item(L, contiguous_units((L.one.n + kBwChunk - 1) / kBwChunk));
@@ -165,27 +294,68 @@ __global__ __launch_bounds__(kBlock) void k_block_weights(Launch L, int mark_eli
   for (int i = threadIdx.x; i < k; i += kBlock) s_w[i] = 0;
   __syncthreads();
   int err = 0;
-  constexpr int kPer = kBwChunk / kBlock;
+  constexpr int kRow = 8;                               // consecutive vertices per thread
+  constexpr int kPer = kBwChunk / (kBlock * kRow);
+  // eligible flags eight at a time where the caller's array allows it
+  const bool wide_flags = ((uintptr_t)D.eligible & 7) == 0;
+  const bool nibbles = k <= 16;
   for (int it = 0; it < wi.count; ++it) {
     const long long base = ((long long)wi.first + (long long)it * wi.stride) * kBwChunk;
     // every vertex's block and weight requested before the first wait
-    int blk[kPer], cw[kPer];
+    int blk[kPer][kRow], cw[kPer][kRow];
 #pragma unroll
     for (int j = 0; j < kPer; ++j) {
-      const long long v = base + (long long)j * kBlock + threadIdx.x;
-      blk[j] = v < n ? D.part[v] : 0;
-      cw[j] = v < n && D.vwgt ? D.vwgt[v] : 1;
+      const long long v = base + ((long long)j * kBlock + threadIdx.x) * kRow;
+      if (v + kRow <= n) {
+#pragma unroll
+        for (int h = 0; h < kRow; h += 4) {
+          const i32x4u x = load4_unaligned(D.part + v + h);
+#pragma unroll
+          for (int q = 0; q < 4; ++q) blk[j][h + q] = x[q];
+        }
+        if (D.vwgt) {
+#pragma unroll
+          for (int h = 0; h < kRow; h += 4) {
+            const i32x4u x = load4_unaligned(D.vwgt + v + h);
+#pragma unroll
+            for (int q = 0; q < 4; ++q) cw[j][h + q] = x[q];
+          }
+        }
+      } else {
+#pragma unroll
+        for (int q = 0; q < kRow; ++q) {
+          blk[j][q] = v + q < n ? D.part[v + q] : 0;
+          cw[j][q] = v + q < n && D.vwgt ? D.vwgt[v + q] : 1;
+        }
+      }
     }
 #pragma unroll
     for (int j = 0; j < kPer; ++j) {
-      const long long v = base + (long long)j * kBlock + threadIdx.x;
-      if (v < n) {
-        if (mark_eligible) D.eligible[v] = 1;
-        D.part8[v] = (unsigned char)blk[j];
-        if ((unsigned)blk[j] < (unsigned)k)
-          atomicAdd(&s_w[blk[j]], (unsigned long long)cw[j]);
+      const long long v = base + ((long long)j * kBlock + threadIdx.x) * kRow;
+      if (v >= n) continue;
+      const int have = n - v < kRow ? (int)(n - v) : kRow;
+      unsigned long long packed = 0;
+#pragma unroll
+      for (int q = 0; q < kRow; ++q) {
+        if (q < have) {
+          if ((unsigned)blk[j][q] < (unsigned)k)
+            atomicAdd(&s_w[blk[j][q]], (unsigned long long)(D.vwgt ? cw[j][q] : 1));
+          else
+            err = kErrPart;
+          packed |= nibbles ? (unsigned long long)(blk[j][q] & 15) << (4 * q)
+                            : (unsigned long long)(blk[j][q] & 255) << (8 * q);
+        }
+      }
+      // part8 holds whole groups of eight past n (see ws_layout)
+      if (nibbles)
+        *reinterpret_cast<unsigned*>(D.part8 + v / 2) = (unsigned)packed;
+      else
+        *reinterpret_cast<unsigned long long*>(D.part8 + v) = packed;
+      if (mark_eligible) {
+        if (wide_flags && have == kRow)
+          *reinterpret_cast<unsigned long long*>(D.eligible + v) = 0x0101010101010101ull;
         else
-          err = kErrPart;
+          for (int q = 0; q < have; ++q) D.eligible[v + q] = 1;
       }
     }
   }
@@ -226,26 +396,26 @@ static unsigned grid_cap(long long items, int per_block, int cap) {
   return (unsigned)b;
 }
 
-// Lanes per net for the net-centric sweeps (pin counts, finalize): enough
-// lanes to hold every word of the net record (2 + 2 * bit_words(k), padded),
-// and no more than that (but 8 for 4 < k <= 64): most nets have only a
-// handful of pins, so narrower groups put more nets' loads in flight per
-// wavefront.
+// Lanes per net for the finalize: enough lanes to hold every word of the net
+// record (2 + 2 * bit_words(k), padded), and no more than that (but 8 for
+// 4 < k <= 64): most nets have only a handful of pins, so narrower groups put
+// more nets' loads in flight per wavefront.
 int group_lanes(int k) {
   if (k <= 4) return 4;
   return net_words(k) > 8 ? net_words(k) : 8;
 }
 
-size_t pincount_lds(int G, int k) { return sizeof(int) * (size_t)(kBlock / G) * k; }
+size_t pincount_lds(int k) {
+  return sizeof(unsigned) * (size_t)(kBlock / kWave) *
+         ((size_t)count_nets(k) * count_stride(k) + k);
+}
 
-GroupKernel pincount_kernel(int k) { return pincount_kernel_g(group_lanes(k)); }
-
-GroupKernel pincount_kernel_g(int G) {
-  switch (G) {
+GroupKernel pincount_kernel(int k) {
+  switch (bit_words(k)) {
+    case 1: return k_pincounts<1>;
+    case 2: return k_pincounts<2>;
     case 4: return k_pincounts<4>;
-    case 8: return k_pincounts<8>;
-    case 16: return k_pincounts<16>;
-    default: return k_pincounts<32>;
+    default: return k_pincounts<8>;
   }
 }
 
@@ -254,8 +424,8 @@ void single_count_plan(const InstDesc& d, CountPlan& plan) {
   const Launch L = single_launch(d);
   PlanLaunch pc;
   pc.kernel = (void*)pincount_kernel(d.k);
-  pc.grid = grid_cap(d.m, kBlock / group_lanes(d.k), kStateGrid);
-  pc.lds = pincount_lds(group_lanes(d.k), d.k);
+  pc.grid = grid_cap(d.m, kCountUnit, kStateGrid);
+  pc.lds = pincount_lds(d.k);
   pc.L = L;
   plan.pincounts.push_back(pc);
   plan.instances.grid = 1;
