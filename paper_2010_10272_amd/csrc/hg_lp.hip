@@ -1135,7 +1135,7 @@ __global__ __launch_bounds__(kBlock) void k_finalize_cached(Launch L) {
       const unsigned old_word = gl >= 2 && gl < 2 + 2 * wk ? rec[gl] : 0u;
       NetBits nb = net_bits<G>(k, gl, [&](int i2) { return row[i2]; });
       if (gl >= 1 && gl < 2 + 2 * wk) rec[gl] = nb.word;
-      if (D.view != kViewFull) write_views(D, e, gl, nb);
+      write_views(D, e, gl, nb, true);
       if (gl == 1) dcheck += (long long)(lam_old - nb.lambda) * w;
       const long long b = D.eptr[e], t = D.eptr[e + 1];
       if (gl == 0) {
@@ -1156,134 +1156,187 @@ __global__ __launch_bounds__(kBlock) void k_finalize_cached(Launch L) {
   }
 }
 
-// Unit: a block of kFinalChunk (1024) nets.  Every thread reads four touched
-// flags with one load; the touched nets of the block are listed in LDS.
-// Groups of G lanes then rebuild each listed net's Lambda, S and lambda from
-// its final Phi row and clear its flag; the lane that rewrites lambda(e)
-// reads the old value first, so the drop (lambda_old - lambda_new) * w(e)
-// summed over touched nets checks the attributed total.  Last, the pins of
-// all listed nets are made eligible as one flattened list spread over the
-// whole workgroup (offsets by a prefix sum, owner by binary search), so a
-// long net does not serialize on one group.  With the gain cache the group
-// walks its net's pins itself (cache_net_delta marks them too).  Single
-// instance: contiguous XCD-aware runs of blocks.
-constexpr int kMarkSlots = 4;   // pin positions per thread in flight in the marks
+// Unit: a block of kFinalChunk (1024) nets, a quarter of it per wavefront.  The
+// wavefronts work on their own (no barrier): each reads its quarter's touched
+// flags, four per lane, queues the touched nets in LDS and takes them 64 at a
+// time.  Groups of G lanes rebuild each net's Lambda, S and lambda from its
+// final Phi row (the rows of several nets per group in flight); the lane that
+// rewrites lambda(e) reads the old value first, so the drop (lambda_old -
+// lambda_new) * w(e) summed over touched nets checks the attributed total.
+// Then the pins of the 64 nets are made eligible as one run laid end to end,
+// so a long net does not serialize on one group: a position's net is the count
+// of net starts at or before it (a flag per position in LDS, one ballot).
+// What bounds it is the chain flags -> offsets, rows -> pins -> marks, so what
+// counts is how many wavefronts run it at a time; a workgroup's list with a
+// scan and a binary search per pin kept four wavefronts waiting for each other:
+// netlist 73 -> 63 us per round, matrix k = 8 46 -> 39, k = 64 71 -> 61, tiny
+// 11 -> 7, 64 small hypergraphs 193 -> 127 (three widths).
+// Single instance: contiguous XCD-aware runs of blocks.
+constexpr int kMarkSlots = 4;                // pin positions per lane in flight in the marks
+constexpr int kFinalQuarter = kFinalChunk / (kBlock / kWave);   // 256 nets: four flags per lane
+static_assert(kFinalQuarter == 4 * kWave, "one 4-byte load of flags per lane");
+
+struct FinalizeLds {
+  int queue[kWave + kFinalQuarter];          // touched nets waiting
+  int shift[kWave];                          // first pin - place in the run, per net of a batch
+  unsigned char flag[kMarkSlots * kWave];
+};
+
+// Rows of q[0 .. cnt), cnt <= 64, G lanes per net, MC = ceil(k / G) rounded up.
+// Returns this lane's part of the lambda drop.
+template <int G, int MC>
+__device__ __forceinline__ long long finalize_rows(const InstDesc& D, const int* q, int cnt) {
+  constexpr int kAt = kWave / G;                           // nets per step
+  constexpr int kSteps = MC >= 8 ? 1 : MC >= 4 ? 2 : 4;    // steps in flight
+  constexpr int R = kSteps < G ? kSteps : G;
+  const int lane = lane_id(), gl = lane % G, grp = lane / G;
+  const int k = D.k, wk = bit_words(k), rw = D.rw;
+  long long drop = 0;
+  for (int i0 = 0; i0 < cnt; i0 += kAt * R) {
+    int e[R], cv[R][MC], lam_old[R], w[R];
+#pragma unroll
+    for (int r = 0; r < R; ++r) {
+      const int i = i0 + r * kAt + grp;
+      e[r] = q[i < cnt ? i : 0];
+      const int* row = D.phi + (long long)e[r] * k;
+      const unsigned* rec = D.netstate + (long long)e[r] * rw;
+#pragma unroll
+      for (int c = 0; c < MC; ++c) {
+        const int x = c * G + gl;
+        cv[r][c] = row[x < k ? x : k - 1];
+      }
+      lam_old[r] = w[r] = 0;
+      if (gl == 1) {
+        lam_old[r] = (int)rec[1];
+        w[r] = (int)rec[0];
+      }
+    }
+#pragma unroll
+    for (int r = 0; r < R; ++r) {
+      const bool live = i0 + r * kAt + grp < cnt;
+      const NetBits nb = net_bits_of<G, MC>(k, gl, cv[r]);
+      if (live) {
+        unsigned* rec = D.netstate + (long long)e[r] * rw;
+        if (gl >= 1 && gl < 2 + 2 * wk) rec[gl] = nb.word;
+        if (gl == 1) drop += (long long)(lam_old[r] - nb.lambda) * w[r];
+      }
+      write_views(D, e[r], gl, nb, live);
+    }
+  }
+  return drop;
+}
+
+template <int G>
+__device__ __forceinline__ void finalize_sweep(const InstDesc& D, const WorkItem& wi,
+                                               FinalizeLds& M, unsigned long long* s_sums) {
+  const int lane = lane_id(), wv = threadIdx.x / kWave;
+  const int k = D.k, chunks = (k + G - 1) / G;
+  long long dcheck = 0, tpins = 0;
+  int ntouched = 0;
+  for (int q = 0; q < kMarkSlots; ++q) M.flag[q * kWave + lane] = 0;
+  auto batch = [&](const int* q, int cnt) {
+    // lane's net: its pin range, its flag
+    int len = 0;
+    long long b = 0;
+    if (lane < cnt) {
+      const int e = q[lane];
+      b = D.eptr[e];
+      len = (int)(D.eptr[e + 1] - b);
+      D.touched[e] = 0;
+    }
+    if (chunks <= 1) dcheck += finalize_rows<G, 1>(D, q, cnt);
+    else if (chunks <= 2) dcheck += finalize_rows<G, 2>(D, q, cnt);
+    else if (chunks <= 4) dcheck += finalize_rows<G, 4>(D, q, cnt);
+    else dcheck += finalize_rows<G, 8>(D, q, cnt);
+    const int incl = wave_incl_scan(len);
+    const int total = last_lane(incl), first = incl - len;
+    ntouched += lane < cnt ? 1 : 0;
+    tpins += len;
+    M.shift[lane] = (int)b - first;                        // pin positions are below 2^31
+    int before = -1;                                       // last net starting before this step
+    for (int s = 0; s < total; s += kMarkSlots * kWave) {
+      if (len > 0 && first >= s && first < s + kMarkSlots * kWave) M.flag[first - s] = 1;
+      wave_lds_sync();
+      int v[kMarkSlots];
+#pragma unroll
+      for (int x = 0; x < kMarkSlots; ++x) {
+        const int p = s + x * kWave + lane;
+        const int here = M.flag[x * kWave + lane];
+        M.flag[x * kWave + lane] = 0;
+        const unsigned long long starts = __ballot(here != 0);
+        const int net = lanes_below(starts, before) + here;
+        before += __popcll(starts);
+        v[x] = p < total ? D.pins[M.shift[net] + p] : -1;
+      }
+#pragma unroll
+      for (int x = 0; x < kMarkSlots; ++x)
+        if (v[x] >= 0) D.eligible[v[x]] = 1;
+      wave_lds_sync();
+    }
+    wave_lds_sync();
+  };
+  // four flags per lane in one load (the flag array is padded to whole blocks
+  // and zero past m; the workspace keeps it 4-byte aligned); the next block's
+  // flags are loaded while this block is finalized
+  auto flags_at = [&](int it) {
+    const long long c = (long long)wi.first + (long long)it * wi.stride;
+    return it < wi.count ? *reinterpret_cast<const unsigned*>(
+                               D.touched + c * kFinalChunk + wv * kFinalQuarter + 4 * lane)
+                         : 0u;
+  };
+  unsigned next = flags_at(0);
+  int qn = 0;                                              // nets queued (wave-uniform)
+  // one call site of batch: the extra last iteration empties the queue
+  for (int it = 0; it <= wi.count; ++it) {
+    if (it < wi.count) {
+      const unsigned f4 = next;
+      next = flags_at(it + 1);
+      const int e0 = (int)(((long long)wi.first + (long long)it * wi.stride) * kFinalChunk) +
+                     wv * kFinalQuarter + 4 * lane;
+      int mine = 0;
+#pragma unroll
+      for (int x = 0; x < 4; ++x) mine += ((f4 >> (8 * x)) & 0xffu) != 0;
+      const int incl = wave_incl_scan(mine);
+      int at = qn + incl - mine;
+#pragma unroll
+      for (int x = 0; x < 4; ++x)
+        if ((f4 >> (8 * x)) & 0xffu) M.queue[at++] = e0 + x;
+      qn += last_lane(incl);
+      wave_lds_sync();
+    }
+    while (qn >= kWave || (it == wi.count && qn > 0)) {
+      const int cnt = qn < kWave ? qn : kWave;
+      batch(M.queue + (qn - cnt), cnt);                    // the last ones: nothing moves
+      qn -= cnt;
+    }
+  }
+  // counts below 2^31 (nets, pins): two to a sum
+  const long long np = wave_sum((long long)ntouched | (tpins << 32));
+  dcheck = wave_sum(dcheck);
+  if (lane == 0) {
+    atomicAdd(&s_sums[0], (unsigned long long)np);
+    atomicAdd(&s_sums[1], (unsigned long long)dcheck);
+  }
+  __syncthreads();
+  if (threadIdx.x == 0) {
+    const int sl = blockIdx.x % kSlots;
+    const unsigned long long nt = s_sums[0] & 0xffffffffu, tp = s_sums[0] >> 32;
+    if (s_sums[1]) atomicAdd(&D.ctr->slot[kCtrDeltaCheck][sl], s_sums[1]);
+    if (nt) atomicAdd(&D.ctr->slot[kCtrTouched][sl], nt);
+    if (tp) atomicAdd(&D.ctr->slot[kCtrTouchedPins][sl], tp);
+  }
+}
 
 template <int G>
 __global__ __launch_bounds__(kBlock) void k_finalize(Launch L) {
-  __shared__ int s_list[kFinalChunk];
-  __shared__ int s_off[kFinalChunk];        // first flattened pin position of each listed net
-  __shared__ int s_beg[kFinalChunk];        // eptr of each listed net (P < 2^31)
-  __shared__ long long s_tmp[kBlock / kWave];
-  __shared__ unsigned s_cnt;
-  constexpr int kGroups = kBlock / G;
-  constexpr int kFlags = kFinalChunk / kBlock;   // 4
+  __shared__ FinalizeLds s_wave[kBlock / kWave];
+  __shared__ unsigned long long s_sums[2];
   const WorkItem wi = work_item(L, xcd_block((L.one.m + kFinalChunk - 1) / kFinalChunk));
   if (wi.count == 0) return;
   const InstDesc D = inst_desc(L, wi.inst);
-  const int grp = threadIdx.x / G, gl = threadIdx.x % G;
-  const int k = D.k, wk = bit_words(k), rw = D.rw;
-  long long dcheck = 0, ntouched = 0, tpins = 0;
-  // four flags per thread in one load (the flag array is padded to whole
-  // blocks and zero past m; the workspace keeps it 4-byte aligned); the next
-  // block's flags are loaded while this block is finalized
-  unsigned next_f4 = *reinterpret_cast<const unsigned*>(
-      D.touched + (long long)wi.first * kFinalChunk + (long long)threadIdx.x * kFlags);
-  for (int it = 0; it < wi.count; ++it) {
-    const long long c = (long long)wi.first + (long long)it * wi.stride;
-    if (threadIdx.x == 0) s_cnt = 0;
-    __syncthreads();
-    const long long e0 = c * kFinalChunk + (long long)threadIdx.x * kFlags;
-    const unsigned f4 = next_f4;
-    if (it + 1 < wi.count)
-      next_f4 = *reinterpret_cast<const unsigned*>(D.touched + e0 + (long long)wi.stride * kFinalChunk);
-    int mine = 0;
-#pragma unroll
-    for (int q = 0; q < kFlags; ++q) mine += ((f4 >> (8 * q)) & 0xffu) != 0;
-    const int incl = wave_incl_scan(mine);
-    int base = 0;
-    if (lane_id() == kWave - 1 && incl) base = (int)atomicAdd(&s_cnt, (unsigned)incl);
-    base = __shfl(base, kWave - 1) + incl - mine;
-#pragma unroll
-    for (int q = 0; q < kFlags; ++q)
-      if ((f4 >> (8 * q)) & 0xffu) s_list[base++] = (int)(e0 + q);
-    __syncthreads();
-    const int cnt = (int)s_cnt;
-    ntouched += cnt;
-    for (int i = grp; i < cnt; i += kGroups) {
-      const int e = s_list[i];
-      const int* row = D.phi + (long long)e * k;
-      unsigned* rec = D.netstate + (long long)e * rw;
-      int lam_old = 0, w = 0;
-      if (gl == 1) {
-        lam_old = (int)rec[1];
-        w = (int)rec[0];
-      }
-      const long long b = D.eptr[e], t = D.eptr[e + 1];
-      NetBits nb = net_bits<G>(k, gl, [&](int i2) { return row[i2]; });
-      if (gl >= 1 && gl < 2 + 2 * wk) rec[gl] = nb.word;
-      if (D.view != kViewFull) write_views(D, e, gl, nb);
-      if (gl == 1) dcheck += (long long)(lam_old - nb.lambda) * w;
-      if (gl == 0) {
-        D.touched[e] = 0;
-        tpins += t - b;
-        s_beg[i] = (int)b;
-        s_off[i] = (int)(t - b);          // the length, until the scan below
-      }
-    }
-    {
-      __syncthreads();
-      // flattened pin positions: exclusive prefix of the lengths (four list
-      // entries per thread)
-      int len[kFlags];
-      long long sum = 0;
-#pragma unroll
-      for (int q = 0; q < kFlags; ++q) {
-        const int i = threadIdx.x * kFlags + q;
-        len[q] = i < cnt ? s_off[i] : 0;
-        sum += len[q];
-      }
-      long long total64;
-      long long off = block_excl_scan64(sum, s_tmp, &total64);
-#pragma unroll
-      for (int q = 0; q < kFlags; ++q) {
-        const int i = threadIdx.x * kFlags + q;
-        if (i < cnt) s_off[i] = (int)off;
-        off += len[q];
-      }
-      __syncthreads();
-      const int total = (int)total64;     // at most P < 2^31
-      for (int j0 = threadIdx.x; j0 < total; j0 += kBlock * kMarkSlots) {
-        int at[kMarkSlots];
-#pragma unroll
-        for (int q = 0; q < kMarkSlots; ++q) {
-          const int j = j0 + q * kBlock < total ? j0 + q * kBlock : j0;
-          // owner: the last listed net whose first position is <= j
-          int lo = 0, hi = cnt - 1;
-          while (lo < hi) {
-            const int mid = (lo + hi + 1) >> 1;
-            if (s_off[mid] <= j) lo = mid; else hi = mid - 1;
-          }
-          at[q] = s_beg[lo] + (j - s_off[lo]);
-        }
-        int v[kMarkSlots];
-#pragma unroll
-        for (int q = 0; q < kMarkSlots; ++q) v[q] = D.pins[at[q]];
-#pragma unroll
-        for (int q = 0; q < kMarkSlots; ++q)
-          if (j0 + q * kBlock < total) D.eligible[v[q]] = 1;
-      }
-    }
-    __syncthreads();
-  }
-  dcheck = block_sum64(dcheck, s_tmp);
-  tpins = block_sum64(tpins, s_tmp);
-  if (threadIdx.x == 0) {
-    const int sl = blockIdx.x % kSlots;
-    if (dcheck) atomicAdd(&D.ctr->slot[kCtrDeltaCheck][sl], (unsigned long long)dcheck);
-    if (ntouched) atomicAdd(&D.ctr->slot[kCtrTouched][sl], (unsigned long long)ntouched);
-    if (tpins) atomicAdd(&D.ctr->slot[kCtrTouchedPins][sl], (unsigned long long)tpins);
-  }
+  if (threadIdx.x < 2) s_sums[threadIdx.x] = 0;
+  __syncthreads();
+  finalize_sweep<G>(D, wi, s_wave[threadIdx.x / kWave], s_sums);
 }
 
 // Unit: one instance.  Fold the apply's block-weight slots into block_w, sum

@@ -16,46 +16,29 @@ struct NetBits {
   unsigned word;   // record word with index = lane-in-group (valid for 1 <= gl < 2+2W)
 };
 
-// get(i) -> Phi(e,i).  The first MC chunks' counts are loaded up front,
-// unconditionally (indices past k clamped, values masked), so that their
-// loads are in flight together; further chunks are read one at a time.
-template <int G, int MC, typename Get>
-__device__ __forceinline__ NetBits net_bits_mc(int k, int gl, Get get) {
+// The bits from the counts cv[c] = Phi(e, c * G + gl) of this lane (MC of them,
+// at least ceil(k / G); those past k are ignored).
+template <int G, int MC>
+__device__ __forceinline__ NetBits net_bits_of(int k, int gl, const int (&cv)[MC]) {
   const int wk = bit_words(k);
   const int shift = (G == kWave) ? 0 : (lane_id() / G) * G;
   const unsigned long long gmask = (G == kWave) ? ~0ull : ((1ull << (G % kWave)) - 1);
   NetBits r;
   r.lambda = 0;
   r.word = 0;
-  const int nchunks = (k + G - 1) / G;
-  int cvs[MC];
 #pragma unroll
   for (int c = 0; c < MC; ++c) {
-    const int i = c * G + gl;
-    cvs[c] = get(i < k ? i : k - 1);
-  }
-#pragma unroll
-  for (int c = 0; c < MC; ++c)
-    if (!(c < nchunks && c * G + gl < k)) cvs[c] = 0;
-  for (int c = 0; c < nchunks; ++c) {
-    int i = c * G + gl;
-    int cv = 0;
-    if (c < MC) {
-#pragma unroll
-      for (int x = 0; x < MC; ++x)
-        if (x == c) cv = cvs[x];
-    } else if (i < k) {
-      cv = get(i);
-    }
-    unsigned long long nz = (__ballot(cv > 0) >> shift) & gmask;
-    unsigned long long one = (__ballot(cv == 1) >> shift) & gmask;
+    if (c * G >= k) break;                  // the same for every lane
+    const int x = c * G + gl < k ? cv[c] : 0;
+    const unsigned long long nz = (__ballot(x > 0) >> shift) & gmask;
+    const unsigned long long one = (__ballot(x == 1) >> shift) & gmask;
     r.lambda += __popcll(nz);
     if (G <= 32) {                    // chunk c fills bits [c*G % 32, +G) of word c*G/32
       const int wd = (c * G) >> 5, sh = (c * G) & 31;
       if (gl == 2 + wd) r.word |= (unsigned)nz << sh;
       if (gl == 2 + wk + wd) r.word |= (unsigned)one << sh;
     } else {
-      int j0 = 2 * c;
+      const int j0 = 2 * c;
       if (gl == 2 + j0) r.word = (unsigned)nz;
       if (gl == 3 + j0) r.word = (unsigned)(nz >> 32);
       if (gl == 2 + wk + j0) r.word = (unsigned)one;
@@ -66,9 +49,21 @@ __device__ __forceinline__ NetBits net_bits_mc(int k, int gl, Get get) {
   return r;
 }
 
-// Record bits of one net with G lanes: as many up-front loads as k has
-// chunks of G blocks (1, 2, 4, or 8 and more).  k is the same for every lane
-// of the wavefront, so the branch does not diverge.
+// Record bits of one net with G lanes; get(i) -> Phi(e,i).  Every chunk's count
+// is requested up front (indices past k clamped), as many as k has chunks of G
+// blocks rounded up to 1, 2, 4 or 8.  k is the same for every lane of the
+// wavefront, so the branch does not diverge.
+template <int G, int MC, typename Get>
+__device__ __forceinline__ NetBits net_bits_mc(int k, int gl, Get get) {
+  int cv[MC];
+#pragma unroll
+  for (int c = 0; c < MC; ++c) {
+    const int i = c * G + gl;
+    cv[c] = get(i < k ? i : k - 1);
+  }
+  return net_bits_of<G, MC>(k, gl, cv);
+}
+
 template <int G, typename Get>
 __device__ __forceinline__ NetBits net_bits(int k, int gl, Get get) {
   const int nchunks = (k + G - 1) / G;
@@ -81,10 +76,12 @@ __device__ __forceinline__ NetBits net_bits(int k, int gl, Get get) {
 // Write net e's entry of the compact Lambda/S views (NetView) from the record
 // words held by the group's lanes (lane 2.. holds Lambda, then S): the one
 // behind the records, and the refine call's own narrower one when there is
-// one.  All lanes of the group must call it.
+// one.  All lanes of the wavefront must call it; only `live` groups write.
 __device__ __forceinline__ void write_views(const InstDesc& D, long long e, int gl,
-                                            const NetBits& b) {
+                                            const NetBits& b, bool live) {
+  if (D.view == kViewFull || D.view == kViewUnit) return;
   const unsigned next = __shfl(b.word, lane_id() + 1);   // the word of lane gl + 1
+  if (!live) return;
   if (D.view == kView16) {
     if (gl == 2) {
       D.view_ptr[e] = (b.word & 0xffffu) | (next << 16);
