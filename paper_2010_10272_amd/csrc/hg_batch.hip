@@ -170,8 +170,9 @@ size_t build_plans(const std::vector<BatchMember>& mem, const std::vector<int>& 
     }
     if (cp) {
       KindItems* p = variant(pc, (void*)pincount_kernel(k));
-      add_split(*p, i, ceil_div(g->m, kBlock), S.count_chunks, home[i]);
-      p->lds = std::max(p->lds, pincount_lds(k));
+      const int unit = count_unit(k, g->m);            // at most kBlock nets
+      add_split(*p, i, ceil_div(g->m, unit), S.count_chunks * (kBlock / unit), home[i]);
+      p->lds = std::max(p->lds, pincount_lds(k, g->m));
       add_split(verts, i, ceil_div(g->n, kBwChunk), 1, home[i]);
     }
     inst.flat.push_back(WorkItem{i, 0, 1, 1});

@@ -39,6 +39,16 @@ struct CountPlan {
   PlanLaunch vertices;      // block weights: units of kBwChunk vertices
 };
 
+// Nets per unit of the pin counts: 64 per wavefront (32 for k > 128, whose
+// counters fill the LDS), fewer where that leaves under eight wavefronts per
+// compute unit (1,510 nets at k = 100: pin counts and gains 50 us with 64, 41
+// with 8).
+__host__ __device__ inline int count_unit(int k, long long m) {
+  int nets = k > 128 ? 32 : 64;
+  while (nets > 8 && m < 2048LL * nets) nets >>= 1;
+  return nets * (kBlock / kWave);
+}
+
 constexpr int kBwChunk = kBlock * 16;   // vertices per unit of the block-weight sweep
 
 SelectKernel select_kernel(int k, int view, long long P, int n);
@@ -46,8 +56,8 @@ SelectKernel select_kernel(int k, int view, long long P, int n);
 // gain-cache deltas (it must be used exactly when the descriptor has a cache)
 FinalizeKernel finalize_kernel(int k, bool cache);
 FinalizeKernel finalize_kernel_g(int G, bool cache);   // G lanes per net (4, 8, 16 or 32)
-GroupKernel pincount_kernel(int k);          // units of 256 nets
-size_t pincount_lds(int k);                  // its dynamic LDS bytes
+GroupKernel pincount_kernel(int k);          // units of count_unit nets
+size_t pincount_lds(int k, long long m);     // its dynamic LDS bytes
 GainsKernel gains_kernel(int k, int view);
 int group_lanes(int k);
 

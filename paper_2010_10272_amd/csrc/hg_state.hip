@@ -36,12 +36,9 @@ __device__ __forceinline__ WorkItem contiguous_units(long long units) {
 // beyond (2 and 4 MB on a 4M-vertex netlist, where an XCD's L2 has 4 MB, instead
 // of 16 MB).  If that sweep met an id outside [0, k), the ids come from the
 // partition itself, so that such vertices are skipped.
-constexpr int kCountUnit = kBlock;           // nets per unit: 64 per wavefront
 constexpr int kCountFlight = 4;              // pins in flight per lane
 constexpr int kByteNet = 255;                // longest net whose counts surely fit a byte
 
-// Nets a wavefront takes at a time (the counters of 64 fill the LDS for k > 128).
-__host__ __device__ __forceinline__ int count_nets(int k) { return k > 128 ? 32 : 64; }
 // Words of a net's byte counters in LDS: odd, so that lanes reading their own
 // nets' word i use all banks.
 __host__ __device__ __forceinline__ int count_stride(int k) { return ((k + 3) / 4) | 1; }
@@ -73,7 +70,7 @@ __device__ void count_long_net(const InstDesc& D, long long e, long long b, long
   for (int i = lane; i < k; i += kWave) D.phi[e * k + i] = cnt[i];
 }
 
-// Unit: kCountUnit consecutive nets.  What bounds it: the block ids' gathers
+// Unit: count_unit consecutive nets.  What bounds it: the block ids' gathers
 // (lines outstanding per compute unit).  A lane group per net (8 lanes, four
 // slots each) left two thirds of the gather slots empty on nets of ten pins and
 // half the lanes idle; here every lane has a pin.  Pins of a net in one block
@@ -87,11 +84,13 @@ __global__ __launch_bounds__(kBlock) void k_pincounts(Launch L) {
   extern __shared__ unsigned s_count[];   // per wave: NW x stride byte counters, k words
   __shared__ unsigned char s_flag[kBlock / kWave][kCountFlight * kWave];
   __shared__ long long s_km1;
-  const WorkItem wi = work_item(L, contiguous_units((L.one.m + kCountUnit - 1) / kCountUnit));
+  const WorkItem wi = work_item(L, contiguous_units((L.one.m + count_unit(L.one.k, L.one.m) - 1) /
+                                                     count_unit(L.one.k, L.one.m)));
   if (wi.count == 0) return;
   const InstDesc D = inst_desc(L, wi.inst);
   const int k = D.k, m = D.m;
-  const int NW = count_nets(k), stride = count_stride(k);
+  const int unit_nets = count_unit(k, m), NW = unit_nets / (kBlock / kWave);
+  const int stride = count_stride(k);
   const int lane = lane_id(), wv = threadIdx.x / kWave;
   unsigned* cnt = s_count + (size_t)wv * (NW * stride + k);
   int* big = reinterpret_cast<int*>(cnt + NW * stride);
@@ -111,13 +110,12 @@ __global__ __launch_bounds__(kBlock) void k_pincounts(Launch L) {
   for (int q = 0; q < kCountFlight; ++q) flag[q * kWave + lane] = 0;
   for (int i = lane; i < NW * stride; i += kWave) cnt[i] = 0;
   long long km1_local = 0;
-  const int per_wave = kCountUnit / (kBlock / kWave), turns = per_wave / NW;
   // first net of turn `it`, and lane's pin range in it (the next turn's is
   // loaded while this one's pins are counted)
   auto first_net = [&](int it) {
-    const long long unit = (long long)wi.first + (long long)(it / turns) * wi.stride;
-    return it < wi.count * turns ? unit * kCountUnit + wv * per_wave + (it % turns) * NW
-                                 : (long long)m;
+    return it < wi.count
+               ? ((long long)wi.first + (long long)it * wi.stride) * unit_nets + wv * NW
+               : (long long)m;
   };
   long long nb = 0, nt = 0;
   auto load_range = [&](long long e0) {
@@ -128,7 +126,7 @@ __global__ __launch_bounds__(kBlock) void k_pincounts(Launch L) {
     }
   };
   load_range(first_net(0));
-  for (int it = 0; it < wi.count * turns; ++it) {
+  for (int it = 0; it < wi.count; ++it) {
     const long long e0 = first_net(it);
     const long long b = nb;
     const int len = (int)(nt - nb);
@@ -405,9 +403,9 @@ int group_lanes(int k) {
   return net_words(k) > 8 ? net_words(k) : 8;
 }
 
-size_t pincount_lds(int k) {
-  return sizeof(unsigned) * (size_t)(kBlock / kWave) *
-         ((size_t)count_nets(k) * count_stride(k) + k);
+size_t pincount_lds(int k, long long m) {
+  return sizeof(unsigned) *
+         ((size_t)count_unit(k, m) * count_stride(k) + (size_t)(kBlock / kWave) * k);
 }
 
 GroupKernel pincount_kernel(int k) {
@@ -424,8 +422,8 @@ void single_count_plan(const InstDesc& d, CountPlan& plan) {
   const Launch L = single_launch(d);
   PlanLaunch pc;
   pc.kernel = (void*)pincount_kernel(d.k);
-  pc.grid = grid_cap(d.m, kCountUnit, kStateGrid);
-  pc.lds = pincount_lds(d.k);
+  pc.grid = grid_cap(d.m, count_unit(d.k, d.m), kStateGrid);
+  pc.lds = pincount_lds(d.k, d.m);
   pc.L = L;
   plan.pincounts.push_back(pc);
   plan.instances.grid = 1;
