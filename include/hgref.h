@@ -356,10 +356,8 @@ typedef struct {
   int32_t select_chunks;     /* 256-vertex chunks per select workgroup, 1..64    */
   int32_t finalize_chunks;   /* 1024-net blocks per finalize workgroup, 1..64    */
   int32_t count_chunks;      /* 256-net chunks per pin-count workgroup, 1..64    */
-  int32_t net_lanes;         /* lanes per net in the finalize
-                                sweep: 0 = the minimum for k (4 for k <= 4, 8
-                                for k <= 64, 16 for k <= 128, else 32), or 4, 8,
-                                16, 32 (raised to that minimum)                  */
+  int32_t net_lanes;         /* 0, 4, 8, 16 or 32; has no effect any more (the
+                                finalize takes a lane per net for every k)       */
 } hg_schedule;
 
 /* Size classes, by vertex count n: [0, 2^13), [2^13, 2^16), [2^16, 2^19),

@@ -226,11 +226,13 @@ InstDesc make_desc(hg_graph_s* g, int k, long long lmax, int* part, int* phi,
   return d;
 }
 
-// The load's sort buffers are free once the graph is loaded; calls that count
-// the pins before their rounds keep the select's view there (at most 2 bytes a
-// net, and P >= m words).
-void keep_sweep_view(hg_graph_s* g, InstDesc& d) {
-  const int v = sweep_view(d.view, d.k);
+// Calls that count the pins before their rounds keep part8 up to date and a
+// narrower view for the select.  The load's sort buffers are free once the graph
+// is loaded: the view (at most 2 bytes a net, and P >= m words) goes there.
+// batch: members of k <= 4 share the launch, and so the view, of k <= 8.
+void keep_private_copies(hg_graph_s* g, InstDesc& d, bool batch) {
+  d.kept = 1;
+  const int v = sweep_view(d.view, d.k, batch);
   if (v == d.view) return;
   d.sweep = v;
   d.sview = (unsigned char*)(g->ws + g->lay.lkey[0]);
@@ -421,7 +423,7 @@ static hipError_t enqueue_refine(hg_graph g, int k, long long lmax, int rounds, 
                                  hipStream_t s) {
   hg::InstDesc d = hg::make_desc(g, k, lmax, part, phi, netstate, (long long*)block_w, eligible,
                                  nullptr, (long long*)km1, stats);
-  hg::keep_sweep_view(g, d);
+  hg::keep_private_copies(g, d, false);
   hg::CountPlan cplan;
   hg::single_count_plan(d, cplan);
   hipError_t e = hg::launch_counts(cplan, true, true, s);

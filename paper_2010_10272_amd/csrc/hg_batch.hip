@@ -38,21 +38,21 @@ size_t align256(size_t x) { return (x + 255) & ~(size_t)255; }
 
 long long ceil_div(long long a, long long b) { return (a + b - 1) / b; }
 
-int net_lanes(int k, int want) { return want > group_lanes(k) ? want : group_lanes(k); }
-
 // Work items of one launch, queued per XCD (split) or in one list.
 struct KindItems {
   void* kernel = nullptr;
+  void* kept_kernel = nullptr;
   size_t lds = 0;
   std::vector<WorkItem> q[kNumXcd];
   std::vector<WorkItem> flat;
 };
 
-KindItems* variant(std::vector<KindItems>& v, void* kernel) {
+KindItems* variant(std::vector<KindItems>& v, void* kernel, void* kept_kernel = nullptr) {
   for (KindItems& x : v)
-    if (x.kernel == kernel) return &x;
+    if (x.kernel == kernel && x.kept_kernel == kept_kernel) return &x;
   v.push_back(KindItems());
   v.back().kernel = kernel;
+  v.back().kept_kernel = kept_kernel;
   return &v.back();
 }
 
@@ -152,14 +152,16 @@ size_t build_plans(const std::vector<BatchMember>& mem, const std::vector<int>& 
                            nullptr, M.km1, M.stats);
     d.hist_reps = home[i] < 0 ? kHistReplicas : 1;
     d.round_base = M.round_base;
+    keep_private_copies(g, d, true);
     descs[i] = d;
     const int k = M.k;
-    const int G = net_lanes(k, S.net_lanes);
     if (rp) {
-      add_split(*variant(sel, (void*)select_kernel(k, d.sweep, d.P, d.n)), i, ceil_div(g->n, kBlock),
-                S.select_chunks, home[i]);
-      add_split(*variant(fin, (void*)finalize_kernel_g(G, false)), i, ceil_div(g->m, kFinalChunk),
-                S.finalize_chunks, home[i]);
+      add_split(*variant(sel, (void*)select_kernel(k, d.view, d.P, d.n),
+                         (void*)select_kernel(k, d.sweep, d.P, d.n)),
+                i, ceil_div(g->n, kBlock), S.select_chunks, home[i]);
+      KindItems* f = variant(fin, (void*)finalize_kernel(k, false));
+      add_split(*f, i, ceil_div(g->m, kFinalChunk), S.finalize_chunks, home[i]);
+      f->lds = std::max(f->lds, finalize_lds(k, false));
       for (long long h = 0; h < ceil_div(g->info.heavy_count, kHeavyPerGroup); ++h)
         heavy.flat.push_back(WorkItem{i, (int)h, 1, 1});
       if (g->info.heavy_count > 0) any_heavy = true;
@@ -210,6 +212,7 @@ size_t build_plans(const std::vector<BatchMember>& mem, const std::vector<int>& 
     }
     L.xoff[kNumXcd] = (int)run;
     pl.kernel = kind.kernel;
+    pl.kept_kernel = kind.kept_kernel;
     pl.lds = kind.lds;
     pl.grid = (unsigned)(longest * kNumXcd);
     pl.L = L;
@@ -249,11 +252,24 @@ size_t build_plans(const std::vector<BatchMember>& mem, const std::vector<int>& 
     for (const KindItems& k : pc) {
       cp->pincounts.push_back(PlanLaunch());
       emit_split(k, cp->pincounts.back());
+      cp->pincounts.back().L.kept = 1;   // the private views too, whoever runs the rounds
     }
     emit_flat(inst, cp->instances);
     emit_split(verts, cp->vertices);
   }
   return ok ? off : 0;
+}
+
+RoundPlan kept_plan(const RoundPlan& plan) {
+  RoundPlan p = plan;
+  for (PlanLaunch& pl : p.select) {
+    pl.kernel = pl.kept_kernel;
+    pl.L.kept = 1;
+  }
+  for (PlanLaunch& pl : p.heavy) pl.L.kept = 1;
+  for (PlanLaunch& pl : p.finalize) pl.L.kept = 1;
+  p.approve.L.kept = 1;
+  return p;
 }
 
 }  // namespace hg
@@ -268,6 +284,7 @@ struct hg_batch_s {
   hipEvent_t copied = nullptr;  // the last table copy
   bool copy_pending = false;
   hg::RoundPlan round;
+  hg::RoundPlan kept_round;     // the same for refine calls (InstDesc::kept)
   hg::CountPlan counts;
   unsigned long long table_gen = 0;
   void* graph_exec = nullptr;
@@ -305,7 +322,10 @@ hg_status build_tables(hg_batch_s* b, const std::vector<int>& which, const hg_sc
 }
 
 hg_status build_all(hg_batch_s* b, hipStream_t s) {
-  return build_tables(b, iota_vec(b->members.size()), b->sched, s, b->round, b->counts);
+  const hg_status st =
+      build_tables(b, iota_vec(b->members.size()), b->sched, s, b->round, b->counts);
+  if (st == HG_OK) b->kept_round = kept_plan(b->round);
+  return st;
 }
 
 void drop_graph(hg_batch_s* b) {
@@ -438,7 +458,7 @@ hg_status hg_batch_refine(hg_batch b, int32_t rounds, int32_t use_graph, void* s
   if (rounds < 0) return fail(HG_ERR_INVALID, "rounds must be >= 0");
   hipStream_t s = (hipStream_t)stream;
   if (!use_graph) {
-    HG_TRY(hg::enqueue_batch(b->round, b->counts, rounds, s), "batch refine");
+    HG_TRY(hg::enqueue_batch(b->kept_round, b->counts, rounds, s), "batch refine");
     return HG_OK;
   }
   if (!b->graph_exec || b->graph_rounds != rounds || b->graph_gen != b->table_gen) {
@@ -450,7 +470,7 @@ hg_status hg_batch_refine(hg_batch b, int32_t rounds, int32_t use_graph, void* s
     }
     hipStream_t cs = (hipStream_t)b->cap_stream;
     HG_TRY(hipStreamBeginCapture(cs, hipStreamCaptureModeThreadLocal), "hipStreamBeginCapture");
-    hipError_t e = hg::enqueue_batch(b->round, b->counts, rounds, cs);
+    hipError_t e = hg::enqueue_batch(b->kept_round, b->counts, rounds, cs);
     hipGraph_t graph = nullptr;
     hipError_t e2 = hipStreamEndCapture(cs, &graph);
     if (e != hipSuccess) {
@@ -510,11 +530,12 @@ hg_status hg_batch_autotune(hg_batch b, int32_t* part_save, int64_t save_elems, 
   auto trial_ms = [&](const std::vector<int>& which, const hg_schedule* trial, float* best_ms) {
     hg_status r = hg::build_tables(b, which, trial, s, rp, cp);
     if (r != HG_OK) return r;
+    const hg::RoundPlan kept = hg::kept_plan(rp);
     *best_ms = 1e30f;
     for (int rep = 0; rep < repeats; ++rep) {
       if ((r = restore(which)) != HG_OK) return r;
       HG_TRY(hipEventRecord(ev[0], s), "hipEventRecord");
-      HG_TRY(hg::enqueue_batch(rp, cp, 1, s), "tuning trial");
+      HG_TRY(hg::enqueue_batch(kept, cp, 1, s), "tuning trial");
       HG_TRY(hipEventRecord(ev[1], s), "hipEventRecord");
       HG_TRY(hipEventSynchronize(ev[1]), "hipEventSynchronize");
       float ms = 0.0f;
@@ -524,28 +545,24 @@ hg_status hg_batch_autotune(hg_batch b, int32_t* part_save, int64_t save_elems, 
     return (hg_status)HG_OK;
   };
   static const int kChunkCands[] = {1, 2, 4, 8, 16};
-  static const int kLaneCands[] = {0, 8, 16, 32};
   for (int c = 0; c < HG_SIZE_CLASSES && st == HG_OK; ++c) {
     std::vector<int> which;
     for (int i = 0; i < cnt; ++i)
       if (b->members[i].cls == c) which.push_back(i);
     if (which.empty()) continue;
-    for (int field = 0; field < 4 && st == HG_OK; ++field) {
-      const int* cands = field == 3 ? kLaneCands : kChunkCands;
-      const int ncand = field == 3 ? 4 : 5;
+    for (int field = 0; field < 3 && st == HG_OK; ++field) {
       int32_t* slot = field == 0   ? &cur[c].select_chunks
                       : field == 1 ? &cur[c].finalize_chunks
-                      : field == 2 ? &cur[c].count_chunks
-                                   : &cur[c].net_lanes;
+                                   : &cur[c].count_chunks;
       float best_t = 1e30f;
       int best_v = *slot;
-      for (int j = 0; j < ncand && st == HG_OK; ++j) {
-        *slot = cands[j];
+      for (int j = 0; j < 5 && st == HG_OK; ++j) {
+        *slot = kChunkCands[j];
         float t = 0.0f;
         st = trial_ms(which, cur, &t);
         if (st == HG_OK && t < best_t) {
           best_t = t;
-          best_v = cands[j];
+          best_v = kChunkCands[j];
         }
       }
       *slot = best_v;

@@ -113,6 +113,7 @@ struct InstDesc {
   int hist_stride;               // k_max * kBuckets: distance between histogram replicas
   int hist_reps;                 // histogram replicas in use (workgroup b adds to b % hist_reps)
   int sweep;                     // NetView that the select reads: view, or sview's kind
+  int kept;                      // part8 follows part: this call counted the pins and runs the rounds
   int round_base;                // round r's record goes to stats[r - round_base]
   long long P, lmax;
   const long long* eptr;
@@ -142,7 +143,7 @@ struct InstDesc {
   int* err_flags;
   unsigned long long* red;
   long long* bw_slots;           // kSlots x k block-weight deltas of a round's moves
-  unsigned char* part8;          // packed copy of part written by the block-weight sweep
+  unsigned char* part8;          // packed copy of part: 4 bits a vertex for k <= 16, else 8
   unsigned char* appr;           // monotone rounds: approve marks moves here instead of applying
   int4* seq_cell;                // monotone rounds: per (net, block) cells the marking sets empty
   int* cache;                    // gain cache (b[n], w(I)[n], p[n*k]); null: none
@@ -170,7 +171,7 @@ struct Launch {
   int round;                     // round record index: stats + round (k_round_stats)
   int split;
   int xoff[kNumXcd + 1];
-  int pad;
+  int kept;                      // batch: InstDesc::kept of every member (0: nor is sview)
   InstDesc one;
 };
 
@@ -193,7 +194,11 @@ __device__ __forceinline__ WorkItem work_item(const Launch& L, WorkItem fallback
 }
 
 __device__ __forceinline__ InstDesc inst_desc(const Launch& L, int inst) {
-  return L.descs ? L.descs[inst] : L.one;
+  if (!L.descs) return L.one;
+  InstDesc d = L.descs[inst];
+  d.kept = L.kept;
+  if (!L.kept) d.sweep = d.view;
+  return d;
 }
 
 // Launch argument for one instance (kernels take their units from blockIdx).
@@ -204,7 +209,7 @@ inline Launch single_launch(const InstDesc& d) {
   L.round = 0;
   L.split = 0;
   for (int x = 0; x <= kNumXcd; ++x) L.xoff[x] = 0;
-  L.pad = 0;
+  L.kept = d.kept;
   L.one = d;
   return L;
 }
@@ -274,8 +279,8 @@ __host__ __device__ inline int net_view(int k, bool unit_nets) {
 }
 
 // The copy that a refine call keeps for its select sweeps, or `view` itself.
-inline int sweep_view(int view, int k) {
-  return view != kView16 ? view : k <= 4 ? kView4 : k <= 8 ? kView8 : kView16;
+inline int sweep_view(int view, int k, bool batch) {
+  return view != kView16 ? view : k <= 4 && !batch ? kView4 : k <= 8 ? kView8 : kView16;
 }
 
 __host__ __device__ inline int view_bytes(int view) {
@@ -376,6 +381,6 @@ inline int lds_buckets(int k) {
 InstDesc make_desc(hg_graph_s* g, int k, long long lmax, int* part, int* phi,
                    unsigned* netstate, long long* block_w, unsigned char* eligible,
                    unsigned char* moved, long long* km1, hg_round_stats* stats);
-void keep_sweep_view(hg_graph_s* g, InstDesc& d);
+void keep_private_copies(hg_graph_s* g, InstDesc& d, bool batch);
 
 }  // namespace hg

@@ -4,6 +4,7 @@
 
 #include <vector>
 
+#include "hg_count.h"
 #include "hg_internal.h"
 
 namespace hg {
@@ -17,19 +18,24 @@ typedef void (*GainsKernel)(Launch);
 
 struct PlanLaunch {
   void* kernel = nullptr;   // for templated kernels: which instantiation
+  void* kept_kernel = nullptr;   // batched select: the same where the private views are kept
   unsigned grid = 0;
-  size_t lds = 0;           // dynamic LDS bytes (pin counts)
+  size_t lds = 0;           // dynamic LDS bytes (pin counts, finalize)
   Launch L{};
 };
 
 // One LP round: select launches (one per kernel variant in a batch), heavy
 // select, per-block kernels (threshold, overflow, tilescan), tiles, approve,
-// finalize launches (one per group width), stats.
+// finalize launches (one per bitset width), stats.
 struct RoundPlan {
   std::vector<PlanLaunch> select, heavy, finalize;
   PlanLaunch blocks, tiles, approve, stats;
   bool any_heavy = false;
 };
+
+// The plan of calls that count the pins and run the rounds (InstDesc::kept), from
+// a batch's plan.
+RoundPlan kept_plan(const RoundPlan& plan);
 
 // Pin counts (one launch per bitset width), then the per-instance km1 slot
 // sums, the block-weight reset and sweep.
@@ -39,12 +45,11 @@ struct CountPlan {
   PlanLaunch vertices;      // block weights: units of kBwChunk vertices
 };
 
-// Nets per unit of the pin counts: 64 per wavefront (32 for k > 128, whose
-// counters fill the LDS), fewer where that leaves under eight wavefronts per
-// compute unit (1,510 nets at k = 100: pin counts and gains 50 us with 64, 41
-// with 8).
+// Nets per unit of the pin counts: as many as a wavefront counts at a time,
+// fewer where that leaves under eight wavefronts per compute unit (1,510 nets
+// at k = 100: pin counts and gains 50 us with 64, 45 with 8).
 __host__ __device__ inline int count_unit(int k, long long m) {
-  int nets = k > 128 ? 32 : 64;
+  int nets = count_nets(k);
   while (nets > 8 && m < 2048LL * nets) nets >>= 1;
   return nets * (kBlock / kWave);
 }
@@ -52,14 +57,13 @@ __host__ __device__ inline int count_unit(int k, long long m) {
 constexpr int kBwChunk = kBlock * 16;   // vertices per unit of the block-weight sweep
 
 SelectKernel select_kernel(int k, int view, long long P, int n);
-// lanes per net: group_lanes(k); cache: the variant that also applies the
-// gain-cache deltas (it must be used exactly when the descriptor has a cache)
+// cache: the variant that also applies the gain-cache deltas (it must be used
+// exactly when the descriptor has a cache)
 FinalizeKernel finalize_kernel(int k, bool cache);
-FinalizeKernel finalize_kernel_g(int G, bool cache);   // G lanes per net (4, 8, 16 or 32)
+size_t finalize_lds(int k, bool cache);      // its dynamic LDS bytes
 GroupKernel pincount_kernel(int k);          // units of count_unit nets
 size_t pincount_lds(int k, long long m);     // its dynamic LDS bytes
 GainsKernel gains_kernel(int k, int view);
-int group_lanes(int k);
 
 // Enqueue one round; the round record goes to stats[round] of every instance.
 hipError_t launch_round(const RoundPlan& plan, int round, hipStream_t s, hipEvent_t* marks);

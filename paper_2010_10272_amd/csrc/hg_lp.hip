@@ -14,12 +14,12 @@
 //   tilescan   per target block: the tile where the budget runs out.
 //   approve    per tile: decide every candidate; the one boundary tile per
 //              block is resolved by a workgroup-wide prefix sum in vertex
-//              order.  Approved moves are applied right away: Phi updated
-//              with integer atomics (order-independent), the attributed km1
-//              change summed from the atomics' old values (subsection
-//              "Attributed Gains"), touched nets flagged.
-//   finalize   per touched net: Lambda, S and lambda recomputed from the
-//              final Phi row, its pins made eligible for the next round.
+//              order.  Approved moves are applied right away: part, block
+//              weights, touched nets flagged.
+//   finalize   per touched net: Phi, Lambda, S and lambda counted from its
+//              pins, the attributed km1 change summed from the blocks that
+//              left and entered Lambda (subsection "Attributed Gains"), its
+//              pins made eligible for the next round.
 //   stats      one workgroup per instance sums the counter slots into the
 //              round record.
 //
@@ -30,10 +30,10 @@
 #include <limits.h>
 
 #include "hg_bits.h"
+#include "hg_count.h"
 #include "hg_device.h"
 #include "hg_internal.h"
 #include "hg_lp.h"
-#include "hg_netrec.h"
 #include "hg_sweep.h"
 
 namespace hg {
@@ -786,9 +786,11 @@ __global__ __launch_bounds__(kBlock) void k_tilescan(Launch L) {
 // part, moved flags and block-weight deltas per mover, then the movers'
 // incident nets as one flattened range split over all 256 threads (so a tile
 // with few movers still keeps four wavefronts busy, and a high-degree mover is
-// spread over the workgroup).  Phi is updated with integer atomics whose old
-// values give the attributed km1 change; every incident net gets its touched
-// flag (a plain byte store: all writers store the same value).
+// spread over the workgroup): every incident net gets its touched flag (a plain
+// byte store: all writers store the same value).  Phi is left to the finalize,
+// which counts the touched nets' pins anew: it visits those pins anyway to make
+// them eligible, where two atomics per mover and net, 20 G a second for the
+// whole GPU, were two thirds of this kernel's time.
 // The mover owning flattened incidence j: the largest i < count with
 // s_off[i] <= j.
 __device__ __forceinline__ int list_owner(const int* s_off, int count, long long j) {
@@ -801,8 +803,8 @@ __device__ __forceinline__ int list_owner(const int* s_off, int count, long long
 }
 
 __device__ void apply_list(const InstDesc& D, const int* s_list, const int* s_tgt, int count,
-                           int* s_from, long long* s_beg, int* s_off, long long* s_tmp,
-                           unsigned long long* s_dW, long long& delta, long long& moved_pins,
+                           long long* s_beg, int* s_off, long long* s_tmp,
+                           unsigned long long* s_dW, long long& moved_pins,
                            long long& approved) {
   // per mover: move it, record where its incident nets start
   long long my_len = 0;
@@ -819,10 +821,10 @@ __device__ void apply_list(const InstDesc& D, const int* s_list, const int* s_tg
       const int len = (int)(D.vptr[u + 1] - b);
       const long long cu = D.vwgt ? D.vwgt[u] : 1;
       D.part[u] = t;
+      if (D.kept) move_packed(D, u, a, t);
       if (D.moved) D.moved[u] = 1;
       atomicAdd(&s_dW[t], (unsigned long long)cu);
       atomicAdd(&s_dW[a], (unsigned long long)(-cu));
-      s_from[i] = a;
       s_beg[i] = b;
       lens[q] = len;
       my_len += len;
@@ -838,19 +840,9 @@ __device__ void apply_list(const InstDesc& D, const int* s_list, const int* s_tg
     off += lens[q];
   }
   __syncthreads();
-  const int k = D.k;
   for (long long j = threadIdx.x; j < total; j += kBlock) {
     const int lo = list_owner(s_off, count, j);
-    const int e = D.vnets[s_beg[lo] + (j - s_off[lo])];
-    const int ao = s_from[lo], to = s_tgt[lo];
-    const int oa = atomicSub(&D.phi[(long long)e * k + ao], 1);
-    const int ot = atomicAdd(&D.phi[(long long)e * k + to], 1);
-    if (oa == 1 || ot == 0) {
-      const int w = D.unit_nets ? 1 : (int)D.netstate[(long long)e * D.rw];
-      if (oa == 1) delta += w;    // Phi(e, a) drops to zero
-      if (ot == 0) delta -= w;    // Phi(e, t) rises from zero
-    }
-    D.touched[e] = 1;
+    D.touched[D.vnets[s_beg[lo] + (j - s_off[lo])]] = 1;
   }
 }
 
@@ -991,15 +983,14 @@ __global__ __launch_bounds__(kBlock) void k_approve_apply(Launch L) {
   }
   __syncthreads();
   const int count = (int)s_count;
-  long long delta = 0, moved_pins = 0, approved = 0;
+  long long moved_pins = 0, approved = 0;
   if (count > 0 && D.appr) {
     // monotone round: only mark; the moves are ordered, re-gained and cut later
     mark_list(D, s_list, s_tgt, count, s_from, s_beg, s_off, s_tmp);
     if (threadIdx.x == 0)
       atomicAdd(&D.ctr->slot[kCtrMarked][blockIdx.x % kSlots], (unsigned long long)count);
   } else if (count > 0) {
-    apply_list(D, s_list, s_tgt, count, s_from, s_beg, s_off, s_tmp, s_dW, delta, moved_pins,
-               approved);
+    apply_list(D, s_list, s_tgt, count, s_beg, s_off, s_tmp, s_dW, moved_pins, approved);
   }
   __syncthreads();
   // block-weight deltas go to one of kSlots partial rows (a single row
@@ -1008,13 +999,13 @@ __global__ __launch_bounds__(kBlock) void k_approve_apply(Launch L) {
   long long* my_dw = D.bw_slots + (size_t)(blockIdx.x % kSlots) * k;
   for (int i = threadIdx.x; i < k; i += kBlock)
     if (s_dW[i]) atomicAdd((unsigned long long*)&my_dw[i], s_dW[i]);
-  delta = block_sum64(delta, s_tmp);
-  moved_pins = block_sum64(moved_pins, s_tmp);
-  approved = block_sum64(approved, s_tmp);
+  // both below 2^31: one sum
+  const long long both = block_sum64(moved_pins | (approved << 32), s_tmp);
+  moved_pins = both & 0xffffffffLL;
+  approved = both >> 32;
   if (threadIdx.x == 0) {
     const int sl = blockIdx.x % kSlots;
     RoundCounters* ctr = D.ctr;
-    if (delta) atomicAdd(&ctr->slot[kCtrDeltaAttr][sl], (unsigned long long)delta);
     if (moved_pins) atomicAdd(&ctr->slot[kCtrMovedPins][sl], (unsigned long long)moved_pins);
     if (approved) atomicAdd(&ctr->slot[kCtrApproved][sl], (unsigned long long)approved);
   }
@@ -1022,258 +1013,149 @@ __global__ __launch_bounds__(kBlock) void k_approve_apply(Launch L) {
 
 // --------------------------------------------------------------- finalize
 
-// Unit: a chunk of kFinalChunk nets.  The workgroup reads their touched
-// flags (coalesced), lists the touched ones in LDS and hands them to groups
-// of G lanes: Lambda, S and lambda are rebuilt from the final Phi row, the
-// flag is cleared and every pin becomes eligible.  The lane that rewrites
-// lambda(e) reads the old value first, so the drop (lambda_old - lambda_new)
-// * w(e) summed over touched nets checks the attributed total.  Single
-// instance: contiguous XCD-aware runs of chunks.
-// Gain cache update of one touched net e (subsection "Gain Caching"): the
-// four update rules, summed over all moves of the round, change p_i(v) for
-// every pin v by +w(e) when block i lost its last pin of e and by -w(e)
-// when it gained its first, and b(v) of a pin that did not move (block c)
-// by +w(e) when c now holds exactly one pin of e and by -w(e) when it no
-// longer does.  Moved vertices get b recomputed after the round.  Every lane
-// of the group calls this with its record word before (old_w) and after
-// (new_w) the round; the pins are also made eligible.
-template <int G>
-__device__ void cache_net_delta(const InstDesc& D, long long e, int wk, int gl, unsigned old_w,
-                                unsigned new_w, long long b, long long t) {
-  const int base = lane_id() - gl;
-  unsigned lo[8], ln[8], so[8], sn[8];
-#pragma unroll
-  for (int x = 0; x < 8; ++x) {
-    const int lam = 2 + (x < wk ? x : 0), sgl = 2 + wk + (x < wk ? x : 0);
-    lo[x] = __shfl(old_w, base + lam);
-    ln[x] = __shfl(new_w, base + lam);
-    so[x] = __shfl(old_w, base + sgl);
-    sn[x] = __shfl(new_w, base + sgl);
-  }
-  const int w = D.ewgt ? D.ewgt[e] : 1;
+// Unit: a block of kFinalChunk (1024) nets, a quarter of it per wavefront.  The
+// wavefronts work on their own (no barrier): each reads its quarter's touched
+// flags, four per lane, queues the touched nets in LDS and takes them as many
+// at a time as it can count (64, or 32 for k > 128): their pins are made
+// eligible and counted by block (count_batch), every lane rewrites the record of
+// its net.  The record's old Lambda gives the attributed km1 change, w(e) for
+// every block that left it and -w(e) for every one that entered; the drop
+// (lambda_old - lambda_new) * w(e) checks it.  Because everything is counted from
+// the final partition, nothing depends on the order of the moves (the paper
+// needs a spin-lock per net for this).
+// What bounds it is the chain flags -> offsets, records -> pins -> blocks and the
+// scattered eligible stores.  Counting anew costs more here than rereading Phi
+// rows that the approve had updated by atomics, but less than those atomics
+// (approve + finalize per round, us: netlist 66 + 63 -> 23 + 96, matrix k = 8
+// 41 + 39 -> 14 + 54, k = 64 49 + 61 -> 13 + 73, 64 small hypergraphs 50 + 127
+// -> 22 + 96; with the gain cache, which then needs no second variant of the
+// walk, 41 + 147 -> 14 + 113).  Blocks from part8 instead of part: matrix k = 8
+// 71 -> 54, k = 64 86 -> 73.
+// Single instance: contiguous XCD-aware runs of blocks.
+constexpr int kFinalQuarter = kFinalChunk / (kBlock / kWave);   // 256 nets: four flags per lane
+static_assert(kFinalQuarter == 4 * kWave, "one 4-byte load of flags per lane");
+constexpr int kFinalQueue = kWave + kFinalQuarter;              // touched nets waiting
+
+// Gain-cache deltas of a batch of nets (subsection "Gain Caching"): the four
+// update rules, summed over all moves of the round, change p_i(v) for every pin
+// v of net e by +w(e) when block i lost its last pin of e and by -w(e) when it
+// gained its first, and b(v) of a pin that did not move (block c) by +w(e) when
+// c now holds exactly one pin of e and by -w(e) when it no longer does.  Moved
+// vertices get b recomputed after the round.  Only nets whose sets changed are
+// walked: `nets` of them, lane i < nets holding pins [b, b + len), their changes
+// in the LDS words `chg`, [word][count_nets]: changed and old Lambda, changed
+// and new S, w(e), b, len.
+constexpr __host__ __device__ int cache_nets(int wk) { return wk == 8 ? 32 : kWave; }
+constexpr __host__ __device__ int cache_words(int wk) { return (4 * wk + 3) * cache_nets(wk); }
+
+template <int WK>
+__device__ __forceinline__ void cache_deltas(const InstDesc& D, const CountLds& M,
+                                             const unsigned* chg, long long b, int len) {
+  constexpr int CN = cache_nets(WK);
   const int ks = cache_stride(D.k);
   int* cb = D.cache;
   int* cp = D.cache + cache_pbase(D.n);
-  unsigned dl = 0, ds = 0;
+  int v[kCountFlight];
+  for_pins<false>(
+      D.pins, M, b, len, [&](int pin, int q) { v[q] = pin; },
+      [&](int net, int q) {
+        if (v[q] < 0) return;
+        const int w = (int)chg[4 * WK * CN + net];
+        unsigned any = 0;
 #pragma unroll
-  for (int x = 0; x < 8; ++x) {
-    dl |= lo[x] ^ ln[x];
-    ds |= so[x] ^ sn[x];
-  }
-  for (long long p = b + gl; p < t; p += G) {
-    const int v = D.pins[p];
-    D.eligible[v] = 1;
-    if (dl) {
-#pragma unroll
-      for (int x = 0; x < 8; ++x) {
-        if (x >= wk) break;
-        unsigned d = lo[x] ^ ln[x];
-        while (d) {
-          const int bit = __ffs(d) - 1;
-          d &= d - 1;
-          atomicAdd(&cp[(long long)v * ks + x * 32 + bit], ((lo[x] >> bit) & 1u) ? w : -w);
+        for (int x = 0; x < WK; ++x) {
+          unsigned d = chg[x * CN + net];
+          const unsigned old = chg[(WK + x) * CN + net];
+          any |= chg[(2 * WK + x) * CN + net];
+          while (d) {
+            const int bit = __ffs(d) - 1;
+            d &= d - 1;
+            atomicAdd(&cp[(long long)v[q] * ks + x * 32 + bit], ((old >> bit) & 1u) ? w : -w);
+          }
         }
-      }
-    }
-    if (ds && !D.moved[v]) {
-      const int c = D.part[v];
-      unsigned dso = 0, dsn = 0;
-#pragma unroll
-      for (int x = 0; x < 8; ++x)
-        if (x == (c >> 5)) {
-          dso = so[x];
-          dsn = sn[x];
+        if (any && !D.moved[v[q]]) {
+          const int c = D.part[v[q]];
+          if ((unsigned)c < (unsigned)D.k) {
+            const int x = c >> 5, bit = c & 31;
+            if ((chg[(2 * WK + x) * CN + net] >> bit) & 1u)
+              atomicAdd(&cb[v[q]], ((chg[(3 * WK + x) * CN + net] >> bit) & 1u) ? w : -w);
+          }
         }
-      const int bit = c & 31;
-      if (((dso ^ dsn) >> bit) & 1u) atomicAdd(&cb[v], ((dsn >> bit) & 1u) ? w : -w);
-    }
-  }
+      });
 }
 
-// Gain-cache rounds: the same record rebuild, with the cache deltas of each
-// touched net applied by its group while it walks the net's pins (and marks
-// them eligible).  Unit: a chunk of kCachedChunk nets, one touched flag per
-// thread; many small units keep the atomics-heavy pin walks spread over
-// the whole GPU.
-constexpr int kCachedChunk = kBlock;
-constexpr int kCachedGrid = 16384;   // persistent workgroups of the cached finalize
-
-template <int G>
-__global__ __launch_bounds__(kBlock) void k_finalize_cached(Launch L) {
-  __shared__ int s_list[kCachedChunk];
-  __shared__ long long s_tmp[kBlock / kWave];
-  __shared__ unsigned s_cnt;
-  constexpr int kGroups = kBlock / G;
-  const WorkItem wi = work_item(L, xcd_block((L.one.m + kCachedChunk - 1) / kCachedChunk));
+template <int WK, bool CACHE>
+__global__ __launch_bounds__(kBlock) void k_finalize(Launch L) {
+  extern __shared__ unsigned s_final[];   // per wavefront: count_words, the queue, cache_words
+  __shared__ unsigned long long s_sums[3];
+  const WorkItem wi = work_item(L, xcd_block((L.one.m + kFinalChunk - 1) / kFinalChunk));
   if (wi.count == 0) return;
   const InstDesc D = inst_desc(L, wi.inst);
-  const int grp = threadIdx.x / G, gl = threadIdx.x % G;
-  const int k = D.k, wk = bit_words(k), rw = D.rw;
-  long long dcheck = 0, ntouched = 0, tpins = 0;
-  for (int it = 0; it < wi.count; ++it) {
-    const long long c = (long long)wi.first + (long long)it * wi.stride;
-    if (threadIdx.x == 0) s_cnt = 0;
-    __syncthreads();
-    // one flag per thread (the flag array is padded to whole chunks, zero past m)
-    const long long e0 = c * kCachedChunk + threadIdx.x;
-    const bool t0 = D.touched[e0] != 0;
-    const int slot = wave_append(&s_cnt, t0);
-    if (t0) s_list[slot] = (int)e0;
-    __syncthreads();
-    const int cnt = (int)s_cnt;
-    ntouched += cnt;
-    for (int i = grp; i < cnt; i += kGroups) {
-      const int e = s_list[i];
-      const int* row = D.phi + (long long)e * k;
-      unsigned* rec = D.netstate + (long long)e * rw;
-      int lam_old = 0, w = 0;
-      if (gl == 1) {
-        lam_old = (int)rec[1];
-        w = (int)rec[0];
-      }
-      // the record's Lambda / S words before this round
-      const unsigned old_word = gl >= 2 && gl < 2 + 2 * wk ? rec[gl] : 0u;
-      NetBits nb = net_bits<G>(k, gl, [&](int i2) { return row[i2]; });
-      if (gl >= 1 && gl < 2 + 2 * wk) rec[gl] = nb.word;
-      write_views(D, e, gl, nb, true);
-      if (gl == 1) dcheck += (long long)(lam_old - nb.lambda) * w;
-      const long long b = D.eptr[e], t = D.eptr[e + 1];
-      if (gl == 0) {
-        D.touched[e] = 0;
-        tpins += t - b;
-      }
-      cache_net_delta<G>(D, e, wk, gl, old_word, nb.word, b, t);
-    }
-    __syncthreads();
-  }
-  dcheck = block_sum64(dcheck, s_tmp);
-  tpins = block_sum64(tpins, s_tmp);
-  if (threadIdx.x == 0) {
-    const int sl = blockIdx.x % kSlots;
-    if (dcheck) atomicAdd(&D.ctr->slot[kCtrDeltaCheck][sl], (unsigned long long)dcheck);
-    if (ntouched) atomicAdd(&D.ctr->slot[kCtrTouched][sl], (unsigned long long)ntouched);
-    if (tpins) atomicAdd(&D.ctr->slot[kCtrTouchedPins][sl], (unsigned long long)tpins);
-  }
-}
-
-// Unit: a block of kFinalChunk (1024) nets, a quarter of it per wavefront.  The
-// wavefronts work on their own (no barrier): each reads its quarter's touched
-// flags, four per lane, queues the touched nets in LDS and takes them 64 at a
-// time.  Groups of G lanes rebuild each net's Lambda, S and lambda from its
-// final Phi row (the rows of several nets per group in flight); the lane that
-// rewrites lambda(e) reads the old value first, so the drop (lambda_old -
-// lambda_new) * w(e) summed over touched nets checks the attributed total.
-// Then the pins of the 64 nets are made eligible as one run laid end to end,
-// so a long net does not serialize on one group: a position's net is the count
-// of net starts at or before it (a flag per position in LDS, one ballot).
-// What bounds it is the chain flags -> offsets, rows -> pins -> marks, so what
-// counts is how many wavefronts run it at a time; a workgroup's list with a
-// scan and a binary search per pin kept four wavefronts waiting for each other:
-// netlist 73 -> 63 us per round, matrix k = 8 46 -> 39, k = 64 71 -> 61, tiny
-// 11 -> 7, 64 small hypergraphs 193 -> 127 (three widths).
-// Single instance: contiguous XCD-aware runs of blocks.
-constexpr int kMarkSlots = 4;                // pin positions per lane in flight in the marks
-constexpr int kFinalQuarter = kFinalChunk / (kBlock / kWave);   // 256 nets: four flags per lane
-static_assert(kFinalQuarter == 4 * kWave, "one 4-byte load of flags per lane");
-
-struct FinalizeLds {
-  int queue[kWave + kFinalQuarter];          // touched nets waiting
-  int shift[kWave];                          // first pin - place in the run, per net of a batch
-  unsigned char flag[kMarkSlots * kWave];
-};
-
-// Rows of q[0 .. cnt), cnt <= 64, G lanes per net, MC = ceil(k / G) rounded up.
-// Returns this lane's part of the lambda drop.
-template <int G, int MC>
-__device__ __forceinline__ long long finalize_rows(const InstDesc& D, const int* q, int cnt) {
-  constexpr int kAt = kWave / G;                           // nets per step
-  constexpr int kSteps = MC >= 8 ? 1 : MC >= 4 ? 2 : 4;    // steps in flight
-  constexpr int R = kSteps < G ? kSteps : G;
-  const int lane = lane_id(), gl = lane % G, grp = lane / G;
-  const int k = D.k, wk = bit_words(k), rw = D.rw;
-  long long drop = 0;
-  for (int i0 = 0; i0 < cnt; i0 += kAt * R) {
-    int e[R], cv[R][MC], lam_old[R], w[R];
-#pragma unroll
-    for (int r = 0; r < R; ++r) {
-      const int i = i0 + r * kAt + grp;
-      e[r] = q[i < cnt ? i : 0];
-      const int* row = D.phi + (long long)e[r] * k;
-      const unsigned* rec = D.netstate + (long long)e[r] * rw;
-#pragma unroll
-      for (int c = 0; c < MC; ++c) {
-        const int x = c * G + gl;
-        cv[r][c] = row[x < k ? x : k - 1];
-      }
-      lam_old[r] = w[r] = 0;
-      if (gl == 1) {
-        lam_old[r] = (int)rec[1];
-        w[r] = (int)rec[0];
-      }
-    }
-#pragma unroll
-    for (int r = 0; r < R; ++r) {
-      const bool live = i0 + r * kAt + grp < cnt;
-      const NetBits nb = net_bits_of<G, MC>(k, gl, cv[r]);
-      if (live) {
-        unsigned* rec = D.netstate + (long long)e[r] * rw;
-        if (gl >= 1 && gl < 2 + 2 * wk) rec[gl] = nb.word;
-        if (gl == 1) drop += (long long)(lam_old[r] - nb.lambda) * w[r];
-      }
-      write_views(D, e[r], gl, nb, live);
-    }
-  }
-  return drop;
-}
-
-template <int G>
-__device__ __forceinline__ void finalize_sweep(const InstDesc& D, const WorkItem& wi,
-                                               FinalizeLds& M, unsigned long long* s_sums) {
+  if (threadIdx.x < 3) s_sums[threadIdx.x] = 0;
+  __syncthreads();
   const int lane = lane_id(), wv = threadIdx.x / kWave;
-  const int k = D.k, chunks = (k + G - 1) / G;
-  long long dcheck = 0, tpins = 0;
-  int ntouched = 0;
-  for (int q = 0; q < kMarkSlots; ++q) M.flag[q * kWave + lane] = 0;
+  const int k = D.k, NW = count_nets(k);
+  const int words = count_words(k, NW) + kFinalQueue + (CACHE ? cache_words(WK) : 0);
+  const CountLds M = count_lds(s_final + (size_t)wv * words, k, NW);
+  int* queue = reinterpret_cast<int*>(s_final + (size_t)wv * words + count_words(k, NW));
+  unsigned* chg = reinterpret_cast<unsigned*>(queue + kFinalQueue);
+  const Blocks block = blocks_of(D, D.kept != 0);
+  const bool vec_phi = aligned_rows(D);
+  long long attr = 0, drop = 0;
+  int ntouched = 0, tpins = 0;               // nets and pins: below 2^31
   auto batch = [&](const int* q, int cnt) {
-    // lane's net: its pin range, its flag
-    int len = 0;
-    long long b = 0;
+    int len = 0, w = 0, lambda = 0;
+    long long e = 0, b = 0;
+    unsigned lam[WK], one[WK];
+#pragma unroll
+    for (int x = 0; x < WK; ++x) lam[x] = one[x] = 0;
     if (lane < cnt) {
-      const int e = q[lane];
+      e = q[lane];
       b = D.eptr[e];
       len = (int)(D.eptr[e + 1] - b);
+      read_record<WK>(D, e, w, lambda, lam, one);
       D.touched[e] = 0;
     }
-    if (chunks <= 1) dcheck += finalize_rows<G, 1>(D, q, cnt);
-    else if (chunks <= 2) dcheck += finalize_rows<G, 2>(D, q, cnt);
-    else if (chunks <= 4) dcheck += finalize_rows<G, 4>(D, q, cnt);
-    else dcheck += finalize_rows<G, 8>(D, q, cnt);
-    const int incl = wave_incl_scan(len);
-    const int total = last_lane(incl), first = incl - len;
-    ntouched += lane < cnt ? 1 : 0;
-    tpins += len;
-    M.shift[lane] = (int)b - first;                        // pin positions are below 2^31
-    int before = -1;                                       // last net starting before this step
-    for (int s = 0; s < total; s += kMarkSlots * kWave) {
-      if (len > 0 && first >= s && first < s + kMarkSlots * kWave) M.flag[first - s] = 1;
-      wave_lds_sync();
-      int v[kMarkSlots];
+    NetSets<WK> N;
+    count_batch<WK, false>(
+        D, M, e, b, len, cnt, vec_phi, block, [&](int v) { D.eligible[v] = 1; }, N);
+    bool changed = false;
+    if (lane < cnt) {
+      write_record<WK, false>(D, e, w, N.lambda, N.lam, N.one);
+      int left = 0;
 #pragma unroll
-      for (int x = 0; x < kMarkSlots; ++x) {
-        const int p = s + x * kWave + lane;
-        const int here = M.flag[x * kWave + lane];
-        M.flag[x * kWave + lane] = 0;
-        const unsigned long long starts = __ballot(here != 0);
-        const int net = lanes_below(starts, before) + here;
-        before += __popcll(starts);
-        v[x] = p < total ? D.pins[M.shift[net] + p] : -1;
+      for (int x = 0; x < WK; ++x) {
+        left += __popc(lam[x] & ~N.lam[x]) - __popc(N.lam[x] & ~lam[x]);
+        changed |= lam[x] != N.lam[x] || one[x] != N.one[x];
       }
+      attr += (long long)left * w;
+      drop += (long long)(lambda - N.lambda) * w;
+      ntouched += 1;
+      tpins += len;
+    }
+    if constexpr (CACHE) {
+      // the changed nets to the first lanes
+      constexpr int CN = cache_nets(WK);
+      const unsigned long long mask = __ballot(changed);
+      const int at = lanes_below(mask, 0), nets = __popcll(mask);
+      if (changed) {
 #pragma unroll
-      for (int x = 0; x < kMarkSlots; ++x)
-        if (v[x] >= 0) D.eligible[v[x]] = 1;
+        for (int x = 0; x < WK; ++x) {
+          chg[x * CN + at] = lam[x] ^ N.lam[x];
+          chg[(WK + x) * CN + at] = lam[x];
+          chg[(2 * WK + x) * CN + at] = one[x] ^ N.one[x];
+          chg[(3 * WK + x) * CN + at] = N.one[x];
+        }
+        chg[4 * WK * CN + at] = (unsigned)w;
+        chg[(4 * WK + 1) * CN + at] = (unsigned)b;      // pin positions are below 2^31
+        chg[(4 * WK + 2) * CN + at] = (unsigned)len;
+      }
+      wave_lds_sync();
+      const long long cb = lane < nets ? (long long)chg[(4 * WK + 1) * CN + lane] : 0;
+      const int cl = lane < nets ? (int)chg[(4 * WK + 2) * CN + lane] : 0;
+      cache_deltas<WK>(D, M, chg, cb, cl);
       wave_lds_sync();
     }
-    wave_lds_sync();
   };
   // four flags per lane in one load (the flag array is padded to whole blocks
   // and zero past m; the workspace keeps it 4-byte aligned); the next block's
@@ -1300,43 +1182,33 @@ __device__ __forceinline__ void finalize_sweep(const InstDesc& D, const WorkItem
       int at = qn + incl - mine;
 #pragma unroll
       for (int x = 0; x < 4; ++x)
-        if ((f4 >> (8 * x)) & 0xffu) M.queue[at++] = e0 + x;
+        if ((f4 >> (8 * x)) & 0xffu) queue[at++] = e0 + x;
       qn += last_lane(incl);
       wave_lds_sync();
     }
-    while (qn >= kWave || (it == wi.count && qn > 0)) {
-      const int cnt = qn < kWave ? qn : kWave;
-      batch(M.queue + (qn - cnt), cnt);                    // the last ones: nothing moves
+    while (qn >= NW || (it == wi.count && qn > 0)) {
+      const int cnt = qn < NW ? qn : NW;
+      batch(queue + (qn - cnt), cnt);                      // the last ones: nothing moves
       qn -= cnt;
     }
   }
-  // counts below 2^31 (nets, pins): two to a sum
-  const long long np = wave_sum((long long)ntouched | (tpins << 32));
-  dcheck = wave_sum(dcheck);
+  const long long np = wave_sum((long long)ntouched | ((long long)tpins << 32));
+  attr = wave_sum(attr);
+  drop = wave_sum(drop);
   if (lane == 0) {
     atomicAdd(&s_sums[0], (unsigned long long)np);
-    atomicAdd(&s_sums[1], (unsigned long long)dcheck);
+    atomicAdd(&s_sums[1], (unsigned long long)attr);
+    atomicAdd(&s_sums[2], (unsigned long long)drop);
   }
   __syncthreads();
   if (threadIdx.x == 0) {
     const int sl = blockIdx.x % kSlots;
     const unsigned long long nt = s_sums[0] & 0xffffffffu, tp = s_sums[0] >> 32;
-    if (s_sums[1]) atomicAdd(&D.ctr->slot[kCtrDeltaCheck][sl], s_sums[1]);
+    if (s_sums[1]) atomicAdd(&D.ctr->slot[kCtrDeltaAttr][sl], s_sums[1]);
+    if (s_sums[2]) atomicAdd(&D.ctr->slot[kCtrDeltaCheck][sl], s_sums[2]);
     if (nt) atomicAdd(&D.ctr->slot[kCtrTouched][sl], nt);
     if (tp) atomicAdd(&D.ctr->slot[kCtrTouchedPins][sl], tp);
   }
-}
-
-template <int G>
-__global__ __launch_bounds__(kBlock) void k_finalize(Launch L) {
-  __shared__ FinalizeLds s_wave[kBlock / kWave];
-  __shared__ unsigned long long s_sums[2];
-  const WorkItem wi = work_item(L, xcd_block((L.one.m + kFinalChunk - 1) / kFinalChunk));
-  if (wi.count == 0) return;
-  const InstDesc D = inst_desc(L, wi.inst);
-  if (threadIdx.x < 2) s_sums[threadIdx.x] = 0;
-  __syncthreads();
-  finalize_sweep<G>(D, wi, s_wave[threadIdx.x / kWave], s_sums);
 }
 
 // Unit: one instance.  Fold the apply's block-weight slots into block_w, sum
@@ -1411,8 +1283,6 @@ __global__ __launch_bounds__(kBlock) void k_round_stats(Launch L) {
 
 // --------------------------------------------------------------- launch
 
-int group_lanes(int k);
-
 // Kernel selection per instance shape (shared with the batch planner).
 // Entries in flight per vertex: eight where the average degree is 12 or more
 // and an entry is at most two words (half the dependent load steps for the
@@ -1439,23 +1309,20 @@ SelectKernel select_kernel(int k, int view, long long P, int n) {
   }
 }
 
-// The plain finalize reads one Phi row and writes one record per net: for
-// k <= 16 four lanes hold the record and the row's counts, and narrower
-// groups put twice as many nets in flight per wave (its pins are marked by
-// the whole workgroup).  The cache variant walks the pins in the group.
-FinalizeKernel finalize_kernel(int k, bool cache) {
-  return finalize_kernel_g(!cache && k <= 16 ? 4 : group_lanes(k), cache);
-}
-
 // The gain-cache update lives in its own instantiation: the plain one then
 // needs far fewer registers (more workgroups per compute unit).
-FinalizeKernel finalize_kernel_g(int G, bool cache) {
-  switch (G) {
-    case 4: return cache ? k_finalize_cached<4> : k_finalize<4>;
-    case 8: return cache ? k_finalize_cached<8> : k_finalize<8>;
-    case 16: return cache ? k_finalize_cached<16> : k_finalize<16>;
-    default: return cache ? k_finalize_cached<32> : k_finalize<32>;
+FinalizeKernel finalize_kernel(int k, bool cache) {
+  switch (bit_words(k)) {
+    case 1: return cache ? k_finalize<1, true> : k_finalize<1, false>;
+    case 2: return cache ? k_finalize<2, true> : k_finalize<2, false>;
+    case 4: return cache ? k_finalize<4, true> : k_finalize<4, false>;
+    default: return cache ? k_finalize<8, true> : k_finalize<8, false>;
   }
+}
+
+size_t finalize_lds(int k, bool cache) {
+  return sizeof(unsigned) * (size_t)(kBlock / kWave) *
+         (count_words(k, count_nets(k)) + kFinalQueue + (cache ? cache_words(bit_words(k)) : 0));
 }
 
 // Launch one round of every kernel for a batch (items per kernel kind) or a
@@ -1497,7 +1364,7 @@ hipError_t launch_round_back(const RoundPlan& plan, int round, hipStream_t s, hi
 hipError_t launch_round_finalize(const RoundPlan& plan, hipStream_t s, hipEvent_t* marks) {
   if (marks) (void)hipEventRecord(marks[2], s);
   for (const PlanLaunch& pl : plan.finalize)
-    hipLaunchKernelGGL((FinalizeKernel)pl.kernel, dim3(pl.grid), dim3(kBlock), 0, s, pl.L);
+    hipLaunchKernelGGL((FinalizeKernel)pl.kernel, dim3(pl.grid), dim3(kBlock), pl.lds, s, pl.L);
   return hipGetLastError();
 }
 
@@ -1534,10 +1401,9 @@ void single_round_plan(const InstDesc& d, RoundPlan& plan) {
   plan.approve.L = L;
   PlanLaunch fin;
   fin.kernel = (void*)finalize_kernel(d.k, d.cache != nullptr);
-  const long long unit = d.cache ? kCachedChunk : kFinalChunk;
-  const long long cap = d.cache ? kCachedGrid : kFinalizeGrid;
-  long long fchunks = ((long long)d.m + unit - 1) / unit;
-  fin.grid = (unsigned)(fchunks < cap ? fchunks : cap);
+  fin.lds = finalize_lds(d.k, d.cache != nullptr);
+  const long long fchunks = ((long long)d.m + kFinalChunk - 1) / kFinalChunk;
+  fin.grid = (unsigned)(fchunks < kFinalizeGrid ? fchunks : kFinalizeGrid);
   fin.L = L;
   plan.finalize.push_back(fin);
   plan.stats.grid = 1;

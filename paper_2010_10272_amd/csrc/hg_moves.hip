@@ -342,8 +342,8 @@ __global__ __launch_bounds__(kBlock) void k_prefix_pick(const int* t_dev, const 
 }
 
 // Apply moves [0, best[1]) of a sorted monotone-round sequence: part, moved,
-// Phi (integer atomics; their old values give the attributed km1 change),
-// touched nets, block-weight deltas (slots), counters.
+// touched nets, block-weight deltas (slots), counters.  (Phi and the km1 change
+// come from the finalize.)
 __global__ __launch_bounds__(kBlock) void k_apply_prefix(Seq S, const long long* best,
                                                          InstDesc D) {
   __shared__ unsigned long long s_dW[HG_MAX_K];
@@ -353,7 +353,7 @@ __global__ __launch_bounds__(kBlock) void k_apply_prefix(Seq S, const long long*
   const int k = D.k;
   for (int i = threadIdx.x; i < k; i += kBlock) s_dW[i] = 0;
   __syncthreads();
-  long long delta = 0, moved_pins = 0, approved = 0;
+  long long moved_pins = 0, approved = 0;
   for (int tile = blockIdx.x; tile * kSeqTile < p; tile += gridDim.x) {
     {
       const int j = tile * kSeqTile + threadIdx.x;
@@ -368,32 +368,24 @@ __global__ __launch_bounds__(kBlock) void k_apply_prefix(Seq S, const long long*
       }
     }
     // part is read by for_incidences (source blocks): update it only after
-    for_incidences(S, p, tile, [&](int, int, int a, int b, int e) {
-      const int oa = atomicSub(&D.phi[(long long)e * k + a], 1);
-      const int ot = atomicAdd(&D.phi[(long long)e * k + b], 1);
-      if (oa == 1 || ot == 0) {
-        const int w = D.ewgt ? D.ewgt[e] : 1;
-        if (oa == 1) delta += w;
-        if (ot == 0) delta -= w;
-      }
-      D.touched[e] = 1;
-    });
+    for_incidences(S, p, tile, [&](int, int, int, int, int e) { D.touched[e] = 1; });
     {
       const int j = tile * kSeqTile + threadIdx.x;
       int u, a, b;
-      if (threadIdx.x < kSeqTile && j < p && seq_move(S, j, u, a, b)) D.part[u] = b;
+      if (threadIdx.x < kSeqTile && j < p && seq_move(S, j, u, a, b)) {
+        D.part[u] = b;
+        if (D.kept) move_packed(D, u, a, b);
+      }
     }
   }
   __syncthreads();
   long long* my_dw = D.bw_slots + (size_t)(blockIdx.x % kSlots) * k;
   for (int i = threadIdx.x; i < k; i += kBlock)
     if (s_dW[i]) atomicAdd((unsigned long long*)&my_dw[i], s_dW[i]);
-  delta = block_sum64(delta, s_tmp2);
   moved_pins = block_sum64(moved_pins, s_tmp2);
   approved = block_sum64(approved, s_tmp2);
   if (threadIdx.x == 0) {
     const int sl = blockIdx.x % kSlots;
-    if (delta) atomicAdd(&D.ctr->slot[kCtrDeltaAttr][sl], (unsigned long long)delta);
     if (moved_pins) atomicAdd(&D.ctr->slot[kCtrMovedPins][sl], (unsigned long long)moved_pins);
     if (approved) atomicAdd(&D.ctr->slot[kCtrApproved][sl], (unsigned long long)approved);
   }
@@ -1162,7 +1154,7 @@ hg_status hg_refine_exact(hg_graph g, int32_t k, double eps, int32_t rounds, int
   hipStream_t s = (hipStream_t)stream;
   hg::InstDesc d = hg::make_desc(g, k, lmax, part, phi, netstate, (long long*)block_w, eligible,
                                  nullptr, (long long*)km1_out, stats);
-  hg::keep_sweep_view(g, d);
+  hg::keep_private_copies(g, d, false);
   hg::CountPlan cplan;
   hg::single_count_plan(d, cplan);
   HG_TRY(hg::launch_counts(cplan, true, true, s), "pin counts");

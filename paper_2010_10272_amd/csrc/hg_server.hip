@@ -399,6 +399,7 @@ hipError_t enqueue_step(hg_server_s* s, Lane& ln, const std::vector<Job*>& run, 
     InstDesc d = make_desc(M.g, M.k, M.lmax, M.part, M.phi, M.netstate, M.block_w, M.eligible,
                            nullptr, M.km1, M.stats);
     d.round_base = M.round_base;
+    keep_private_copies(M.g, d, true);
     if (nj > 0) {
       CountPlan cp;
       single_count_plan(d, cp);
@@ -424,6 +425,7 @@ hipError_t enqueue_step(hg_server_s* s, Lane& ln, const std::vector<Job*>& run, 
     if (end && !join.empty())
       end = build_plans(mem, join, s->sched, ln.table[h], ln.host[h], end, ln.half_bytes, nullptr,
                         &ln.cp);
+    ln.rp = kept_plan(ln.rp);
     if (end == 0) return hipErrorOutOfMemory;   // checked by the caller beforehand
     e = hipMemcpyAsync(ln.table[h], ln.host[h], end, hipMemcpyHostToDevice, cs);
     if (e != hipSuccess) return e;

@@ -8,10 +8,10 @@
 // each lane builds its net's bitsets from its counters, and the rows leave as
 // whole lines.  No global atomics touch Phi, so the result is deterministic by
 // construction.
+#include "hg_count.h"
 #include "hg_device.h"
 #include "hg_internal.h"
 #include "hg_lp.h"
-#include "hg_netrec.h"
 
 namespace hg {
 
@@ -36,53 +36,18 @@ __device__ __forceinline__ WorkItem contiguous_units(long long units) {
 // beyond (2 and 4 MB on a 4M-vertex netlist, where an XCD's L2 has 4 MB, instead
 // of 16 MB).  If that sweep met an id outside [0, k), the ids come from the
 // partition itself, so that such vertices are skipped.
-constexpr int kCountFlight = 4;              // pins in flight per lane
-constexpr int kByteNet = 255;                // longest net whose counts surely fit a byte
-
-// Words of a net's byte counters in LDS: odd, so that lanes reading their own
-// nets' word i use all banks.
-__host__ __device__ __forceinline__ int count_stride(int k) { return ((k + 3) / 4) | 1; }
-
-// Counters -> bits: bit i of `nz` / `one` for byte i of x non-zero / equal to one.
-__device__ __forceinline__ void byte_bits(unsigned x, unsigned& nz, unsigned& one) {
-  constexpr unsigned low7 = 0x7f7f7f7fu;
-  const unsigned a = (((x & low7) + low7) | x) & ~low7;               // bytes != 0
-  const unsigned y = x ^ 0x01010101u;
-  const unsigned b = ~((((y & low7) + low7) | y) | low7);             // bytes == 1
-  // the four top bits to bits 0..3
-  nz = ((a >> 7) * 0x10204080u) >> 28;
-  one = ((b >> 7) * 0x10204080u) >> 28;
-}
-
-// Counts of one net longer than kByteNet by the whole wavefront, in 32-bit
-// words (`cnt`, k of them): Phi row, and its bits into the lane that owns it.
-template <typename Block>
-__device__ void count_long_net(const InstDesc& D, long long e, long long b, long long t, int* cnt,
-                               Block block) {
-  const int lane = lane_id(), k = D.k;
-  for (int i = lane; i < k; i += kWave) cnt[i] = 0;
-  wave_lds_sync();
-  for (long long p = b + lane; p < t; p += kWave) {
-    const unsigned v = block(D.pins[p]);
-    if (v < (unsigned)k) atomicAdd(&cnt[v], 1);
-  }
-  wave_lds_sync();
-  for (int i = lane; i < k; i += kWave) D.phi[e * k + i] = cnt[i];
-}
-
+//
 // Unit: count_unit consecutive nets.  What bounds it: the block ids' gathers
 // (lines outstanding per compute unit).  A lane group per net (8 lanes, four
 // slots each) left two thirds of the gather slots empty on nets of ten pins and
-// half the lanes idle; here every lane has a pin.  Pins of a net in one block
-// are often neighbours, so each run of equal (net, block) adds once.  (Four
-// consecutive pins per lane need a third fewer operations, but their gathers
-// touch more lines at a time: netlist 370 -> 404 us.)  Per call, before and
-// now: netlist 56.5M pins, k = 16 523 -> 367 us (gathers 135 of them, Phi
-// stores 65), matrix 10M pins k = 8 82 -> 48, k = 64 128 -> 95.
+// half the lanes idle; here every lane has a pin.  (Four consecutive pins per
+// lane need a third fewer operations, but their gathers touch more lines at a
+// time: netlist 370 -> 404 us.)  Per call, before and now: netlist 56.5M pins,
+// k = 16 523 -> 348 us (gathers 135 of them, Phi stores 65), matrix 10M pins
+// k = 8 82 -> 48, k = 64 128 -> 95.
 template <int WK>
 __global__ __launch_bounds__(kBlock) void k_pincounts(Launch L) {
-  extern __shared__ unsigned s_count[];   // per wave: NW x stride byte counters, k words
-  __shared__ unsigned char s_flag[kBlock / kWave][kCountFlight * kWave];
+  extern __shared__ unsigned s_count[];   // count_words per wavefront
   __shared__ long long s_km1;
   const WorkItem wi = work_item(L, contiguous_units((L.one.m + count_unit(L.one.k, L.one.m) - 1) /
                                                      count_unit(L.one.k, L.one.m)));
@@ -90,25 +55,12 @@ __global__ __launch_bounds__(kBlock) void k_pincounts(Launch L) {
   const InstDesc D = inst_desc(L, wi.inst);
   const int k = D.k, m = D.m;
   const int unit_nets = count_unit(k, m), NW = unit_nets / (kBlock / kWave);
-  const int stride = count_stride(k);
   const int lane = lane_id(), wv = threadIdx.x / kWave;
-  unsigned* cnt = s_count + (size_t)wv * (NW * stride + k);
-  int* big = reinterpret_cast<int*>(cnt + NW * stride);
-  unsigned char* flag = s_flag[wv];
-  const bool checked = (*D.err_flags & kErrPart) == 0;
-  const bool nibbles = k <= 16;
-  auto block = [&](int v) -> unsigned {
-    if (!checked) return (unsigned)D.part[v];
-    if (!nibbles) return D.part8[v];
-    return (D.part8[(unsigned)v >> 1] >> (4 * (v & 1))) & 15u;
-  };
-  // Phi rows leave as 16-byte streaming stores when rows are 16-byte aligned
-  const bool vec_phi = (k & 3) == 0 && ((uintptr_t)D.phi & 15) == 0;
+  const CountLds M = count_lds(s_count + (size_t)wv * count_words(k, NW), k, NW);
+  const Blocks block = blocks_of(D, true);
+  const bool vec_phi = aligned_rows(D);
   if (threadIdx.x == 0) s_km1 = 0;
   __syncthreads();
-#pragma unroll
-  for (int q = 0; q < kCountFlight; ++q) flag[q * kWave + lane] = 0;
-  for (int i = lane; i < NW * stride; i += kWave) cnt[i] = 0;
   long long km1_local = 0;
   // first net of turn `it`, and lane's pin range in it (the next turn's is
   // loaded while this one's pins are counted)
@@ -134,111 +86,12 @@ __global__ __launch_bounds__(kBlock) void k_pincounts(Launch L) {
     if (e0 >= m) continue;                                  // the same for the whole wave
     const int nets = m - e0 < NW ? (int)(m - e0) : NW;
     const long long e = e0 + lane;
-    const unsigned long long is_long = __ballot(len > kByteNet);
-    const int incl = wave_incl_scan(len);
-    const int total = last_lane(incl), first = incl - len;  // this net's place in the run
-    const long long run = __shfl(b, 0);
-    const int* pins = D.pins + run;
-    wave_lds_sync();
-    int before = -1;                                        // last net starting before this step
-    for (int s = 0; s < total; s += kCountFlight * kWave) {
-      int v[kCountFlight];
-#pragma unroll
-      for (int q = 0; q < kCountFlight; ++q) {
-        const int p = s + q * kWave + lane;
-        v[q] = p < total ? pins[p] : -1;
-      }
-      if (len > 0 && first >= s && first < s + kCountFlight * kWave) flag[first - s] = 1;
-      unsigned id[kCountFlight];
-#pragma unroll
-      for (int q = 0; q < kCountFlight; ++q) id[q] = v[q] >= 0 ? block(v[q]) : ~0u;
-      wave_lds_sync();
-#pragma unroll
-      for (int q = 0; q < kCountFlight; ++q) {
-        const unsigned here = flag[q * kWave + lane];
-        flag[q * kWave + lane] = 0;
-        const unsigned long long starts = __ballot(here != 0);
-        const int net = lanes_below(starts, before) + (int)here;
-        before += __popcll(starts);
-        bool live = id[q] < (unsigned)k;
-        if (is_long) live = live && !((is_long >> (net & 63)) & 1ull);
-        // one add per run of equal (net, block) in neighbouring lanes
-        const unsigned key = live ? ((unsigned)net << 8) | id[q] : ~0u;
-        const unsigned prev = lane_before(key);
-        const unsigned long long heads = __ballot(lane == 0 || key != prev);
-        if (live && ((heads >> lane) & 1ull)) {
-          const unsigned long long later = heads >> lane >> 1;
-          const int run_len = later ? __ffsll((long long)later) : kWave - lane;
-          atomicAdd(&cnt[net * stride + (id[q] >> 2)], (unsigned)run_len << (8 * (id[q] & 3)));
-        }
-      }
-      wave_lds_sync();
-    }
-    // lane's net: bitsets from its counters
-    unsigned lam[WK], one[WK];
-    int lambda = 0;
-#pragma unroll
-    for (int w = 0; w < WK; ++w) {
-      lam[w] = one[w] = 0;
-      if (lane < nets) {
-        for (int j = 0; j < 8 && w * 32 + 4 * j < k; ++j) {
-          unsigned nz, on;
-          byte_bits(cnt[lane * stride + w * 8 + j], nz, on);
-          lam[w] |= nz << (4 * j);
-          one[w] |= on << (4 * j);
-        }
-      }
-      lambda += __popc(lam[w]);
-    }
-    // Phi rows: the run of rows, 16 bytes (or one count) per lane and step
-    if (vec_phi) {
-      const int words = k >> 2, all = nets * words;
-      int row = lane / words, col = lane % words;           // words <= 64
-      const int drow = kWave / words, dcol = kWave % words;
-      for (int i = lane; i < all; i += kWave) {
-        const unsigned x = cnt[row * stride + col];
-        const i32x4 o = {(int)(x & 255u), (int)((x >> 8) & 255u), (int)((x >> 16) & 255u),
-                         (int)(x >> 24)};
-        if (!((is_long >> row) & 1ull))
-          __builtin_nontemporal_store(o, reinterpret_cast<i32x4*>(D.phi + e0 * k) + i);
-        row += drow;
-        col += dcol;
-        if (col >= words) {
-          col -= words;
-          ++row;
-        }
-      }
-    } else {
-      for (int i = lane; i < nets * k; i += kWave) {
-        const int row = i / k, col = i % k;
-        if (!((is_long >> row) & 1ull))
-          D.phi[e0 * k + i] = (int)((cnt[row * stride + (col >> 2)] >> (8 * (col & 3))) & 255u);
-      }
-    }
-    wave_lds_sync();
-    for (int i = lane; i < nets * stride; i += kWave) cnt[i] = 0;   // for the next nets
-    for (unsigned long long left = is_long; left; left &= left - 1) {
-      const int j = __ffsll((long long)left) - 1;
-      const long long lb = __shfl(b, j);
-      count_long_net(D, e0 + j, lb, lb + __shfl(len, j), big, block);
-      if (lane == j) {
-        lambda = 0;
-#pragma unroll
-        for (int w = 0; w < WK; ++w) {
-          lam[w] = one[w] = 0;
-          for (int i = 0; i < 32 && w * 32 + i < k; ++i) {
-            lam[w] |= (big[w * 32 + i] > 0 ? 1u : 0u) << i;
-            one[w] |= (big[w * 32 + i] == 1 ? 1u : 0u) << i;
-          }
-          lambda += __popc(lam[w]);
-        }
-      }
-      wave_lds_sync();
-    }
+    NetSets<WK> N;
+    count_batch<WK, true>(D, M, e, b, len, nets, vec_phi, block, [](int) {}, N);
     if (lane < nets) {
       const int w = D.ewgt ? D.ewgt[e] : 1;
-      write_record<WK>(D, e, w, lambda, lam, one);
-      km1_local += (long long)(lambda - 1) * w;
+      write_record<WK, true>(D, e, w, N.lambda, N.lam, N.one);
+      km1_local += (long long)(N.lambda - 1) * w;
     }
   }
   km1_local = wave_sum(km1_local);
@@ -394,18 +247,9 @@ static unsigned grid_cap(long long items, int per_block, int cap) {
   return (unsigned)b;
 }
 
-// Lanes per net for the finalize: enough lanes to hold every word of the net
-// record (2 + 2 * bit_words(k), padded), and no more than that (but 8 for
-// 4 < k <= 64): most nets have only a handful of pins, so narrower groups put
-// more nets' loads in flight per wavefront.
-int group_lanes(int k) {
-  if (k <= 4) return 4;
-  return net_words(k) > 8 ? net_words(k) : 8;
-}
-
 size_t pincount_lds(int k, long long m) {
-  return sizeof(unsigned) *
-         ((size_t)count_unit(k, m) * count_stride(k) + (size_t)(kBlock / kWave) * k);
+  const int nets = count_unit(k, m) / (kBlock / kWave);
+  return sizeof(unsigned) * (size_t)(kBlock / kWave) * count_words(k, nets);
 }
 
 GroupKernel pincount_kernel(int k) {
