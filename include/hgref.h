@@ -354,7 +354,7 @@ typedef struct {
  * speed differs (hg_batch_autotune measures). */
 typedef struct {
   int32_t select_chunks;     /* 256-vertex chunks per select workgroup, 1..64    */
-  int32_t finalize_chunks;   /* 1024-net blocks per finalize workgroup, 1..64    */
+  int32_t finalize_chunks;   /* 256-net blocks per finalize workgroup, 1..64     */
   int32_t count_chunks;      /* 256-net chunks per pin-count workgroup, 1..64    */
   int32_t net_lanes;         /* 0, 4, 8, 16 or 32; has no effect any more (the
                                 finalize takes a lane per net for every k)       */

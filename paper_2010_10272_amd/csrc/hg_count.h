@@ -103,7 +103,7 @@ struct NetSets {
 // none -- laid end to end, kCountFlight per lane at a time: `load(v, q)` is called
 // for the pins of a step (v = -1 past the end) once all of its pins are on their
 // way, then `take(net, q)` with the lane index of each pin's net.  So a step waits
-// once for its pins and once for what load fetches (netlist, 3.6M pins: pin counts
+// once for its pins and once for what load fetches (netlist, 56.5M pins: pin counts
 // 483 us with load called pin by pin, 370 so).  RUN: the nets are neighbours,
 // their pins one run already.  A position's net is the count of net starts at or
 // before it: a flag per position in LDS, one ballot.  Nets come in the first

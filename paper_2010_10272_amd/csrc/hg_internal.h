@@ -26,7 +26,7 @@ constexpr int kSmallRow = 64;          // incidence rows up to this length sort 
 constexpr int kNumXcd = 8;             // MI355X: 8 XCDs, each with its own L2
 constexpr int kLdsHistEntries = 2048;  // per-workgroup LDS gain histogram (k * buckets)
 constexpr int kSelectGrid = 2048;      // persistent workgroups of the select sweep
-constexpr int kFinalizeGrid = 2048;    // persistent workgroups of the finalize sweep
+constexpr int kFinalizeGrid = 4096;    // persistent workgroups of the finalize sweep
 
 // Validation bits raised on the device.
 enum : int {

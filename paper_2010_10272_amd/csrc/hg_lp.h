@@ -9,7 +9,7 @@
 
 namespace hg {
 
-constexpr int kFinalChunk = 4 * kBlock;   // nets per unit of the finalize sweep (4 flags per thread)
+constexpr int kFinalChunk = kBlock;   // nets per unit of the finalize sweep
 
 typedef void (*SelectKernel)(Launch);
 typedef void (*FinalizeKernel)(Launch);

@@ -1013,10 +1013,10 @@ __global__ __launch_bounds__(kBlock) void k_approve_apply(Launch L) {
 
 // --------------------------------------------------------------- finalize
 
-// Unit: a block of kFinalChunk (1024) nets, a quarter of it per wavefront.  The
+// Unit: a block of kFinalChunk (256) nets, a quarter of it per wavefront.  The
 // wavefronts work on their own (no barrier): each reads its quarter's touched
-// flags, four per lane, queues the touched nets in LDS and takes them as many
-// at a time as it can count (64, or 32 for k > 128): their pins are made
+// flags, queues the touched nets in LDS and takes them as many at a time as it
+// can count (64, or 32 for k > 128): their pins are made
 // eligible and counted by block (count_batch), every lane rewrites the record of
 // its net.  The record's old Lambda gives the attributed km1 change, w(e) for
 // every block that left it and -w(e) for every one that entered; the drop
@@ -1026,15 +1026,15 @@ __global__ __launch_bounds__(kBlock) void k_approve_apply(Launch L) {
 // What bounds it is the chain flags -> offsets, records -> pins -> blocks and the
 // scattered eligible stores.  Counting anew costs more here than rereading Phi
 // rows that the approve had updated by atomics, but less than those atomics
-// (approve + finalize per round, us: netlist 66 + 63 -> 23 + 96, matrix k = 8
-// 41 + 39 -> 14 + 54, k = 64 49 + 61 -> 13 + 73, 64 small hypergraphs 50 + 127
-// -> 22 + 96; with the gain cache, which then needs no second variant of the
-// walk, 41 + 147 -> 14 + 113).  Blocks from part8 instead of part: matrix k = 8
-// 71 -> 54, k = 64 86 -> 73.
+// (approve + finalize per round, us: netlist 66 + 63 -> 23 + 82, matrix k = 8
+// 41 + 39 -> 14 + 52, k = 64 49 + 61 -> 13 + 68, 64 small hypergraphs 50 + 127
+// -> 22 + 87; with the gain cache, which then needs no second variant of the
+// walk, 41 + 147 -> 14 + 104).  Blocks from part8 instead of part: matrix k = 8
+// 71 -> 54, k = 64 86 -> 73.  A wavefront's life is a few such chains, so small
+// units in many resident workgroups even them out (1024 nets, 2048 workgroups:
+// netlist 96, k = 8 54, k = 64 74, weighted 12.0 against 8.7).
 // Single instance: contiguous XCD-aware runs of blocks.
-constexpr int kFinalQuarter = kFinalChunk / (kBlock / kWave);   // 256 nets: four flags per lane
-static_assert(kFinalQuarter == 4 * kWave, "one 4-byte load of flags per lane");
-constexpr int kFinalQueue = kWave + kFinalQuarter;              // touched nets waiting
+constexpr int kFinalQueue = 2 * kWave;   // touched nets waiting
 
 // Gain-cache deltas of a batch of nets (subsection "Gain Caching"): the four
 // update rules, summed over all moves of the round, change p_i(v) for every pin
@@ -1085,7 +1085,7 @@ __device__ __forceinline__ void cache_deltas(const InstDesc& D, const CountLds& 
 }
 
 template <int WK, bool CACHE>
-__global__ __launch_bounds__(kBlock) void k_finalize(Launch L) {
+__global__ __launch_bounds__(kBlock, !CACHE && WK <= 2 ? 8 : 4) void k_finalize(Launch L) {
   extern __shared__ unsigned s_final[];   // per wavefront: count_words, the queue, cache_words
   __shared__ unsigned long long s_sums[3];
   const WorkItem wi = work_item(L, xcd_block((L.one.m + kFinalChunk - 1) / kFinalChunk));
@@ -1157,33 +1157,24 @@ __global__ __launch_bounds__(kBlock) void k_finalize(Launch L) {
       wave_lds_sync();
     }
   };
-  // four flags per lane in one load (the flag array is padded to whole blocks
-  // and zero past m; the workspace keeps it 4-byte aligned); the next block's
-  // flags are loaded while this block is finalized
-  auto flags_at = [&](int it) {
+  // the next block's flags are loaded while this block is finalized (flags past
+  // m are zero up to a whole block)
+  auto flag_at = [&](int it) {
     const long long c = (long long)wi.first + (long long)it * wi.stride;
-    return it < wi.count ? *reinterpret_cast<const unsigned*>(
-                               D.touched + c * kFinalChunk + wv * kFinalQuarter + 4 * lane)
-                         : 0u;
+    return it < wi.count ? D.touched[c * kFinalChunk + threadIdx.x] : (unsigned char)0;
   };
-  unsigned next = flags_at(0);
+  unsigned char next = flag_at(0);
   int qn = 0;                                              // nets queued (wave-uniform)
   // one call site of batch: the extra last iteration empties the queue
   for (int it = 0; it <= wi.count; ++it) {
     if (it < wi.count) {
-      const unsigned f4 = next;
-      next = flags_at(it + 1);
-      const int e0 = (int)(((long long)wi.first + (long long)it * wi.stride) * kFinalChunk) +
-                     wv * kFinalQuarter + 4 * lane;
-      int mine = 0;
-#pragma unroll
-      for (int x = 0; x < 4; ++x) mine += ((f4 >> (8 * x)) & 0xffu) != 0;
-      const int incl = wave_incl_scan(mine);
-      int at = qn + incl - mine;
-#pragma unroll
-      for (int x = 0; x < 4; ++x)
-        if ((f4 >> (8 * x)) & 0xffu) queue[at++] = e0 + x;
-      qn += last_lane(incl);
+      const bool mine = next != 0;
+      next = flag_at(it + 1);
+      const unsigned long long mask = __ballot(mine);
+      if (mine)
+        queue[lanes_below(mask, qn)] =
+            (int)(((long long)wi.first + (long long)it * wi.stride) * kFinalChunk) + threadIdx.x;
+      qn += __popcll(mask);
       wave_lds_sync();
     }
     while (qn >= NW || (it == wi.count && qn > 0)) {

@@ -44,7 +44,7 @@ __device__ __forceinline__ WorkItem contiguous_units(long long units) {
 // lane need a third fewer operations, but their gathers touch more lines at a
 // time: netlist 370 -> 404 us.)  Per call, before and now: netlist 56.5M pins,
 // k = 16 523 -> 348 us (gathers 135 of them, Phi stores 65), matrix 10M pins
-// k = 8 82 -> 48, k = 64 128 -> 95.
+// k = 8 82 -> 43, k = 64 128 -> 74.
 template <int WK>
 __global__ __launch_bounds__(kBlock) void k_pincounts(Launch L) {
   extern __shared__ unsigned s_count[];   // count_words per wavefront
