@@ -194,7 +194,8 @@ InstDesc make_desc(hg_graph_s* g, int k, long long lmax, int* part, int* phi,
   d.heavy_count = g->info.heavy_count;
   d.num_tiles = g->lay.num_tiles;
   d.hist_stride = g->k_max * kBuckets;
-  d.hist_reps = kHistReplicas;
+  // (brief rounds reread the histogram in every workgroup)
+  d.hist_reps = brief_rounds(d.n, k, d.heavy_count) ? 1 : kHistReplicas;
   d.lmax = lmax;
   d.eptr = g->eptr;
   d.pins = g->pins;

@@ -78,6 +78,20 @@ struct Threshold {
   long long rem_tile; // budget left inside tile tau
 };
 
+// Rounds of one small graph leave out two launches that have next to nothing to
+// do: every tile-sum workgroup finds the thresholds of all k blocks itself, every
+// approve workgroup scans their tile sums.  One wavefront covers kBriefTiles tile
+// sums in one step (131,072 vertices); past 16 blocks the scans cost more than
+// the launches.  Five rounds, us, before and now: n = 1,000 k = 2 166 -> 150,
+// n = 16,000 k = 8 213 -> 200, n = 131,072 k = 2 240 -> 226, k = 16 301 -> 294; but
+// n = 60,000 k = 32 305 -> 314, k = 64 285 -> 331.  Heavy vertices need the separate
+// threshold (k_overflow_resolve).
+constexpr int kBriefTiles = 256;
+constexpr int kBriefMaxK = 16;
+inline bool brief_rounds(int n, int k, int heavy_count) {
+  return n <= kBriefTiles * kTile && k <= kBriefMaxK && heavy_count == 0;
+}
+
 // Facts gathered at load time (device side, copied to the host once).
 struct LoadInfo {
   int err;

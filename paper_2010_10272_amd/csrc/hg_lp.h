@@ -31,6 +31,7 @@ struct RoundPlan {
   std::vector<PlanLaunch> select, heavy, finalize;
   PlanLaunch blocks, tiles, approve, stats;
   bool any_heavy = false;
+  bool brief = false;       // no threshold, no tile scan (brief_rounds)
 };
 
 // The plan of calls that count the pins and run the rounds (InstDesc::kept), from

@@ -681,18 +681,116 @@ __global__ __launch_bounds__(kBlock) void k_overflow_resolve(Launch L) {
 
 // --------------------------------------------------------------- tiles
 
-// Unit: one tile of kTile vertices.
+// Brief rounds: gstar of every block into s_g, and with `publish` into D.thr for
+// the approve.  A wavefront per block, lane i its buckets 255 - 4 i and the three
+// below.
+__device__ __forceinline__ void brief_thresholds(const InstDesc& D, int* s_g, bool publish) {
+  constexpr int kAhead = 4, kWaves = kBlock / kWave;
+  const int lane = lane_id(), k = D.k;
+  for (int t0 = threadIdx.x / kWave; t0 < k; t0 += kAhead * kWaves) {
+    ulonglong2 lo[kAhead], hi[kAhead];
+    long long bw[kAhead];
+#pragma unroll
+    for (int q = 0; q < kAhead; ++q) {
+      const int t = t0 + q * kWaves;
+      lo[q] = hi[q] = ulonglong2{0, 0};
+      bw[q] = 0;
+      if (t < k) {
+        const ulonglong2* col = reinterpret_cast<const ulonglong2*>(
+            D.hist + (size_t)t * kBuckets + (kBuckets - 4) - 4 * lane);
+        lo[q] = col[0];
+        hi[q] = col[1];
+        bw[q] = D.block_w[t];
+      }
+    }
+#pragma unroll
+    for (int q = 0; q < kAhead; ++q) {
+      const int t = t0 + q * kWaves;
+      if (t >= k) break;
+      const long long h[4] = {(long long)hi[q].y, (long long)hi[q].x, (long long)lo[q].y,
+                              (long long)lo[q].x};
+      const long long mine = h[0] + h[1] + h[2] + h[3];
+      const long long budget = D.lmax - bw[q];
+      long long above = wave_incl_scan64(mine) - mine;        // weight of higher gains
+      int at = -1;
+      long long rem = 0;
+#pragma unroll
+      for (int x = 0; x < 4; ++x) {
+        if (at < 0 && h[x] > 0 && above + h[x] > budget) {
+          at = kBuckets - 1 - 4 * lane - x;
+          rem = budget - above;
+        }
+        above += h[x];
+      }
+      const unsigned long long hits = __ballot(at >= 0);
+      const int first = hits ? __ffsll((long long)hits) - 1 : 0;
+      if (lane == first) {
+        s_g[t] = at;
+        if (publish) D.thr[t] = Threshold{at, D.num_tiles, rem, 0};
+      }
+    }
+  }
+}
+
+// Brief rounds: gstar of every block, the tile where each block that is cut runs
+// out of budget, and what is left of it there, from the tile sums (as
+// k_tilescan).  A wavefront per block, lane i tiles 4 i .. 4 i + 3.
+__device__ __forceinline__ void brief_tiles(const InstDesc& D, int* s_g, int* s_tau,
+                                            long long* s_remt) {
+  constexpr int kAhead = 4, kWaves = kBlock / kWave;
+  static_assert(kBriefTiles == 4 * kWave, "four tiles a lane");
+  const int lane = lane_id(), k = D.k, num_tiles = D.num_tiles;
+  for (int t0 = threadIdx.x / kWave; t0 < k; t0 += kAhead * kWaves) {
+    long long v[kAhead][4], rem[kAhead];
+    int g[kAhead];
+#pragma unroll
+    for (int q = 0; q < kAhead; ++q) {
+      const int t = t0 + q * kWaves;
+      const bool in = t < k;
+      g[q] = in ? D.thr[t].gstar : -1;
+      rem[q] = in ? D.thr[t].rem : 0;
+#pragma unroll
+      for (int x = 0; x < 4; ++x)
+        v[q][x] = in && 4 * lane + x < num_tiles
+                      ? D.tilesum[(long long)t * num_tiles + 4 * lane + x]
+                      : 0;
+    }
+#pragma unroll
+    for (int q = 0; q < kAhead; ++q) {
+      const int t = t0 + q * kWaves;
+      if (t >= k) break;
+      const long long mine = v[q][0] + v[q][1] + v[q][2] + v[q][3];
+      long long run = wave_incl_scan64(mine) - mine;
+      int at = num_tiles;
+      long long left = 0;
+#pragma unroll
+      for (int x = 0; x < 4; ++x) {
+        if (at == num_tiles && v[q][x] > 0 && run + v[q][x] > rem[q]) {
+          at = 4 * lane + x;
+          left = rem[q] - run;
+        }
+        run += v[q][x];
+      }
+      // (a block that is not cut has no tile sums: nothing has its gain -1)
+      const unsigned long long hits = __ballot(at < num_tiles);
+      const int first = hits ? __ffsll((long long)hits) - 1 : 0;
+      if (lane == first) {
+        s_g[t] = g[q];
+        s_tau[t] = at;
+        s_remt[t] = left;
+      }
+    }
+  }
+}
+
+// Unit: one tile of kTile vertices.  BRIEF: a brief round (InstDesc::brief).
+template <bool BRIEF>
 __global__ __launch_bounds__(kBlock) void k_tilesum(Launch L) {
   __shared__ unsigned long long s_sum[HG_MAX_K];
   __shared__ int s_g[HG_MAX_K];
   const WorkItem wi = work_item(L, single_unit(blockIdx.x));
   const InstDesc D = inst_desc(L, wi.inst);
   const int k = D.k;
-  for (int i = threadIdx.x; i < k; i += kBlock) {
-    s_sum[i] = 0;
-    s_g[i] = D.thr[i].gstar;
-  }
-  __syncthreads();
   const int tile = wi.first;
   const long long base = (long long)tile * kTile;
   // every candidate word and weight of this thread requested before the first wait
@@ -704,6 +802,12 @@ __global__ __launch_bounds__(kBlock) void k_tilesum(Launch L) {
     x[j] = u < D.n ? D.cand[u] : -1;
     cw[j] = u < D.n && D.vwgt ? D.vwgt[u] : 1;
   }
+  if constexpr (BRIEF) brief_thresholds(D, s_g, tile == 0);
+  for (int i = threadIdx.x; i < k; i += kBlock) {
+    s_sum[i] = 0;
+    if constexpr (!BRIEF) s_g[i] = D.thr[i].gstar;
+  }
+  __syncthreads();
 #pragma unroll
   for (int j = 0; j < kPerThreadTile; ++j) {
     if (x[j] >= 0) {
@@ -890,7 +994,8 @@ __device__ void mark_list(const InstDesc& D, const int* s_list, const int* s_tgt
 // Unit: a tile of kTile vertices (count = 1), or -- boundary workgroups --
 // the tile of target block `first` where its budget runs out (count = -1).
 // Single instance: workgroups [0, num_tiles) are tiles (XCD-remapped), the
-// k after them the boundary workgroups.
+// k after them the boundary workgroups.  BRIEF: a brief round.
+template <bool BRIEF>
 __global__ __launch_bounds__(kBlock) void k_approve_apply(Launch L) {
   __shared__ int s_list[kTile];
   __shared__ int s_tgt[kTile];
@@ -899,6 +1004,7 @@ __global__ __launch_bounds__(kBlock) void k_approve_apply(Launch L) {
   __shared__ long long s_beg[kTile];
   __shared__ int s_g[HG_MAX_K];
   __shared__ int s_tau[HG_MAX_K];
+  __shared__ long long s_remt[BRIEF ? kBriefMaxK : 1];
   __shared__ unsigned long long s_dW[HG_MAX_K];
   __shared__ long long s_tmp[kBlock / kWave];
   __shared__ unsigned s_count;
@@ -912,23 +1018,32 @@ __global__ __launch_bounds__(kBlock) void k_approve_apply(Launch L) {
   const WorkItem wi = work_item(L, fb);
   const InstDesc D = inst_desc(L, wi.inst);
   const int k = D.k, n = D.n, num_tiles = D.num_tiles;
+  const long long* __restrict__ cand = D.cand;
+  const int tile = wi.first;        // (count >= 0)
+  long long xs[kPerThreadTile];     // requested before the first wait
+  if (wi.count >= 0) {
+#pragma unroll
+    for (int j = 0; j < kPerThreadTile; ++j) {
+      const long long u = (long long)tile * kTile + (long long)j * kBlock + threadIdx.x;
+      xs[j] = u < n ? cand[u] : -1;
+    }
+  }
+  if constexpr (BRIEF) {
+    brief_tiles(D, s_g, s_tau, s_remt);
+    if (wi.count < 0)               // for the next round
+      D.hist[(size_t)wi.first * kBuckets + threadIdx.x] = 0;
+  }
   for (int i = threadIdx.x; i < k; i += kBlock) {
-    s_g[i] = D.thr[i].gstar;
-    s_tau[i] = D.thr[i].tau;
+    if constexpr (!BRIEF) {
+      s_g[i] = D.thr[i].gstar;
+      s_tau[i] = D.thr[i].tau;
+    }
     s_dW[i] = 0;
   }
   if (threadIdx.x == 0) s_count = 0;
   __syncthreads();
-  const long long* __restrict__ cand = D.cand;
   if (wi.count >= 0) {
-    const int tile = wi.first;
     const long long base = (long long)tile * kTile;
-    long long xs[kPerThreadTile];   // requested before the first wait
-#pragma unroll
-    for (int j = 0; j < kPerThreadTile; ++j) {
-      const long long u = base + (long long)j * kBlock + threadIdx.x;
-      xs[j] = u < n ? cand[u] : -1;
-    }
 #pragma unroll
     for (int j = 0; j < kPerThreadTile; ++j) {
       const long long u = base + (long long)j * kBlock + threadIdx.x;
@@ -949,7 +1064,11 @@ __global__ __launch_bounds__(kBlock) void k_approve_apply(Launch L) {
   } else {
     // the tile where block t's budget runs out: prefix sums in vertex order
     const int t = wi.first;
-    const Threshold r = D.thr[t];
+    Threshold r = D.thr[t];
+    if constexpr (BRIEF) {
+      r.tau = s_tau[t];
+      r.rem_tile = s_remt[t];
+    }
     if (r.gstar < 0 || r.tau >= num_tiles) return;   // whole workgroup leaves together
     const long long base = (long long)r.tau * kTile + (long long)threadIdx.x * kPerThreadTile;
     long long mine = 0;
@@ -1334,13 +1453,19 @@ hipError_t launch_round_front(const RoundPlan& plan, hipStream_t s, hipEvent_t* 
   for (const PlanLaunch& pl : plan.heavy)
     hipLaunchKernelGGL(k_select_heavy, dim3(pl.grid), dim3(kBlock), 0, s, pl.L);
   if (marks) (void)hipEventRecord(marks[1], s);
+  if (plan.brief) {
+    hipLaunchKernelGGL(k_tilesum<true>, dim3(plan.tiles.grid), dim3(kBlock), 0, s, plan.tiles.L);
+    hipLaunchKernelGGL(k_approve_apply<true>, dim3(plan.approve.grid), dim3(kBlock), 0, s,
+                       plan.approve.L);
+    return hipGetLastError();
+  }
   hipLaunchKernelGGL(k_threshold, dim3(plan.blocks.grid), dim3(kBlock), 0, s, plan.blocks.L);
   if (plan.any_heavy)
     hipLaunchKernelGGL(k_overflow_resolve, dim3(plan.blocks.grid), dim3(kBlock), 0, s,
                        plan.blocks.L);
-  hipLaunchKernelGGL(k_tilesum, dim3(plan.tiles.grid), dim3(kBlock), 0, s, plan.tiles.L);
+  hipLaunchKernelGGL(k_tilesum<false>, dim3(plan.tiles.grid), dim3(kBlock), 0, s, plan.tiles.L);
   hipLaunchKernelGGL(k_tilescan, dim3(plan.blocks.grid), dim3(kBlock), 0, s, plan.blocks.L);
-  hipLaunchKernelGGL(k_approve_apply, dim3(plan.approve.grid), dim3(kBlock), 0, s,
+  hipLaunchKernelGGL(k_approve_apply<false>, dim3(plan.approve.grid), dim3(kBlock), 0, s,
                      plan.approve.L);
   return hipGetLastError();
 }
@@ -1384,6 +1509,7 @@ void single_round_plan(const InstDesc& d, RoundPlan& plan) {
     plan.heavy.push_back(hv);
     plan.any_heavy = true;
   }
+  plan.brief = brief_rounds(d.n, d.k, d.heavy_count);
   plan.blocks.grid = (unsigned)d.k;
   plan.blocks.L = L;
   plan.tiles.grid = (unsigned)d.num_tiles;

@@ -108,7 +108,6 @@ hg_status hg_lp_round_noalloc(hg_graph g, int32_t k, int64_t max_block_w, int32_
   d.touched = base + lay.touched;
   d.hist = (unsigned long long*)(base + lay.hist);
   d.hist_stride = k * hg::kBuckets;
-  d.hist_reps = hg::kHistReplicas;
   d.overflow = (int*)(base + lay.overflow);
   d.thr = (hg::Threshold*)(base + lay.thr);
   d.tilesum = (long long*)(base + lay.tilesum);
