@@ -18,6 +18,8 @@
 #include <string.h>
 
 #include <algorithm>
+#include <array>
+#include <map>
 #include <new>
 #include <vector>
 
@@ -25,12 +27,15 @@
 
 namespace hg {
 
+// Short workgroups: 64 hypergraphs of up to 200,000 vertices, eight rounds, 2145 us
+// with {1, 1, 1}, {2, 2, 2}, {4, 4, 4}, 2047 so.
 const hg_schedule kDefaultSchedule[HG_SIZE_CLASSES] = {
-    {1, 1, 1, 0}, {2, 2, 2, 0}, {4, 4, 4, 0}, {8, 8, 8, 0}};
+    {1, 1, 1, 0}, {2, 2, 1, 0}, {2, 2, 1, 0}, {4, 4, 2, 0}};
 
 namespace {
 
 constexpr int kMaxScheduleChunks = 64;
+constexpr long long kSpreadCost = 1 << 16;      // P + n: fewer stay on one XCD (see build_plans)
 constexpr int kHeavyPerGroup = kBlock / kWave;   // heavy vertices per select workgroup
 constexpr size_t kLaunchSlack = 32 * 256;       // 256-byte alignment of every launch's table
 
@@ -119,25 +124,47 @@ size_t build_plans(const std::vector<BatchMember>& mem, const std::vector<int>& 
                    const hg_schedule* sched, char* dev, char* host, size_t at, size_t cap,
                    RoundPlan* rp, CountPlan* cp) {
   const int cnt = (int)which.size();
-  // XCD placement: longest processing time first on P + n
+  // XCD placement: longest processing time first on P + n, by the sum of an XCD's
+  // shares of the members whose select is one launch and of all members.
+  // (Launches run one after another: members balanced over all of them together
+  // can still leave one XCD with most of a launch.)  A member is spread over all
+  // XCDs where one XCD would be left with it, but not below 2^16 pins and
+  // vertices, which are too few to split eight ways.  Eight rounds of k from 2 to
+  // 128, us, balanced over all launches together and now: 64 hypergraphs of up
+  // to 200,000 vertices 2705 -> 2152, 10 of up to 300,000 1293 -> 1064, 40 of up to
+  // 8,000 723 -> 710.
   std::vector<long long> cost(cnt);
-  long long total = 0;
+  std::vector<const void*> launch(cnt);
   for (int i = 0; i < cnt; ++i) {
-    const hg_graph_s* g = mem[which[i]].g;
+    const BatchMember& M = mem[which[i]];
+    const hg_graph_s* g = M.g;
+    const int view = net_view(M.k, g->unit_nets);
     cost[i] = g->P + g->n;
-    total += cost[i];
+    launch[i] = (const void*)select_kernel(M.k, sweep_view(view, M.k, true), g->P, g->n);
   }
   std::vector<int> order(cnt), home(cnt, -1);
   for (int i = 0; i < cnt; ++i) order[i] = i;
   std::stable_sort(order.begin(), order.end(), [&](int a, int c) { return cost[a] > cost[c]; });
-  long long load[kNumXcd] = {0};
+  std::map<const void*, std::array<long long, kNumXcd + 1>> loads;   // the last: their total
+  std::array<long long, kNumXcd + 1> all{};
+  for (int i = 0; i < cnt; ++i) {
+    loads[launch[i]][kNumXcd] += cost[i];
+    all[kNumXcd] += cost[i];
+  }
   for (int i : order) {
-    if (cost[i] * 16 > total) continue;   // spread over every XCD
+    auto& load = loads[launch[i]];
+    if (cost[i] * 16 > all[kNumXcd] ||
+        (cost[i] * 16 > load[kNumXcd] && cost[i] >= kSpreadCost))
+      continue;                                   // spread over every XCD
+    auto share = [&](int x) {
+      return (double)load[x] / load[kNumXcd] + (double)all[x] / all[kNumXcd];
+    };
     int best = 0;
     for (int x = 1; x < kNumXcd; ++x)
-      if (load[x] < load[best]) best = x;
+      if (share(x) < share(best)) best = x;
     home[i] = best;
     load[best] += cost[i];
+    all[best] += cost[i];
   }
 
   std::vector<InstDesc> descs(cnt);
