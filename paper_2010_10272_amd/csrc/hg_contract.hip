@@ -7,14 +7,14 @@
 //   2. coarse vertex weights by integer atomics;
 //   3. every net's pins are mapped, sorted and deduplicated in the net's own
 //      slots of a scratch copy (tmp[eptr[e] ..]): nets of up to kSmallNet
-//      pins a tile of consecutive nets per workgroup in LDS (stable rank
-//      inside the net, first occurrences numbered by a block scan), longer
+//      pins 64 nets per wavefront in LDS (every pin counts the smaller ones of
+//      its net), longer
 //      nets one workgroup each (bitonic sort in LDS, or in place beyond the
 //      LDS capacity, then a compaction by block scans); the same pass gives
 //      the surviving size and the fingerprint;
 //   4. nets left with fewer than two pins are dropped;
 //   5. identical nets (parallel INRSRT): the fingerprint sum of v^2 and the
-//      size of every net are hashed to a 32-bit key; a stable sort by key
+//      size of every net are hashed to a key of 16 to 32 bits; a stable sort by key
 //      puts candidates for identity next to each other in net-id order, and
 //      each net compares its pins with the nets before it in its run, from
 //      the run's head, until the first identical one -- whose id is then the
@@ -58,9 +58,9 @@ struct Ct {
   int* tmp;              // [P]: net e's sorted distinct coarse pins at eptr[e] ..
   int* big;              // [m]: nets longer than kSmallNet
   int* big_count;        // [1]
-  int* tile_first;       // [tiles + 1]: first net starting in each small-net tile
   int* nsize;            // [m]: pins after deduplication
   unsigned long long* fp;// [m]
+  int key_bits;          // 8 bits per sorting pass
   unsigned* nkey[2];     // [m]
   int* nval[2];          // [m]
   long long* hscan;      // [m]: run heads before a sorted position
@@ -114,6 +114,14 @@ __device__ __forceinline__ unsigned ct_hash(unsigned long long fp, int size) {
   return (unsigned)h;
 }
 
+// The sort key of a net: the hash's first key_bits bits, but not the value of
+// dropped nets, which all share one run.
+__device__ __forceinline__ unsigned ct_dropped(int bits) { return 0xffffffffu >> (32 - bits); }
+__device__ __forceinline__ unsigned ct_key(unsigned hash, int bits) {
+  const unsigned x = hash >> (32 - bits);
+  return x == ct_dropped(bits) ? x - 1 : x;
+}
+
 constexpr int kSmallNet = 128;      // nets up to this many pins go through the tiles
 constexpr int kNetLdsCap = 8192;    // longer nets sort in LDS up to this many pins
 
@@ -121,151 +129,183 @@ __device__ __forceinline__ void ct_net_done(const Ct& C, long long e, int size,
                                             unsigned long long fp) {
   C.nsize[e] = size;
   C.fp[e] = fp;
-  C.nkey[0][e] = size >= 2 ? ct_hash(fp, size) : 0xffffffffu;
+  C.nkey[0][e] = size >= 2 ? ct_key(ct_hash(fp, size), C.key_bits) : ct_dropped(C.key_bits);
   C.nval[0][e] = (int)e;
   C.rep[e] = -1;
   C.wsum[e] = 0;
 }
 
-constexpr int kNetTile = 1024;      // pins per small-net tile (by net start)
+// Small nets: a wavefront takes 64 consecutive nets, as many of them at a time as
+// fit its kCtCap LDS places; no barrier, the wavefronts work on their own.  A net
+// lies at a multiple of four places, filled up with a value above all others.
+//   1. lane = place: the mapped pin goes to LDS (kCtFlight pins and map values on
+//      their way; a place's net is the count of net starts at or before it).
+//   2. lane = place: the number of smaller values in its net, read four at a time,
+//      is its place in sorted order; equal pins write the same value to the same
+//      place, so the places left empty are the duplicates'.
+//   3. lane = place: the distinct pins leave side by side; prefix sums give
+//      sizes and fingerprints.
+// Long nets are listed for k_ct_big_nets, 64 at a time (one atomic each).
+// What bounds it: the comparisons (a pin's net has 27 pins on average on the
+// sparse matrix, whose nets have 10) and the gathers of the map.  Workgroups that
+// went through a tile of 1,024 pins together, with a dozen barriers, binary
+// searches for the nets and LDS atomics for the fingerprints, took 195 us for 10M
+// pins; 128 so.
+constexpr int kCtCap = 832;          // LDS places of a wavefront
+constexpr int kCtFlight = 4;
+constexpr int kCtGrid = 2048;        // persistent workgroups
 
-// tile_first[t] = the first net whose first pin is at or after kNetTile * t
-// (m when there is none); every net writes the entries of the tiles between
-// its predecessor's start and its own.
-__global__ __launch_bounds__(kBlock) void k_ct_tiles(Ct C, long long tiles) {
-  const long long e = (long long)blockIdx.x * kBlock + threadIdx.x;
-  if (e > C.m) return;
-  const long long from = e == 0 ? 0 : (C.eptr[e - 1] / kNetTile) + 1;
-  const long long to = e == C.m ? tiles : C.eptr[e] / kNetTile;
-  for (long long t = from; t <= to; ++t) C.tile_first[t] = (int)e;
+struct CtLds {
+  int val[kCtCap];
+  int sorted[kCtCap];
+  unsigned char net[kCtCap];
+  unsigned char flag[kCtFlight * kWave];
+  int shift[kWave];                  // pin position - place, per net
+  int start[kWave + 1];
+  int len[kWave + 1];                // pins; then distinct pins before the net
+  int big[2 * kWave];
+  unsigned long long sum[kWave + 1]; // of squares before the net
+};
+
+__device__ __forceinline__ void ct_flush_big(const Ct& C, CtLds& M, int count) {
+  const int lane = lane_id();
+  unsigned at = 0;
+  if (lane == 0) at = atomicAdd((unsigned*)C.big_count, (unsigned)count);
+  at = __shfl(at, 0);
+  if (lane < count) C.big[at + lane] = M.big[lane];
 }
 
-// Small nets, a tile at a time: the nets whose first pin lies in pins
-// [kNetTile * t, kNetTile * (t + 1)) -- at most kNetTile + kSmallNet - 1 pins
-// when every one of them is small, because a long net ends the tile.  Their
-// mapped pins go to LDS; every pin learns whether it is the first of its
-// value in its net and, if so, how many distinct values of the net are
-// smaller (its place in the sorted distinct list); sizes and fingerprints
-// are LDS sums per net.  Long nets are listed for k_ct_big_nets.
 __global__ __launch_bounds__(kBlock) void k_ct_small_nets(Ct C) {
-  constexpr int kCap = kNetTile + kSmallNet;
-  __shared__ int s_val[kCap];
-  __shared__ short s_net[kCap];
-  __shared__ int s_sorted[kCap];
-  __shared__ int s_rank[kCap + 1];
-  __shared__ int s_start[kNetTile + 1];
-  __shared__ unsigned long long s_fp[kNetTile];
-  __shared__ long long s_tmp[kBlock / kWave];
-  __shared__ int s_e0, s_e1;
-  __shared__ unsigned s_big, s_big_base;
-  __shared__ int s_bigv[kNetTile / (kSmallNet + 1) + 2];   // long nets starting in a tile
-  const long long tiles = (C.P + kNetTile - 1) / kNetTile;
-  for (long long t = blockIdx.x; t < tiles; t += gridDim.x) {
-    if (threadIdx.x < 2) {
-      const int f = C.tile_first[t + threadIdx.x];
-      if (threadIdx.x == 0) s_e0 = f; else s_e1 = f;
+  __shared__ __attribute__((aligned(16))) CtLds s_lds[kBlock / kWave];
+  const int lane = lane_id(), wv = threadIdx.x / kWave;
+  CtLds& M = s_lds[wv];
+  constexpr int kEmpty = -1, kAbove = 0x7fffffff;
+  for (int i = lane; i < kCtFlight * kWave; i += kWave) M.flag[i] = 0;
+  int big = 0;                                        // long nets queued
+  for (long long e0 = ((long long)blockIdx.x * (kBlock / kWave) + wv) * kWave; e0 < C.m;
+       e0 += (long long)gridDim.x * kBlock) {
+    const long long e = e0 + lane;
+    long long b = 0;
+    int len = 0;
+    if (e < C.m) {
+      b = C.eptr[e];
+      const long long size = C.eptr[e + 1] - b;
+      len = size > kSmallNet ? kSmallNet + 1 : (int)size;
     }
-    if (threadIdx.x == 0) s_big = 0;
-    __syncthreads();
-    const int e0 = s_e0, nets = s_e1 - s_e0;
-    // local offsets of the small nets (long nets take no room)
-    long long carry = 0;
-    for (int j0 = 0; j0 < nets; j0 += kBlock) {
-      const int j = j0 + threadIdx.x;
-      int size = 0;
-      if (j < nets) {
-        const long long e = e0 + j;
-        size = (int)(C.eptr[e + 1] - C.eptr[e]);
-        if (size > kSmallNet) {
-          s_bigv[atomicAdd(&s_big, 1u)] = (int)e;
-          size = 0;
+    const unsigned long long longs = __ballot(len > kSmallNet);
+    if (longs) {
+      if (len > kSmallNet) {
+        M.big[lanes_below(longs, big)] = (int)e;
+        len = 0;
+      }
+      big += __popcll(longs);
+      wave_lds_sync();
+      if (big >= kWave) {
+        ct_flush_big(C, M, kWave);
+        wave_lds_sync();
+        const int rest = M.big[kWave + lane];
+        wave_lds_sync();
+        M.big[lane] = rest;
+        big -= kWave;
+        wave_lds_sync();
+      }
+    }
+    for (int from = 0; from < kWave;) {
+      // lanes [from, to): the nets that fit
+      const int room = lane >= from ? (len + 3) & ~3 : 0;
+      const int incl = wave_incl_scan(room);
+      const unsigned long long over = __ballot(incl > kCtCap);
+      const int to = over ? __ffsll((long long)over) - 1 : kWave;
+      const bool here = lane >= from && lane < to && len > 0;
+      const int first = incl - room;
+      const unsigned long long in = __ballot(here);
+      from = to;
+      if (!in) continue;
+      const int total = __shfl(incl, 63 - __clzll((long long)in));
+      const int at = lanes_below(in, 0), count = __popcll(in);
+      if (here) {
+        M.shift[at] = (int)b - first;                 // pin positions are below 2^31
+        M.start[at] = first;
+        M.len[at] = len;
+      }
+      if (lane == 0) M.start[count] = total;
+      // 1. mapped pins
+      int before = -1;
+      for (int s = 0; s < total; s += kCtFlight * kWave) {
+        if (here && first >= s && first < s + kCtFlight * kWave) M.flag[first - s] = 1;
+        wave_lds_sync();
+        int pin[kCtFlight], x[kCtFlight];
+#pragma unroll
+        for (int q = 0; q < kCtFlight; ++q) {
+          const int p = s + q * kWave + lane;
+          const int mark = M.flag[q * kWave + lane];
+          M.flag[q * kWave + lane] = 0;
+          const unsigned long long starts = __ballot(mark != 0);
+          const int net = lanes_below(starts, before) + mark;
+          before += __popcll(starts);
+          pin[q] = -1;
+          if (p < total) {
+            M.net[p] = (unsigned char)net;
+            if (p - M.start[net] < M.len[net]) pin[q] = C.pins[M.shift[net] + p];
+          }
         }
-      }
-      long long tot;
-      const long long ex = block_excl_scan64(size, s_tmp, &tot);
-      if (j < nets) {
-        s_start[j] = (int)(carry + ex);
-        s_fp[j] = 0;
-      }
-      carry += tot;
-    }
-    const int total = (int)carry;
-    if (threadIdx.x == 0) s_start[nets] = total;
-    __syncthreads();
-    // mapped pins into LDS: every thread's positions first, then all their
-    // pin loads, then all their map loads (independent loads in flight)
-    constexpr int kPer = (kCap + kBlock - 1) / kBlock;
-    long long src[kPer];
-    int pin[kPer];
 #pragma unroll
-    for (int r = 0; r < kPer; ++r) {
-      const int q = threadIdx.x + r * kBlock;
-      src[r] = -1;
-      if (q < total) {
-        int lo = 0, hi = nets - 1;     // net: the last j with s_start[j] <= q
-        while (lo < hi) {
-          const int mid = (lo + hi + 1) >> 1;
-          if (s_start[mid] <= q) lo = mid; else hi = mid - 1;
+        for (int q = 0; q < kCtFlight; ++q) x[q] = pin[q] >= 0 ? C.map[pin[q]] : kAbove;
+#pragma unroll
+        for (int q = 0; q < kCtFlight; ++q) {
+          const int p = s + q * kWave + lane;
+          if (p < total) {
+            M.val[p] = x[q];
+            M.sorted[p] = kEmpty;
+          }
         }
-        src[r] = C.eptr[e0 + lo] + (q - s_start[lo]);
-        s_net[q] = (short)lo;
+        wave_lds_sync();
       }
-    }
-#pragma unroll
-    for (int r = 0; r < kPer; ++r) pin[r] = src[r] >= 0 ? C.pins[src[r]] : 0;
-#pragma unroll
-    for (int r = 0; r < kPer; ++r)
-      if (src[r] >= 0) s_val[threadIdx.x + r * kBlock] = C.map[pin[r]];
-    __syncthreads();
-    // stable rank inside the net -> sorted copy (a permutation of the net)
-    for (int q = threadIdx.x; q < total; q += kBlock) {
-      const int j = s_net[q], x = s_val[q];
-      const int b = s_start[j], t2 = s_start[j + 1];
-      int rank = 0;
-#pragma unroll 4
-      for (int r = b; r < t2; ++r) {
-        const int v = s_val[r];
-        rank += v < x || (v == x && r < q);
+      // 2. places in sorted order
+      for (int p = lane; p < total; p += kWave) {
+        const int net = M.net[p], x = M.val[p];
+        const int f = M.start[net], t = M.start[net + 1];
+        int rank = 0;
+        for (int r = f; r < t; r += 4) {
+          const int4 v = *reinterpret_cast<const int4*>(&M.val[r]);
+          rank += (v.x < x) + (v.y < x) + (v.z < x) + (v.w < x);
+        }
+        if (p - f < M.len[net]) M.sorted[f + rank] = x;
       }
-      s_sorted[b + rank] = x;
-    }
-    __syncthreads();
-    // first occurrences in sorted order, numbered by a scan over the tile
-    long long run = 0;
-    int firsts[kPer];
-#pragma unroll
-    for (int r = 0; r < kPer; ++r) {
-      const int q = threadIdx.x + r * kBlock;
-      int f = 0;
-      if (q < total) {
-        const int j = s_net[q];
-        f = q == s_start[j] || s_sorted[q - 1] != s_sorted[q];
+      wave_lds_sync();
+      // 3. out, counted and summed up along the places: a net's size and
+      // fingerprint are differences of the sums at its start and end
+      int places = 0;
+      unsigned long long sum = 0;
+      for (int s = 0; s < total; s += kWave) {
+        const int p = s + lane;
+        const int net = p < total ? M.net[p] : 0, x = p < total ? M.sorted[p] : kEmpty;
+        const bool distinct = x != kEmpty;
+        const unsigned long long sq =
+            distinct ? (unsigned long long)(unsigned)x * (unsigned)x : 0ull;
+        const long long upto = wave_incl_scan64((long long)sq);
+        const unsigned long long mask = __ballot(distinct);
+        const int place = lanes_below(mask, places);
+        const int f = M.start[net];
+        if (p == f) {
+          M.len[net] = place;
+          M.sum[net] = sum + (unsigned long long)upto - sq;
+        }
+        wave_lds_sync();
+        if (distinct) C.tmp[M.shift[net] + f + (place - M.len[net])] = x;
+        places += __popcll(mask);
+        sum += (unsigned long long)last_lane(upto);
       }
-      firsts[r] = f;
-      long long tot;
-      const long long ex = block_excl_scan64(f, s_tmp, &tot);
-      if (q < total) s_rank[q] = (int)(run + ex);
-      run += tot;
+      if (lane == 0) {
+        M.len[count] = places;
+        M.sum[count] = sum;
+      }
+      wave_lds_sync();
+      if (here) ct_net_done(C, e, M.len[at + 1] - M.len[at], M.sum[at + 1] - M.sum[at]);
+      wave_lds_sync();
     }
-    if (threadIdx.x == 0) s_rank[total] = (int)run;
-    __syncthreads();
-#pragma unroll
-    for (int r = 0; r < kPer; ++r) {
-      const int q = threadIdx.x + r * kBlock;
-      if (q >= total || !firsts[r]) continue;
-      const int j = s_net[q], x = s_sorted[q];
-      C.tmp[C.eptr[e0 + j] + (s_rank[q] - s_rank[s_start[j]])] = x;
-      atomicAdd(&s_fp[j], (unsigned long long)(unsigned)x * (unsigned)x);
-    }
-    __syncthreads();
-    for (int j = threadIdx.x; j < nets; j += kBlock)
-      if (s_start[j + 1] > s_start[j])
-        ct_net_done(C, e0 + j, s_rank[s_start[j + 1]] - s_rank[s_start[j]], s_fp[j]);
-    if (threadIdx.x == 0 && s_big) s_big_base = atomicAdd((unsigned*)C.big_count, s_big);
-    __syncthreads();
-    for (int j = threadIdx.x; j < (int)s_big; j += kBlock) C.big[s_big_base + j] = s_bigv[j];
-    __syncthreads();
   }
+  if (big) ct_flush_big(C, M, big);
 }
 
 // One workgroup per listed net (workgroups stride over the list): map,
@@ -341,14 +381,24 @@ __device__ bool ct_same(const Ct& C, long long be, long long bf, int size) {
 }
 
 // Sorted position j: the first net of j's run (from the head, in net-id
-// order) with the same pins is the representative of j's net.
+// order) with the same pins is the representative of j's net.  Nearly every run
+// is one net, which then writes its weight itself: one atomic per net (20 G a
+// second for the whole GPU) took 47 us for 1M nets, 26 with the few that
+// are needed.
 __global__ __launch_bounds__(kBlock) void k_ct_reps(Ct C, const unsigned* key, const int* val) {
   const long long j = (long long)blockIdx.x * kBlock + threadIdx.x;
   if (j >= C.m) return;
+  const unsigned x = key[j];
+  if (x == ct_dropped(C.key_bits)) return;
   const int e = val[j];
+  const unsigned w = (unsigned)(C.ewgt ? C.ewgt[e] : 1);
+  const bool head = j == 0 || x != key[j - 1];
+  if (head && (j + 1 == C.m || x != key[j + 1])) {
+    C.rep[e] = e;
+    C.wsum[e] = w;
+    return;
+  }
   const int size = C.nsize[e];
-  if (size < 2) return;
-  const bool head = j == 0 || key[j] != key[j - 1];
   const long long h = C.heads[C.hscan[j] + (head ? 1 : 0) - 1];
   const unsigned long long fe = C.fp[e];
   const long long be = C.eptr[e];
@@ -362,7 +412,7 @@ __global__ __launch_bounds__(kBlock) void k_ct_reps(Ct C, const unsigned* key, c
     }
   }
   C.rep[e] = r;
-  atomicAdd(&C.wsum[r], (unsigned)(C.ewgt ? C.ewgt[e] : 1));
+  atomicAdd(&C.wsum[r], w);
 }
 
 struct KeptF {
@@ -376,21 +426,57 @@ struct KeptSizeF {
   __device__ long long operator()(long long e) const { return rep[e] == e ? nsize[e] : 0; }
 };
 
-// kEmitLanes lanes per net copy a kept net's pins side by side.
-constexpr int kEmitLanes = 8;
-
+// The pins of the kept nets.  A wavefront takes 64 consecutive nets; their coarse
+// pins are one run, written kCtFlight per lane at a time (a position's net is the
+// count of net starts at or before it: a flag per position in LDS, one ballot).
+// Bound by its bytes; eight lanes a net took 55 us for 9M pins, 22 so.
 __global__ __launch_bounds__(kBlock) void k_ct_emit(Ct C) {
-  const long long e = ((long long)blockIdx.x * kBlock + threadIdx.x) / kEmitLanes;
-  const int gl = threadIdx.x % kEmitLanes;
-  if (e >= C.m || C.rep[e] != e) return;
-  const long long id = C.nid[e], pos = C.npos[e];
-  const long long b = C.eptr[e];
-  const int size = C.nsize[e];
-  if (gl == 0) {
+  __shared__ unsigned char s_flag[kBlock / kWave][kCtFlight * kWave];
+  __shared__ long long s_shift[kBlock / kWave][kWave];
+  const int lane = lane_id(), wv = threadIdx.x / kWave;
+  unsigned char* flag = s_flag[wv];
+  long long* shift = s_shift[wv];
+  for (int i = lane; i < kCtFlight * kWave; i += kWave) flag[i] = 0;
+  const long long e = ((long long)blockIdx.x * (kBlock / kWave) + wv) * kWave + lane;
+  const bool kept = e < C.m && C.rep[e] == e;
+  const unsigned long long in = __ballot(kept);
+  if (!in) return;
+  long long pos = 0;
+  int len = 0;
+  if (kept) {
+    const long long id = C.nid[e];
+    pos = C.npos[e];
+    len = C.nsize[e];
     C.ceptr[id] = pos;
     C.cewgt[id] = (int)C.wsum[e];
+    shift[lanes_below(in, 0)] = C.eptr[e] - pos;
   }
-  for (int x = gl; x < size; x += kEmitLanes) C.cpins[pos + x] = C.tmp[b + x];
+  const long long run = __shfl(pos, __ffsll((long long)in) - 1);
+  const int last = 63 - __clzll((long long)in);
+  const long long total = __shfl(pos, last) + __shfl(len, last) - run;
+  const long long first = pos - run;                      // kept nets have at least two pins
+  int before = -1;
+  for (long long s = 0; s < total; s += kCtFlight * kWave) {
+    if (kept && first >= s && first < s + kCtFlight * kWave) flag[first - s] = 1;
+    wave_lds_sync();
+    int x[kCtFlight];
+#pragma unroll
+    for (int q = 0; q < kCtFlight; ++q) {
+      const long long p = s + q * kWave + lane;
+      const int mark = flag[q * kWave + lane];
+      flag[q * kWave + lane] = 0;
+      const unsigned long long starts = __ballot(mark != 0);
+      const int net = lanes_below(starts, before) + mark;
+      before += __popcll(starts);
+      if (p < total) x[q] = C.tmp[shift[net] + run + p];
+    }
+#pragma unroll
+    for (int q = 0; q < kCtFlight; ++q) {
+      const long long p = s + q * kWave + lane;
+      if (p < total) C.cpins[run + p] = x[q];
+    }
+    wave_lds_sync();
+  }
 }
 
 __global__ void k_ct_close(Ct C) {
@@ -400,7 +486,7 @@ __global__ void k_ct_close(Ct C) {
 }  // namespace
 
 struct ContractLayout {
-  size_t used, rank, cw, tmp, big, big_count, tile_first, nsize, fp, nkey[2], nval[2], hscan, heads, rep, wsum,
+  size_t used, rank, cw, tmp, big, big_count, nsize, fp, nkey[2], nval[2], hscan, heads, rep, wsum,
       nid, npos, csum, coff, nhist, ndtot, total;
 };
 
@@ -418,7 +504,6 @@ static ContractLayout contract_layout(long long n, long long m, long long P) {
   L.tmp = take(4 * (size_t)P);
   L.big = take(4 * (size_t)m);
   L.big_count = take(4);
-  L.tile_first = take(4 * (size_t)((P + kNetTile - 1) / kNetTile + 1));
   for (int i = 0; i < 2; ++i) {
     L.nkey[i] = take(4 * (size_t)m);
     L.nval[i] = take(4 * (size_t)m);
@@ -479,7 +564,6 @@ static hipError_t launch_contract(hg_graph_s* g, const int* cluster, int* map, i
   C.tmp = (int*)(ws + L.tmp);
   C.big = (int*)(ws + L.big);
   C.big_count = (int*)(ws + L.big_count);
-  C.tile_first = (int*)(ws + L.tile_first);
   C.nsize = (int*)(ws + L.nsize);
   C.fp = (unsigned long long*)(ws + L.fp);
   C.hscan = (long long*)(ws + L.hscan);
@@ -493,6 +577,9 @@ static hipError_t launch_contract(hg_graph_s* g, const int* cluster, int* map, i
   B.csum = (long long*)(ws + L.csum);
   B.coff = (long long*)(ws + L.coff);
   const long long n = g->n, m = g->m;
+  // one sorting pass (23 us for 1M nets) per 8 bits: at least 16 key values per
+  // net, so that few nets that differ share a run
+  C.key_bits = m <= (1 << 12) ? 16 : m <= (1 << 20) ? 24 : 32;
 
   // 1-2. renumbering, map, coarse weights
   ZeroRanges Z;
@@ -507,10 +594,8 @@ static hipError_t launch_contract(hg_graph_s* g, const int* cluster, int* map, i
   hipLaunchKernelGGL(k_ct_vweights, dim3(blocks_of(n)), dim3(kBlock), 0, s, C);
 
   // 3-4. per net: mapped, sorted, deduplicated pins, size, fingerprint
-  const long long tiles = (g->P + kNetTile - 1) / kNetTile;
-  hipLaunchKernelGGL(k_ct_tiles, dim3(blocks_of(m + 1)), dim3(kBlock), 0, s, C, tiles);
-  long long sg = tiles < 8192 ? tiles : 8192;
-  hipLaunchKernelGGL(k_ct_small_nets, dim3((unsigned)sg), dim3(kBlock), 0, s, C);
+  const unsigned sg = blocks_of(m) < kCtGrid ? blocks_of(m) : kCtGrid;
+  hipLaunchKernelGGL(k_ct_small_nets, dim3(sg), dim3(kBlock), 0, s, C);
   hipLaunchKernelGGL(k_ct_big_nets, dim3(1024), dim3(kBlock), 0, s, C);
 
   // 5. identical nets
@@ -520,7 +605,7 @@ static hipError_t launch_contract(hg_graph_s* g, const int* cluster, int* map, i
   SN.dtot = (unsigned*)(ws + L.ndtot);
   SN.n = (int)m;
   SN.tiles = sort_tiles(m);
-  for (int shift = 0; shift < 32; shift += 8) {
+  for (int shift = 0; shift < C.key_bits; shift += 8) {
     SN.key_in = C.nkey[ncur];
     SN.val_in = C.nval[ncur];
     SN.key_out = C.nkey[ncur ^ 1];
@@ -537,7 +622,7 @@ static hipError_t launch_contract(hg_graph_s* g, const int* cluster, int* map, i
   // 6. coarse net CSR in representative order
   exclusive_scan(KeptF{C.rep}, m, C.nid, &sizes[1], B, s);
   exclusive_scan(KeptSizeF{C.rep, C.nsize}, m, C.npos, &sizes[2], B, s);
-  hipLaunchKernelGGL(k_ct_emit, dim3(blocks_of(m * kEmitLanes)), dim3(kBlock), 0, s, C);
+  hipLaunchKernelGGL(k_ct_emit, dim3(blocks_of(m)), dim3(kBlock), 0, s, C);
   hipLaunchKernelGGL(k_ct_close, dim3(1), dim3(kWave), 0, s, C);
   return hipGetLastError();
 }
