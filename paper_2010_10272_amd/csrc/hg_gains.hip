@@ -18,9 +18,7 @@ namespace hg {
 // Row u of `gains` (k int64) and benefit[u] are written.
 // With `cache` set, the sweeps fill a gain cache instead (subsection "Gain
 // Caching"): b(u), w(I(u)) and the row p_i(u) = w(I(u)) - conn_i (0 for the
-// own block), laid out as cache_pbase / cache_stride say.  With only_over
-// set, only vertices of blocks heavier than L_max are filled (the rows the
-// rebalancer reads).
+// own block), laid out as cache_pbase / cache_stride say.
 // Staged output of a wavefront's gain rows (k a multiple of S): the lanes
 // put S gains of their own rows into LDS, then write them out as 64 rows of
 // S * 8 contiguous bytes, S / 2 lanes per row, so that every store covers
@@ -64,7 +62,7 @@ __device__ __forceinline__ void write_rows_staged(long long (*stage)[kStageMax +
 template <int WK, int VIEW>
 __global__ __launch_bounds__(kBlock) void k_gains_light(Launch L, long long* __restrict__ gains,
                                                         long long* __restrict__ benefit,
-                                                        int* __restrict__ cache, int only_over) {
+                                                        int* __restrict__ cache) {
   // rows of a multiple of 8 blocks leave through LDS (write_rows_staged)
   __shared__ long long s_stage[kBlock / kWave][kWave][kStageMax + 1];
   WorkItem fb;
@@ -77,8 +75,7 @@ __global__ __launch_bounds__(kBlock) void k_gains_light(Launch L, long long* __r
   const int k = D.k;
   const long long u = (long long)wi.first * kBlock + threadIdx.x;
   const bool staged = !cache && gains && k % 8 == 0;
-  // done: nothing to compute for this lane (out of range, invalid block, or
-  // a block within L_max when only overloaded blocks are asked for);
+  // done: nothing to compute for this lane (out of range, invalid block);
   // have: this lane's row was computed here (a light vertex)
   bool done = false;
   int a = 0;
@@ -96,8 +93,6 @@ __global__ __launch_bounds__(kBlock) void k_gains_light(Launch L, long long* __r
       }
       done = true;
       a = 0;
-    } else if (only_over && D.block_w[a] <= D.lmax) {
-      done = true;
     }
   } else {
     done = true;
@@ -159,7 +154,8 @@ __global__ __launch_bounds__(kBlock) void k_gains_light(Launch L, long long* __r
     write_rows_staged<8, WK>(stage, gains, k, row0, rows, have, a, base, C);
 }
 
-// Unit: 4 consecutive heavy-list entries (one per wavefront).
+// Unit: 4 consecutive heavy-list entries (one per wavefront).  With only_over
+// set, only vertices of blocks heavier than L_max (the rows the rebalancer reads).
 __global__ __launch_bounds__(kBlock) void k_gains_heavy(Launch L, long long* __restrict__ gains,
                                                         long long* __restrict__ benefit,
                                                         int* __restrict__ cache, int only_over) {
@@ -237,18 +233,25 @@ GainsKernel gains_kernel(int k, int view) {
 }
 
 hipError_t launch_gains(hg_graph_s* g, const InstDesc& d, long long* gains, long long* benefit,
-                        hipStream_t s, int* cache, int only_over) {
-  typedef void (*K)(Launch, long long*, long long*, int*, int);
+                        hipStream_t s, int* cache) {
+  typedef void (*K)(Launch, long long*, long long*, int*);
   const Launch L = single_launch(d);
   unsigned grid = (unsigned)(((long long)d.n + kBlock - 1) / kBlock);
   hipLaunchKernelGGL((K)(void*)gains_kernel(d.k, d.view), dim3(grid), dim3(kBlock), 0, s, L,
-                     gains, benefit, cache, only_over);
+                     gains, benefit, cache);
   if (d.heavy_count > 0) {
     unsigned hg = (unsigned)((d.heavy_count + (kBlock / kWave) - 1) / (kBlock / kWave));
-    hipLaunchKernelGGL(k_gains_heavy, dim3(hg), dim3(kBlock), 0, s, L, gains, benefit, cache,
-                       only_over);
+    hipLaunchKernelGGL(k_gains_heavy, dim3(hg), dim3(kBlock), 0, s, L, gains, benefit, cache, 0);
   }
   (void)g;
+  return hipGetLastError();
+}
+
+hipError_t launch_over_rows(const InstDesc& d, int* cache, hipStream_t s) {
+  hipLaunchKernelGGL(k_gains_heavy,
+                     dim3((unsigned)((d.heavy_count + (kBlock / kWave) - 1) / (kBlock / kWave))),
+                     dim3(kBlock), 0, s, single_launch(d), (long long*)nullptr,
+                     (long long*)nullptr, cache, 1);
   return hipGetLastError();
 }
 

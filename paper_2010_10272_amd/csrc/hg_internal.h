@@ -215,6 +215,25 @@ __device__ __forceinline__ InstDesc inst_desc(const Launch& L, int inst) {
   return d;
 }
 
+// XCD-aware strided split of `units` over `grid` workgroups: XCD x owns the
+// contiguous range [x*per_xcd, (x+1)*per_xcd) and its workgroups take
+// neighbouring units side by side.
+__device__ __forceinline__ WorkItem xcd_sweep(long long units) {
+  const int xcd = blockIdx.x % kNumXcd;
+  const int wg_on_xcd = (gridDim.x - xcd + kNumXcd - 1) / kNumXcd;
+  const int li = blockIdx.x / kNumXcd;
+  const long long per_xcd = (units + kNumXcd - 1) / kNumXcd;
+  const long long c_begin = xcd * per_xcd;
+  long long c_end = c_begin + per_xcd;
+  if (c_end > units) c_end = units;
+  WorkItem w;
+  w.inst = 0;
+  w.first = (int)(c_begin + li);
+  w.stride = wg_on_xcd;
+  w.count = c_begin + li < c_end ? (int)((c_end - (c_begin + li) + wg_on_xcd - 1) / wg_on_xcd) : 0;
+  return w;
+}
+
 // Launch argument for one instance (kernels take their units from blockIdx).
 inline Launch single_launch(const InstDesc& d) {
   Launch L;

@@ -87,10 +87,11 @@ hipError_t launch_cached_round(const RoundPlan& plan, int round, hipStream_t s,
 hipError_t launch_counts(const CountPlan& plan, bool want_km1, bool mark_eligible, hipStream_t s);
 void single_count_plan(const InstDesc& d, CountPlan& plan);
 
-// All gains (or, with `cache`, a gain cache: b, w(I), p rows; see hgref.h;
-// with only_over, only the rows of vertices in blocks heavier than d.lmax).
+// All gains (or, with `cache`, a gain cache: b, w(I), p rows; see hgref.h).
 hipError_t launch_gains(hg_graph_s* g, const InstDesc& d, long long* gains, long long* benefit,
-                        hipStream_t s, int* cache = nullptr, int only_over = 0);
+                        hipStream_t s, int* cache = nullptr);
+// The gain cache's entries of the heavy vertices in blocks heavier than d.lmax.
+hipError_t launch_over_rows(const InstDesc& d, int* cache, hipStream_t s);
 hipError_t launch_km1(hg_graph_s* g, int k, const unsigned* netstate, long long* km1,
                       hipStream_t s);
 

@@ -44,6 +44,7 @@
 #include "hg_internal.h"
 #include "hg_lp.h"
 #include "hg_sort.h"
+#include "hg_sweep.h"
 
 namespace hg {
 namespace {
@@ -525,77 +526,126 @@ __global__ __launch_bounds__(kBlock) void k_rb_begin(InstDesc D, Rb R) {
   }
 }
 
-// G lanes per vertex read its penalty row in 16-byte quads.  Every vertex
-// gets defaults (not moved, not proposed, no candidate, key 0, value u);
-// those of overloaded blocks look for the best block i != Pi(u) with
-// c(V_i) + c(u) <= L_max by (p_i(u) asc = gain desc, c(V_i) asc, i asc).
-template <int G>
-__global__ __launch_bounds__(kBlock) void k_rb_select(InstDesc D, Rb R, unsigned* key, int* val) {
+// Candidates: every vertex gets defaults (not moved, not proposed, no candidate,
+// key 0, value u); those of overloaded blocks look for the best block
+// i != Pi(u) with c(V_i) + c(u) <= L_max by (gain desc, c(V_i) asc, i asc).
+//
+// The light sweep, as the label-propagation select: each wavefront queues the
+// vertices of overloaded blocks (few) of its slices and computes 64 of them at a
+// time, the gains straight from the counters.  (Penalty rows of those vertices
+// written by the gains sweep, whose wavefronts were mostly idle lanes, and read
+// back by a second kernel: 65 + 55 us per round on the matrix with k = 64, 24
+// so.)  Rows left to the wavefront path: k_rb_heavy.
+template <int WK, int VIEW>
+__global__ __launch_bounds__(kBlock) void k_rb_light(InstDesc D, Rb R, unsigned* key, int* val) {
   __shared__ long long s_W[HG_MAX_K];
+  __shared__ unsigned s_open[WK], s_some[WK];   // blocks with room for any, for some vertex
   __shared__ long long s_tmp[kBlock / kWave];
+  __shared__ int s_q[kBlock / kWave][2 * kWave];
   const int k = D.k, n = D.n;
   const long long lmax = D.lmax;
-  for (int i = threadIdx.x; i < k; i += kBlock) s_W[i] = D.block_w[i];
+  for (int i = threadIdx.x; i < WK; i += kBlock) s_open[i] = s_some[i] = 0;
   __syncthreads();
-  const int gl = threadIdx.x % G;
-  constexpr int kPer = kBlock / G;
-  const int Q = cache_stride(k) / 4;
-  const int4* __restrict__ rows = (const int4*)(R.cache + cache_pbase(n));
+  for (int i = threadIdx.x; i < k; i += kBlock) {
+    const long long W = D.block_w[i];
+    s_W[i] = W;
+    if (W + D.cmax <= lmax)
+      atomicOr(&s_open[i >> 5], 1u << (i & 31));
+    else if (W < lmax)
+      atomicOr(&s_some[i >> 5], 1u << (i & 31));
+  }
+  __syncthreads();
+  const int lane = lane_id();
+  int* my_q = s_q[threadIdx.x / kWave];
   long long n_cons = 0, n_pins = 0, n_cand = 0;
-  for (long long base = (long long)blockIdx.x * kPer; base < n; base += (long long)gridDim.x * kPer) {
-    const long long u = base + threadIdx.x / G;
-    if (u >= n) continue;
-    if (gl == 0) {
-      D.moved[u] = 0;
-      R.prop[u] = 0;
-      D.cand[u] = -1;
-      key[u] = 0;
-      val[u] = (int)u;
+  auto wave_vertices = [&](const long long u, const bool act) {
+    int a = 0, deg = 0;
+    long long b0 = 0, cu = 1;
+    if (act) {
+      a = D.part[u];
+      b0 = D.vptr[u];
+      const long long len = D.vptr[u + 1] - b0;
+      if (D.vwgt) cu = D.vwgt[u];
+      if (len <= kLightLimit) deg = (int)len;
+      else b0 = -1;                              // the heavy kernel's
     }
-    const int a = D.part[u];
-    if ((unsigned)a >= (unsigned)k) {
-      if (gl == 0) atomicOr(D.err_flags, kErrPart);
-      continue;
-    }
-    if (s_W[a] <= lmax) continue;
-    const long long cu = D.vwgt ? D.vwgt[u] : 1;
-    int bp = 0, bi = -1;
-    long long bw = 0;
-    for (int q = gl; q < Q; q += G) {
-      const int4 p4 = rows[u * Q + q];
-      const int pv[4] = {p4.x, p4.y, p4.z, p4.w};
+    const bool mine = act && b0 >= 0;
+    RowSums<WK, VIEW> S;
+    walk_row<WK, VIEW, 4>(D, D.view_ptr, mine ? b0 : 0, deg, a, S);
+    if (!mine || S.heavy) return;
+    n_cons += 1;
+    n_pins += deg;
+    unsigned F[WK], any = 0;
 #pragma unroll
-      for (int j = 0; j < 4; ++j) {
-        const int i = q * 4 + j;
-        if (i >= k || i == a) continue;
+    for (int w = 0; w < WK; ++w) {
+      F[w] = s_open[w];
+      unsigned rest = s_some[w];
+      while (rest) {
+        const int b = __ffs(rest) - 1;
+        rest &= rest - 1;
+        if (s_W[w * 32 + b] + cu <= lmax) F[w] |= 1u << b;
+      }
+      if (w == a >> 5) F[w] &= ~(1u << (a & 31));
+      any |= F[w];
+    }
+    if (!any) return;
+    const int conn = (int)S.C.narrow_to_max(F);
+    int t = -1;
+    long long tw = 0;
+#pragma unroll
+    for (int w = 0; w < WK; ++w) {
+      unsigned x = F[w];
+      while (x) {
+        const int i = w * 32 + __ffs(x) - 1;
+        x &= x - 1;
         const long long Wi = s_W[i];
-        if (Wi + cu > lmax) continue;
-        if (bi < 0 || pv[j] < bp || (pv[j] == bp && Wi < bw)) {
-          bp = pv[j];
-          bi = i;
-          bw = Wi;
+        if (t < 0 || Wi < tw) {
+          t = i;
+          tw = Wi;
         }
       }
     }
-#pragma unroll
-    for (int o = G / 2; o > 0; o >>= 1) {
-      const int op = __shfl_xor(bp, o, G), oi = __shfl_xor(bi, o, G);
-      const long long ow = __shfl_xor(bw, o, G);
-      if (oi >= 0 && (bi < 0 || op < bp || (op == bp && (ow < bw || (ow == bw && oi < bi))))) {
-        bp = op;
-        bi = oi;
-        bw = ow;
+    const int g = S.ben - S.tot + conn;
+    D.cand[u] = pack_cand(g, t);
+    key[u] = R.bias - (unsigned)g;
+    n_cand += 1;
+  };
+  const WorkItem run = xcd_sweep((n + kBlock - 1) / kBlock);
+  int qn = 0;                                    // wave-uniform
+  for (int it = 0; it <= run.count; ++it) {
+    long long u = 0;
+    bool act = false, go = false;
+    if (it < run.count) {
+      u = (long long)(run.first + it * run.stride) * kBlock + threadIdx.x;
+      bool over = false;
+      if (u < n) {
+        const int a = D.part[u];
+        D.moved[u] = 0;
+        R.prop[u] = 0;
+        D.cand[u] = -1;
+        key[u] = 0;
+        val[u] = (int)u;
+        if ((unsigned)a >= (unsigned)k)
+          atomicOr(D.err_flags, kErrPart);
+        else
+          over = s_W[a] > lmax;
       }
+      const unsigned long long mask = __ballot(over);
+      if (over) my_q[lanes_below(mask, qn)] = (int)u;
+      qn += __popcll(mask);                      // < 2 * kWave
+      wave_lds_sync();
+      if (qn >= kWave) {
+        qn -= kWave;
+        u = my_q[qn + lane];                     // the last 64: nothing moves
+        act = go = true;
+        wave_lds_sync();
+      }
+    } else if (qn > 0) {
+      go = true;
+      act = lane < qn;
+      u = act ? my_q[lane] : 0;
     }
-    if (gl != 0) continue;
-    n_cons += 1;
-    n_pins += D.vptr[u + 1] - D.vptr[u];
-    if (bi >= 0) {
-      const int g = R.cache[u] - bp;
-      D.cand[u] = pack_cand(g, bi);
-      key[u] = R.bias - (unsigned)g;
-      n_cand += 1;
-    }
+    if (go) wave_vertices(u, act);
   }
   n_cons = block_sum64(n_cons, s_tmp);
   n_pins = block_sum64(n_pins, s_tmp);
@@ -607,6 +657,78 @@ __global__ __launch_bounds__(kBlock) void k_rb_select(InstDesc D, Rb R, unsigned
     if (n_pins) atomicAdd(&ctr->slot[kCtrActivePins][sl], (unsigned long long)n_pins);
     if (n_cand) atomicAdd(&ctr->slot[kCtrCandidates][sl], (unsigned long long)n_cand);
   }
+}
+
+typedef void (*RbLight)(InstDesc, Rb, unsigned*, int*);
+static RbLight rb_light_kernel(int k, int view) {
+  switch (view) {
+    case kView16: return k_rb_light<1, kView16>;
+    case kView32: return k_rb_light<1, kView32>;
+    case kView64: return k_rb_light<2, kView64>;
+    case kViewUnit:
+      return bit_words(k) == 4 ? k_rb_light<4, kViewUnit> : k_rb_light<8, kViewUnit>;
+    default: break;
+  }
+  switch (bit_words(k)) {
+    case 1: return k_rb_light<1, kViewFull>;
+    case 2: return k_rb_light<2, kViewFull>;
+    case 4: return k_rb_light<4, kViewFull>;
+    default: return k_rb_light<8, kViewFull>;
+  }
+}
+
+// The heavy vertices of overloaded blocks, a wavefront each, from their penalty
+// rows in 16-byte quads (the light sweep wrote their defaults).
+__global__ __launch_bounds__(kBlock) void k_rb_heavy(InstDesc D, Rb R, unsigned* key) {
+  const int k = D.k, n = D.n;
+  const long long lmax = D.lmax;
+  const int idx = (int)blockIdx.x * (kBlock / kWave) + threadIdx.x / kWave;
+  if (idx >= D.heavy_count) return;
+  const long long u = D.heavy_list[idx];
+  const int a = D.part[u], lane = lane_id();
+  if ((unsigned)a >= (unsigned)k || D.block_w[a] <= lmax) return;
+  const int Q = cache_stride(k) / 4;             // <= 64: one quad a lane
+  const int4* __restrict__ rows = (const int4*)(R.cache + cache_pbase(n));
+  const long long cu = D.vwgt ? D.vwgt[u] : 1;
+  int bp = 0, bi = -1;
+  long long bw = 0;
+  if (lane < Q) {
+    const int4 p4 = rows[u * Q + lane];
+    const int pv[4] = {p4.x, p4.y, p4.z, p4.w};
+#pragma unroll
+    for (int j = 0; j < 4; ++j) {
+      const int i = lane * 4 + j;
+      if (i >= k || i == a) continue;
+      const long long Wi = D.block_w[i];
+      if (Wi + cu > lmax) continue;
+      if (bi < 0 || pv[j] < bp || (pv[j] == bp && Wi < bw)) {
+        bp = pv[j];
+        bi = i;
+        bw = Wi;
+      }
+    }
+  }
+#pragma unroll
+  for (int o = kWave / 2; o > 0; o >>= 1) {
+    const int op = __shfl_xor(bp, o), oi = __shfl_xor(bi, o);
+    const long long ow = __shfl_xor(bw, o);
+    if (oi >= 0 && (bi < 0 || op < bp || (op == bp && (ow < bw || (ow == bw && oi < bi))))) {
+      bp = op;
+      bi = oi;
+      bw = ow;
+    }
+  }
+  if (lane != 0) return;
+  if (bi >= 0) {
+    const int g = R.cache[u] - bp;
+    D.cand[u] = pack_cand(g, bi);
+    key[u] = R.bias - (unsigned)g;
+  }
+  const int sl = blockIdx.x % kSlots;
+  RoundCounters* ctr = D.ctr;
+  atomicAdd(&ctr->slot[kCtrEligible][sl], 1ull);
+  atomicAdd(&ctr->slot[kCtrActivePins][sl], (unsigned long long)(D.vptr[u + 1] - D.vptr[u]));
+  if (bi >= 0) atomicAdd(&ctr->slot[kCtrCandidates][sl], 1ull);
 }
 
 // Regroup keys: item i of `order` gets key = source block (by_target = 0)
@@ -968,23 +1090,16 @@ static hipError_t launch_rebalance_round(hg_graph_s* g, InstDesc d, char* ws, hi
   unsigned* key[2] = {(unsigned*)(ws + L.key[0]), (unsigned*)(ws + L.key[1])};
   int* val[2] = {(int*)(ws + L.val[0]), (int*)(ws + L.val[1])};
   hipLaunchKernelGGL(k_rb_begin, dim3(1), dim3(kBlock), 0, s, d, R);
-  hipError_t e = launch_gains(g, d, nullptr, nullptr, s, (int*)(ws + L.cache), 1);
-  if (e != hipSuccess) return e;
-  // candidates: lanes per vertex as the penalty row needs
-  const int q = cache_stride(k) / 4;
-  int G = 1;
-  while (G < q && G < kWave) G <<= 1;
-  typedef void (*SelK)(InstDesc, Rb, unsigned*, int*);
-  SelK sel = G == 1    ? (SelK)k_rb_select<1>
-             : G == 2  ? (SelK)k_rb_select<2>
-             : G == 4  ? (SelK)k_rb_select<4>
-             : G == 8  ? (SelK)k_rb_select<8>
-             : G == 16 ? (SelK)k_rb_select<16>
-             : G == 32 ? (SelK)k_rb_select<32>
-                       : (SelK)k_rb_select<64>;
-  long long sg = ((long long)n + kBlock / G - 1) / (kBlock / G);
-  if (sg > 4096) sg = 4096;
-  hipLaunchKernelGGL(sel, dim3((unsigned)sg), dim3(kBlock), 0, s, d, R, key[0], val[0]);
+  const unsigned chunks = grid_of(n, kBlock);
+  hipLaunchKernelGGL(rb_light_kernel(k, d.view),
+                     dim3(chunks < kSelectGrid ? chunks : (unsigned)kSelectGrid), dim3(kBlock), 0, s,
+                     d, R, key[0], val[0]);
+  if (d.heavy_count > 0) {
+    const hipError_t eh = launch_over_rows(d, (int*)(ws + L.cache), s);
+    if (eh != hipSuccess) return eh;
+    hipLaunchKernelGGL(k_rb_heavy, dim3(grid_of(d.heavy_count, kBlock / kWave)), dim3(kBlock), 0, s,
+                       d, R, key[0]);
+  }
   int cur = 0;
   auto pass = [&](int shift) {
     SortPass P;
@@ -1052,7 +1167,7 @@ static hipError_t launch_rebalance_round(hg_graph_s* g, InstDesc d, char* ws, hi
   S.err_flags = d.err_flags;
   hipLaunchKernelGGL(k_apply_prefix, dim3(grid_of(n, kSeqTile)), dim3(kBlock), 0, s, S,
                      (const long long*)R.best, d);
-  e = hipGetLastError();
+  hipError_t e = hipGetLastError();
   if (e != hipSuccess) return e;
   RoundPlan plan;
   single_round_plan(d, plan);
