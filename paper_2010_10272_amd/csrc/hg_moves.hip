@@ -280,15 +280,26 @@ __global__ __launch_bounds__(kBlock) void k_seq_gains(Seq S, long long* gains, l
 
 // One workgroup: exclusive scan of the chunk sums.
 __global__ __launch_bounds__(kBlock) void k_prefix_top(const long long* csum, long long* coff,
-                                                       int chunks) {
+                                                       const int* items) {
+  constexpr int kPer = 8;            // consecutive sums per thread, all on their way at once
   __shared__ long long s_tmp[kBlock / kWave];
+  const int chunks = (*items + kBlock - 1) / kBlock;
   long long carry = 0;
-  for (int b = 0; b < chunks; b += kBlock) {
-    const int i = b + threadIdx.x;
-    const long long v = i < chunks ? csum[i] : 0;
+  for (int b = 0; b < chunks; b += kBlock * kPer) {
+    const int first = b + threadIdx.x * kPer;
+    long long v[kPer], mine = 0;
+#pragma unroll
+    for (int q = 0; q < kPer; ++q) {
+      v[q] = first + q < chunks ? csum[first + q] : 0;
+      mine += v[q];
+    }
     long long tot;
-    const long long ex = block_excl_scan64(v, s_tmp, &tot);
-    if (i < chunks) coff[i] = carry + ex;
+    long long run = carry + block_excl_scan64(mine, s_tmp, &tot);
+#pragma unroll
+    for (int q = 0; q < kPer; ++q) {
+      if (first + q < chunks) coff[first + q] = run;
+      run += v[q];
+    }
     carry += tot;
   }
 }
@@ -502,7 +513,8 @@ struct Rb {
   int* cnt_src;                // [k + 1]: candidates per source (sentinel k last)
   int* cnt_tgt;                // [k + 1]: proposals per target
   int* cnt_slots;              // [kSlots][k + 1]: per-workgroup-slot counts, summed into cnt
-  unsigned char* prop;         // [n]: proposed this round
+  unsigned char* prop;         // [n]: marks candidates for the first sort, then proposals
+  int* count;                  // [1]: candidates
   int* mt;                     // [n]: target of sorted item i (own block: rejected)
   int* gord;                   // [n]: candidates in (gain desc, id asc) order
   long long* scan;             // [n]: exclusive prefix of item weights
@@ -526,8 +538,8 @@ __global__ __launch_bounds__(kBlock) void k_rb_begin(InstDesc D, Rb R) {
   }
 }
 
-// Candidates: every vertex gets defaults (not moved, not proposed, no candidate,
-// key 0, value u); those of overloaded blocks look for the best block
+// Candidates: every vertex gets defaults (not moved, no candidate, no mark); those
+// of overloaded blocks look for the best block
 // i != Pi(u) with c(V_i) + c(u) <= L_max by (gain desc, c(V_i) asc, i asc).
 //
 // The light sweep, as the label-propagation select: each wavefront queues the
@@ -537,7 +549,7 @@ __global__ __launch_bounds__(kBlock) void k_rb_begin(InstDesc D, Rb R) {
 // back by a second kernel: 65 + 55 us per round on the matrix with k = 64, 24
 // so.)  Rows left to the wavefront path: k_rb_heavy.
 template <int WK, int VIEW>
-__global__ __launch_bounds__(kBlock) void k_rb_light(InstDesc D, Rb R, unsigned* key, int* val) {
+__global__ __launch_bounds__(kBlock) void k_rb_light(InstDesc D, Rb R) {
   __shared__ long long s_W[HG_MAX_K];
   __shared__ unsigned s_open[WK], s_some[WK];   // blocks with room for any, for some vertex
   __shared__ long long s_tmp[kBlock / kWave];
@@ -607,7 +619,7 @@ __global__ __launch_bounds__(kBlock) void k_rb_light(InstDesc D, Rb R, unsigned*
     }
     const int g = S.ben - S.tot + conn;
     D.cand[u] = pack_cand(g, t);
-    key[u] = R.bias - (unsigned)g;
+    R.prop[u] = 1;
     n_cand += 1;
   };
   const WorkItem run = xcd_sweep((n + kBlock - 1) / kBlock);
@@ -623,8 +635,6 @@ __global__ __launch_bounds__(kBlock) void k_rb_light(InstDesc D, Rb R, unsigned*
         D.moved[u] = 0;
         R.prop[u] = 0;
         D.cand[u] = -1;
-        key[u] = 0;
-        val[u] = (int)u;
         if ((unsigned)a >= (unsigned)k)
           atomicOr(D.err_flags, kErrPart);
         else
@@ -659,7 +669,7 @@ __global__ __launch_bounds__(kBlock) void k_rb_light(InstDesc D, Rb R, unsigned*
   }
 }
 
-typedef void (*RbLight)(InstDesc, Rb, unsigned*, int*);
+typedef void (*RbLight)(InstDesc, Rb);
 static RbLight rb_light_kernel(int k, int view) {
   switch (view) {
     case kView16: return k_rb_light<1, kView16>;
@@ -679,7 +689,7 @@ static RbLight rb_light_kernel(int k, int view) {
 
 // The heavy vertices of overloaded blocks, a wavefront each, from their penalty
 // rows in 16-byte quads (the light sweep wrote their defaults).
-__global__ __launch_bounds__(kBlock) void k_rb_heavy(InstDesc D, Rb R, unsigned* key) {
+__global__ __launch_bounds__(kBlock) void k_rb_heavy(InstDesc D, Rb R) {
   const int k = D.k, n = D.n;
   const long long lmax = D.lmax;
   const int idx = (int)blockIdx.x * (kBlock / kWave) + threadIdx.x / kWave;
@@ -722,7 +732,7 @@ __global__ __launch_bounds__(kBlock) void k_rb_heavy(InstDesc D, Rb R, unsigned*
   if (bi >= 0) {
     const int g = R.cache[u] - bp;
     D.cand[u] = pack_cand(g, bi);
-    key[u] = R.bias - (unsigned)g;
+    R.prop[u] = 1;
   }
   const int sl = blockIdx.x % kSlots;
   RoundCounters* ctr = D.ctr;
@@ -731,9 +741,12 @@ __global__ __launch_bounds__(kBlock) void k_rb_heavy(InstDesc D, Rb R, unsigned*
   if (bi >= 0) atomicAdd(&ctr->slot[kCtrCandidates][sl], 1ull);
 }
 
-// Regroup keys: item i of `order` gets key = source block (by_target = 0)
-// or, for proposals, target block (by_target = 1); everything else the
-// sentinel k.  Counts per key go to the count slots (k_rb_sum_counts).
+// Regroup keys: candidate i of `order` gets key = source block (by_target = 0)
+// or, for proposals, target block (by_target = 1), the others the sentinel k.
+// Counts per key go to the count slots (k_rb_sum_counts).  (This and the kernels
+// below have a thread per vertex, but only candidates are items: their number
+// is known on the device alone.  Sorting all vertices, the others with a
+// sentinel: kernels of three rounds on the matrix with k = 64 858 us, 745 so.)
 __global__ __launch_bounds__(kBlock) void k_rb_keys(InstDesc D, Rb R, const int* order,
                                                     int by_target, unsigned* key_out,
                                                     int* val_out) {
@@ -742,14 +755,16 @@ __global__ __launch_bounds__(kBlock) void k_rb_keys(InstDesc D, Rb R, const int*
   for (int i = threadIdx.x; i <= k; i += kBlock) s_cnt[i] = 0;
   __syncthreads();
   const long long i = (long long)blockIdx.x * kBlock + threadIdx.x;
-  const bool live = i < D.n;
+  const int count = *R.count;
+  if ((long long)blockIdx.x * kBlock >= count) return;
+  const bool live = i < count;
   int key = k;
   if (live) {
     const int u = order[i];
     const long long c = D.cand[u];
     if (!by_target) {
       R.gord[i] = u;
-      if (c != -1) key = D.part[u];
+      key = D.part[u];
     } else if (R.prop[u]) {
       key = (int)(c & 0xffffffffLL);
     }
@@ -803,16 +818,17 @@ struct RbItems {
   const int* val;
   const int* vwgt;
   unsigned sentinel;
-  int n;
+  const int* count;
 };
 
 __device__ __forceinline__ long long rb_weight(const RbItems& I, long long i) {
-  if (i >= I.n || I.key[i] == I.sentinel) return 0;
+  if (i >= *I.count || I.key[i] == I.sentinel) return 0;
   return I.vwgt ? I.vwgt[I.val[i]] : 1;
 }
 
 __global__ __launch_bounds__(kBlock) void k_rb_chunk_sums(RbItems I, long long* csum) {
   __shared__ long long s_tmp[kBlock / kWave];
+  if ((long long)blockIdx.x * kBlock >= *I.count) return;
   const long long v = rb_weight(I, (long long)blockIdx.x * kBlock + threadIdx.x);
   const long long tot = block_sum64(v, s_tmp);
   if (threadIdx.x == 0) csum[blockIdx.x] = tot;
@@ -822,9 +838,10 @@ __global__ __launch_bounds__(kBlock) void k_rb_scan(RbItems I, const long long* 
                                                     long long* scan) {
   __shared__ long long s_tmp[kBlock / kWave];
   const long long i = (long long)blockIdx.x * kBlock + threadIdx.x;
+  if ((long long)blockIdx.x * kBlock >= *I.count) return;
   long long tot;
   const long long ex = block_excl_scan64(rb_weight(I, i), s_tmp, &tot);
-  if (i < I.n) scan[i] = coff[blockIdx.x] + ex;
+  if (i < *I.count) scan[i] = coff[blockIdx.x] + ex;
 }
 
 // Start of every key's segment: exclusive scan of the counts (k + 1 <= 257
@@ -844,10 +861,11 @@ __device__ void rb_segment_starts(const int* cnt, int k, long long* s_start, lon
 __global__ __launch_bounds__(kBlock) void k_rb_propose(InstDesc D, Rb R, RbItems I) {
   __shared__ long long s_start[HG_MAX_K + 1];
   __shared__ long long s_tmp[kBlock / kWave];
+  if ((long long)blockIdx.x * kBlock >= *R.count) return;
   rb_segment_starts(R.cnt_src, D.k, s_start, s_tmp);
   const long long i = (long long)blockIdx.x * kBlock + threadIdx.x;
   long long np = 0;
-  if (i < I.n && I.key[i] != I.sentinel) {
+  if (i < *R.count && I.key[i] != I.sentinel) {
     const int a = (int)I.key[i];
     const long long pre = R.scan[i] - R.scan[s_start[a]];
     if (pre < R.excess[a]) {
@@ -865,9 +883,10 @@ __global__ __launch_bounds__(kBlock) void k_rb_propose(InstDesc D, Rb R, RbItems
 __global__ __launch_bounds__(kBlock) void k_rb_approve(InstDesc D, Rb R, RbItems I) {
   __shared__ long long s_start[HG_MAX_K + 1];
   __shared__ long long s_tmp[kBlock / kWave];
+  if ((long long)blockIdx.x * kBlock >= *R.count) return;
   rb_segment_starts(R.cnt_tgt, D.k, s_start, s_tmp);
   const long long i = (long long)blockIdx.x * kBlock + threadIdx.x;
-  if (i >= I.n) return;
+  if (i >= *R.count) return;
   const int u = I.val[i];
   int to = D.part[u];
   if (I.key[i] != I.sentinel) {
@@ -1059,7 +1078,7 @@ static RebalLayout rebal_layout(long long n, int k) {
   L.cnt_src = take(sizeof(int) * (HG_MAX_K + 1));
   L.cnt_tgt = take(sizeof(int) * (HG_MAX_K + 1));
   L.cnt_slots = take(sizeof(int) * kSlots * (HG_MAX_K + 1));
-  L.best = take(sizeof(long long) * 2);
+  L.best = take(sizeof(long long) * 3);   // and the number of candidates
   L.hist = take(sizeof(unsigned) * (size_t)kDigits * L.sort_tiles);
   L.dtot = take(sizeof(unsigned) * kDigits);
   L.total = off;
@@ -1085,6 +1104,7 @@ static hipError_t launch_rebalance_round(hg_graph_s* g, InstDesc d, char* ws, hi
   R.csum = (long long*)(ws + L.csum);
   R.coff = (long long*)(ws + L.coff);
   R.best = (long long*)(ws + L.best);
+  R.count = (int*)(R.best + 2);
   const long long maxw = g->info.max_incident_weight;   // |gain| <= maxw
   R.bias = (unsigned)maxw;
   unsigned* key[2] = {(unsigned*)(ws + L.key[0]), (unsigned*)(ws + L.key[1])};
@@ -1093,15 +1113,15 @@ static hipError_t launch_rebalance_round(hg_graph_s* g, InstDesc d, char* ws, hi
   const unsigned chunks = grid_of(n, kBlock);
   hipLaunchKernelGGL(rb_light_kernel(k, d.view),
                      dim3(chunks < kSelectGrid ? chunks : (unsigned)kSelectGrid), dim3(kBlock), 0, s,
-                     d, R, key[0], val[0]);
+                     d, R);
   if (d.heavy_count > 0) {
     const hipError_t eh = launch_over_rows(d, (int*)(ws + L.cache), s);
     if (eh != hipSuccess) return eh;
     hipLaunchKernelGGL(k_rb_heavy, dim3(grid_of(d.heavy_count, kBlock / kWave)), dim3(kBlock), 0, s,
-                       d, R, key[0]);
+                       d, R);
   }
   int cur = 0;
-  auto pass = [&](int shift) {
+  auto pass = [&](int shift, bool first) {
     SortPass P;
     P.key_in = key[cur];
     P.val_in = val[cur];
@@ -1112,18 +1132,26 @@ static hipError_t launch_rebalance_round(hg_graph_s* g, InstDesc d, char* ws, hi
     P.n = n;
     P.tiles = L.sort_tiles;
     P.shift = shift;
+    if (first) {                // the marked vertices, keys bias - gain
+      P.marks = R.prop;
+      P.cand = d.cand;
+      P.top = R.bias;
+      P.count_out = R.count;
+    } else {
+      P.n_dev = R.count;
+    }
     sort_pass(P, s);
     cur ^= 1;
   };
   // (gain desc, id asc): keys bias - gain lie in [0, 2 * bias]
   int bits = 1;
   while (bits < 32 && (1ull << bits) <= 2ull * (unsigned long long)maxw) ++bits;
-  for (int shift = 0; shift < bits; shift += 8) pass(shift);
+  for (int shift = 0; shift < bits; shift += 8) pass(shift, shift == 0);
   const int kbits = k < 256 ? 8 : 16;   // block keys 0..k, the sentinel k included
   const unsigned grid = grid_of(n, kBlock);
   auto scan = [&](const RbItems& I) {
     hipLaunchKernelGGL(k_rb_chunk_sums, dim3(L.chunks), dim3(kBlock), 0, s, I, R.csum);
-    hipLaunchKernelGGL(k_prefix_top, dim3(1), dim3(kBlock), 0, s, R.csum, R.coff, L.chunks);
+    hipLaunchKernelGGL(k_prefix_top, dim3(1), dim3(kBlock), 0, s, R.csum, R.coff, R.count);
     hipLaunchKernelGGL(k_rb_scan, dim3(L.chunks), dim3(kBlock), 0, s, I, R.coff, R.scan);
   };
   // by source block, proposals per source
@@ -1131,11 +1159,11 @@ static hipError_t launch_rebalance_round(hg_graph_s* g, InstDesc d, char* ws, hi
                      val[cur ^ 1]);
   hipLaunchKernelGGL(k_rb_sum_counts, dim3(1), dim3(kBlock), 0, s, d, R, R.cnt_src, 0);
   cur ^= 1;
-  for (int shift = 0; shift < kbits; shift += 8) pass(shift);
+  for (int shift = 0; shift < kbits; shift += 8) pass(shift, false);
   RbItems I;
   I.vwgt = g->vwgt;
   I.sentinel = (unsigned)k;
-  I.n = n;
+  I.count = R.count;
   I.key = key[cur];
   I.val = val[cur];
   scan(I);
@@ -1145,7 +1173,7 @@ static hipError_t launch_rebalance_round(hg_graph_s* g, InstDesc d, char* ws, hi
                      val[cur ^ 1]);
   hipLaunchKernelGGL(k_rb_sum_counts, dim3(1), dim3(kBlock), 0, s, d, R, R.cnt_tgt, 1);
   cur ^= 1;
-  for (int shift = 0; shift < kbits; shift += 8) pass(shift);
+  for (int shift = 0; shift < kbits; shift += 8) pass(shift, false);
   I.key = key[cur];
   I.val = val[cur];
   scan(I);
