@@ -154,6 +154,7 @@ __device__ __forceinline__ void ct_net_done(const Ct& C, long long e, int size,
 constexpr int kCtCap = 832;          // LDS places of a wavefront
 constexpr int kCtFlight = 4;
 constexpr int kCtGrid = 2048;        // persistent workgroups
+constexpr int kCtBigGrid = 1280;     // as many as reside (kNetLdsCap words each)
 
 struct CtLds {
   int val[kCtCap];
@@ -308,11 +309,13 @@ __global__ __launch_bounds__(kBlock) void k_ct_small_nets(Ct C) {
   if (big) ct_flush_big(C, M, big);
 }
 
-// One workgroup per listed net (workgroups stride over the list): map,
-// bitonic sort (LDS when it fits), then keep first occurrences in order by
-// block scans over chunks of the sorted row.
+// One workgroup per listed net (workgroups stride over the list).  Up to kBlock
+// pins, a thread each: sorted by counting the smaller ones, as the small nets
+// (five barriers; a bitonic sort of 256 has 36: 38,000 nets of 129 to 205 pins 428
+// us, 300 so).  Longer: map, bitonic sort (LDS when it fits), then keep first
+// occurrences in order by block scans over chunks of the sorted row.
 __global__ __launch_bounds__(kBlock) void k_ct_big_nets(Ct C) {
-  __shared__ int s_row[kNetLdsCap];
+  __shared__ __attribute__((aligned(16))) int s_row[kNetLdsCap];
   __shared__ long long s_tmp[kBlock / kWave];
   __shared__ int s_prev;
   const int count = *C.big_count;
@@ -320,9 +323,35 @@ __global__ __launch_bounds__(kBlock) void k_ct_big_nets(Ct C) {
     const int e = C.big[idx];
     const long long b = C.eptr[e];
     const int len = (int)(C.eptr[e + 1] - b);
+    int* row = C.tmp + b;
+    if (len <= kBlock) {
+      constexpr int kEmpty = -1;
+      int* sorted = s_row + kBlock;
+      const int i = threadIdx.x;
+      const int x = i < len ? C.map[C.pins[b + i]] : 0x7fffffff;
+      s_row[i] = x;
+      sorted[i] = kEmpty;
+      __syncthreads();
+      int rank = 0;
+      for (int r = 0; r < len; r += 4) {
+        const int4 v = *reinterpret_cast<const int4*>(&s_row[r]);
+        rank += (v.x < x) + (v.y < x) + (v.z < x) + (v.w < x);
+      }
+      if (i < len) sorted[rank] = x;              // equal pins: the same place
+      __syncthreads();
+      const int y = sorted[i];
+      const bool distinct = y != kEmpty;
+      const unsigned long long sq = distinct ? (unsigned long long)(unsigned)y * (unsigned)y : 0ull;
+      long long size;
+      const long long at = block_excl_scan64(distinct, s_tmp, &size);
+      if (distinct) row[at] = y;
+      const unsigned long long f = (unsigned long long)block_sum64((long long)sq, s_tmp);
+      if (i == 0) ct_net_done(C, e, (int)size, f);
+      __syncthreads();
+      continue;
+    }
     int pow2 = 1;
     while (pow2 < len) pow2 <<= 1;
-    int* row = C.tmp + b;
     if (pow2 <= kNetLdsCap) {
       for (int i = threadIdx.x; i < len; i += kBlock) s_row[i] = C.map[C.pins[b + i]];
       __syncthreads();
@@ -596,7 +625,7 @@ static hipError_t launch_contract(hg_graph_s* g, const int* cluster, int* map, i
   // 3-4. per net: mapped, sorted, deduplicated pins, size, fingerprint
   const unsigned sg = blocks_of(m) < kCtGrid ? blocks_of(m) : kCtGrid;
   hipLaunchKernelGGL(k_ct_small_nets, dim3(sg), dim3(kBlock), 0, s, C);
-  hipLaunchKernelGGL(k_ct_big_nets, dim3(1024), dim3(kBlock), 0, s, C);
+  hipLaunchKernelGGL(k_ct_big_nets, dim3(kCtBigGrid), dim3(kBlock), 0, s, C);
 
   // 5. identical nets
   int ncur = 0;
