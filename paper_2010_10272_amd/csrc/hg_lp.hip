@@ -501,22 +501,59 @@ __global__ __launch_bounds__(kBlock) void k_select_cached(Launch L) {
   });
 }
 
+constexpr unsigned kMoversGrid = 1024;   // persistent workgroups
+
 // b(u) of every vertex that moved this round, from the finalized net records
-// (the nets where u is the only pin of its new block).  Unit: one vertex.
+// (the nets where u is the only pin of its new block).  Each wavefront queues the
+// moved vertices (few) of its slices and walks 64 rows at a time, four nets of
+// each on their way (matrix, k = 8, per round: a thread per vertex 25 us, 12 so).
 __global__ __launch_bounds__(kBlock) void k_cache_movers(Launch L) {
+  __shared__ int s_q[kBlock / kWave][2 * kWave];
   const InstDesc D = L.one;
-  const long long u = (long long)blockIdx.x * kBlock + threadIdx.x;
-  if (u >= D.n || !D.moved[u]) return;
-  const int a = D.part[u];
-  const int wk = bit_words(D.k);
-  const int sw = 2 + wk + (a >> 5);
-  const unsigned bit = 1u << (a & 31);
-  int ben = 0;
-  for (long long j = D.vptr[u]; j < D.vptr[u + 1]; ++j) {
-    const unsigned* r = D.netstate + (long long)D.vnets[j] * D.rw;
-    if (r[sw] & bit) ben += (int)r[0];
+  const WorkItem run = xcd_sweep(((long long)D.n + kBlock - 1) / kBlock);
+  const int lane = lane_id(), wk = bit_words(D.k), rw = D.rw;
+  int* my_q = s_q[threadIdx.x / kWave];
+  auto wave_vertices = [&](int cnt) {
+    if (lane >= cnt) return;
+    const int u = my_q[lane], a = D.part[u];
+    const unsigned* rec = D.netstate + 2 + wk + (a >> 5);
+    const unsigned bit = 1u << (a & 31);
+    const long long b0 = D.vptr[u], b1 = D.vptr[u + 1];
+    int ben = 0;
+    for (long long j = b0; j < b1; j += 4) {
+      long long at[4];
+      unsigned set[4];
+#pragma unroll
+      for (int q = 0; q < 4; ++q) at[q] = (long long)D.vnets[j + q < b1 ? j + q : j] * rw;
+#pragma unroll
+      for (int q = 0; q < 4; ++q) set[q] = rec[at[q]];
+#pragma unroll
+      for (int q = 0; q < 4; ++q)
+        if (j + q < b1 && (set[q] & bit)) ben += D.unit_nets ? 1 : (int)D.netstate[at[q]];
+    }
+    D.cache[u] = ben;
+  };
+  int qn = 0;                                    // wave-uniform
+  for (int it = 0; it <= run.count; ++it) {
+    if (it < run.count) {
+      const long long u = ((long long)run.first + (long long)it * run.stride) * kBlock +
+                          threadIdx.x;
+      const bool moved = u < D.n && D.moved[u];
+      const unsigned long long mask = __ballot(moved);
+      if (moved) my_q[lanes_below(mask, qn)] = (int)u;
+      qn += __popcll(mask);                      // < 2 * kWave
+      wave_lds_sync();
+    }
+    if (qn >= kWave || (it == run.count && qn > 0)) {
+      const int cnt = qn < kWave ? qn : kWave;
+      wave_vertices(cnt);
+      const int rest = lane < qn - cnt ? my_q[kWave + lane] : 0;
+      wave_lds_sync();
+      my_q[lane] = rest;
+      qn -= cnt;
+      wave_lds_sync();
+    }
   }
-  D.cache[u] = ben;
 }
 
 int cached_group(int k) {
@@ -553,8 +590,9 @@ hipError_t launch_cached_round(const RoundPlan& plan, int round, hipStream_t s,
   if (e == hipSuccess) e = launch_round_finalize(plan, s, marks);
   if (e != hipSuccess) return e;
   const InstDesc& d = plan.stats.L.one;
-  hipLaunchKernelGGL(k_cache_movers, dim3((unsigned)((d.n + kBlock - 1) / kBlock)), dim3(kBlock),
-                     0, s, plan.stats.L);
+  const unsigned chunks = (unsigned)((d.n + kBlock - 1) / kBlock);
+  hipLaunchKernelGGL(k_cache_movers, dim3(chunks < kMoversGrid ? chunks : kMoversGrid),
+                     dim3(kBlock), 0, s, plan.stats.L);
   return launch_round_stats(plan, round, s, marks);
 }
 
