@@ -171,7 +171,7 @@ int64_t hg_max_block_weight(hg_graph g, int32_t k, double eps);
  *   netstate  uint32[m*hg_net_words(k)]  OUT: per-net record (see above)
  *   block_w   int64[k]        OUT: c(V_i)
  *   km1_out   int64[1] or NULL OUT: sum_e (lambda(e) - 1) w(e)
- * Each net is counted by one group of lanes, so no atomics touch Phi. */
+ * Each net is counted by one wavefront, so no atomics touch Phi. */
 hg_status hg_compute_pincounts(hg_graph g, int32_t k, const int32_t* part, int32_t* phi,
                                uint32_t* netstate, int64_t* block_w, int64_t* km1_out,
                                void* stream);
@@ -203,9 +203,9 @@ hg_status hg_gains(hg_graph g, int32_t k, const int32_t* part, const uint32_t* n
  *     c(V_t) + c(u) < c(V_Pi(u));
  *  3. per target block t, candidates in (gain desc, vertex id asc) order are
  *     approved as the longest prefix with c(V_t) + prefix weight <= L_max;
- *  4. approved moves are applied at once: part, phi (integer atomics),
- *     netstate of every touched net and block_w are updated, *km1 drops by
- *     the attributed gain (subsection "Attributed Gains");
+ *  4. approved moves are applied at once: part and block_w are updated, phi and
+ *     netstate of every touched net counted anew, *km1 drops by the attributed
+ *     gain (subsection "Attributed Gains");
  *  5. eligible is rewritten to mark every pin of every net holding a moved
  *     vertex (the movers and their neighbours), and moved[v] = 1 for movers.
  *   part, phi, netstate, block_w  in/out state of one partition (consistent)
@@ -396,7 +396,7 @@ hg_status hg_batch_refine(hg_batch b, int32_t rounds, int32_t use_graph, void* s
 
 /* Measure schedules and keep the fastest per size class.  For each class
  * present, each field of the schedule in turn takes each of its candidate
- * values (chunks 1, 2, 4, 8, 16; lanes 0, 2x minimum); a trial runs
+ * values (chunks 1, 2, 4, 8, 16); a trial runs
  * hg_batch_start and one round on the members of that class, `repeats` times
  * (best time wins).  The members' partitions are saved into part_save
  * (device int32, at least the sum of their n) first and restored after every
