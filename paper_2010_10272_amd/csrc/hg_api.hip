@@ -156,7 +156,7 @@ WsLayout ws_layout(int n, int m, long long P, int k_max) {
   L.overflow = take(sizeof(int) * (size_t)k_max);
   L.thr = take(sizeof(Threshold) * (size_t)k_max);
   L.tilesum = take(sizeof(long long) * (size_t)k_max * (size_t)L.num_tiles);
-  L.ctr = take(sizeof(RoundCounters));
+  L.ctr = take(2 * sizeof(RoundCounters));   // the second for late rounds
   L.info = take(sizeof(LoadInfo));
   L.scan = take(sizeof(long long) * (size_t)L.scan_blocks);
   L.flags = take(256);
@@ -317,7 +317,7 @@ hg_status hg_load_csr(int32_t n, int32_t m, int64_t P, const int64_t* eptr, cons
   Z.add(ws + lay.touched, (long long)hg::touched_bytes(m));
   Z.add(ws + lay.hist, (long long)sizeof(long long) * hg::kHistReplicas * k_max * hg::kBuckets);
   Z.add(ws + lay.overflow, (long long)sizeof(int) * k_max);
-  Z.add(ws + lay.ctr, (long long)sizeof(hg::RoundCounters));
+  Z.add(ws + lay.ctr, 2 * (long long)sizeof(hg::RoundCounters));
   Z.add(ws + lay.flags, (long long)sizeof(int) * 64);
   Z.add(ws + lay.red, (long long)sizeof(long long) * hg::kSlots);
   Z.add(ws + lay.bw_slots, (long long)sizeof(long long) * hg::kSlots * k_max);
@@ -425,6 +425,7 @@ static hipError_t enqueue_refine(hg_graph g, int k, long long lmax, int rounds, 
   hg::InstDesc d = hg::make_desc(g, k, lmax, part, phi, netstate, (long long*)block_w, eligible,
                                  nullptr, (long long*)km1, stats);
   hg::keep_private_copies(g, d, false);
+  hg::RoundCounters* const ctr = d.ctr;
   hg::CountPlan cplan;
   hg::single_count_plan(d, cplan);
   hipError_t e = hg::launch_counts(cplan, true, true, s);
@@ -433,7 +434,13 @@ static hipError_t enqueue_refine(hg_graph g, int k, long long lmax, int rounds, 
     hipEvent_t* marks = nullptr;
     if (timing_marks(g, s, &marks, r > 0) != HG_OK) return hipErrorUnknown;
     d.stats = stats + r;
+    if (!marks) {                 // (the phase times include the records)
+      d.late = 1;
+      d.prev = r > 0 ? d.ctr : nullptr;
+      d.ctr = ctr + (r & 1);
+    }
     hg::single_round_plan(d, plan);
+    plan.record = !d.late || r + 1 == rounds;
     e = hg::launch_round(plan, 0, s, marks);
   }
   return e;

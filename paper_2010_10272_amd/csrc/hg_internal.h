@@ -67,7 +67,9 @@ enum CounterId : int {
 struct RoundCounters {
   unsigned long long slot[kNumCounters][kSlots];
   unsigned int any_overflow;       // some block's threshold fell into the ">=255" bucket
-  unsigned int pad[63];
+  unsigned int pad;
+  long long max_block_w;           // late rounds: the finalize's, for the record
+  unsigned int pad2[60];
 };
 
 // Approval threshold of one target block.
@@ -154,6 +156,11 @@ struct InstDesc {
   Threshold* thr;
   long long* tilesum;
   RoundCounters* ctr;
+  // Late rounds (refine calls): the finalize folds the block weights, and round
+  // r's record is written beside round r + 1's thresholds instead of by a launch
+  // of its own, from the other of two sets of counters.
+  int late;
+  RoundCounters* prev;           // the round before's counters, to be recorded; null: none
   int* err_flags;
   unsigned long long* red;
   long long* bw_slots;           // kSlots x k block-weight deltas of a round's moves

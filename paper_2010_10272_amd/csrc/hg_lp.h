@@ -32,6 +32,7 @@ struct RoundPlan {
   PlanLaunch blocks, tiles, approve, stats;
   bool any_heavy = false;
   bool brief = false;       // no threshold, no tile scan (brief_rounds)
+  bool record = true;       // false: the next round's launches write the record
 };
 
 // The plan of calls that count the pins and run the rounds (InstDesc::kept), from

@@ -38,10 +38,11 @@
 
 namespace hg {
 
-// Contiguous XCD-aware split: workgroup blockIdx gets units [lb*per, (lb+1)*per).
-__device__ __forceinline__ WorkItem xcd_block(long long units) {
-  const long long lb = xcd_remap(blockIdx.x, gridDim.x);
-  const long long per = (units + gridDim.x - 1) / gridDim.x;
+// Contiguous XCD-aware split: workgroup blockIdx < grid gets units
+// [lb*per, (lb+1)*per).
+__device__ __forceinline__ WorkItem xcd_block(long long units, unsigned grid) {
+  const long long lb = xcd_remap(blockIdx.x, grid);
+  const long long per = (units + grid - 1) / grid;
   long long end = (lb + 1) * per;
   if (end > units) end = units;
   WorkItem w;
@@ -596,6 +597,108 @@ hipError_t launch_cached_round(const RoundPlan& plan, int round, hipStream_t s,
   return launch_round_stats(plan, round, s, marks);
 }
 
+// Block weights and round record (one workgroup each).  Fold the apply's
+// block-weight slots into block_w; returns the heaviest of this thread's blocks.
+template <int A>
+__device__ __forceinline__ long long fold_block_weights(const InstDesc& D) {
+  long long mx = LLONG_MIN;
+  // slot cells A at a time are requested before the stores that clear them (not
+  // one round trip per cell)
+  for (int i = threadIdx.x; i < D.k; i += kBlock) {
+    long long* col = D.bw_slots + i;
+    const size_t ks = (size_t)D.k;
+    long long d = D.block_w[i];
+    for (int s0 = 0; s0 < kSlots; s0 += A) {
+      long long cells[A];
+#pragma unroll
+      for (int q = 0; q < A; ++q) cells[q] = col[(s0 + q) * ks];
+#pragma unroll
+      for (int q = 0; q < A; ++q) d += cells[q];
+#pragma unroll
+      for (int q = 0; q < A; ++q) col[(s0 + q) * ks] = 0;
+    }
+    D.block_w[i] = d;
+    mx = d > mx ? d : mx;
+  }
+  return mx;
+}
+
+// The largest of the workgroup's values, in two halves around a barrier.
+__device__ __forceinline__ void block_max64_put(long long v, long long* s_max /*[kBlock/kWave]*/) {
+  v = wave_max(v);
+  if (lane_id() == 0) s_max[threadIdx.x / kWave] = v;
+}
+__device__ __forceinline__ long long block_max64_get(const long long* s_max) {   // after a barrier
+  long long m = s_max[0];
+  for (int i = 1; i < kBlock / kWave; ++i) m = s_max[i] > m ? s_max[i] : m;
+  return m;
+}
+
+// A workgroup's view of the counter slots: wavefront w holds rows w, w + 4, ...
+constexpr int kCounterRows = (kNumCounters + kBlock / kWave - 1) / (kBlock / kWave);
+struct CounterRows {
+  unsigned long long v[kCounterRows];
+  __device__ __forceinline__ void load(const RoundCounters* ctr) {
+#pragma unroll
+    for (int r = 0; r < kCounterRows; ++r) {
+      const int c = (int)threadIdx.x / kWave + r * (kBlock / kWave);
+      v[r] = c < kNumCounters ? ctr->slot[c][lane_id()] : 0ull;
+    }
+  }
+};
+
+// Sum the counter slots, write the round record, move km1 by the attributed
+// drop, reset the counters.  `mx`: the heaviest of the thread's blocks.
+__device__ __forceinline__ void write_record(const InstDesc& D, RoundCounters* ctr,
+                                             const CounterRows& rows, long long mx,
+                                             hg_round_stats* out) {
+  __shared__ long long s_sum[kNumCounters];
+  __shared__ long long s_max[kBlock / kWave];
+  const int lane = lane_id(), wv = threadIdx.x / kWave;
+#pragma unroll
+  for (int r = 0; r < kCounterRows; ++r) {
+    const int c = wv + r * (kBlock / kWave);
+    if (c < kNumCounters) {
+      const long long sum = wave_sum((long long)rows.v[r]);
+      if (lane == 0) s_sum[c] = sum;
+      ctr->slot[c][lane] = 0;
+    }
+  }
+  block_max64_put(mx, s_max);
+  __syncthreads();
+  if (threadIdx.x == 0) {
+    hg_round_stats st;
+    st.eligible = s_sum[kCtrEligible];
+    st.boundary = s_sum[kCtrBoundary];
+    st.candidates = s_sum[kCtrCandidates];
+    st.approved = s_sum[kCtrApproved];
+    st.moved_pins = s_sum[kCtrMovedPins];
+    st.touched_nets = s_sum[kCtrTouched];
+    st.km1_delta = s_sum[kCtrDeltaAttr];
+    st.km1_delta_recomputed = s_sum[kCtrDeltaCheck];
+    st.active_pins = s_sum[kCtrActivePins];
+    st.touched_pins = s_sum[kCtrTouchedPins];
+    st.km1_after = *D.km1 - st.km1_delta;
+    st.max_block_weight = block_max64_get(s_max);
+    *D.km1 = st.km1_after;
+    *out = st;
+    ctr->any_overflow = 0;
+  }
+}
+
+// Late rounds: the last workgroup of the thresholds (or of the brief rounds' tile
+// sums) writes the record of the round before.  (A launch of its own for five
+// microseconds of work each round: n = 10,000 k = 2, five rounds, 154 us per call,
+// 138 so; matrix, ten rounds, k = 8 1434 -> 1382, k = 64 2025 -> 1984; netlist step
+// 4376 -> 4320.)
+__device__ __forceinline__ bool records_previous(const InstDesc& D) {
+  if (!D.prev || blockIdx.x + 1 != gridDim.x) return false;
+  CounterRows rows;
+  rows.load(D.prev);
+  write_record(D, D.prev, rows, D.prev->max_block_w, D.stats - 1);
+  return true;
+}
+
 // --------------------------------------------------------------- threshold
 
 // Unit: one target block t.  Thread j looks at gain bucket 255 - j (summed
@@ -605,6 +708,7 @@ __global__ __launch_bounds__(kBlock) void k_threshold(Launch L) {
   __shared__ int s_first;
   const WorkItem wi = work_item(L, single_unit(blockIdx.x));
   const InstDesc D = inst_desc(L, wi.inst);
+  if (records_previous(D)) return;
   const int t = wi.first;
   const int bucket = kBuckets - 1 - threadIdx.x;
   long long h = 0;
@@ -808,6 +912,9 @@ __global__ __launch_bounds__(kBlock) void k_tilesum(Launch L) {
   __shared__ int s_g[HG_MAX_K];
   const WorkItem wi = work_item(L, single_unit(blockIdx.x));
   const InstDesc D = inst_desc(L, wi.inst);
+  if constexpr (BRIEF) {
+    if (records_previous(D)) return;
+  }
   const int k = D.k;
   const int tile = wi.first;
   const long long base = (long long)tile * kTile;
@@ -1225,7 +1332,19 @@ template <int WK, bool CACHE>
 __global__ __launch_bounds__(kBlock, !CACHE && WK <= 2 ? 8 : 4) void k_finalize(Launch L) {
   extern __shared__ unsigned s_final[];   // per wavefront: count_words, the queue, cache_words
   __shared__ unsigned long long s_sums[3];
-  const WorkItem wi = work_item(L, xcd_block((L.one.m + kFinalChunk - 1) / kFinalChunk));
+  // late rounds: one workgroup more, for the block weights
+  // (refine calls have no gain cache)
+  if constexpr (!CACHE) {
+    if (!L.items && L.one.late && blockIdx.x + 1 == gridDim.x) {
+      __shared__ long long s_max[kBlock / kWave];
+      block_max64_put(fold_block_weights<8>(L.one), s_max);   // (16: spills)
+      __syncthreads();
+      if (threadIdx.x == 0) L.one.ctr->max_block_w = block_max64_get(s_max);
+      return;
+    }
+  }
+  const WorkItem wi = work_item(L, xcd_block((L.one.m + kFinalChunk - 1) / kFinalChunk,
+                                             gridDim.x - (!CACHE && L.one.late ? 1 : 0)));
   if (wi.count == 0) return;
   const InstDesc D = inst_desc(L, wi.inst);
   if (threadIdx.x < 3) s_sums[threadIdx.x] = 0;
@@ -1339,74 +1458,14 @@ __global__ __launch_bounds__(kBlock, !CACHE && WK <= 2 ? 8 : 4) void k_finalize(
   }
 }
 
-// Unit: one instance.  Fold the apply's block-weight slots into block_w, sum
-// the counter slots, write the round record, move km1 by the attributed drop,
-// reset the slots and counters for the next round.
+// Unit: one instance.  Late rounds: the finalize has folded the block weights.
 __global__ __launch_bounds__(kBlock) void k_round_stats(Launch L) {
-  __shared__ long long s_sum[kNumCounters];
-  __shared__ long long s_max[kBlock / kWave];
   const WorkItem wi = work_item(L, single_unit(0));
   const InstDesc D = inst_desc(L, wi.inst);
-  RoundCounters* ctr = D.ctr;
-  const int lane = lane_id(), wv = threadIdx.x / kWave;
-  // loads of the counter rows, and of the slot cells 16 at a time, are
-  // issued before the stores that clear them (not one round trip per cell)
-  constexpr int kRows = (kNumCounters + kBlock / kWave - 1) / (kBlock / kWave);
-  unsigned long long v[kRows];
-#pragma unroll
-  for (int r = 0; r < kRows; ++r) {
-    const int c = wv + r * (kBlock / kWave);
-    v[r] = c < kNumCounters ? ctr->slot[c][lane] : 0ull;
-  }
-  long long mx = LLONG_MIN;
-  for (int i = threadIdx.x; i < D.k; i += kBlock) {
-    long long* col = D.bw_slots + i;
-    const size_t ks = (size_t)D.k;
-    long long d = D.block_w[i];
-    for (int s0 = 0; s0 < kSlots; s0 += 16) {      // 16 loads in flight, then the clears
-      long long cells[16];
-#pragma unroll
-      for (int q = 0; q < 16; ++q) cells[q] = col[(s0 + q) * ks];
-#pragma unroll
-      for (int q = 0; q < 16; ++q) d += cells[q];
-#pragma unroll
-      for (int q = 0; q < 16; ++q) col[(s0 + q) * ks] = 0;
-    }
-    D.block_w[i] = d;
-    mx = d > mx ? d : mx;
-  }
-#pragma unroll
-  for (int r = 0; r < kRows; ++r) {
-    const int c = wv + r * (kBlock / kWave);
-    if (c < kNumCounters) {
-      const long long sum = wave_sum((long long)v[r]);
-      if (lane == 0) s_sum[c] = sum;
-      ctr->slot[c][lane] = 0;
-    }
-  }
-  mx = wave_max(mx);
-  if (lane == 0) s_max[wv] = mx;
-  __syncthreads();
-  if (threadIdx.x == 0) {
-    long long m = s_max[0];
-    for (int i = 1; i < kBlock / kWave; ++i) m = s_max[i] > m ? s_max[i] : m;
-    hg_round_stats st;
-    st.eligible = s_sum[kCtrEligible];
-    st.boundary = s_sum[kCtrBoundary];
-    st.candidates = s_sum[kCtrCandidates];
-    st.approved = s_sum[kCtrApproved];
-    st.moved_pins = s_sum[kCtrMovedPins];
-    st.touched_nets = s_sum[kCtrTouched];
-    st.km1_delta = s_sum[kCtrDeltaAttr];
-    st.km1_delta_recomputed = s_sum[kCtrDeltaCheck];
-    st.active_pins = s_sum[kCtrActivePins];
-    st.touched_pins = s_sum[kCtrTouchedPins];
-    st.km1_after = *D.km1 - st.km1_delta;
-    st.max_block_weight = m;
-    *D.km1 = st.km1_after;
-    D.stats[L.round - D.round_base] = st;
-    ctr->any_overflow = 0;
-  }
+  CounterRows rows;              // on their way before the fold waits
+  rows.load(D.ctr);
+  const long long mx = D.late ? D.ctr->max_block_w : fold_block_weights<16>(D);
+  write_record(D, D.ctr, rows, mx, D.stats + (L.round - D.round_base));
 }
 
 // --------------------------------------------------------------- launch
@@ -1471,13 +1530,14 @@ hipError_t launch_round_front(const RoundPlan& plan, hipStream_t s, hipEvent_t* 
   for (const PlanLaunch& pl : plan.heavy)
     hipLaunchKernelGGL(k_select_heavy, dim3(pl.grid), dim3(kBlock), 0, s, pl.L);
   if (marks) (void)hipEventRecord(marks[1], s);
+  const unsigned extra = plan.tiles.L.one.prev ? 1 : 0;   // the record of the round before
   if (plan.brief) {
-    hipLaunchKernelGGL(k_tilesum<true>, dim3(plan.tiles.grid), dim3(kBlock), 0, s, plan.tiles.L);
+    hipLaunchKernelGGL(k_tilesum<true>, dim3(plan.tiles.grid + extra), dim3(kBlock), 0, s, plan.tiles.L);
     hipLaunchKernelGGL(k_approve_apply<true>, dim3(plan.approve.grid), dim3(kBlock), 0, s,
                        plan.approve.L);
     return hipGetLastError();
   }
-  hipLaunchKernelGGL(k_threshold, dim3(plan.blocks.grid), dim3(kBlock), 0, s, plan.blocks.L);
+  hipLaunchKernelGGL(k_threshold, dim3(plan.blocks.grid + extra), dim3(kBlock), 0, s, plan.blocks.L);
   if (plan.any_heavy)
     hipLaunchKernelGGL(k_overflow_resolve, dim3(plan.blocks.grid), dim3(kBlock), 0, s,
                        plan.blocks.L);
@@ -1492,7 +1552,7 @@ hipError_t launch_round_front(const RoundPlan& plan, hipStream_t s, hipEvent_t* 
 hipError_t launch_round_back(const RoundPlan& plan, int round, hipStream_t s, hipEvent_t* marks) {
   hipError_t e = launch_round_finalize(plan, s, marks);
   if (e != hipSuccess) return e;
-  return launch_round_stats(plan, round, s, marks);
+  return plan.record ? launch_round_stats(plan, round, s, marks) : hipSuccess;
 }
 
 hipError_t launch_round_finalize(const RoundPlan& plan, hipStream_t s, hipEvent_t* marks) {
@@ -1538,7 +1598,7 @@ void single_round_plan(const InstDesc& d, RoundPlan& plan) {
   fin.kernel = (void*)finalize_kernel(d.k, d.cache != nullptr);
   fin.lds = finalize_lds(d.k, d.cache != nullptr);
   const long long fchunks = ((long long)d.m + kFinalChunk - 1) / kFinalChunk;
-  fin.grid = (unsigned)(fchunks < kFinalizeGrid ? fchunks : kFinalizeGrid);
+  fin.grid = (unsigned)(fchunks < kFinalizeGrid ? fchunks : kFinalizeGrid) + (d.late ? 1 : 0);
   fin.L = L;
   plan.finalize.push_back(fin);
   plan.stats.grid = 1;
