@@ -15,6 +15,7 @@
 namespace hg {
 
 constexpr int kCountFlight = 4;              // pins in flight per lane
+constexpr int kCountStep = kCountFlight * kWave;
 constexpr int kByteNet = 255;                // longest net whose counts surely fit a byte
 
 // Most nets a wavefront counts at a time (64 nets' counters fill the LDS for
@@ -26,13 +27,20 @@ __host__ __device__ inline int count_stride(int k) { return ((k + 3) / 4) | 1; }
 // LDS words of one wavefront that counts `nets` nets at a time: the counters,
 // k words for a long net, a flag byte per position in flight, one word a net.
 __host__ __device__ inline int count_words(int k, int nets) {
-  return nets * count_stride(k) + k + kCountFlight * kWave / 4 + kWave;
+  return nets * count_stride(k) + k + kCountStep / 4 + kWave;
 }
+
+// A run of pins is walked kCountStep places at a time.  It has fewer than 2^31
+// places, but its last step may end beyond: places and steps are unsigned.
+typedef unsigned RunPlace;
+__host__ __device__ inline bool run_left(RunPlace s, int total) { return s < (RunPlace)total; }
+// Place `first` within the step at s; kCountStep or more: not in it.
+__host__ __device__ inline RunPlace in_step(int first, RunPlace s) { return (RunPlace)first - s; }
 
 struct CountLds {
   unsigned* cnt;               // [nets][stride], zero between calls
   int* big;                    // [k]
-  unsigned char* flag;         // [kCountFlight * kWave], zero between calls
+  unsigned char* flag;         // [kCountStep], zero between calls
   int* shift;                  // [kWave]: first pin - place in the run, per net
   int stride;
 };
@@ -44,7 +52,7 @@ __device__ __forceinline__ CountLds count_lds(unsigned* base, int k, int nets) {
   M.cnt = base;
   M.big = reinterpret_cast<int*>(base + nets * M.stride);
   M.flag = reinterpret_cast<unsigned char*>(M.big + k);
-  M.shift = M.big + k + kCountFlight * kWave / 4;
+  M.shift = M.big + k + kCountStep / 4;
   for (int i = lane_id(); i < nets * M.stride; i += kWave) M.cnt[i] = 0;
   reinterpret_cast<unsigned*>(M.flag)[lane_id()] = 0;
   return M;
@@ -118,7 +126,7 @@ __device__ __forceinline__ void for_pins(const int* __restrict__ pins, const Cou
   if constexpr (RUN) pins += __shfl(b, 0);
   else M.shift[lane] = (int)b - first;                     // pin positions are below 2^31
   int before = -1;                                         // last net starting before this step
-  for (int s = 0; s < total; s += kCountFlight * kWave) {
+  for (RunPlace s = 0; run_left(s, total); s += kCountStep) {
     int net[kCountFlight], v[kCountFlight];
     auto nets_of = [&]() {
       wave_lds_sync();
@@ -134,17 +142,17 @@ __device__ __forceinline__ void for_pins(const int* __restrict__ pins, const Cou
     if constexpr (RUN) {
 #pragma unroll
       for (int q = 0; q < kCountFlight; ++q) {
-        const int p = s + q * kWave + lane;
-        v[q] = p < total ? pins[p] : -1;
+        const RunPlace p = s + q * kWave + lane;
+        v[q] = run_left(p, total) ? pins[p] : -1;
       }
     }
-    if (len > 0 && first >= s && first < s + kCountFlight * kWave) M.flag[first - s] = 1;
+    if (len > 0 && in_step(first, s) < kCountStep) M.flag[in_step(first, s)] = 1;
     if constexpr (!RUN) {
       nets_of();
 #pragma unroll
       for (int q = 0; q < kCountFlight; ++q) {
-        const int p = s + q * kWave + lane;
-        v[q] = p < total ? pins[M.shift[net[q]] + p] : -1;
+        const RunPlace p = s + q * kWave + lane;
+        v[q] = run_left(p, total) ? pins[(RunPlace)M.shift[net[q]] + p] : -1;
       }
     }
 #pragma unroll

@@ -236,11 +236,11 @@ hipError_t launch_gains(hg_graph_s* g, const InstDesc& d, long long* gains, long
                         hipStream_t s, int* cache) {
   typedef void (*K)(Launch, long long*, long long*, int*);
   const Launch L = single_launch(d);
-  unsigned grid = (unsigned)(((long long)d.n + kBlock - 1) / kBlock);
+  unsigned grid = (unsigned)units_of(d.n, kBlock);
   hipLaunchKernelGGL((K)(void*)gains_kernel(d.k, d.view), dim3(grid), dim3(kBlock), 0, s, L,
                      gains, benefit, cache);
   if (d.heavy_count > 0) {
-    unsigned hg = (unsigned)((d.heavy_count + (kBlock / kWave) - 1) / (kBlock / kWave));
+    unsigned hg = (unsigned)(units_of(d.heavy_count, kBlock / kWave));
     hipLaunchKernelGGL(k_gains_heavy, dim3(hg), dim3(kBlock), 0, s, L, gains, benefit, cache, 0);
   }
   (void)g;
@@ -249,7 +249,7 @@ hipError_t launch_gains(hg_graph_s* g, const InstDesc& d, long long* gains, long
 
 hipError_t launch_over_rows(const InstDesc& d, int* cache, hipStream_t s) {
   hipLaunchKernelGGL(k_gains_heavy,
-                     dim3((unsigned)((d.heavy_count + (kBlock / kWave) - 1) / (kBlock / kWave))),
+                     dim3((unsigned)(units_of(d.heavy_count, kBlock / kWave))),
                      dim3(kBlock), 0, s, single_launch(d), (long long*)nullptr,
                      (long long*)nullptr, cache, 1);
   return hipGetLastError();

@@ -72,6 +72,12 @@ struct RoundCounters {
   unsigned int pad2[60];
 };
 
+// Units of `per` items that cover `items` items (counts may lie just below 2^31, so
+// no sum of them is made in 32 bits).
+__host__ __device__ inline int units_of(long long items, int per) {
+  return (int)((items + per - 1) / per);
+}
+
 // Approval threshold of one target block.
 struct Threshold {
   int gstar;          // gains > gstar approved; == gstar decided by vertex order; -1: all approved

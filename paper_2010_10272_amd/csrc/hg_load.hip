@@ -913,13 +913,14 @@ __global__ void k_pin_pairs(int m, const long long* eptr, int* val) {
   s_start[w][lane] = 0;
   wave_lds_sync();
   int before = 0;                                // nets starting before this step
-  for (int base = 0; base < total; base += kWave) {
-    if (len > 0 && first >= base && first < base + kWave) s_start[w][first - base] = 1;
+  // (unsigned: the last step may end beyond 2^31)
+  for (unsigned base = 0; base < (unsigned)total; base += kWave) {
+    if (len > 0 && (unsigned)first - base < kWave) s_start[w][first - base] = 1;
     wave_lds_sync();
     const unsigned long long starts = __ballot(s_start[w][lane] != 0);
     s_start[w][lane] = 0;
     wave_lds_sync();
-    if (base + lane < total)
+    if (base + lane < (unsigned)total)
       val[run + base + lane] = first_net + before + __popcll(starts & upto) - 1;
     before += __popcll(starts);
   }

@@ -101,7 +101,7 @@ __global__ __launch_bounds__(kBlock) void k_select_light(Launch L) {
   __shared__ unsigned long long s_sums[2];
   __shared__ int s_q[kBlock / kWave][2 * kWave];   // per-wave queues of eligible vertices
   const InstDesc D0 = L.one;
-  const WorkItem wi = work_item(L, xcd_sweep((D0.n + kBlock - 1) / kBlock));
+  const WorkItem wi = work_item(L, xcd_sweep(units_of(D0.n, kBlock)));
   if (wi.count == 0) return;
   const InstDesc D = inst_desc(L, wi.inst);
   const int k = D.k, B = D.lds_buckets, n = D.n;
@@ -395,7 +395,7 @@ __global__ __launch_bounds__(kBlock) void k_select_cached(Launch L) {
   __shared__ unsigned long long s_hist[kLdsHistEntries];
   __shared__ unsigned long long s_sums[2];
   const InstDesc D0 = L.one;
-  const WorkItem wi = work_item(L, xcd_sweep((D0.n + kBlock - 1) / kBlock));
+  const WorkItem wi = work_item(L, xcd_sweep(units_of(D0.n, kBlock)));
   if (wi.count == 0) return;
   const InstDesc D = inst_desc(L, wi.inst);
   const int k = D.k, B = D.lds_buckets, n = D.n;
@@ -511,7 +511,7 @@ constexpr unsigned kMoversGrid = 1024;   // persistent workgroups
 __global__ __launch_bounds__(kBlock) void k_cache_movers(Launch L) {
   __shared__ int s_q[kBlock / kWave][2 * kWave];
   const InstDesc D = L.one;
-  const WorkItem run = xcd_sweep(((long long)D.n + kBlock - 1) / kBlock);
+  const WorkItem run = xcd_sweep(units_of(D.n, kBlock));
   const int lane = lane_id(), wk = bit_words(D.k), rw = D.rw;
   int* my_q = s_q[threadIdx.x / kWave];
   auto wave_vertices = [&](int cnt) {
@@ -591,7 +591,7 @@ hipError_t launch_cached_round(const RoundPlan& plan, int round, hipStream_t s,
   if (e == hipSuccess) e = launch_round_finalize(plan, s, marks);
   if (e != hipSuccess) return e;
   const InstDesc& d = plan.stats.L.one;
-  const unsigned chunks = (unsigned)((d.n + kBlock - 1) / kBlock);
+  const unsigned chunks = (unsigned)units_of(d.n, kBlock);
   hipLaunchKernelGGL(k_cache_movers, dim3(chunks < kMoversGrid ? chunks : kMoversGrid),
                      dim3(kBlock), 0, s, plan.stats.L);
   return launch_round_stats(plan, round, s, marks);
@@ -1343,7 +1343,7 @@ __global__ __launch_bounds__(kBlock, !CACHE && WK <= 2 ? 8 : 4) void k_finalize(
       return;
     }
   }
-  const WorkItem wi = work_item(L, xcd_block((L.one.m + kFinalChunk - 1) / kFinalChunk,
+  const WorkItem wi = work_item(L, xcd_block(units_of(L.one.m, kFinalChunk),
                                              gridDim.x - (!CACHE && L.one.late ? 1 : 0)));
   if (wi.count == 0) return;
   const InstDesc D = inst_desc(L, wi.inst);
@@ -1574,7 +1574,7 @@ hipError_t launch_round_stats(const RoundPlan& plan, int round, hipStream_t s, h
 void single_round_plan(const InstDesc& d, RoundPlan& plan) {
   plan = RoundPlan();
   const Launch L = single_launch(d);
-  const long long chunks = ((long long)d.n + kBlock - 1) / kBlock;
+  const int chunks = units_of(d.n, kBlock);
   PlanLaunch sel;
   sel.kernel = (void*)select_kernel(d.k, d.sweep, d.P, d.n);
   sel.grid = (unsigned)(chunks < kSelectGrid ? chunks : kSelectGrid);
@@ -1582,7 +1582,7 @@ void single_round_plan(const InstDesc& d, RoundPlan& plan) {
   plan.select.push_back(sel);
   if (d.heavy_count > 0) {
     PlanLaunch hv;
-    hv.grid = (unsigned)((d.heavy_count + (kBlock / kWave) - 1) / (kBlock / kWave));
+    hv.grid = (unsigned)(units_of(d.heavy_count, kBlock / kWave));
     hv.L = L;
     plan.heavy.push_back(hv);
     plan.any_heavy = true;
@@ -1597,7 +1597,7 @@ void single_round_plan(const InstDesc& d, RoundPlan& plan) {
   PlanLaunch fin;
   fin.kernel = (void*)finalize_kernel(d.k, d.cache != nullptr);
   fin.lds = finalize_lds(d.k, d.cache != nullptr);
-  const long long fchunks = ((long long)d.m + kFinalChunk - 1) / kFinalChunk;
+  const int fchunks = units_of(d.m, kFinalChunk);
   fin.grid = (unsigned)(fchunks < kFinalizeGrid ? fchunks : kFinalizeGrid) + (d.late ? 1 : 0);
   fin.L = L;
   plan.finalize.push_back(fin);

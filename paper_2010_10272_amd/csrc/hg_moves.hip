@@ -283,7 +283,7 @@ __global__ __launch_bounds__(kBlock) void k_prefix_top(const long long* csum, lo
                                                        const int* items) {
   constexpr int kPer = 8;            // consecutive sums per thread, all on their way at once
   __shared__ long long s_tmp[kBlock / kWave];
-  const int chunks = (*items + kBlock - 1) / kBlock;
+  const int chunks = units_of(*items, kBlock);
   long long carry = 0;
   for (int b = 0; b < chunks; b += kBlock * kPer) {
     const int first = b + threadIdx.x * kPer;
@@ -622,7 +622,7 @@ __global__ __launch_bounds__(kBlock) void k_rb_light(InstDesc D, Rb R) {
     R.prop[u] = 1;
     n_cand += 1;
   };
-  const WorkItem run = xcd_sweep((n + kBlock - 1) / kBlock);
+  const WorkItem run = xcd_sweep(units_of(n, kBlock));
   int qn = 0;                                    // wave-uniform
   for (int it = 0; it <= run.count; ++it) {
     long long u = 0;

@@ -49,8 +49,7 @@ template <int WK>
 __global__ __launch_bounds__(kBlock) void k_pincounts(Launch L) {
   extern __shared__ unsigned s_count[];   // count_words per wavefront
   __shared__ long long s_km1;
-  const WorkItem wi = work_item(L, contiguous_units((L.one.m + count_unit(L.one.k, L.one.m) - 1) /
-                                                     count_unit(L.one.k, L.one.m)));
+  const WorkItem wi = work_item(L, contiguous_units(units_of(L.one.m, count_unit(L.one.k, L.one.m))));
   if (wi.count == 0) return;
   const InstDesc D = inst_desc(L, wi.inst);
   const int k = D.k, m = D.m;
@@ -138,7 +137,7 @@ __global__ __launch_bounds__(kBlock) void k_count_epilogue(Launch L, int want_km
 // also made eligible (the start of a refinement).
 __global__ __launch_bounds__(kBlock) void k_block_weights(Launch L, int mark_eligible) {
   __shared__ unsigned long long s_w[HG_MAX_K];
-  const WorkItem wi = work_item(L, contiguous_units((L.one.n + kBwChunk - 1) / kBwChunk));
+  const WorkItem wi = work_item(L, contiguous_units(units_of(L.one.n, kBwChunk)));
   if (wi.count == 0) return;
   const InstDesc D = inst_desc(L, wi.inst);
   const int k = D.k, n = D.n;
