@@ -156,7 +156,7 @@ WsLayout ws_layout(int n, int m, long long P, int k_max) {
   L.overflow = take(sizeof(int) * (size_t)k_max);
   L.thr = take(sizeof(Threshold) * (size_t)k_max);
   L.tilesum = take(sizeof(long long) * (size_t)k_max * (size_t)L.num_tiles);
-  L.ctr = take(2 * sizeof(RoundCounters));   // the second for late rounds
+  L.ctr = take(sizeof(RoundCounters));
   L.info = take(sizeof(LoadInfo));
   L.scan = take(sizeof(long long) * (size_t)L.scan_blocks);
   L.flags = take(256);
@@ -168,10 +168,15 @@ WsLayout ws_layout(int n, int m, long long P, int k_max) {
   L.lval = take(sizeof(int) * (size_t)P);
   L.lhist = take(sizeof(unsigned) * (size_t)kDigits * (size_t)sort_tiles(P));
   L.ldtot = take(sizeof(unsigned) * kDigits);
-  const LoadSplit sp = load_split(n, P);
-  L.lbase = take(sizeof(unsigned) * 2 * ((size_t)sp.buckets + sp.coarse + 1));
   L.lpart = take(sizeof(LoadPart) * kLoadGrid);
   L.total = off;
+  // A load and the rounds share space, each where the other needs none: the load's
+  // bucket tables (2 * (buckets + coarse + 1) words with buckets <= n: at most
+  // 8.125 n + 16 bytes) lie in the 16 n bytes per vertex that its last kernels
+  // and the rounds fill, the late rounds' second set of counters in its parts.
+  L.lbase = L.cand;
+  L.ctr2 = L.lpart;
+  static_assert(sizeof(RoundCounters) <= sizeof(LoadPart) * kLoadGrid, "shared");
   return L;
 }
 
@@ -317,7 +322,8 @@ hg_status hg_load_csr(int32_t n, int32_t m, int64_t P, const int64_t* eptr, cons
   Z.add(ws + lay.touched, (long long)hg::touched_bytes(m));
   Z.add(ws + lay.hist, (long long)sizeof(long long) * hg::kHistReplicas * k_max * hg::kBuckets);
   Z.add(ws + lay.overflow, (long long)sizeof(int) * k_max);
-  Z.add(ws + lay.ctr, 2 * (long long)sizeof(hg::RoundCounters));
+  Z.add(ws + lay.ctr, (long long)sizeof(hg::RoundCounters));
+  Z.add(ws + lay.ctr2, (long long)sizeof(hg::RoundCounters));
   Z.add(ws + lay.flags, (long long)sizeof(int) * 64);
   Z.add(ws + lay.red, (long long)sizeof(long long) * hg::kSlots);
   Z.add(ws + lay.bw_slots, (long long)sizeof(long long) * hg::kSlots * k_max);
@@ -425,7 +431,7 @@ static hipError_t enqueue_refine(hg_graph g, int k, long long lmax, int rounds, 
   hg::InstDesc d = hg::make_desc(g, k, lmax, part, phi, netstate, (long long*)block_w, eligible,
                                  nullptr, (long long*)km1, stats);
   hg::keep_private_copies(g, d, false);
-  hg::RoundCounters* const ctr = d.ctr;
+  hg::RoundCounters* const ctr[2] = {d.ctr, (hg::RoundCounters*)(g->ws + g->lay.ctr2)};
   hg::CountPlan cplan;
   hg::single_count_plan(d, cplan);
   hipError_t e = hg::launch_counts(cplan, true, true, s);
@@ -437,7 +443,7 @@ static hipError_t enqueue_refine(hg_graph g, int k, long long lmax, int rounds, 
     if (!marks) {                 // (the phase times include the records)
       d.late = 1;
       d.prev = r > 0 ? d.ctr : nullptr;
-      d.ctr = ctr + (r & 1);
+      d.ctr = ctr[r & 1];
     }
     hg::single_round_plan(d, plan);
     plan.record = !d.late || r + 1 == rounds;

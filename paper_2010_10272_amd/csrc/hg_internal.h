@@ -282,8 +282,10 @@ struct WsLayout {
   size_t bw_slots;   // kSlots x k_max block-weight deltas (apply), folded in by the round record
   size_t part8;      // up to n bytes: the partition in 4 or 8 bits a vertex (pin-count gathers)
   size_t lkey[2], lval, lhist, ldtot;   // load only: radix-sort buffers of the transpose
-  size_t lbase;      // load only: bucket starts and write cursors (LoadSplit)
   size_t lpart;      // load only: per-workgroup partial facts (LoadPart[kLoadGrid])
+  // inside others (see ws_layout)
+  size_t lbase;      // load only: bucket starts and write cursors (LoadSplit)
+  size_t ctr2;       // late rounds: the second set of counters
   size_t total;
   int num_tiles;
   int scan_blocks;
