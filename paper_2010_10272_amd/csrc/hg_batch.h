@@ -32,8 +32,10 @@ extern const hg_schedule kDefaultSchedule[HG_SIZE_CLASSES];
 int size_class(int n);
 bool valid_schedule(const hg_schedule& s);
 
-// Table bytes members `which` of `mem` can need, for any schedule.
-size_t table_bound(const std::vector<BatchMember>& mem, const std::vector<int>& which);
+// Table bytes that the round plan (and / or the pin-count plan) of members `which`
+// of `mem` can need, for any schedule.
+size_t table_bound(const std::vector<BatchMember>& mem, const std::vector<int>& which,
+                   bool rounds, bool counts);
 
 // Build the descriptors and work tables of members `which` under `sched`
 // into the host staging buffer `host` at byte offset `at` (capacity `cap`),

@@ -37,7 +37,10 @@ namespace {
 constexpr int kMaxScheduleChunks = 64;
 constexpr long long kSpreadCost = 1 << 16;      // P + n: fewer stay on one XCD (see build_plans)
 constexpr int kHeavyPerGroup = kBlock / kWave;   // heavy vertices per select workgroup
-constexpr size_t kLaunchSlack = 32 * 256;       // 256-byte alignment of every launch's table
+// 256-byte alignment of the descriptors and of every launch's table: at most 13
+// select variants and 4 finalize ones, 5 others; 4 pin-count variants, 2 others.
+constexpr size_t kRoundSlack = 23 * 256;
+constexpr size_t kCountSlack = 7 * 256;
 
 size_t align256(size_t x) { return (x + 255) & ~(size_t)255; }
 
@@ -100,24 +103,30 @@ bool valid_schedule(const hg_schedule& s) {
          chunks_ok(s.count_chunks) && (l == 0 || l == 4 || l == 8 || l == 16 || l == 32);
 }
 
-size_t table_bound(const std::vector<BatchMember>& mem, const std::vector<int>& which) {
+size_t table_bound(const std::vector<BatchMember>& mem, const std::vector<int>& which,
+                   bool rounds, bool counts) {
   long long items = 0;
   for (int i : which) {
     const BatchMember& x = mem[i];
     const hg_graph_s* g = x.g;
     const long long tiles = ceil_div(g->n, kTile);
-    items += ceil_div(g->n, kBlock);                                 // select
-    items += ceil_div(g->info.heavy_count, kHeavyPerGroup);          // heavy select
-    items += x.k;                                                    // per block
-    items += tiles;                                                  // tile sums
-    items += tiles + x.k;                                            // approve
-    items += ceil_div(g->m, kFinalChunk);                            // finalize
-    items += ceil_div(g->m, kBlock);                                 // pin counts
-    items += ceil_div(g->n, kBwChunk);                               // block weights
-    items += 2;                                                      // per member
+    if (rounds) {
+      items += ceil_div(g->n, kBlock);                               // select
+      items += ceil_div(g->info.heavy_count, kHeavyPerGroup);        // heavy select
+      items += x.k;                                                  // per block
+      items += tiles;                                                // tile sums
+      items += tiles + x.k;                                          // approve
+      items += ceil_div(g->m, kFinalChunk);                          // finalize
+      items += 1;                                                    // per member
+    }
+    if (counts) {
+      items += ceil_div(g->m, kBlock);                               // pin counts
+      items += ceil_div(g->n, kBwChunk);                             // block weights
+      items += 1;                                                    // per member
+    }
   }
   return align256(sizeof(InstDesc) * which.size()) + sizeof(WorkItem) * (size_t)items +
-         kLaunchSlack;
+         (rounds ? kRoundSlack : 0) + (counts ? kCountSlack : 0);
 }
 
 size_t build_plans(const std::vector<BatchMember>& mem, const std::vector<int>& which,
@@ -412,7 +421,7 @@ extern "C" {
 size_t hg_batch_table_bytes(const hg_instance* members, int32_t count) {
   std::vector<hg::BatchMember> mem;
   if (hg::check_members(members, count, mem) != HG_OK) return 0;
-  return hg::table_bound(mem, hg::iota_vec(mem.size()));
+  return hg::table_bound(mem, hg::iota_vec(mem.size()), true, true);
 }
 
 hg_status hg_batch_get_schedule(hg_batch b, hg_schedule* sched) {
@@ -432,7 +441,7 @@ hg_status hg_batch_create(const hg_instance* members, int32_t count, const hg_sc
     for (int c = 0; c < HG_SIZE_CLASSES; ++c)
       if (!hg::valid_schedule(sched[c]))
         return fail(HG_ERR_INVALID, "schedule of size class %d is out of range", c);
-  const size_t need = hg::table_bound(mem, hg::iota_vec(mem.size()));
+  const size_t need = hg::table_bound(mem, hg::iota_vec(mem.size()), true, true);
   if (!table || table_bytes < need)
     return fail(HG_ERR_WORKSPACE, "batch table needs %zu bytes (got %zu)", need, table_bytes);
   hg_batch_s* b = new (std::nothrow) hg_batch_s();

@@ -517,16 +517,18 @@ size_t gather_step(hg_server_s* s, Lane& ln, std::vector<Job*>& run) {
   while (!ln.ready.empty()) {
     Job* j = ln.ready.front();
     std::vector<BatchMember> mem;
-    std::vector<int> all;
-    for (size_t i = 0; i < run.size(); ++i) {
-      mem.push_back(member_of(s, run[i]));
-      all.push_back((int)i);
-    }
+    std::vector<int> all, join;
     j->join_step = ln.step;
-    mem.push_back(member_of(s, j));
-    all.push_back((int)run.size());
-    // round tables of everyone plus count tables of the joiners
-    if (table_bound(mem, all) * 2 > ln.half_bytes) {
+    for (size_t i = 0; i <= run.size(); ++i) {
+      mem.push_back(member_of(s, i < run.size() ? run[i] : j));
+      all.push_back((int)i);
+      if (i + nj >= run.size()) join.push_back((int)i);
+    }
+    // the round tables of everyone and the count tables of the joiners (twice the
+    // tables of everyone would refuse jobs that the smallest table region holds:
+    // n = m = 110,000 in 128 KiB)
+    if (table_bound(mem, all, true, false) + table_bound(mem, join, false, true) >
+        ln.half_bytes) {
       if (run.empty()) {
         ln.ready.pop_front();
         hg_free(j->g);

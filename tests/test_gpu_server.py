@@ -151,3 +151,22 @@ def test_server_max_active_and_failures(H, jobs, alone):
     srv.free()
     srv2.free()
     torch.cuda.synchronize()
+
+
+@pytest.mark.parametrize("n", [20000, 96000, 110000])
+def test_server_smallest_table_region(H, n):
+    """The smallest table region holds the tables of jobs of this size, one after
+    the other or together, and each ends with the result it has alone."""
+    import torch
+    insts = [synth.random_power_law(s, n, n, 2, hi=8, rounds=2) for s in (1, 2, 3)]
+    srv = H.hg_server_create(256 << 20, table_bytes=128 << 10, max_active=3)
+    ids = _submit_all(H, srv, insts, [0, 1, 2])
+    assert H.hg_server_drain(srv, DRAIN_MS) == 0
+    for i, x in enumerate(insts):
+        assert H.hg_server_info(srv, ids[i])["status"] == H.HG_OK
+        g = H.hg_load_csr(x.n, x.eptr, x.pins, x.c, x.w, k_max=2)
+        st = H.State(g, 2, x.part)
+        H.hg_refine(g, st, x.eps, 2, torch.zeros(2 * H.STATS_WORDS, dtype=torch.int64, device="cuda"))
+        part, _, km1 = H.hg_server_result(srv, ids[i])
+        assert np.array_equal(part.numpy(), st.part.cpu().numpy()) and km1 == int(st.km1.item())
+    srv.free()
