@@ -173,9 +173,11 @@ WsLayout ws_layout(int n, int m, long long P, int k_max) {
   // A load and the rounds share space, each where the other needs none: the load's
   // bucket tables (2 * (buckets + coarse + 1) words with buckets <= n: at most
   // 8.125 n + 16 bytes) lie in the 16 n bytes per vertex that its last kernels
-  // and the rounds fill, the late rounds' second set of counters in its parts.
+  // and the rounds fill, the late rounds' second set of counters in its parts, the
+  // list of long nets (fewer than P / kWaveNet) in its second sort buffer.
   L.lbase = L.cand;
   L.ctr2 = L.lpart;
+  L.longs = L.lkey[1];
   static_assert(sizeof(RoundCounters) <= sizeof(LoadPart) * kLoadGrid, "shared");
   return L;
 }
@@ -197,6 +199,8 @@ InstDesc make_desc(hg_graph_s* g, int k, long long lmax, int* part, int* phi,
   d.cmax = g->info.max_vertex_weight;
   d.lds_buckets = lds_buckets(k);
   d.heavy_count = g->info.heavy_count;
+  d.long_count = (int)g->info.long_count;
+  d.long_list = (const int*)(ws + g->lay.longs);
   d.num_tiles = g->lay.num_tiles;
   d.hist_stride = g->k_max * kBuckets;
   // (brief rounds reread the histogram in every workgroup)
@@ -315,6 +319,7 @@ hg_status hg_load_csr(int32_t n, int32_t m, int64_t P, const int64_t* eptr, cons
   if (g->info.total_vertex_weight > (1ULL << 62))
     return bail(fail(HG_ERR_UNSUPPORTED, "total vertex weight exceeds 2^62"));
   e = hg::load_build(g, s);
+  if (e == hipSuccess) e = hg::list_long_nets(g, s);
   if (e != hipSuccess) return bail(hip_fail(e, "incidence build"));
   // zero the round state kept in the workspace
   char* ws = g->ws;

@@ -38,9 +38,10 @@ constexpr int kMaxScheduleChunks = 64;
 constexpr long long kSpreadCost = 1 << 16;      // P + n: fewer stay on one XCD (see build_plans)
 constexpr int kHeavyPerGroup = kBlock / kWave;   // heavy vertices per select workgroup
 // 256-byte alignment of the descriptors and of every launch's table: at most 13
-// select variants and 4 finalize ones, 5 others; 4 pin-count variants, 2 others.
-constexpr size_t kRoundSlack = 23 * 256;
-constexpr size_t kCountSlack = 7 * 256;
+// select variants, 4 finalize ones and 4 of long nets, 5 others; 6 pin-count variants
+// and 4 of long nets, 2 others.
+constexpr size_t kRoundSlack = 27 * 256;
+constexpr size_t kCountSlack = 13 * 256;
 
 size_t align256(size_t x) { return (x + 255) & ~(size_t)255; }
 
@@ -117,10 +118,12 @@ size_t table_bound(const std::vector<BatchMember>& mem, const std::vector<int>& 
       items += tiles;                                                // tile sums
       items += tiles + x.k;                                          // approve
       items += ceil_div(g->m, kFinalChunk);                          // finalize
+      items += long_pieces((int)g->info.long_count);                      // of long nets
       items += 1;                                                    // per member
     }
     if (counts) {
       items += ceil_div(g->m, kBlock);                               // pin counts
+      items += long_pieces((int)g->info.long_count);                      // of long nets
       items += ceil_div(g->n, kBwChunk);                             // block weights
       items += 1;                                                    // per member
     }
@@ -177,7 +180,7 @@ size_t build_plans(const std::vector<BatchMember>& mem, const std::vector<int>& 
   }
 
   std::vector<InstDesc> descs(cnt);
-  std::vector<KindItems> sel, fin, pc;
+  std::vector<KindItems> sel, fin, pc, long_rounds, long_counts;
   KindItems heavy, blocks, tiles, approve, inst, verts;
   bool any_heavy = false;
   for (int i = 0; i < cnt; ++i) {
@@ -191,7 +194,14 @@ size_t build_plans(const std::vector<BatchMember>& mem, const std::vector<int>& 
     keep_private_copies(g, d, true);
     descs[i] = d;
     const int k = M.k;
+    const int pieces = long_pieces(d.long_count);
+    auto add_longs = [&](std::vector<KindItems>& v, void* kernel) {
+      for (int p = 0; p < pieces; ++p)
+        variant(v, kernel)->flat.push_back(
+            WorkItem{i, p, (d.long_count - p + pieces - 1) / pieces, pieces});
+    };
     if (rp) {
+      add_longs(long_rounds, long_round_kernel(k, false));
       add_split(*variant(sel, (void*)select_kernel(k, d.view, d.P, d.n),
                          (void*)select_kernel(k, d.sweep, d.P, d.n)),
                 i, ceil_div(g->n, kBlock), S.select_chunks, home[i]);
@@ -207,10 +217,11 @@ size_t build_plans(const std::vector<BatchMember>& mem, const std::vector<int>& 
       for (int t = 0; t < k; ++t) approve.flat.push_back(WorkItem{i, t, -1, 1});
     }
     if (cp) {
-      KindItems* p = variant(pc, (void*)pincount_kernel(k));
-      const int unit = count_unit(k, g->m);            // at most kBlock nets
+      add_longs(long_counts, long_counts_kernel(k));
+      KindItems* p = variant(pc, (void*)pincount_kernel(k, g->m, g->P, true));
+      const int unit = pincount_unit(k, g->m, g->P, true);
       add_split(*p, i, ceil_div(g->m, unit), S.count_chunks * (kBlock / unit), home[i]);
-      p->lds = std::max(p->lds, pincount_lds(k, g->m));
+      p->lds = std::max(p->lds, pincount_lds(k, g->m, g->P, true));
       add_split(verts, i, ceil_div(g->n, kBwChunk), 1, home[i]);
     }
     inst.flat.push_back(WorkItem{i, 0, 1, 1});
@@ -281,6 +292,10 @@ size_t build_plans(const std::vector<BatchMember>& mem, const std::vector<int>& 
       rp->finalize.push_back(PlanLaunch());
       emit_split(k, rp->finalize.back());
     }
+    for (const KindItems& k : long_rounds) {
+      rp->longs.push_back(PlanLaunch());
+      emit_flat(k, rp->longs.back());
+    }
     emit_flat(inst, rp->stats);
   }
   if (cp) {
@@ -289,6 +304,11 @@ size_t build_plans(const std::vector<BatchMember>& mem, const std::vector<int>& 
       cp->pincounts.push_back(PlanLaunch());
       emit_split(k, cp->pincounts.back());
       cp->pincounts.back().L.kept = 1;   // the private views too, whoever runs the rounds
+    }
+    for (const KindItems& k : long_counts) {
+      cp->longs.push_back(PlanLaunch());
+      emit_flat(k, cp->longs.back());
+      cp->longs.back().L.kept = 1;
     }
     emit_flat(inst, cp->instances);
     emit_split(verts, cp->vertices);
@@ -304,6 +324,7 @@ RoundPlan kept_plan(const RoundPlan& plan) {
   }
   for (PlanLaunch& pl : p.heavy) pl.L.kept = 1;
   for (PlanLaunch& pl : p.finalize) pl.L.kept = 1;
+  for (PlanLaunch& pl : p.longs) pl.L.kept = 1;
   p.approve.L.kept = 1;
   return p;
 }

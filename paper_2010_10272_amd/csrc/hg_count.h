@@ -3,9 +3,10 @@
 //
 // The nets' pins are laid end to end as one run and counted 64 at a time, every
 // lane a pin, into byte counters in LDS; then each lane builds its net's bitsets
-// from its counters and the Phi rows leave as whole lines.  Nets of more than
-// 255 pins, whose counts might not fit a byte, are counted one at a time in
-// 32-bit words.
+// from its counters and the Phi rows leave as whole lines.  Where a net has more
+// than 255 pins, so that a count might not fit a byte, the same places hold its 32-bit
+// counters.  Nets of more than kWaveNet pins are left to a workgroup each
+// (k_long_nets).
 #pragma once
 
 #include "hg_device.h"
@@ -17,6 +18,7 @@ namespace hg {
 constexpr int kCountFlight = 4;              // pins in flight per lane
 constexpr int kCountStep = kCountFlight * kWave;
 constexpr int kByteNet = 255;                // longest net whose counts surely fit a byte
+constexpr int kWaveNet = 2048;               // longest net that a wavefront counts
 
 // Most nets a wavefront counts at a time (64 nets' counters fill the LDS for
 // k > 128).
@@ -24,10 +26,15 @@ __host__ __device__ inline int count_nets(int k) { return k > 128 ? 32 : 64; }
 // Words of a net's byte counters in LDS: odd, so that lanes reading their own
 // nets' word i use all banks.
 __host__ __device__ inline int count_stride(int k) { return ((k + 3) / 4) | 1; }
-// LDS words of one wavefront that counts `nets` nets at a time: the counters,
-// k words for a long net, a flag byte per position in flight, one word a net.
+// Words of a wavefront's counters: `nets` nets of bytes, or one of 32-bit counters.
+__host__ __device__ inline int counter_words(int k, int nets) {
+  const int bytes = nets * count_stride(k);
+  return bytes > k ? bytes : k;
+}
+// LDS words of one wavefront that counts `nets` nets at a time: the counters, a
+// flag byte per position in flight, one word a net.
 __host__ __device__ inline int count_words(int k, int nets) {
-  return nets * count_stride(k) + k + kCountStep / 4 + kWave;
+  return counter_words(k, nets) + kCountStep / 4 + kWave;
 }
 
 // A run of pins is walked kCountStep places at a time.  It has fewer than 2^31
@@ -39,21 +46,21 @@ __host__ __device__ inline RunPlace in_step(int first, RunPlace s) { return (Run
 
 struct CountLds {
   unsigned* cnt;               // [nets][stride], zero between calls
-  int* big;                    // [k]
   unsigned char* flag;         // [kCountStep], zero between calls
   int* shift;                  // [kWave]: first pin - place in the run, per net
   int stride;
+  int words;                   // of cnt
 };
 
 // The wavefront's share of the LDS words at `base`, cleared.
 __device__ __forceinline__ CountLds count_lds(unsigned* base, int k, int nets) {
   CountLds M;
   M.stride = count_stride(k);
+  M.words = counter_words(k, nets);
   M.cnt = base;
-  M.big = reinterpret_cast<int*>(base + nets * M.stride);
-  M.flag = reinterpret_cast<unsigned char*>(M.big + k);
-  M.shift = M.big + k + kCountStep / 4;
-  for (int i = lane_id(); i < nets * M.stride; i += kWave) M.cnt[i] = 0;
+  M.flag = reinterpret_cast<unsigned char*>(base + M.words);
+  M.shift = reinterpret_cast<int*>(base + M.words + kCountStep / 4);
+  for (int i = lane_id(); i < M.words; i += kWave) M.cnt[i] = 0;
   reinterpret_cast<unsigned*>(M.flag)[lane_id()] = 0;
   return M;
 }
@@ -74,20 +81,49 @@ __device__ __forceinline__ void byte_bits(unsigned x, unsigned& nz, unsigned& on
 // of part's bytes, so more of it stays in the L1s) where it is valid, that is
 // where the block-weight sweep just wrote it or the rounds since then kept it, and
 // no block was out of range; else part.
+//
+// The blocks of N pins (v = -1: none, and then ~0) are read together: all loads
+// first, in no branch of their own (a pin without a vertex reads vertex 0's place),
+// and what has to be done to the values after them.  With a branch, a load and a
+// shift per pin the compiler waited for each before the next, and through generic
+// pointers for the LDS too (pin counts of 10M pins, k = 8 55 -> 52 us, k = 64 84 -> 75).
 struct Blocks {
   const int* part;
   const unsigned char* part8;
-  bool packed, nibbles;
-  __device__ __forceinline__ unsigned operator()(int v) const {
-    if (!packed) return (unsigned)part[v];
-    if (!nibbles) return part8[v];
-    return (part8[(unsigned)v >> 1] >> (4 * (v & 1))) & 15u;
+  bool packed;
+  int two;                     // 1: two vertices a byte
+  template <int N>
+  __device__ __forceinline__ void operator()(const int (&v)[N], unsigned (&id)[N]) const {
+    if (packed) {
+#pragma unroll
+      for (int q = 0; q < N; ++q) id[q] = global_ptr(part8)[(unsigned)(v[q] < 0 ? 0 : v[q]) >> two];
+#pragma unroll
+      for (int q = 0; q < N; ++q) {
+        const unsigned half = (id[q] >> (4 * (v[q] & 1))) & 15u;
+        id[q] = v[q] < 0 ? ~0u : two ? half : id[q];
+      }
+    } else {
+#pragma unroll
+      for (int q = 0; q < N; ++q) id[q] = (unsigned)global_ptr(part)[v[q] < 0 ? 0 : v[q]];
+#pragma unroll
+      for (int q = 0; q < N; ++q) id[q] = v[q] < 0 ? ~0u : id[q];
+    }
   }
 };
 
 __device__ __forceinline__ Blocks blocks_of(const InstDesc& D, bool valid) {
-  return Blocks{D.part, D.part8, valid && (*D.err_flags & kErrPart) == 0, D.k <= 16};
+  return Blocks{D.part, D.part8, valid && (*D.err_flags & kErrPart) == 0, D.k <= 16 ? 1 : 0};
 }
+
+// Makes pins eligible for the next round.
+struct EligiblePins {
+  unsigned char* eligible;
+  __device__ __forceinline__ void operator()(const int (&v)[kCountFlight]) const {
+#pragma unroll
+    for (int q = 0; q < kCountFlight; ++q)
+      if (v[q] >= 0) global_out(eligible)[v[q]] = 1;
+  }
+};
 
 // Vertex u moves from block a to block t: its place in part8 (two vertices share
 // a byte, and other movers their word: an exclusive or).
@@ -107,24 +143,39 @@ struct NetSets {
   int lambda;
 };
 
+// Words h and h + 1 of a net's sets from the ballots over its blocks 32 h .. 32 h + 63,
+// where `mine`.
+template <int WK>
+__device__ __forceinline__ void set_words(NetSets<WK>& N, int h, unsigned long long nz,
+                                          unsigned long long one, bool mine) {
+  if (!mine) return;
+  N.lam[h] = (unsigned)nz;
+  N.one[h] = (unsigned)one;
+  if (h + 1 < WK) {
+    N.lam[h + 1] = (unsigned)(nz >> 32);
+    N.one[h + 1] = (unsigned)(one >> 32);
+  }
+  N.lambda += __popcll(nz);
+}
+
 // The pins of the wavefront's nets -- lane's net is pins [b, b + len), len = 0:
-// none -- laid end to end, kCountFlight per lane at a time: `load(v, q)` is called
-// for the pins of a step (v = -1 past the end) once all of its pins are on their
-// way, then `take(net, q)` with the lane index of each pin's net.  So a step waits
-// once for its pins and once for what load fetches (netlist, 56.5M pins: pin counts
-// 483 us with load called pin by pin, 370 so).  RUN: the nets are neighbours,
-// their pins one run already.  A position's net is the count of net starts at or
-// before it: a flag per position in LDS, one ballot.  Nets come in the first
-// lanes, each of at least one pin (else the flags would miss one).  Every lane
-// calls.
+// none -- laid end to end, kCountFlight per lane at a time: `load(v)` gets the
+// pins of a step (-1 past the end), then `take(net, q)` is called for each with the
+// rank of its net among those that are there.  So a step waits once for its pins and
+// once for what load fetches.
+// RUN: the nets are neighbours in the first lanes, their pins one run already.  A
+// position's net is the count of net starts at or before it: a flag per position
+// in LDS, one ballot.  Every lane calls.
 template <bool RUN, typename LoadF, typename TakeF>
-__device__ __forceinline__ void for_pins(const int* __restrict__ pins, const CountLds& M,
-                                         long long b, int len, LoadF load, TakeF take) {
+__device__ __forceinline__ void for_pins(const int* pin_array, const CountLds& M, long long b,
+                                         int len, LoadF load, TakeF take) {
+  auto pins = global_ptr(pin_array);
   const int lane = lane_id();
   const int incl = wave_incl_scan(len);
   const int total = last_lane(incl), first = incl - len;   // this net's place in the run
   if constexpr (RUN) pins += __shfl(b, 0);
-  else M.shift[lane] = (int)b - first;                     // pin positions are below 2^31
+  else if (const int at = lanes_below(__ballot(len > 0), 0); len > 0)
+    M.shift[at] = (int)b - first;                          // pin positions are below 2^31
   int before = -1;                                         // last net starting before this step
   for (RunPlace s = 0; run_left(s, total); s += kCountStep) {
     int net[kCountFlight], v[kCountFlight];
@@ -155,8 +206,7 @@ __device__ __forceinline__ void for_pins(const int* __restrict__ pins, const Cou
         v[q] = run_left(p, total) ? pins[(RunPlace)M.shift[net[q]] + p] : -1;
       }
     }
-#pragma unroll
-    for (int q = 0; q < kCountFlight; ++q) load(v[q], q);
+    load(v);
     if constexpr (RUN) nets_of();
 #pragma unroll
     for (int q = 0; q < kCountFlight; ++q) take(net[q], q);
@@ -164,68 +214,52 @@ __device__ __forceinline__ void for_pins(const int* __restrict__ pins, const Cou
   }
 }
 
-// Counts of one net longer than kByteNet by the whole wavefront, in 32-bit
-// words: its Phi row, and the counts left in M.big.
-template <typename Block>
-__device__ void count_long_net(const InstDesc& D, const CountLds& M, long long e, long long b,
-                               long long t, Block block) {
-  const int lane = lane_id(), k = D.k;
-  for (int i = lane; i < k; i += kWave) M.big[i] = 0;
-  wave_lds_sync();
-  for (long long p = b + lane; p < t; p += kWave) {
-    const unsigned v = block(D.pins[p]);
-    if (v < (unsigned)k) atomicAdd(&M.big[v], 1);
+// One add per run of equal keys in neighbouring lanes (pins of a net in one block
+// are often neighbours).  `live` lanes' key is below 2^32 - 1; add(n) is called by
+// the first lane of each run of n.  Every lane calls.
+template <typename Add>
+__device__ __forceinline__ void add_runs(bool live, unsigned key, Add add) {
+  const int lane = lane_id();
+  key = live ? key : ~0u;
+  const unsigned prev = lane_before(key);
+  const unsigned long long heads = __ballot(lane == 0 || key != prev);
+  if (live && ((heads >> lane) & 1ull)) {
+    const unsigned long long later = heads >> lane >> 1;
+    add(later ? __ffsll((long long)later) : kWave - lane);
   }
-  wave_lds_sync();
-  for (int i = lane; i < k; i += kWave) D.phi[e * k + i] = M.big[i];
 }
 
-// Pin counts of the wavefront's `nets` nets: lane i < nets owns net e, pins
-// [b, b + len) (len = 0 in the other lanes).  block(v) is v's block, anything
-// >= k where it counts nowhere; pin(v) is called once for every pin of the nets.
-// Writes the Phi rows and leaves lane's sets in N.  Pins of a net in one block
-// are often neighbours, so each run of equal (net, block) adds once.  vec_phi:
-// rows are 16-byte aligned and leave as 16-byte streaming stores.  Every lane
-// calls.
+// Counts of the nets of `in` lanes, each of at most kByteNet pins: byte counters, the
+// nets' in the order of their lanes; N is set for every lane.
 template <int WK, bool RUN, typename Block, typename Pin>
-__device__ __forceinline__ void count_batch(const InstDesc& D, const CountLds& M, long long e,
-                                            long long b, int len, int nets, bool vec_phi,
+__device__ __forceinline__ void count_bytes(const InstDesc& D, const CountLds& M, long long e,
+                                            long long b, int len, bool in, bool vec_phi,
                                             Block block, Pin pin, NetSets<WK>& N) {
   const int lane = lane_id(), k = D.k, stride = M.stride;
-  const unsigned long long is_long = __ballot(len > kByteNet);
+  const unsigned long long nets_in = __ballot(in);
+  const int nets = __popcll(nets_in), mine = RUN ? lane : lanes_below(nets_in, 0);
   wave_lds_sync();
   unsigned id[kCountFlight];
   for_pins<RUN>(
-      D.pins, M, b, len,
-      [&](int v, int q) {
-        id[q] = ~0u;
-        if (v >= 0) {
-          pin(v);
-          id[q] = block(v);
-        }
+      D.pins, M, b, in ? len : 0,
+      [&](const int (&v)[kCountFlight]) {
+        block(v, id);
+        pin(v);
       },
       [&](int net, int q) {
-        bool live = id[q] < (unsigned)k;
-        if (is_long) live = live && !((is_long >> (net & 63)) & 1ull);
-        // one add per run of equal (net, block) in neighbouring lanes
-        const unsigned key = live ? ((unsigned)net << 8) | id[q] : ~0u;
-        const unsigned prev = lane_before(key);
-        const unsigned long long heads = __ballot(lane == 0 || key != prev);
-        if (live && ((heads >> lane) & 1ull)) {
-          const unsigned long long later = heads >> lane >> 1;
-          const int run_len = later ? __ffsll((long long)later) : kWave - lane;
-          atomicAdd(&M.cnt[net * stride + (id[q] >> 2)], (unsigned)run_len << (8 * (id[q] & 3)));
-        }
+        add_runs(id[q] < (unsigned)k, ((unsigned)net << 8) | id[q], [&](int n) {
+          atomicAdd(&M.cnt[net * stride + (id[q] >> 2)], (unsigned)n << (8 * (id[q] & 3)));
+        });
       });
   // lane's net: bitsets from its counters
   N.lambda = 0;
 #pragma unroll
   for (int w = 0; w < WK; ++w) {
     N.lam[w] = N.one[w] = 0;
-    if (lane < nets) {
+    if (in) {
       for (int j = 0; j < 8 && w * 32 + 4 * j < k; ++j) {
         unsigned nz, on;
-        byte_bits(M.cnt[lane * stride + w * 8 + j], nz, on);
+        byte_bits(M.cnt[mine * stride + w * 8 + j], nz, on);
         N.lam[w] |= nz << (4 * j);
         N.one[w] |= on << (4 * j);
       }
@@ -234,7 +268,7 @@ __device__ __forceinline__ void count_batch(const InstDesc& D, const CountLds& M
   }
   // Phi rows, 16 bytes (or one count) per lane and step; M.shift now holds the
   // nets' ids
-  M.shift[lane] = (int)e;
+  if (in) M.shift[mine] = (int)e;
   wave_lds_sync();
   if (vec_phi) {
     const int words = k >> 2, all = nets * words;
@@ -244,9 +278,8 @@ __device__ __forceinline__ void count_batch(const InstDesc& D, const CountLds& M
       const unsigned x = M.cnt[row * stride + col];
       const i32x4 o = {(int)(x & 255u), (int)((x >> 8) & 255u), (int)((x >> 16) & 255u),
                        (int)(x >> 24)};
-      if (!((is_long >> row) & 1ull))
-        __builtin_nontemporal_store(
-            o, reinterpret_cast<i32x4*>(D.phi + (long long)M.shift[row] * k) + col);
+      __builtin_nontemporal_store(
+          o, global_out(reinterpret_cast<i32x4*>(D.phi + (long long)M.shift[row] * k)) + col);
       row += drow;
       col += dcol;
       if (col >= words) {
@@ -257,30 +290,93 @@ __device__ __forceinline__ void count_batch(const InstDesc& D, const CountLds& M
   } else {
     for (int i = lane; i < nets * k; i += kWave) {
       const int row = i / k, col = i % k;
-      if (!((is_long >> row) & 1ull))
-        D.phi[(long long)M.shift[row] * k + col] =
-            (int)((M.cnt[row * stride + (col >> 2)] >> (8 * (col & 3))) & 255u);
+      global_out(D.phi)[(long long)M.shift[row] * k + col] =
+          (int)((M.cnt[row * stride + (col >> 2)] >> (8 * (col & 3))) & 255u);
     }
   }
   wave_lds_sync();
   for (int i = lane; i < nets * stride; i += kWave) M.cnt[i] = 0;   // for the next nets
-  for (unsigned long long left = is_long; left; left &= left - 1) {
-    const int j = __ffsll((long long)left) - 1;
-    const long long lb = __shfl(b, j);
-    count_long_net(D, M, M.shift[j], lb, lb + __shfl(len, j), block);
-    if (lane == j) {
-      N.lambda = 0;
+}
+
+// The same for the longer nets of lanes `left`, one net after the other: 32-bit
+// counters, kCountStep pins a step, the next step's pins (or the next net's) on their
+// way while this one's are counted; the sets and the Phi row by ballots.  N is set
+// for those lanes.  (Pin counts of 2,000 nets of 1,500 pins, k = 8, per call, us: a
+// lane group per net 45, 64 pins a step after a first walk past them 136, so 32.)
+template <int WK, typename Block, typename Pin>
+__device__ __forceinline__ void count_mid_nets(const InstDesc& D, const CountLds& M, long long e,
+                                               long long b, int len, unsigned long long left,
+                                               Block block, Pin pin, NetSets<WK>& N) {
+  const int lane = lane_id(), k = D.k;
+  int owner = 0, size = 0, s = 0;            // wave-uniform: this step's net and place
+  long long at = 0;
+  int next[kCountFlight];
+  // the pins of the step after place s of the net, or of the next net's first
+  auto advance = [&]() {
+    s += kCountStep;
+    if (s >= size) {
+      owner = left ? __ffsll((long long)left) - 1 : -1;
+      left &= left - 1;
+      s = 0;
+      size = owner < 0 ? 0 : __builtin_amdgcn_readlane(len, owner);
+      at = owner < 0 ? 0 : lane_value(b, owner);
+    }
 #pragma unroll
-      for (int w = 0; w < WK; ++w) {
-        N.lam[w] = N.one[w] = 0;
-        for (int i = 0; i < 32 && w * 32 + i < k; ++i) {
-          N.lam[w] |= (M.big[w * 32 + i] > 0 ? 1u : 0u) << i;
-          N.one[w] |= (M.big[w * 32 + i] == 1 ? 1u : 0u) << i;
-        }
-        N.lambda += __popc(N.lam[w]);
+    for (int q = 0; q < kCountFlight; ++q) {
+      const int p = s + q * kWave + lane;
+      next[q] = p < size ? global_ptr(D.pins)[at + p] : -1;
+    }
+  };
+  advance();
+  while (owner >= 0) {
+    const int net = owner;
+    unsigned id[kCountFlight];
+    block(next, id);
+    pin(next);
+    advance();
+#pragma unroll
+    for (int q = 0; q < kCountFlight; ++q)
+      add_runs(id[q] < (unsigned)k, id[q], [&](int n) { atomicAdd(&M.cnt[id[q]], (unsigned)n); });
+    if (s > 0) continue;                     // more of the same net
+    wave_lds_sync();
+    const long long phi_row = lane_value(e, net) * k;
+    if (lane == net) N.lambda = 0;
+#pragma unroll
+    for (int h = 0; h < WK; h += 2) {
+      const int i = h * 32 + lane;
+      const int x = i < k ? (int)M.cnt[i] : 0;
+      if (i < k) {
+        M.cnt[i] = 0;                        // for the next net
+        global_out(D.phi)[phi_row + i] = x;
       }
+      set_words<WK>(N, h, __ballot(x != 0), __ballot(x == 1), lane == net);
     }
     wave_lds_sync();
+  }
+}
+
+// Pin counts of the wavefront's nets: lane owns net e, pins [b, b + len), len = 0:
+// none.  RUN: neighbouring nets in the first lanes.  block(v, id) gives the blocks of a
+// lane's kCountFlight pins (-1: none), anything >= k where a pin counts nowhere;
+// pin(v) gets the same pins, every pin of the nets once.
+// Writes the Phi rows and leaves lane's sets in N.  Nets of more than kWaveNet
+// pins are passed over: neither counted nor written.  vec_phi: rows are 16-byte
+// aligned and leave as 16-byte streaming stores.  Every lane calls.
+template <int WK, bool RUN, typename Block, typename Pin>
+__device__ __forceinline__ void count_batch(const InstDesc& D, const CountLds& M, long long e,
+                                            long long b, int len, bool vec_phi, Block block,
+                                            Pin pin, NetSets<WK>& N) {
+  const bool in = len > 0 && len <= kByteNet;
+  if constexpr (RUN) {
+    if (!__any(len > kByteNet)) {
+      count_bytes<WK, true>(D, M, e, b, len, in, vec_phi, block, pin, N);
+      return;
+    }
+  }
+  count_bytes<WK, false>(D, M, e, b, len, in, vec_phi, block, pin, N);
+  if (const unsigned long long rest = __ballot(len > kByteNet && len <= kWaveNet)) {
+    wave_lds_sync();
+    count_mid_nets<WK>(D, M, e, b, len, rest, block, pin, N);
   }
 }
 

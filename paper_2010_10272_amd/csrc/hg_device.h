@@ -82,6 +82,13 @@ template <typename T>
 __device__ __forceinline__ T wave_sum(T v) {
   return last_lane(wave_scan_op(v, [](T a, T b) { return a + b; }));
 }
+// The value of lane `from`, the same for the whole wave.
+__device__ __forceinline__ long long lane_value(long long v, int from) {
+  const unsigned lo = (unsigned)__builtin_amdgcn_readlane((int)(unsigned)v, from);
+  const unsigned hi =
+      (unsigned)__builtin_amdgcn_readlane((int)(unsigned)((unsigned long long)v >> 32), from);
+  return (long long)(((unsigned long long)hi << 32) | lo);
+}
 // The value of the lane before (0 in lane 0).
 __device__ __forceinline__ unsigned lane_before(unsigned v) {
   return (unsigned)__builtin_amdgcn_update_dpp(0, (int)v, 0x138 /* wave_shr:1 */, 0xf, 0xf, false);
@@ -165,6 +172,11 @@ __device__ __forceinline__ int cand_gain(long long x) { return (int)(x >> 32); }
 template <typename T>
 __device__ __forceinline__ const __attribute__((address_space(1))) T* global_ptr(const T* p) {
   return (const __attribute__((address_space(1))) T*)p;
+}
+
+template <typename T>
+__device__ __forceinline__ __attribute__((address_space(1))) T* global_out(T* p) {
+  return (__attribute__((address_space(1))) T*)p;
 }
 
 // Plain vector types for 8- and 16-byte global loads and nontemporal stores

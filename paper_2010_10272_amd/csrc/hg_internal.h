@@ -112,7 +112,8 @@ struct LoadInfo {
   unsigned long long total_net_weight;
   int big_rows;       // incidence rows longer than kSmallRow
   unsigned max_bucket;  // most pins in one vertex range of the transpose (LoadSplit)
-  int pad[4];
+  unsigned long_count;  // nets of more than kWaveNet pins
+  int pad[3];
 };
 
 // One load workgroup's share of the LoadInfo maxima and sums; the load folds
@@ -137,6 +138,7 @@ struct InstDesc {
   int sweep;                     // NetView that the select reads: view, or sview's kind
   int kept;                      // part8 follows part: this call counted the pins and runs the rounds
   int round_base;                // round r's record goes to stats[r - round_base]
+  int long_count;                // nets of more than kWaveNet pins, in long_list
   long long P, lmax;
   const long long* eptr;
   const int* pins;
@@ -145,6 +147,7 @@ struct InstDesc {
   const long long* vptr;
   const int* vnets;
   const int* heavy_list;
+  const int* long_list;
   int* part;
   int* phi;
   unsigned* netstate;
@@ -286,6 +289,7 @@ struct WsLayout {
   // inside others (see ws_layout)
   size_t lbase;      // load only: bucket starts and write cursors (LoadSplit)
   size_t ctr2;       // late rounds: the second set of counters
+  size_t longs;      // the nets of more than kWaveNet pins
   size_t total;
   int num_tiles;
   int scan_blocks;
@@ -411,6 +415,7 @@ hipError_t fill_i32(int* p, int v, long long count, hipStream_t s);
 
 hipError_t load_check(hg_graph_s* g, hipStream_t s);
 hipError_t load_build(hg_graph_s* g, hipStream_t s);
+hipError_t list_long_nets(hg_graph_s* g, hipStream_t s);   // after load_build
 
 // Gain cache (int32): b(u) at [u], w(I(u)) at [n + u], and the penalty row
 // p_0(u) .. p_{k-1}(u) at [cache_pbase(n) + u * cache_stride(k)], rows padded

@@ -26,9 +26,9 @@ struct PlanLaunch {
 
 // One LP round: select launches (one per kernel variant in a batch), heavy
 // select, per-block kernels (threshold, overflow, tilescan), tiles, approve,
-// finalize launches (one per bitset width), stats.
+// finalize launches (one per bitset width; likewise for long nets), stats.
 struct RoundPlan {
-  std::vector<PlanLaunch> select, heavy, finalize;
+  std::vector<PlanLaunch> select, heavy, finalize, longs;
   PlanLaunch blocks, tiles, approve, stats;
   bool any_heavy = false;
   bool brief = false;       // no threshold, no tile scan (brief_rounds)
@@ -39,20 +39,23 @@ struct RoundPlan {
 // a batch's plan.
 RoundPlan kept_plan(const RoundPlan& plan);
 
-// Pin counts (one launch per bitset width), then the per-instance km1 slot
-// sums, the block-weight reset and sweep.
+// Pin counts (one launch per bitset width; likewise for long nets), then the
+// per-instance km1 slot sums, the block-weight reset and sweep.
 struct CountPlan {
-  std::vector<PlanLaunch> pincounts;
+  std::vector<PlanLaunch> pincounts, longs;
   PlanLaunch instances;     // one workgroup per instance
   PlanLaunch vertices;      // block weights: units of kBwChunk vertices
 };
 
 // Nets per unit of the pin counts: as many as a wavefront counts at a time,
 // fewer where that leaves under eight wavefronts per compute unit (1,510 nets
-// at k = 100: pin counts and gains 50 us with 64, 45 with 8).
-__host__ __device__ inline int count_unit(int k, long long m) {
+// at k = 100: pin counts and gains 50 us with 64, 45 with 8); of long nets fewer
+// still, up to 32 wavefronts while each has 512 pins (200 nets of 300, k = 8: 11.4 us
+// with 1,024 pins, 8.6 so, 6.8 with 256; 10,000 of 300 14.8, 14.2, 17.1).
+__host__ __device__ inline int count_unit(int k, long long m, long long P) {
   int nets = count_nets(k);
   while (nets > 8 && m < 2048LL * nets) nets >>= 1;
+  while (nets > 1 && m < 8192LL * nets && nets / 2 * P >= 512 * m) nets >>= 1;
   return nets * (kBlock / kWave);
 }
 
@@ -63,9 +66,19 @@ SelectKernel select_kernel(int k, int view, long long P, int n);
 // exactly when the descriptor has a cache)
 FinalizeKernel finalize_kernel(int k, bool cache);
 size_t finalize_lds(int k, bool cache);      // its dynamic LDS bytes
-GroupKernel pincount_kernel(int k);          // units of count_unit nets
-size_t pincount_lds(int k, long long m);     // its dynamic LDS bytes
+// The pin-count kernel, the nets of its units (at most kBlock), its dynamic LDS bytes.
+GroupKernel pincount_kernel(int k, long long m, long long P, bool batch);
+int pincount_unit(int k, long long m, long long P, bool batch);
+size_t pincount_lds(int k, long long m, long long P, bool batch);
 GainsKernel gains_kernel(int k, int view);
+// Nets of more than kWaveNet pins (InstDesc::long_list): the kernels of their pin
+// counts and rounds, a single instance's launch (none without such nets), the
+// work items of a batch member, the launches.
+void* long_counts_kernel(int k);
+void* long_round_kernel(int k, bool cache);
+void plan_long(const InstDesc& d, void* kernel, std::vector<PlanLaunch>& out);
+int long_pieces(int long_count);
+void launch_long(const std::vector<PlanLaunch>& plan, hipStream_t s);
 
 // Enqueue one round; the round record goes to stats[round] of every instance.
 hipError_t launch_round(const RoundPlan& plan, int round, hipStream_t s, hipEvent_t* marks);

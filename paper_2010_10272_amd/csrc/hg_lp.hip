@@ -16,7 +16,7 @@
 //              block is resolved by a workgroup-wide prefix sum in vertex
 //              order.  Approved moves are applied right away: part, block
 //              weights, touched nets flagged.
-//   finalize   per touched net: Phi, Lambda, S and lambda counted from its
+//   finalize   per touched net (k_long_nets where it is long): Phi, Lambda, S and lambda counted from its
 //              pins, the attributed km1 change summed from the blocks that
 //              left and entered Lambda (subsection "Attributed Gains"), its
 //              pins made eligible for the next round.
@@ -32,6 +32,7 @@
 #include "hg_bits.h"
 #include "hg_count.h"
 #include "hg_device.h"
+#include "hg_gain_deltas.h"
 #include "hg_internal.h"
 #include "hg_lp.h"
 #include "hg_sweep.h"
@@ -1281,14 +1282,11 @@ __global__ __launch_bounds__(kBlock) void k_approve_apply(Launch L) {
 constexpr int kFinalQueue = 2 * kWave;   // touched nets waiting
 
 // Gain-cache deltas of a batch of nets (subsection "Gain Caching"): the four
-// update rules, summed over all moves of the round, change p_i(v) for every pin
-// v of net e by +w(e) when block i lost its last pin of e and by -w(e) when it
-// gained its first, and b(v) of a pin that did not move (block c) by +w(e) when
-// c now holds exactly one pin of e and by -w(e) when it no longer does.  Moved
-// vertices get b recomputed after the round.  Only nets whose sets changed are
-// walked: `nets` of them, lane i < nets holding pins [b, b + len), their changes
-// in the LDS words `chg`, [word][count_nets]: changed and old Lambda, changed
-// and new S, w(e), b, len.
+// update rules, summed over all moves of the round, for every pin of a net
+// (pin_deltas).  Moved vertices get b recomputed after the round.  Only nets
+// whose sets changed are walked: `nets` of them, lane i < nets holding pins
+// [b, b + len), their changes in the LDS words `chg`, [word][count_nets]: changed
+// and old Lambda, changed and new S, w(e), b, len.
 constexpr __host__ __device__ int cache_nets(int wk) { return wk == 8 ? 32 : kWave; }
 constexpr __host__ __device__ int cache_words(int wk) { return (4 * wk + 3) * cache_nets(wk); }
 
@@ -1296,35 +1294,17 @@ template <int WK>
 __device__ __forceinline__ void cache_deltas(const InstDesc& D, const CountLds& M,
                                              const unsigned* chg, long long b, int len) {
   constexpr int CN = cache_nets(WK);
-  const int ks = cache_stride(D.k);
-  int* cb = D.cache;
-  int* cp = D.cache + cache_pbase(D.n);
   int v[kCountFlight];
   for_pins<false>(
-      D.pins, M, b, len, [&](int pin, int q) { v[q] = pin; },
-      [&](int net, int q) {
-        if (v[q] < 0) return;
-        const int w = (int)chg[4 * WK * CN + net];
-        unsigned any = 0;
+      D.pins, M, b, len,
+      [&](const int (&pins)[kCountFlight]) {
 #pragma unroll
-        for (int x = 0; x < WK; ++x) {
-          unsigned d = chg[x * CN + net];
-          const unsigned old = chg[(WK + x) * CN + net];
-          any |= chg[(2 * WK + x) * CN + net];
-          while (d) {
-            const int bit = __ffs(d) - 1;
-            d &= d - 1;
-            atomicAdd(&cp[(long long)v[q] * ks + x * 32 + bit], ((old >> bit) & 1u) ? w : -w);
-          }
-        }
-        if (any && !D.moved[v[q]]) {
-          const int c = D.part[v[q]];
-          if ((unsigned)c < (unsigned)D.k) {
-            const int x = c >> 5, bit = c & 31;
-            if ((chg[(2 * WK + x) * CN + net] >> bit) & 1u)
-              atomicAdd(&cb[v[q]], ((chg[(3 * WK + x) * CN + net] >> bit) & 1u) ? w : -w);
-          }
-        }
+        for (int q = 0; q < kCountFlight; ++q) v[q] = pins[q];
+      },
+      [&](int net, int q) {
+        if (v[q] >= 0)
+          pin_deltas<WK>(D, v[q], (int)chg[4 * WK * CN + net],
+                         [&](int x) { return chg[x * CN + net]; });
       });
 }
 
@@ -1361,22 +1341,23 @@ __global__ __launch_bounds__(kBlock, !CACHE && WK <= 2 ? 8 : 4) void k_finalize(
   int ntouched = 0, tpins = 0;               // nets and pins: below 2^31
   auto batch = [&](const int* q, int cnt) {
     int len = 0, w = 0, lambda = 0;
+    bool mine = lane < cnt;
     long long e = 0, b = 0;
     unsigned lam[WK], one[WK];
 #pragma unroll
     for (int x = 0; x < WK; ++x) lam[x] = one[x] = 0;
     if (lane < cnt) {
       e = q[lane];
-      b = D.eptr[e];
-      len = (int)(D.eptr[e + 1] - b);
+      b = global_ptr(D.eptr)[e];
+      len = (int)(global_ptr(D.eptr)[e + 1] - b);
       read_record<WK>(D, e, w, lambda, lam, one);
-      D.touched[e] = 0;
+      mine = len <= kWaveNet;
+      if (mine) global_out(D.touched)[e] = 0;   // the others: k_long_nets
     }
     NetSets<WK> N;
-    count_batch<WK, false>(
-        D, M, e, b, len, cnt, vec_phi, block, [&](int v) { D.eligible[v] = 1; }, N);
+    count_batch<WK, false>(D, M, e, b, len, vec_phi, block, EligiblePins{D.eligible}, N);
     bool changed = false;
-    if (lane < cnt) {
+    if (mine) {
       write_record<WK, false>(D, e, w, N.lambda, N.lam, N.one);
       int left = 0;
 #pragma unroll
@@ -1417,7 +1398,7 @@ __global__ __launch_bounds__(kBlock, !CACHE && WK <= 2 ? 8 : 4) void k_finalize(
   // m are zero up to a whole block)
   auto flag_at = [&](int it) {
     const long long c = (long long)wi.first + (long long)it * wi.stride;
-    return it < wi.count ? D.touched[c * kFinalChunk + threadIdx.x] : (unsigned char)0;
+    return it < wi.count ? global_ptr(D.touched)[c * kFinalChunk + threadIdx.x] : (unsigned char)0;
   };
   unsigned char next = flag_at(0);
   int qn = 0;                                              // nets queued (wave-uniform)
@@ -1559,6 +1540,7 @@ hipError_t launch_round_finalize(const RoundPlan& plan, hipStream_t s, hipEvent_
   if (marks) (void)hipEventRecord(marks[2], s);
   for (const PlanLaunch& pl : plan.finalize)
     hipLaunchKernelGGL((FinalizeKernel)pl.kernel, dim3(pl.grid), dim3(kBlock), pl.lds, s, pl.L);
+  launch_long(plan.longs, s);
   return hipGetLastError();
 }
 
@@ -1601,6 +1583,7 @@ void single_round_plan(const InstDesc& d, RoundPlan& plan) {
   fin.grid = (unsigned)(fchunks < kFinalizeGrid ? fchunks : kFinalizeGrid) + (d.late ? 1 : 0);
   fin.L = L;
   plan.finalize.push_back(fin);
+  plan_long(d, long_round_kernel(d.k, d.cache != nullptr), plan.longs);
   plan.stats.grid = 1;
   plan.stats.L = L;
 }

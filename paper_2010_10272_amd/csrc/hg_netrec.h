@@ -54,7 +54,7 @@ __device__ __forceinline__ void write_record(const InstDesc& D, long long e, int
     r[2 + i] = lam[i];
     r[2 + WK + i] = one[i];
   }
-  u32x4* rec = reinterpret_cast<u32x4*>(D.netstate + e * RW);
+  const auto rec = global_out(reinterpret_cast<u32x4*>(D.netstate + e * RW));
 #pragma unroll
   for (int i = 0; i < RW / 4; ++i) {
     const u32x4 q = {r[4 * i], r[4 * i + 1], r[4 * i + 2], r[4 * i + 3]};
@@ -62,23 +62,24 @@ __device__ __forceinline__ void write_record(const InstDesc& D, long long e, int
   }
   if constexpr (WK == 1) {
     if (D.view == kView16) {
-      D.view_ptr[e] = (lam[0] & 0xffffu) | (one[0] << 16);
+      global_out(D.view_ptr)[e] = (lam[0] & 0xffffu) | (one[0] << 16);
       if (D.sweep == kView8)
-        reinterpret_cast<unsigned short*>(D.sview)[e] = (unsigned short)(lam[0] | (one[0] << 8));
+        global_out(reinterpret_cast<unsigned short*>(D.sview))[e] =
+            (unsigned short)(lam[0] | (one[0] << 8));
       else if (D.sweep == kView4)
-        D.sview[e] = (unsigned char)(lam[0] | (one[0] << 4));
+        global_out(D.sview)[e] = (unsigned char)(lam[0] | (one[0] << 4));
       return;
     }
     if (D.view == kView32) {
       const u32x2 q = {lam[0], one[0]};
-      *reinterpret_cast<u32x2*>(D.view_ptr + 2 * e) = q;
+      *global_out(reinterpret_cast<u32x2*>(D.view_ptr + 2 * e)) = q;
       return;
     }
   }
   if constexpr (WK == 2) {
     if (D.view == kView64) {
       const u32x4 q = {lam[0], lam[1], one[0], one[1]};
-      *reinterpret_cast<u32x4*>(D.view_ptr + 4 * e) = q;
+      *global_out(reinterpret_cast<u32x4*>(D.view_ptr + 4 * e)) = q;
       return;
     }
   }

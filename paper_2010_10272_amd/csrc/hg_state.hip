@@ -49,11 +49,11 @@ template <int WK>
 __global__ __launch_bounds__(kBlock) void k_pincounts(Launch L) {
   extern __shared__ unsigned s_count[];   // count_words per wavefront
   __shared__ long long s_km1;
-  const WorkItem wi = work_item(L, contiguous_units(units_of(L.one.m, count_unit(L.one.k, L.one.m))));
+  const WorkItem wi = work_item(L, contiguous_units(units_of(L.one.m, count_unit(L.one.k, L.one.m, L.one.P))));
   if (wi.count == 0) return;
   const InstDesc D = inst_desc(L, wi.inst);
   const int k = D.k, m = D.m;
-  const int unit_nets = count_unit(k, m), NW = unit_nets / (kBlock / kWave);
+  const int unit_nets = count_unit(k, m, D.P), NW = unit_nets / (kBlock / kWave);
   const int lane = lane_id(), wv = threadIdx.x / kWave;
   const CountLds M = count_lds(s_count + (size_t)wv * count_words(k, NW), k, NW);
   const Blocks block = blocks_of(D, true);
@@ -72,8 +72,8 @@ __global__ __launch_bounds__(kBlock) void k_pincounts(Launch L) {
   auto load_range = [&](long long e0) {
     nb = nt = 0;
     if (lane < NW && e0 + lane < m) {
-      nb = D.eptr[e0 + lane];
-      nt = D.eptr[e0 + lane + 1];
+      nb = global_ptr(D.eptr)[e0 + lane];
+      nt = global_ptr(D.eptr)[e0 + lane + 1];
     }
   };
   load_range(first_net(0));
@@ -83,12 +83,105 @@ __global__ __launch_bounds__(kBlock) void k_pincounts(Launch L) {
     const int len = (int)(nt - nb);
     load_range(first_net(it + 1));
     if (e0 >= m) continue;                                  // the same for the whole wave
-    const int nets = m - e0 < NW ? (int)(m - e0) : NW;
     const long long e = e0 + lane;
     NetSets<WK> N;
-    count_batch<WK, true>(D, M, e, b, len, nets, vec_phi, block, [](int) {}, N);
-    if (lane < nets) {
-      const int w = D.ewgt ? D.ewgt[e] : 1;
+    count_batch<WK, true>(D, M, e, b, len, vec_phi, block,
+                          [](const int (&)[kCountFlight]) {}, N);
+    if (len > 0 && len <= kWaveNet) {                       // longer: k_long_nets
+      const int w = D.ewgt ? global_ptr(D.ewgt)[e] : 1;
+      write_record<WK, true>(D, e, w, N.lambda, N.lam, N.one);
+      km1_local += (long long)(N.lambda - 1) * w;
+    }
+  }
+  km1_local = wave_sum(km1_local);
+  if (lane == 0 && km1_local) atomicAdd((unsigned long long*)&s_km1, (unsigned long long)km1_local);
+  __syncthreads();
+  if (threadIdx.x == 0 && s_km1)
+    atomicAdd(&D.red[blockIdx.x % kSlots], (unsigned long long)s_km1);
+}
+
+// The same where nets are long on average (group_counts): kGroupLanes lanes a net,
+// eight nets a wavefront, 32-bit counters.  A net's pins are consecutive, so no
+// place has to look for its net, and few registers keep many wavefronts in flight;
+// short nets would leave most lanes idle.
+// Unit: kGroupUnit consecutive nets.
+constexpr int kGroupLanes = 8;
+constexpr int kGroupNets = kWave / kGroupLanes;
+constexpr int kGroupUnit = kBlock / kGroupLanes;
+
+template <int WK>
+__global__ __launch_bounds__(kBlock) void k_pincounts_groups(Launch L) {
+  extern __shared__ unsigned s_count[];   // kGroupUnit * (k | 1)
+  __shared__ long long s_km1;
+  const WorkItem wi = work_item(L, contiguous_units(units_of(L.one.m, kGroupUnit)));
+  if (wi.count == 0) return;
+  const InstDesc D = inst_desc(L, wi.inst);
+  const int k = D.k, ks = k | 1, m = D.m;
+  const int lane = lane_id(), wv = threadIdx.x / kWave;
+  const int grp = lane / kGroupLanes, gl = lane % kGroupLanes;
+  unsigned* cnt = s_count + wv * kGroupNets * ks;         // the wavefront's
+  for (int i = lane; i < kGroupNets * ks; i += kWave) cnt[i] = 0;
+  const Blocks block = blocks_of(D, true);
+  const auto pins = global_ptr(D.pins);
+  if (threadIdx.x == 0) s_km1 = 0;
+  __syncthreads();
+  long long km1_local = 0, b = 0, t = 0;
+  // the next net's range is loaded while this one's pins are counted
+  auto net_at = [&](int it) {
+    return ((long long)wi.first + (long long)it * wi.stride) * kGroupUnit + wv * kGroupNets + grp;
+  };
+  auto load_range = [&](int it) {
+    b = t = 0;
+    if (it < wi.count && net_at(it) < m) {
+      b = global_ptr(D.eptr)[net_at(it)];
+      t = global_ptr(D.eptr)[net_at(it) + 1];
+    }
+  };
+  load_range(0);
+  for (int it = 0; it < wi.count; ++it) {
+    const long long e = net_at(it), at = b;
+    const int len = t - b <= kWaveNet ? (int)(t - b) : 0;  // longer: k_long_nets
+    load_range(it + 1);
+    for (int s = gl; s < len; s += kCountFlight * kGroupLanes) {
+      int v[kCountFlight];
+      unsigned id[kCountFlight];
+#pragma unroll
+      for (int q = 0; q < kCountFlight; ++q) {
+        const int p = s + q * kGroupLanes;
+        v[q] = pins[at + (p < len ? p : s)];
+      }
+      block(v, id);
+#pragma unroll
+      for (int q = 0; q < kCountFlight; ++q)
+        if (s + q * kGroupLanes < len && id[q] < (unsigned)k)
+          atomicAdd(&cnt[grp * ks + (int)id[q]], 1u);
+    }
+    wave_lds_sync();
+    NetSets<WK> N;
+    N.lambda = 0;
+#pragma unroll
+    for (int w = 0; w < WK; ++w) N.lam[w] = N.one[w] = 0;
+    const unsigned long long there = __ballot(len > 0);
+#pragma unroll
+    for (int r = 0; r < kGroupNets; ++r) {
+      const int owner = r * kGroupLanes;
+      if (!((there >> owner) & 1ull)) continue;
+      const long long phi_row = lane_value(e, owner) * k;
+#pragma unroll
+      for (int h = 0; h < WK; h += 2) {
+        const int i = h * 32 + lane;
+        int x = 0;
+        if (i < k) {
+          x = (int)cnt[r * ks + i];
+          cnt[r * ks + i] = 0;             // for the next nets
+          global_out(D.phi)[phi_row + i] = x;
+        }
+        set_words<WK>(N, h, __ballot(x != 0), __ballot(x == 1), lane == owner);
+      }
+    }
+    wave_lds_sync();
+    if (gl == 0 && len > 0) {
+      const int w = D.ewgt ? global_ptr(D.ewgt)[e] : 1;
       write_record<WK, true>(D, e, w, N.lambda, N.lam, N.one);
       km1_local += (long long)(N.lambda - 1) * w;
     }
@@ -246,12 +339,33 @@ static unsigned grid_cap(long long items, int per_block, int cap) {
   return (unsigned)b;
 }
 
-size_t pincount_lds(int k, long long m) {
-  const int nets = count_unit(k, m) / (kBlock / kWave);
+// Lane groups for up to 64 blocks and nets of more than 255 pins on average, or of 64
+// where the nets are too few to fill the chip, 64 a wavefront; but not for a few
+// thousand nets, which then get a wavefront each.  n = 100,000, us, k_pincounts and
+// k_pincounts_groups: 100,000 nets of 300, k = 8 86 / 52, k = 64 109 / 73; 30,000 of
+// 100, k = 8 14.4 / 11.2, k = 64 19.5 / 14.3; but 300,000 of 100, k = 64 121 / 124,
+// k = 200 144 / 248; 150,000 of 64, k = 8 33 / 40; 2,100 of 300 9.6 / 12.3.
+// A batch gives a workgroup 256 nets whatever their length: there from 64 pins on
+// (16 members of 200 nets of 300, k = 8, 93 / 38).
+static bool group_counts(int k, long long m, long long P, bool batch) {
+  if (batch) return k <= 64 && P >= 64 * m;
+  return k <= 64 && m >= 4096 && (P > 255 * m || (P >= 64 * m && m < (1 << 16)));
+}
+
+int pincount_unit(int k, long long m, long long P, bool batch) {
+  return group_counts(k, m, P, batch) ? kGroupUnit : count_unit(k, m, P);
+}
+
+size_t pincount_lds(int k, long long m, long long P, bool batch) {
+  if (group_counts(k, m, P, batch)) return sizeof(unsigned) * kGroupUnit * (size_t)(k | 1);
+  const int nets = count_unit(k, m, P) / (kBlock / kWave);
   return sizeof(unsigned) * (size_t)(kBlock / kWave) * count_words(k, nets);
 }
 
-GroupKernel pincount_kernel(int k) {
+GroupKernel pincount_kernel(int k, long long m, long long P, bool batch) {
+  if (group_counts(k, m, P, batch)) {
+    return bit_words(k) == 1 ? k_pincounts_groups<1> : k_pincounts_groups<2>;
+  }
   switch (bit_words(k)) {
     case 1: return k_pincounts<1>;
     case 2: return k_pincounts<2>;
@@ -264,11 +378,12 @@ void single_count_plan(const InstDesc& d, CountPlan& plan) {
   plan = CountPlan();
   const Launch L = single_launch(d);
   PlanLaunch pc;
-  pc.kernel = (void*)pincount_kernel(d.k);
-  pc.grid = grid_cap(d.m, count_unit(d.k, d.m), kStateGrid);
-  pc.lds = pincount_lds(d.k, d.m);
+  pc.kernel = (void*)pincount_kernel(d.k, d.m, d.P, false);
+  pc.grid = grid_cap(d.m, pincount_unit(d.k, d.m, d.P, false), kStateGrid);
+  pc.lds = pincount_lds(d.k, d.m, d.P, false);
   pc.L = L;
   plan.pincounts.push_back(pc);
+  plan_long(d, long_counts_kernel(d.k), plan.longs);
   plan.instances.grid = 1;
   plan.instances.L = L;
   plan.vertices.grid = grid_cap(d.n, kBwChunk, 4096);
@@ -282,6 +397,7 @@ hipError_t launch_counts(const CountPlan& plan, bool want_km1, bool mark_eligibl
                      plan.vertices.L, mark_eligible ? 1 : 0);
   for (const PlanLaunch& pl : plan.pincounts)
     hipLaunchKernelGGL((GroupKernel)pl.kernel, dim3(pl.grid), dim3(kBlock), pl.lds, s, pl.L);
+  launch_long(plan.longs, s);
   hipLaunchKernelGGL(k_count_epilogue, dim3(plan.instances.grid), dim3(kBlock), 0, s,
                      plan.instances.L, want_km1 ? 1 : 0);
   return hipGetLastError();
