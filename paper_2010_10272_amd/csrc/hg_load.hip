@@ -687,24 +687,145 @@ __device__ __forceinline__ bool sort_row(int* row, int d) {
   return dup;
 }
 
+constexpr int kWaveRow = 128;                            // longest row of one wavefront
+constexpr int kBigRows = kBucketCap / (kWaveRow + 1) + 1;
+
+// A bucket's rows of more than kWaveRow nets, as many together as the bits of a word
+// can tell apart (32 and more): a radix sort of (row, net) words by the workgroup,
+// each thread's words in registers, `sorted` (LDS) between the passes.  Bound by the
+// chain of a wavefront's groups of 64 through its digit counters.  (Row after row by
+// a bitonic sort, a load of 100,000 vertices took 304 us with 15 vertices in 600 nets
+// each, 286 with one in 9,500; 138 and 151 so, 107 without such rows, about 160 by
+// radix passes over all pins.  Ranked by a wavefront each, 18 rows of 450 nets made
+// a load of 120 us one of 320.)
+struct BigRows {
+  unsigned short row[kBigRows];                          // the rows
+  unsigned at[kBigRows + 1];                             // first word of each
+};
+
+template <int PER>
+struct RowWords {
+  unsigned word[PER];
+  int per;                                               // in use: a wave holds per * kWave words
+};
+
+__device__ __forceinline__ int word_at(int per, int r) {
+  return ((int)(threadIdx.x / kWave) * per + r) * kWave + lane_id();
+}
+
+// The T words of rows [first, last) of B, from the unsorted rows.  Every thread calls.
+template <int PER>
+__device__ __forceinline__ void load_big_rows(RowWords<PER>& W, const BigRows& B, int first,
+                                              int last, int T, const int* rows,
+                                              const unsigned* start, int net_bits) {
+  W.per = (T + kRowsBlock - 1) / kRowsBlock;
+  const int zero = (int)B.at[first];
+  // a group of 64 words lies in at most two rows
+  int i = first;
+#pragma unroll
+  for (int r = 0; r < PER; ++r) {
+    W.word[r] = 0xffffffffu;
+    if (r < W.per) {
+      const int base = word_at(W.per, r) - lane_id();
+      while (i + 1 < last && (int)B.at[i + 1] - zero <= base) ++i;
+      const int p = base + lane_id();
+      if (p < T) {
+        const int mine = i + (i + 1 < last && (int)B.at[i + 1] - zero <= p ? 1 : 0);
+        W.word[r] = ((unsigned)(mine - first) << net_bits) |
+                    (unsigned)rows[start[B.row[mine]] + (unsigned)(p + zero) - B.at[mine]];
+      }
+    }
+  }
+}
+
+// Sorts them into `sorted`.  cnt: [kRowsWaves][256], wsum: [kRowsWaves], of LDS.
+template <int PER>
+__device__ __forceinline__ void sort_big_rows(RowWords<PER>& W, int T, int bits, unsigned* sorted,
+                                              unsigned short* cnt, unsigned* wsum) {
+  const int wv = threadIdx.x / kWave, lane = lane_id(), tid = threadIdx.x;
+  unsigned short* mine = cnt + wv * kDigits;
+  // passes of equal width
+  const int passes = (bits + 7) / 8, width = (bits + passes - 1) / passes;
+  const unsigned mask = (1u << width) - 1u;
+  for (int shift = 0; shift < bits; shift += width) {
+    for (int i = lane; i < kDigits; i += kWave) mine[i] = 0;
+    wave_lds_sync();
+    unsigned short off[PER];
+#pragma unroll
+    for (int r = 0; r < PER; ++r) {
+      if (r >= W.per) break;
+      const bool live = word_at(W.per, r) < T;
+      const unsigned d = (W.word[r] >> shift) & mask;
+      unsigned long long peers = __ballot(live);
+#pragma unroll
+      for (int bit = 0; bit < 8; ++bit) {
+        if (bit >= width) break;
+        const unsigned long long ones = __ballot((d >> bit) & 1u);
+        peers &= (d >> bit) & 1u ? ones : ~ones;
+      }
+      const unsigned before = mine[d];
+      const int rank = lanes_below(peers, 0);
+      wave_lds_sync();
+      if (live && rank == 0) mine[d] = (unsigned short)(before + (unsigned)__popcll(peers));
+      wave_lds_sync();
+      off[r] = (unsigned short)(before + (unsigned)rank);
+    }
+    __syncthreads();
+    // counts -> the first place of every wave's words of every digit
+    unsigned all = 0, incl = 0;
+    if (tid < kDigits) {
+      for (int w = 0; w < kRowsWaves; ++w) all += cnt[w * kDigits + tid];
+      incl = (unsigned)wave_incl_scan((int)all);
+      if (lane == kWave - 1) wsum[wv] = incl;
+    }
+    __syncthreads();
+    if (tid < kDigits) {
+      unsigned at = incl - all;
+      for (int w = 0; w < wv; ++w) at += wsum[w];
+      for (int w = 0; w < kRowsWaves; ++w) {
+        const unsigned c = cnt[w * kDigits + tid];
+        cnt[w * kDigits + tid] = (unsigned short)at;
+        at += c;
+      }
+    }
+    __syncthreads();
+#pragma unroll
+    for (int r = 0; r < PER; ++r) {
+      if (r >= W.per) break;
+      if (word_at(W.per, r) < T)
+        sorted[mine[(W.word[r] >> shift) & mask] + off[r]] = W.word[r];
+    }
+    __syncthreads();
+    if (shift + width < bits) {
+#pragma unroll
+      for (int r = 0; r < PER; ++r) {
+        if (r >= W.per) break;
+        if (word_at(W.per, r) < T) W.word[r] = sorted[word_at(W.per, r)];
+      }
+      __syncthreads();
+    }
+  }
+}
+
 // One workgroup per bucket: row starts from a count of its pins per vertex,
 // the nets placed in their rows in LDS in any order, then every row sorted
 // (rows of up to 16 and of up to 32 nets by one thread in registers, each
-// kind in wavefronts of its own; rows of up to 512 by one wavefront ranking
-// its entries; longer ones by the workgroup) and the bucket written out.  A
-// vertex twice in a net shows as two equal neighbours.
-__global__ __launch_bounds__(kRowsBlock) void k_bucket_rows(Split S) {
+// kind in wavefronts of its own; rows of up to 128 by one wavefront ranking
+// its entries; all longer ones together by the workgroup) and the bucket written
+// out.  A vertex twice in a net shows as two equal neighbours.
+__global__ __launch_bounds__(kRowsBlock, 6) void k_bucket_rows(Split S) {
   constexpr int kV = 1 << kMaxShift;
   constexpr int kVPer = kV / kRowsBlock;                   // 2
   constexpr int kPer = kBucketCap / kRowsBlock;            // pins per thread
-  constexpr int kWaveRow = 512;                            // longest row of one wavefront
   __shared__ int s_row[kBucketCap];
   __shared__ unsigned s_start[kV + 1];
   __shared__ unsigned s_cur[kV];                           // counts, then write positions
   __shared__ unsigned short s_short[kV];                   // rows of 2..16, and 17..32 from the back
   __shared__ unsigned short s_long[kBucketCap / 33 + 1];
+  __shared__ BigRows s_big;
   __shared__ unsigned s_wsum[kRowsWaves];
-  __shared__ unsigned s_n16, s_n32, s_nlong;
+  __shared__ unsigned s_n16, s_n32, s_nlong, s_nbig;
+  static_assert(sizeof(s_cur) == sizeof(unsigned short) * kRowsWaves * kDigits, "digit counts");
   const int V = 1 << S.L.shift;
   const int b = blockIdx.x;
   const unsigned from = bucket_start(S, b);
@@ -712,7 +833,7 @@ __global__ __launch_bounds__(kRowsBlock) void k_bucket_rows(Split S) {
   const int v0 = b << S.L.shift;
   const int nv = S.n - v0 < V ? S.n - v0 : V;
   for (int i = threadIdx.x; i < kV; i += kRowsBlock) s_cur[i] = 0;
-  if (threadIdx.x == 0) s_n16 = s_n32 = s_nlong = 0;
+  if (threadIdx.x == 0) s_n16 = s_n32 = s_nlong = s_nbig = 0;
   __syncthreads();
   // the whole bucket requested before the first wait
   const unsigned short* low = S.low + from;
@@ -754,7 +875,8 @@ __global__ __launch_bounds__(kRowsBlock) void k_bucket_rows(Split S) {
     for (int q = 0; q < kVPer; ++q) {
       const unsigned d = q ? c : a;
       const int r = i0 + q;
-      if (d > 32) s_long[atomicAdd(&s_nlong, 1u)] = (unsigned short)r;
+      if (d > kWaveRow) s_big.row[atomicAdd(&s_nbig, 1u)] = (unsigned short)r;
+      else if (d > 32) s_long[atomicAdd(&s_nlong, 1u)] = (unsigned short)r;
       else if (d > 16) s_short[kV - 1 - atomicAdd(&s_n32, 1u)] = (unsigned short)r;
       else if (d > 1) s_short[atomicAdd(&s_n16, 1u)] = (unsigned short)r;
     }
@@ -765,7 +887,7 @@ __global__ __launch_bounds__(kRowsBlock) void k_bucket_rows(Split S) {
     if (q * kRowsBlock + (int)threadIdx.x < N) s_row[atomicAdd(&s_cur[lv[q]], 1u)] = net[q];
   __syncthreads();
   bool dup = false;
-  const int n16 = (int)s_n16, n32 = (int)s_n32, nlong = (int)s_nlong;
+  const int n16 = (int)s_n16, n32 = (int)s_n32, nlong = (int)s_nlong, nbig = (int)s_nbig;
   for (int i = threadIdx.x; i < n16; i += kRowsBlock) {
     const int r = s_short[i];
     dup |= sort_row<16>(s_row + s_start[r], (int)(s_start[r + 1] - s_start[r]));
@@ -777,7 +899,6 @@ __global__ __launch_bounds__(kRowsBlock) void k_bucket_rows(Split S) {
   for (int i = wv; i < nlong; i += kRowsWaves) {
     const int r = s_long[i];
     const int d = (int)(s_start[r + 1] - s_start[r]);
-    if (d > kWaveRow) continue;
     int* row = s_row + s_start[r];
     // every lane ranks its entries among the row's (equal entries by place)
     int x[kWaveRow / kWave], rank[kWaveRow / kWave];
@@ -803,19 +924,41 @@ __global__ __launch_bounds__(kRowsBlock) void k_bucket_rows(Split S) {
     wave_lds_sync();
   }
   __syncthreads();
-  for (int i = 0; i < nlong; ++i) {                        // the same rows for every thread
-    const int r = s_long[i];
-    const int d = (int)(s_start[r + 1] - s_start[r]);
-    if (d <= kWaveRow) continue;
-    int* row = s_row + s_start[r];
-    int pow2 = 1;
-    while (pow2 < d) pow2 <<= 1;
-    bitonic_sort_block(d, pow2, [&](int j) { return row[j]; }, [&](int j, int x) { row[j] = x; });
-    for (int j = 1 + threadIdx.x; j < d; j += kRowsBlock) dup |= row[j] == row[j - 1];
+  // the rows that are done leave, and the long ones as they are: these are read back
+  // and take the LDS
+  for (int i = threadIdx.x; i < N; i += kRowsBlock) val[i] = s_row[i];
+  if (nbig > 0) {
+    const int net_bits = S.m > 1 ? 32 - __clz(S.m - 1) : 1;   // net ids are below 2^net_bits
+    if (wv == 0) {                                         // first words, two rows per lane
+      const int i0 = 2 * lane, i1 = i0 + 1;
+      const int r0 = i0 < nbig ? s_big.row[i0] : 0, r1 = i1 < nbig ? s_big.row[i1] : 0;
+      const int d0 = i0 < nbig ? (int)(s_start[r0 + 1] - s_start[r0]) : 0;
+      const int d1 = i1 < nbig ? (int)(s_start[r1 + 1] - s_start[r1]) : 0;
+      const int incl = wave_incl_scan(d0 + d1);
+      if (i0 <= nbig) s_big.at[i0] = (unsigned)(incl - d0 - d1);
+      if (i1 <= nbig) s_big.at[i1] = (unsigned)(incl - d1);
+    }
     __syncthreads();
+    const int together = net_bits > 25 ? 1 << (32 - net_bits) : kBigRows;
+    const unsigned net_mask = (1u << net_bits) - 1u;
+    unsigned* sorted = reinterpret_cast<unsigned*>(s_row);
+    for (int first = 0; first < nbig; first += together) {
+      const int last = first + together < nbig ? first + together : nbig;
+      const int T = (int)(s_big.at[last] - s_big.at[first]);
+      RowWords<kPer> W;
+      load_big_rows(W, s_big, first, last, T, val, s_start, net_bits);
+      sort_big_rows(W, T, net_bits + 32 - __clz(last - first - 1), sorted,
+                    reinterpret_cast<unsigned short*>(s_cur), s_wsum);
+      for (int p = threadIdx.x; p < T; p += kRowsBlock) {
+        const unsigned x = sorted[p], r = first + (x >> net_bits);
+        dup |= p > 0 && x == sorted[p - 1];
+        val[s_start[s_big.row[r]] + (unsigned)p + s_big.at[first] - s_big.at[r]] =
+            (int)(x & net_mask);
+      }
+      __syncthreads();                                     // before `sorted` is filled again
+    }
   }
   if (dup) atomicOr(&S.info->err, kErrDuplicate);
-  for (int i = threadIdx.x; i < N; i += kRowsBlock) val[i] = s_row[i];
 }
 
 static Split make_split(hg_graph_s* g) {

@@ -53,6 +53,13 @@ CASES = {
     # rows on both sides of every class: 16, 32, 512
     "row-classes": lambda: (3000, *rows_of_degrees(3000, [16, 17, 32, 33, 64, 65, 511, 512, 513,
                                                           1500], 2000, 5)),
+    # rows on both sides of what a wavefront ranks, alone, many in a bucket, and more
+    # of them than a bucket can hold of the next class
+    "row-128": lambda: (3000, *rows_of_degrees(3000, [127, 128, 129, 130, 255, 256, 257], 900, 10)),
+    "row-many-129": lambda: (2500, *rows_of_degrees(2500, [129] * 70, 4000, 11)),
+    "row-many-600": lambda: (3000, *rows_of_degrees(3000, [600] * 15, 5000, 12)),
+    "row-9500": lambda: (40_000, *rows_of_degrees(40_000, [9500], 12_000, 13)),
+    "row-two-thirds": lambda: (300, *rows_of_degrees(300, [4000, 2, 4900], 5000, 14)),
     # a vertex in 30,000 nets: no bucket holds it, the radix sort takes over
     "hub": lambda: (9000, *rows_of_degrees(9000, [30_000], 30_000, 6)),
     # long nets across tiles, and more than one coarse range of 64 buckets
@@ -86,3 +93,42 @@ def test_repeated_pin_rejected(H, degree):
     eptr = eptr + (np.arange(eptr.size) > e)
     with pytest.raises(H.HgError, match="twice"):
         H.hg_load_csr(2000, eptr, pins, k_max=2)
+
+
+@pytest.mark.parametrize("degree", [128, 129, 200, 1400])
+@pytest.mark.parametrize("others", [0, 40])
+def test_repeated_pin_rejected_in_long_rows(H, degree, others):
+    """The same in the rows that a workgroup sorts together."""
+    eptr, pins = rows_of_degrees(2000, [degree - 1] + [150] * others, 1500, degree)
+    e = int(np.searchsorted(eptr, np.nonzero(pins == 0)[0][0], side="right") - 1)
+    pins = np.insert(pins, eptr[e], 0)
+    eptr = eptr + (np.arange(eptr.size) > e)
+    with pytest.raises(H.HgError, match="twice"):
+        H.hg_load_csr(2000, eptr, pins, k_max=2)
+
+
+# Two fifths more than the load without such rows: what sorting a bucket's pins in one
+# workgroup may add to a load that all workgroups share.  (Row after row, or a
+# wavefront a row, they took one and a half to four times the load.)
+@pytest.mark.parametrize("degrees", [[200] * 40, [450] * 18, [600] * 15],
+                         ids=["40x200", "18x450", "15x600"])
+def test_time_of_long_rows(H, degrees):
+    import torch
+    n, m, ms = 100_000, 100_000, []
+    for degs in (degrees, []):
+        eptr, pins = rows_of_degrees(n, degs, m, 7)
+        ep, pn = torch.from_numpy(eptr).cuda(), torch.from_numpy(pins).cuda()
+        out = (torch.empty(n + 1, dtype=torch.int64, device="cuda"),
+               torch.empty(pins.size, dtype=torch.int32, device="cuda"),
+               torch.empty(H.hg_workspace_size(n, m, pins.size, 2), dtype=torch.uint8,
+                           device="cuda"))
+        best = float("inf")
+        for _ in range(15):
+            ev = [torch.cuda.Event(enable_timing=True) for _ in range(2)]
+            ev[0].record()
+            H.hg_load_csr(n, ep, pn, k_max=2, out=out)
+            ev[1].record()
+            ev[1].synchronize()
+            best = min(best, ev[0].elapsed_time(ev[1]))
+        ms.append(best)
+    assert ms[0] < 1.4 * ms[1], ms
