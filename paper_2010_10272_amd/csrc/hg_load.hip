@@ -691,13 +691,16 @@ constexpr int kWaveRow = 128;                            // longest row of one w
 constexpr int kBigRows = kBucketCap / (kWaveRow + 1) + 1;
 
 // A bucket's rows of more than kWaveRow nets, as many together as the bits of a word
-// can tell apart (32 and more): a radix sort of (row, net) words by the workgroup,
-// each thread's words in registers, `sorted` (LDS) between the passes.  Bound by the
-// chain of a wavefront's groups of 64 through its digit counters.  (Row after row by
-// a bitonic sort, a load of 100,000 vertices took 304 us with 15 vertices in 600 nets
-// each, 286 with one in 9,500; 138 and 151 so, 107 without such rows, about 160 by
-// radix passes over all pins.  Ranked by a wavefront each, 18 rows of 450 nets made
-// a load of 120 us one of 320.)
+// can tell apart (32 and more): (row, net) words, each thread's in registers.  A
+// word's place is guessed from the row's length, as if its nets were spread evenly;
+// words of neighbouring places share a bin of kBinPlaces, a thread sorts a bin
+// (spread_big_rows).  Where a bin overflows, the words are sorted by radix passes
+// (radix_big_rows), bound by the chain of a wavefront's groups of 64 through its
+// digit counters.  (Row after row by a bitonic sort, a load of 100,000 vertices took
+// 304 us with 15 vertices in 600 nets each, 286 with one in 9,500; by radix passes
+// 138 and 151, 131 and 140 so; 104 without such rows, about 160 by radix passes over
+// all pins.  Ranked by a wavefront each, 18 rows of 450 nets made a load of 120 us
+// one of 320.)
 struct BigRows {
   unsigned short row[kBigRows];                          // the rows
   unsigned at[kBigRows + 1];                             // first word of each
@@ -740,7 +743,7 @@ __device__ __forceinline__ void load_big_rows(RowWords<PER>& W, const BigRows& B
 
 // Sorts them into `sorted`.  cnt: [kRowsWaves][256], wsum: [kRowsWaves], of LDS.
 template <int PER>
-__device__ __forceinline__ void sort_big_rows(RowWords<PER>& W, int T, int bits, unsigned* sorted,
+__device__ __forceinline__ void radix_big_rows(RowWords<PER>& W, int T, int bits, unsigned* sorted,
                                               unsigned short* cnt, unsigned* wsum) {
   const int wv = threadIdx.x / kWave, lane = lane_id(), tid = threadIdx.x;
   unsigned short* mine = cnt + wv * kDigits;
@@ -805,6 +808,58 @@ __device__ __forceinline__ void sort_big_rows(RowWords<PER>& W, int T, int bits,
       __syncthreads();
     }
   }
+}
+
+constexpr int kBinPlaces = 10;
+constexpr int kBinMost = 32;                             // words that a thread sorts
+constexpr int kBins = 1 << kMaxShift;                    // two per thread
+static_assert(kBucketCap <= kBins * kBinPlaces && kBins == 2 * kRowsBlock, "bins");
+
+// The same by bins; false (and nothing sorted) where a bin would not fit.  bin:
+// [kBins] and wsum: [kRowsWaves] of LDS.
+template <int PER>
+__device__ __forceinline__ bool spread_big_rows(const RowWords<PER>& W, const BigRows& B, int first,
+                                                int T, int m, int net_bits, int* sorted,
+                                                unsigned* bin, unsigned* wsum) {
+  const int wv = threadIdx.x / kWave, lane = lane_id(), tid = threadIdx.x;
+  const unsigned net_mask = (1u << net_bits) - 1u;
+  // (a product in floats grows with the net, which is all that a bin needs)
+  auto bin_of = [&](unsigned word) {
+    const int row = first + (int)(word >> net_bits);
+    const int from = (int)(B.at[row] - B.at[first]), d = (int)(B.at[row + 1] - B.at[row]);
+    const int guess = (int)((float)(word & net_mask) * ((float)d / (float)m));
+    return (from + (guess < d ? guess : d - 1)) / kBinPlaces;
+  };
+  bin[tid] = bin[tid + kRowsBlock] = 0;
+  __syncthreads();
+#pragma unroll
+  for (int r = 0; r < PER; ++r)
+    if (r < W.per && word_at(W.per, r) < T) atomicAdd(&bin[bin_of(W.word[r])], 1u);
+  __syncthreads();
+  const unsigned a = bin[2 * tid], c = bin[2 * tid + 1];
+  const int incl = wave_incl_scan((int)(a + c));
+  if (lane == kWave - 1) wsum[wv] = (unsigned)incl;
+  if (__syncthreads_or(a > kBinMost || c > kBinMost)) return false;
+  unsigned st = (unsigned)incl - a - c;
+  for (int w = 0; w < wv; ++w) st += wsum[w];
+  bin[2 * tid] = st;
+  bin[2 * tid + 1] = st + a;
+  __syncthreads();
+  // (as signed numbers, which sort_row compares)
+#pragma unroll
+  for (int r = 0; r < PER; ++r)
+    if (r < W.per && word_at(W.per, r) < T)
+      sorted[atomicAdd(&bin[bin_of(W.word[r])], 1u)] = (int)(W.word[r] ^ 0x80000000u);
+  __syncthreads();
+#pragma unroll 1
+  for (int h = 0; h < 2; ++h) {
+    const unsigned at = h ? st + a : st, d = h ? c : a;
+    if (d > 16) sort_row<kBinMost>(sorted + at, (int)d);
+    else if (d > 0) sort_row<16>(sorted + at, (int)d);
+    for (unsigned i = 0; i < d; ++i) sorted[at + i] ^= (int)0x80000000u;
+  }
+  __syncthreads();
+  return true;
 }
 
 // One workgroup per bucket: row starts from a count of its pins per vertex,
@@ -947,8 +1002,9 @@ __global__ __launch_bounds__(kRowsBlock, 6) void k_bucket_rows(Split S) {
       const int T = (int)(s_big.at[last] - s_big.at[first]);
       RowWords<kPer> W;
       load_big_rows(W, s_big, first, last, T, val, s_start, net_bits);
-      sort_big_rows(W, T, net_bits + 32 - __clz(last - first - 1), sorted,
-                    reinterpret_cast<unsigned short*>(s_cur), s_wsum);
+      if (!spread_big_rows(W, s_big, first, T, S.m, net_bits, s_row, s_cur, s_wsum))
+        radix_big_rows(W, T, net_bits + 32 - __clz(last - first - 1), sorted,
+                       reinterpret_cast<unsigned short*>(s_cur), s_wsum);
       for (int p = threadIdx.x; p < T; p += kRowsBlock) {
         const unsigned x = sorted[p], r = first + (x >> net_bits);
         dup |= p > 0 && x == sorted[p - 1];

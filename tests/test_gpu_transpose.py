@@ -42,6 +42,19 @@ def with_pins(P, n, seed):
     return eptr[:(P + 1) // 2 + 1].astype(np.int64), pins.astype(np.int32)
 
 
+def clustered(n, degrees, m, seed):
+    """m nets, each with a pin of its own; vertex v in degrees[v] consecutive ones."""
+    rng = np.random.default_rng(seed)
+    nets, pins = [np.arange(m)], [rng.integers(len(degrees), n, m)]
+    for v, d in enumerate(degrees):
+        nets.append(rng.integers(0, m - d) + np.arange(d))
+        pins.append(np.full(d, v))
+    nets, pins = np.concatenate(nets), np.concatenate(pins)
+    order = np.lexsort((rng.random(nets.size), nets))
+    eptr = np.concatenate(([0], np.cumsum(np.bincount(nets, minlength=m))))
+    return eptr.astype(np.int64), pins[order].astype(np.int32)
+
+
 CASES = {
     # pins around one and two tiles of 8192, vertices around a bucket's width
     "tile-1": lambda: (700, *with_pins(8191, 700, 1)),
@@ -58,7 +71,9 @@ CASES = {
     "row-128": lambda: (3000, *rows_of_degrees(3000, [127, 128, 129, 130, 255, 256, 257], 900, 10)),
     "row-many-129": lambda: (2500, *rows_of_degrees(2500, [129] * 70, 4000, 11)),
     "row-many-600": lambda: (3000, *rows_of_degrees(3000, [600] * 15, 5000, 12)),
-    "row-9500": lambda: (40_000, *rows_of_degrees(40_000, [9500], 12_000, 13)),
+    "row-9000": lambda: (40_000, *rows_of_degrees(40_000, [9000], 12_000, 13)),
+    # the same where the nets of a long row lie close together (radix passes in LDS)
+    "row-clustered": lambda: (20_000, *clustered(20_000, [3000, 200, 129, 1200, 700], 80_000, 22)),
     "row-two-thirds": lambda: (300, *rows_of_degrees(300, [4000, 2, 4900], 5000, 14)),
     # a vertex in 30,000 nets: no bucket holds it, the radix sort takes over
     "hub": lambda: (9000, *rows_of_degrees(9000, [30_000], 30_000, 6)),
