@@ -171,8 +171,8 @@ WsLayout ws_layout(int n, int m, long long P, int k_max) {
   L.lpart = take(sizeof(LoadPart) * kLoadGrid);
   L.total = off;
   // A load and the rounds share space, each where the other needs none: the load's
-  // bucket tables (2 * (buckets + coarse + 1) words with buckets <= n: at most
-  // 8.125 n + 16 bytes) lie in the 16 n bytes per vertex that its last kernels
+  // tables (2 * (buckets + coarse + 1) + tiles + 1 words with buckets <= n, tiles <= n +
+  // 1: at most 12.125 n + 24 bytes) lie in the 16 n + 1024 bytes that its last kernels
   // and the rounds fill, the late rounds' second set of counters in its parts, the
   // list of long nets (fewer than P / kWaveNet) in its second sort buffer.
   L.lbase = L.cand;

@@ -104,67 +104,56 @@ __device__ __forceinline__ int block_max_int(int v, int* s_tmp) {
   return r;
 }
 
-// Nets: increasing offsets with fixed ends (no empty net), positive weights.
-// With tile_first set, the net holding the first pin of every tile of
-// kPartTile pins is written there (tile_first[tiles] = m - 1).
-__global__ __launch_bounds__(kBlock) void k_check_nets(int m, long long P,
-                                                       const long long* eptr, const int* ewgt,
-                                                       LoadInfo* info, LoadPart* part,
-                                                       int* tile_first, int tiles) {
+// Nets: increasing offsets with fixed ends (no empty net), positive weights.  The net
+// holding the first pin of every tile of kPartTile pins goes to tile_first
+// (tile_first[tiles] = m - 1).  Vertices: positive weights.  (One launch: the second
+// took longer to start than to run on small hypergraphs.)
+__global__ __launch_bounds__(kBlock) void k_check(int m, long long P, const long long* eptr,
+                                                  const int* ewgt, int n, const int* vwgt,
+                                                  LoadInfo* info, LoadPart* part,
+                                                  int* tile_first, int tiles) {
   __shared__ long long s_tmp[kBlock / kWave];
   __shared__ int s_imax[kBlock / kWave];
-  int err = 0, size = 0;
-  long long wsum = 0;
+  int err = 0, size = 0, cmax = 0;
+  long long wsum = 0, csum = 0;
   const long long stride = (long long)gridDim.x * kBlock;
-  for (long long e = (long long)blockIdx.x * kBlock + threadIdx.x; e < m; e += stride) {
+  const long long at = (long long)blockIdx.x * kBlock + threadIdx.x;
+  for (long long e = at; e < m; e += stride) {
     const long long s = eptr[e], t = eptr[e + 1];
     if (e == 0 && s != 0) err |= kErrCsr;
     if (e == m - 1 && t != P) err |= kErrCsr;
     if (t <= s || s < 0 || t > P) err |= kErrCsr;
     else {
       if (t - s > size) size = (int)((t - s) > 0x7fffffffLL ? 0x7fffffff : (t - s));
-      if (tile_first) {
-        // tiles whose first pin lies in [s, t), all below `tiles` as t <= P
-        for (long long x = (s + kPartTile - 1) / kPartTile; x * kPartTile < t; ++x)
-          tile_first[x] = (int)e;
-        if (e == m - 1) tile_first[tiles] = m - 1;
-      }
+      // tiles whose first pin lies in [s, t), all below `tiles` as t <= P
+      for (long long x = (s + kPartTile - 1) / kPartTile; x * kPartTile < t; ++x)
+        tile_first[x] = (int)e;
+      if (e == m - 1) tile_first[tiles] = m - 1;
     }
     const long long w = ewgt ? ewgt[e] : 1;
     if (w <= 0) err |= kErrWeight;
     else wsum += w;
   }
-  if (err) atomicOr(&info->err, err);
-  const int mx = block_max_int(size, s_imax);
-  const long long ws = block_sum64(wsum, s_tmp);
-  if (threadIdx.x == 0) {
-    part[blockIdx.x].max_net_size = mx;
-    part[blockIdx.x].total_net_weight = (unsigned long long)ws;
-  }
-}
-
-__global__ __launch_bounds__(kBlock) void k_check_vertices(int n, const int* vwgt,
-                                                           LoadInfo* info, LoadPart* part) {
-  __shared__ long long s_tmp[kBlock / kWave];
-  __shared__ int s_imax[kBlock / kWave];
-  int err = 0, cmax = 0;
-  long long csum = 0;
-  const long long stride = (long long)gridDim.x * kBlock;
-  for (long long v = (long long)blockIdx.x * kBlock + threadIdx.x; v < n; v += stride) {
+  for (long long v = at; v < n; v += stride) {
     const long long c = vwgt ? vwgt[v] : 1;
     if (c <= 0) {
-      err = kErrWeight;
+      err |= kErrWeight;
     } else {
       csum += c;
       if (c > cmax) cmax = (int)c;
     }
   }
   if (err) atomicOr(&info->err, err);
-  const int mx = block_max_int(cmax, s_imax);
-  const long long cs = block_sum64(csum, s_tmp);
+  size = block_max_int(size, s_imax);
+  cmax = block_max_int(cmax, s_imax);
+  wsum = block_sum64(wsum, s_tmp);
+  csum = block_sum64(csum, s_tmp);
   if (threadIdx.x == 0) {
-    part[blockIdx.x].total_vertex_weight = (unsigned long long)cs;
-    part[blockIdx.x].max_vertex_weight = mx;
+    LoadPart& mine = part[blockIdx.x];
+    mine.max_net_size = size;
+    mine.total_net_weight = (unsigned long long)wsum;
+    mine.total_vertex_weight = (unsigned long long)csum;
+    mine.max_vertex_weight = cmax;
   }
 }
 
@@ -225,6 +214,9 @@ static unsigned grid_cap_load(long long items) {
 // 4096-item tiles (more workgroups: 7% faster on 10M pairs).
 static bool long_load_sort(long long P) { return P >= (1LL << 24); }
 
+static int pin_tiles(long long P) { return (int)((P + kPartTile - 1) / kPartTile); }
+static_assert(kPartTile == kNetTile, "tiles of the sort's nets mode");
+
 // The sort's first pass: the keys are the caller's pins, read in place.
 static SortPass first_load_pass(hg_graph_s* g) {
   SortPass SP;
@@ -283,7 +275,7 @@ LoadSplit load_split(int n, long long P) {
          ((n >> (shift + 1)) >= 512 || (P << shift) / n < 512))
     ++shift;
   const int buckets = ((n - 1) >> shift) + 1;
-  const int tiles = (int)((P + kPartTile - 1) / kPartTile);
+  const int tiles = pin_tiles(P);
   const int grid = tiles < kPartGrid ? tiles : kPartGrid;
   if ((long long)grid * buckets > P) return L;
   L.shift = shift;
@@ -1025,15 +1017,18 @@ static Split make_split(hg_graph_s* g) {
   S.L = load_split(g->n, g->P);
   S.pins = g->pins;
   S.eptr = g->eptr;
-  // the radix sort's scratch: tile table and coarse offsets in its digit
-  // table, the counts where the second split later leaves the low pin bits
-  S.tile_first = (int*)(g->ws + g->lay.lhist);
-  S.ccounts = (unsigned*)(g->ws + g->lay.lhist) + S.L.tiles + 1;
+  // the radix sort's scratch: coarse offsets in its digit table, the counts where
+  // the second split later leaves the low pin bits
+  S.ccounts = (unsigned*)(g->ws + g->lay.lhist);
   S.counts = (unsigned*)(g->ws + g->lay.lkey[1]);
   S.rel = (unsigned*)(g->ws + g->lay.lbase);
   S.cursor = S.rel + S.L.buckets;
   S.cbase = S.cursor + S.L.buckets;
   S.cmost = S.cbase + S.L.coarse + 1;
+  // the tiles' nets behind these tables, where the radix sort's first pass finds them
+  // too; without a split (any number of tiles) in its first key buffer, which the
+  // first pass does not use
+  S.tile_first = S.L.shift >= 0 ? (int*)(S.cmost + S.L.coarse) : (int*)(g->ws + g->lay.lkey[0]);
   S.cpin = (unsigned*)(g->ws + g->lay.lkey[0]);
   S.cnet = (int*)(g->ws + g->lay.lval);
   S.low = (unsigned short*)(g->ws + g->lay.lkey[1]);
@@ -1053,8 +1048,9 @@ hipError_t load_check(hg_graph_s* g, hipStream_t s) {
   if (e != hipSuccess) return e;
   const Split S = make_split(g);
   const bool split = S.L.shift >= 0;
-  hipLaunchKernelGGL(k_check_nets, dim3(grid_cap_load(g->m)), dim3(kBlock), 0, s, g->m, g->P,
-                     g->eptr, g->ewgt, info, part, split ? S.tile_first : nullptr, S.L.tiles);
+  hipLaunchKernelGGL(k_check, dim3(grid_cap_load(g->m > g->n ? g->m : g->n)), dim3(kBlock), 0, s,
+                     g->m, g->P, g->eptr, g->ewgt, g->n, g->vwgt, info, part, S.tile_first,
+                     pin_tiles(g->P));
   // the pins' range check rides on a count that reads every pin anyway: the
   // buckets' or the sort's first digit count (a pin outside [0, n) only lands
   // in some digit's count, and nothing is built unless the checks pass)
@@ -1071,8 +1067,6 @@ hipError_t load_check(hg_graph_s* g, hipStream_t s) {
     else
       hipLaunchKernelGGL(k_sort_hist<kSortPer>, dim3(SP.tiles), dim3(kBlock), 0, s, SP);
   }
-  hipLaunchKernelGGL(k_check_vertices, dim3(grid_cap_load(g->n)), dim3(kBlock), 0, s, g->n,
-                     g->vwgt, info, part);
   hipLaunchKernelGGL(k_fold_load, dim3(1), dim3(kBlock), 0, s, (const LoadPart*)part, info,
                      split ? S.cbase : nullptr, S.cmost, S.L.coarse);
   return hipGetLastError();
@@ -1084,46 +1078,6 @@ constexpr int kBigRowGrid = 256;   // workgroups striding over the long rows
 // then the incidence rows, each listing its nets in increasing id, with no
 // atomics anywhere (so nothing depends on timing).  Row starts come from
 // where the sorted keys change.
-
-// Each wave expands the pins of 64 consecutive nets into the net id of every
-// pin position: the pairs' values (their keys are the pins themselves, which
-// the first sort pass reads in place).  The nets' pins form one contiguous
-// run; it is written 64 positions per step, and a position's net is the
-// count of nets starting at or before it: each net flags its first position
-// of the step in LDS and one ballot gives every lane the count (nets are
-// non-empty, so their starts are distinct).
-__global__ void k_pin_pairs(int m, const long long* eptr, int* val) {
-  __shared__ unsigned char s_start[kBlock / kWave][kWave];
-  const int w = threadIdx.x / kWave, lane = lane_id();
-  const long long wave_global = (long long)blockIdx.x * (kBlock / kWave) + w;
-  const long long e = wave_global * kWave + lane;
-  long long b = 0;
-  int len = 0;
-  if (e < m) {
-    b = eptr[e];
-    len = (int)(eptr[e + 1] - b);
-  }
-  const int incl = wave_incl_scan(len);
-  const int total = __shfl(incl, kWave - 1);
-  const int first = incl - len;                  // this net's offset in the run
-  const long long run = __shfl(b, 0);            // the run starts at the wave's first net
-  const int first_net = (int)(wave_global * kWave);
-  const unsigned long long upto = ~0ull >> (kWave - 1 - lane);   // lanes 0 .. this one
-  s_start[w][lane] = 0;
-  wave_lds_sync();
-  int before = 0;                                // nets starting before this step
-  // (unsigned: the last step may end beyond 2^31)
-  for (unsigned base = 0; base < (unsigned)total; base += kWave) {
-    if (len > 0 && (unsigned)first - base < kWave) s_start[w][first - base] = 1;
-    wave_lds_sync();
-    const unsigned long long starts = __ballot(s_start[w][lane] != 0);
-    s_start[w][lane] = 0;
-    wave_lds_sync();
-    if (base + lane < (unsigned)total)
-      val[run + base + lane] = first_net + before + __popcll(starts & upto) - 1;
-    before += __popcll(starts);
-  }
-}
 
 // vptr[v] = the first sorted position with key >= v; vptr[n] = P.  A pair
 // equal to its predecessor (same pin, same net) is a vertex listed twice in
@@ -1273,22 +1227,25 @@ static void build_by_sort(hg_graph_s* g, bool counted, hipStream_t s) {
   int* val[2];
   val[passes & 1] = g->vnets;
   val[(passes & 1) ^ 1] = scratch;
-  const long long waves = ((long long)g->m + kWave - 1) / kWave;
-  const unsigned blocks = (unsigned)((waves + kBlock / kWave - 1) / (kBlock / kWave));
-  hipLaunchKernelGGL(k_pin_pairs, dim3(blocks), dim3(kBlock), 0, s, g->m, g->eptr, val[0]);
-  // the first pass reads the (validated, non-negative) pins as its keys
+  // the first pass reads the (validated, non-negative) pins as its keys and finds
+  // their nets as it goes.  (Expanding them beforehand took 55 us on a netlist of
+  // 56.5M pins.  The checks of a hypergraph whose fullest bucket turns out too full
+  // cost a count and a scan that come to nothing: with one vertex in 50,000 nets of
+  // that netlist the load took 1423 us before there were ranges, 1487 with both,
+  // 1445 so; 4.3M vertices without ranges 1423 and 1382.)
   SortPass SP = first_load_pass(g);
+  SP.eptr = g->eptr;
+  SP.tile_net = make_split(g).tile_first;
   const bool long_sort = long_load_sort(P);
   for (int q = 0; q < passes; ++q) {
     SP.val_in = val[q & 1];
     SP.key_out = key[(q & 1) ^ 1];
     SP.val_out = val[(q & 1) ^ 1];
     SP.shift = 8 * q;
-    const bool has_counts = q == 0 && counted;
-    if (has_counts && long_sort)
-      sort_pass_counted<kSortPerLong>(SP, s);
-    else if (has_counts)
-      sort_pass_counted(SP, s);
+    if (q == 0 && long_sort)
+      sort_pass_nets<kSortPerLong>(SP, counted, s);
+    else if (q == 0)
+      sort_pass_nets(SP, counted, s);
     else if (long_sort)
       sort_pass<kSortPerLong>(SP, s);
     else

@@ -31,6 +31,8 @@ __device__ __forceinline__ long long sort_item(long long base, int r) {
   return base + (long long)(threadIdx.x / kWave) * (PER * kWave) + r * kWave + lane_id();
 }
 
+constexpr int kNetTile = 8192;              // pins per entry of SortPass::tile_net
+
 struct SortPass {
   const unsigned* key_in;
   const int* val_in;
@@ -42,15 +44,22 @@ struct SortPass {
   // when set, the item count is *n_dev (known only on the device, at most n;
   // tiles past it are empty)
   const int* n_dev = nullptr;
-  // Marks mode (the first pass of a monotone round's move order): item i is
-  // vertex i, present only where marks[i] != 0, with key top - gain(cand[i])
-  // and value i; the scatter clears the marks it reads and workgroup 0
+  // Marks mode (the first pass of a monotone round's move order and of a rebalancing
+  // round's): item i is vertex i, present only where marks[i] != 0, with key
+  // top - gain(cand[i]) and value i.  Gains are at most top; the rebalancer's may be
+  // negative, down to -top, so its keys reach 2 * top.  The scatter clears the marks it reads and workgroup 0
   // stores the number of present items in *count_out.  key_in / val_in are
   // not read.
   unsigned char* marks = nullptr;
   const long long* cand = nullptr;
   unsigned top = 0;
   int* count_out = nullptr;
+  // Nets mode (the loader's first pass, with sort_pass_nets): item i is pin position
+  // i and its value the net that holds it, found from the net offsets and the net of
+  // the first pin of every kNetTile pins (tile_net[tiles] = the last net).  val_in is
+  // not read.
+  const long long* eptr = nullptr;
+  const int* tile_net = nullptr;
   // Range check (the loader's first pass, whose keys are the caller's pins):
   // when err is set, the digit-count kernel also ORs err_bit into *err if a
   // present key is >= key_limit.  The counts stay in range either way.
@@ -83,7 +92,7 @@ __device__ __forceinline__ void sort_load(const SortPass& P, int n, long long ba
 #pragma unroll
     for (int r = 0; r < PER; ++r) {
       live[r] = mk[r] != 0;
-      key[r] = P.top - (unsigned)(int)(x[r] >> 32);   // select gain, 0 <= gain <= top
+      key[r] = P.top - (unsigned)(int)(x[r] >> 32);   // the gain, at most top
       if (want_val) val[r] = (int)sort_item<PER>(base, r);
     }
     return;
@@ -162,7 +171,9 @@ __global__ __launch_bounds__(kBlock) __attribute__((unused)) void k_sort_scan(So
 // that digit (no workgroup barrier inside the walk).  Offsets of the waves
 // before it and of the smaller digits complete the LDS slot, which keeps
 // item order within each digit.
-template <int PER>
+// NETS: nets mode.  A position's net is the tile's first one plus the net starts up to
+// it, counted in a bit per position.
+template <int PER, bool NETS>
 __global__ __launch_bounds__(kBlock) void k_sort_scatter(SortPass P) {
   constexpr int kTile = PER * kBlock;
   __shared__ unsigned s_key[kTile];
@@ -178,7 +189,29 @@ __global__ __launch_bounds__(kBlock) void k_sort_scatter(SortPass P) {
   unsigned key[PER];
   int val[PER];
   bool item[PER];
-  sort_load<PER>(P, n, base, true, key, val, item);
+  sort_load<PER>(P, n, base, !NETS, key, val, item);
+  constexpr int kWords = NETS ? kNetTile / kWave : 1;
+  __shared__ unsigned long long s_start[kWords];          // a bit per net start
+  __shared__ int s_before[kWords];                        // the net before the word
+  if constexpr (NETS) {
+    static_assert(kNetTile % kTile == 0 && kWords == 2 * kWave, "two words per lane of a wavefront");
+    const long long tile = base / kNetTile, first = tile * kNetTile;
+    const int net0 = P.tile_net[tile], net1 = P.tile_net[tile + 1];
+    for (int i = threadIdx.x; i < kWords; i += kBlock) s_start[i] = 0;
+    __syncthreads();
+    for (int e = net0 + 1 + (int)threadIdx.x; e <= net1; e += kBlock) {
+      const long long at = P.eptr[e] - first;            // > 0
+      if (at < kNetTile) atomicOr(&s_start[at >> 6], 1ull << (at & 63));
+    }
+    __syncthreads();
+    if (threadIdx.x < kWave) {
+      const int i = 2 * threadIdx.x;
+      const int c0 = __popcll(s_start[i]), c1 = __popcll(s_start[i + 1]);
+      const int incl = wave_incl_scan(c0 + c1);
+      s_before[i] = net0 + incl - c0 - c1;
+      s_before[i + 1] = net0 + incl - c1;
+    }
+  }
   {
     // digit d = threadIdx.x: its count in this tile is the difference of the
     // scanned per-tile offsets; its LDS run starts after the smaller digits'
@@ -236,7 +269,12 @@ __global__ __launch_bounds__(kBlock) void k_sort_scatter(SortPass P) {
       const unsigned d = digit_of(key[r], P.shift);
       const unsigned slot = s_run[d] + s_wcnt[wv][d] + off[r];
       s_key[slot] = key[r];
-      s_val[slot] = val[r];
+      if constexpr (NETS) {
+        const int word = (int)(sort_item<PER>(base, r) % kNetTile) / kWave;   // the lane's bit
+        s_val[slot] = s_before[word] + __popcll(s_start[word] & (lt << 1 | 1ull));
+      } else {
+        s_val[slot] = val[r];
+      }
     }
   }
   __syncthreads();
@@ -255,15 +293,16 @@ template <int PER = kSortPer>
 inline void sort_pass(const SortPass& P, hipStream_t s) {
   hipLaunchKernelGGL(k_sort_hist<PER>, dim3(P.tiles), dim3(kBlock), 0, s, P);
   hipLaunchKernelGGL(k_sort_scan, dim3(kDigits), dim3(kBlock), 0, s, P);
-  hipLaunchKernelGGL(k_sort_scatter<PER>, dim3(P.tiles), dim3(kBlock), 0, s, P);
+  hipLaunchKernelGGL((k_sort_scatter<PER, false>), dim3(P.tiles), dim3(kBlock), 0, s, P);
 }
 
-// The rest of a pass whose digit counts are already in P.hist (k_sort_hist
-// ran earlier on the same stream with the same P): scan and scatter.
+// The same in nets mode; `counted`: the digit counts are already in P.hist
+// (k_sort_hist ran earlier on the same stream with the same P).
 template <int PER = kSortPer>
-inline void sort_pass_counted(const SortPass& P, hipStream_t s) {
+inline void sort_pass_nets(const SortPass& P, bool counted, hipStream_t s) {
+  if (!counted) hipLaunchKernelGGL(k_sort_hist<PER>, dim3(P.tiles), dim3(kBlock), 0, s, P);
   hipLaunchKernelGGL(k_sort_scan, dim3(kDigits), dim3(kBlock), 0, s, P);
-  hipLaunchKernelGGL(k_sort_scatter<PER>, dim3(P.tiles), dim3(kBlock), 0, s, P);
+  hipLaunchKernelGGL((k_sort_scatter<PER, true>), dim3(P.tiles), dim3(kBlock), 0, s, P);
 }
 
 template <int PER = kSortPer>

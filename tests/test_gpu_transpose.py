@@ -42,6 +42,17 @@ def with_pins(P, n, seed):
     return eptr[:(P + 1) // 2 + 1].astype(np.int64), pins.astype(np.int32)
 
 
+def bucket_of(pins_in_first, n, seed):
+    """Two-pin nets whose first 512 vertices hold so many pins, the other vertices
+    two each."""
+    rng = np.random.default_rng(seed)
+    a = np.arange(pins_in_first) % 512
+    b = 512 + np.arange(pins_in_first) % (n - 512)
+    more = 512 + rng.permutation(n - 512)[:(n - 512) // 2 * 2]
+    pins = np.concatenate([np.stack([a, b], 1).ravel(), more])
+    return np.arange(0, pins.size + 2, 2)[:pins.size // 2 + 1].astype(np.int64), pins.astype(np.int32)
+
+
 def clustered(n, degrees, m, seed):
     """m nets, each with a pin of its own; vertex v in degrees[v] consecutive ones."""
     rng = np.random.default_rng(seed)
@@ -53,6 +64,16 @@ def clustered(n, degrees, m, seed):
     order = np.lexsort((rng.random(nets.size), nets))
     eptr = np.concatenate(([0], np.cumsum(np.bincount(nets, minlength=m))))
     return eptr.astype(np.int64), pins[order].astype(np.int32)
+
+
+def hub_and(n, m, seed):
+    """m nets of two pins and more, every one of them with vertex 0, in 12,000 nets."""
+    m += 12_000
+    rng = np.random.default_rng(seed)
+    more = rng.integers(1, 4, m)
+    pins = np.concatenate([np.concatenate(([0], 1 + rng.choice(n - 1, c, replace=False)))
+                           for c in more])
+    return np.concatenate(([0], np.cumsum(more + 1))).astype(np.int64), pins.astype(np.int32)
 
 
 CASES = {
@@ -75,6 +96,24 @@ CASES = {
     # the same where the nets of a long row lie close together (radix passes in LDS)
     "row-clustered": lambda: (20_000, *clustered(20_000, [3000, 200, 129, 1200, 700], 80_000, 22)),
     "row-two-thirds": lambda: (300, *rows_of_degrees(300, [4000, 2, 4900], 5000, 14)),
+    # a bucket (512 vertices here) that the LDS rows just hold, and one pin more, which
+    # leaves all pins to the radix sort
+    "bucket-full": lambda: (150_000, *bucket_of(10_240, 150_000, 15)),
+    "bucket-over": lambda: (150_000, *bucket_of(10_241, 150_000, 15)),
+    # 1,024 vertices a bucket: every place of its tables
+    "wide-buckets": lambda: (5_000_000, *with_pins(6_000_000, 5_000_000, 16)),
+    # the radix sort's first pass finds the nets: whole tiles of 4,096 and 8,192 pins (from
+    # 2^24 pins on) and one pin more, nets across tiles, single-pin nets, one net over
+    # many tiles
+    "radix-tiles": lambda: (1, np.arange(16_385, dtype=np.int64), np.zeros(16_384, np.int32)),
+    "radix-tiles+1": lambda: (1, np.arange(16_386, dtype=np.int64), np.zeros(16_385, np.int32)),
+    "radix-hub": lambda: (200, *hub_and(200, 8191, 17)),
+    "radix-single-pins": lambda: (3, np.arange(40_001, dtype=np.int64),
+                                  (np.arange(40_000) % 3).astype(np.int32)),
+    "radix-one-net": lambda: (9_000_000, np.array([0, 4_000_001], np.int64),
+                              np.random.default_rng(20).permutation(9_000_000)[:4_000_001]
+                              .astype(np.int32)),
+    "radix-long-tiles": lambda: (9_000_000, *with_pins((1 << 24) + 5, 9_000_000, 21)),
     # a vertex in 30,000 nets: no bucket holds it, the radix sort takes over
     "hub": lambda: (9000, *rows_of_degrees(9000, [30_000], 30_000, 6)),
     # long nets across tiles, and more than one coarse range of 64 buckets
