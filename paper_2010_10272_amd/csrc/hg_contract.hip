@@ -7,7 +7,7 @@
 //   2. coarse vertex weights by integer atomics;
 //   3. every net's pins are mapped, sorted and deduplicated in the net's own
 //      slots of a scratch copy (tmp[eptr[e] ..]): nets of up to kSmallNet
-//      pins 64 nets per wavefront in LDS (every pin counts the smaller ones of
+//      pins up to 64 nets per wavefront in LDS (every pin counts the smaller ones of
 //      its net), longer
 //      nets one workgroup each (bitonic sort in LDS, or in place beyond the
 //      LDS capacity, then a compaction by block scans); the same pass gives
@@ -60,6 +60,7 @@ struct Ct {
   int* big_count;        // [1]
   int* nsize;            // [m]: pins after deduplication
   unsigned long long* fp;// [m]
+  int unit;              // nets per wavefront and turn (ct_unit)
   int key_bits;          // 8 bits per sorting pass
   unsigned* nkey[2];     // [m]
   int* nval[2];          // [m]
@@ -135,7 +136,16 @@ __device__ __forceinline__ void ct_net_done(const Ct& C, long long e, int size,
   C.wsum[e] = 0;
 }
 
-// Small nets: a wavefront takes 64 consecutive nets, as many of them at a time as
+// Consecutive nets per wavefront and turn: 64, fewer where that leaves the chip idle
+// and each still has 512 pins.  (Contraction of 10,000 nets of 128 pins, us, 64 a
+// wavefront 532, so 147; 30,000 of 100 414, 171; 2,000 of 1,500 557, 221.)
+int ct_unit(long long m, long long P) {
+  int nets = kWave;
+  while (nets > 1 && m < 8192LL * nets && nets / 2 * P >= 512 * m) nets >>= 1;
+  return nets;
+}
+
+// Small nets: a wavefront takes `unit` consecutive nets, as many of them at a time as
 // fit its kCtCap LDS places; no barrier, the wavefronts work on their own.  A net
 // lies at a multiple of four places, filled up with a value above all others.
 //   1. lane = place: the mapped pin goes to LDS (kCtFlight pins and map values on
@@ -154,9 +164,12 @@ __device__ __forceinline__ void ct_net_done(const Ct& C, long long e, int size,
 constexpr int kCtCap = 832;          // LDS places of a wavefront
 constexpr int kCtFlight = 4;
 constexpr int kCtGrid = 2048;        // persistent workgroups
-constexpr int kCtBigGrid = 1280;     // as many as reside (kNetLdsCap words each)
+constexpr int kCtBigGrid = 1024;     // as many as reside (a little over kNetLdsCap words each:
+                                     // four a compute unit; 1280 left 256 for a second
+                                     // turn: 10,000 nets of 300 382 us, 322 so)
+constexpr int kCtLongEmit = 2048;    // longer nets leave by a workgroup each
 
-struct CtLds {
+struct alignas(16) CtLds {             // val is read four at a time
   int val[kCtCap];
   int sorted[kCtCap];
   unsigned char net[kCtCap];
@@ -177,18 +190,18 @@ __device__ __forceinline__ void ct_flush_big(const Ct& C, CtLds& M, int count) {
 }
 
 __global__ __launch_bounds__(kBlock) void k_ct_small_nets(Ct C) {
-  __shared__ __attribute__((aligned(16))) CtLds s_lds[kBlock / kWave];
+  __shared__ CtLds s_lds[kBlock / kWave];
   const int lane = lane_id(), wv = threadIdx.x / kWave;
   CtLds& M = s_lds[wv];
   constexpr int kEmpty = -1, kAbove = 0x7fffffff;
   for (int i = lane; i < kCtFlight * kWave; i += kWave) M.flag[i] = 0;
   int big = 0;                                        // long nets queued
-  for (long long e0 = ((long long)blockIdx.x * (kBlock / kWave) + wv) * kWave; e0 < C.m;
-       e0 += (long long)gridDim.x * kBlock) {
+  for (long long e0 = ((long long)blockIdx.x * (kBlock / kWave) + wv) * C.unit; e0 < C.m;
+       e0 += (long long)gridDim.x * (kBlock / kWave) * C.unit) {
     const long long e = e0 + lane;
     long long b = 0;
     int len = 0;
-    if (e < C.m) {
+    if (lane < C.unit && e < C.m) {
       b = C.eptr[e];
       const long long size = C.eptr[e + 1] - b;
       len = size > kSmallNet ? kSmallNet + 1 : (int)size;
@@ -455,21 +468,19 @@ struct KeptSizeF {
   __device__ long long operator()(long long e) const { return rep[e] == e ? nsize[e] : 0; }
 };
 
-// The pins of the kept nets.  A wavefront takes 64 consecutive nets; their coarse
-// pins are one run, written kCtFlight per lane at a time (a position's net is the
-// count of net starts at or before it: a flag per position in LDS, one ballot).
-// Bound by its bytes; eight lanes a net took 55 us for 9M pins, 22 so.
+// The pins of the kept nets.  A wavefront takes `unit` consecutive nets, their pins
+// laid end to end, kCtFlight per lane at a time (a position's net is the count of
+// net starts at or before it: a flag per position in LDS, one ballot).  Bound by its
+// bytes; eight lanes a net took 55 us for 9M pins, 22 so.  Nets of more than
+// kCtLongEmit pins are left to k_ct_emit_long.
 __global__ __launch_bounds__(kBlock) void k_ct_emit(Ct C) {
   __shared__ unsigned char s_flag[kBlock / kWave][kCtFlight * kWave];
-  __shared__ long long s_shift[kBlock / kWave][kWave];
+  __shared__ long long s_from[kBlock / kWave][kWave], s_to[kBlock / kWave][kWave];
   const int lane = lane_id(), wv = threadIdx.x / kWave;
   unsigned char* flag = s_flag[wv];
-  long long* shift = s_shift[wv];
   for (int i = lane; i < kCtFlight * kWave; i += kWave) flag[i] = 0;
-  const long long e = ((long long)blockIdx.x * (kBlock / kWave) + wv) * kWave + lane;
-  const bool kept = e < C.m && C.rep[e] == e;
-  const unsigned long long in = __ballot(kept);
-  if (!in) return;
+  const long long e = ((long long)blockIdx.x * (kBlock / kWave) + wv) * C.unit + lane;
+  const bool kept = lane < C.unit && e < C.m && C.rep[e] == e;
   long long pos = 0;
   int len = 0;
   if (kept) {
@@ -478,33 +489,58 @@ __global__ __launch_bounds__(kBlock) void k_ct_emit(Ct C) {
     len = C.nsize[e];
     C.ceptr[id] = pos;
     C.cewgt[id] = (int)C.wsum[e];
-    shift[lanes_below(in, 0)] = C.eptr[e] - pos;
+    if (len > kCtLongEmit) len = 0;
   }
-  const long long run = __shfl(pos, __ffsll((long long)in) - 1);
-  const int last = 63 - __clzll((long long)in);
-  const long long total = __shfl(pos, last) + __shfl(len, last) - run;
-  const long long first = pos - run;                      // kept nets have at least two pins
+  const int incl = wave_incl_scan(len), first = incl - len;
+  const int total = last_lane(incl);                      // at most kWave * kCtLongEmit
+  if (len > 0) {
+    const int at = lanes_below(__ballot(len > 0), 0);
+    s_from[wv][at] = C.eptr[e] - first;
+    s_to[wv][at] = pos - first;
+  }
   int before = -1;
-  for (long long s = 0; s < total; s += kCtFlight * kWave) {
-    if (kept && first >= s && first < s + kCtFlight * kWave) flag[first - s] = 1;
+  for (int s = 0; s < total; s += kCtFlight * kWave) {
+    if (len > 0 && first >= s && first < s + kCtFlight * kWave) flag[first - s] = 1;
     wave_lds_sync();
     int x[kCtFlight];
+    long long to[kCtFlight];
 #pragma unroll
     for (int q = 0; q < kCtFlight; ++q) {
-      const long long p = s + q * kWave + lane;
+      const int p = s + q * kWave + lane;
       const int mark = flag[q * kWave + lane];
       flag[q * kWave + lane] = 0;
       const unsigned long long starts = __ballot(mark != 0);
       const int net = lanes_below(starts, before) + mark;
       before += __popcll(starts);
-      if (p < total) x[q] = C.tmp[shift[net] + run + p];
+      if (p < total) {
+        x[q] = C.tmp[s_from[wv][net] + p];
+        to[q] = s_to[wv][net] + p;
+      }
     }
 #pragma unroll
-    for (int q = 0; q < kCtFlight; ++q) {
-      const long long p = s + q * kWave + lane;
-      if (p < total) C.cpins[run + p] = x[q];
-    }
+    for (int q = 0; q < kCtFlight; ++q)
+      if (s + q * kWave + lane < total) C.cpins[to[q]] = x[q];
     wave_lds_sync();
+  }
+}
+
+// Kept nets of more than kCtLongEmit pins, a workgroup each (they are among the long
+// nets that k_ct_small_nets listed; launched for hypergraphs that may have some).
+__global__ __launch_bounds__(kBlock) void k_ct_emit_long(Ct C) {
+  const int count = *C.big_count;
+  for (int idx = blockIdx.x; idx < count; idx += gridDim.x) {
+    const int e = C.big[idx], size = C.nsize[e];
+    if (C.rep[e] != e || size <= kCtLongEmit) continue;
+    const int* from = C.tmp + C.eptr[e];
+    int* to = C.cpins + C.npos[e];
+    for (long long i = threadIdx.x; i < size; i += kBlock * kCtFlight) {
+      int x[kCtFlight];
+#pragma unroll
+      for (int q = 0; q < kCtFlight; ++q) x[q] = i + q * kBlock < size ? from[i + q * kBlock] : 0;
+#pragma unroll
+      for (int q = 0; q < kCtFlight; ++q)
+        if (i + q * kBlock < size) to[i + q * kBlock] = x[q];
+    }
   }
 }
 
@@ -606,8 +642,8 @@ static hipError_t launch_contract(hg_graph_s* g, const int* cluster, int* map, i
   B.csum = (long long*)(ws + L.csum);
   B.coff = (long long*)(ws + L.coff);
   const long long n = g->n, m = g->m;
-  // one sorting pass (23 us for 1M nets) per 8 bits: at least 16 key values per
-  // net, so that few nets that differ share a run
+  // one sorting pass (23 us for 1M nets) per 8 bits: at least 16 key values per net
+  // up to 2^28 nets, so that few nets that differ share a run
   C.key_bits = m <= (1 << 12) ? 16 : m <= (1 << 20) ? 24 : 32;
 
   // 1-2. renumbering, map, coarse weights
@@ -623,7 +659,9 @@ static hipError_t launch_contract(hg_graph_s* g, const int* cluster, int* map, i
   hipLaunchKernelGGL(k_ct_vweights, dim3(blocks_of(n)), dim3(kBlock), 0, s, C);
 
   // 3-4. per net: mapped, sorted, deduplicated pins, size, fingerprint
-  const unsigned sg = blocks_of(m) < kCtGrid ? blocks_of(m) : kCtGrid;
+  C.unit = ct_unit(m, g->P);
+  const unsigned units = (unsigned)units_of(m, C.unit * (kBlock / kWave));
+  const unsigned sg = units < kCtGrid ? units : kCtGrid;
   hipLaunchKernelGGL(k_ct_small_nets, dim3(sg), dim3(kBlock), 0, s, C);
   hipLaunchKernelGGL(k_ct_big_nets, dim3(kCtBigGrid), dim3(kBlock), 0, s, C);
 
@@ -651,7 +689,9 @@ static hipError_t launch_contract(hg_graph_s* g, const int* cluster, int* map, i
   // 6. coarse net CSR in representative order
   exclusive_scan(KeptF{C.rep}, m, C.nid, &sizes[1], B, s);
   exclusive_scan(KeptSizeF{C.rep, C.nsize}, m, C.npos, &sizes[2], B, s);
-  hipLaunchKernelGGL(k_ct_emit, dim3(blocks_of(m)), dim3(kBlock), 0, s, C);
+  hipLaunchKernelGGL(k_ct_emit, dim3(units), dim3(kBlock), 0, s, C);
+  if (g->info.max_net_size > kCtLongEmit)
+    hipLaunchKernelGGL(k_ct_emit_long, dim3(kCtBigGrid), dim3(kBlock), 0, s, C);
   hipLaunchKernelGGL(k_ct_close, dim3(1), dim3(kWave), 0, s, C);
   return hipGetLastError();
 }
