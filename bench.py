@@ -23,7 +23,12 @@ kernels' stream during the last timed step), per-round latency p50/p99, the
 recorded-hipGraph refine time, and the CPU oracle on a bounded sample of the
 same rounds, whose records and partitions must equal the timed run's.
 
+Prints one short JSON line: the headline's record, and of every leg its rates, times
+and latencies.  --record FILE writes all that was measured (round records, phases,
+traffic, schedules, server counters) as well.
+
 usage: python bench.py [--gpus 1] [--steps K] [--warmup W] [--no-cpu] [--legs ...]
+                       [--record FILE]
 """
 import argparse
 import json
@@ -1074,6 +1079,58 @@ def attach_traffic(roof, profile):
     roof["round"]["traffic"] = tot
 
 
+# What the printed line keeps of a leg, at any depth.  All of the record is some 30,000
+# characters, more than a reader of the end of the output gets to see.
+# Every leg's value is in pins/s.
+LINE_KEYS = {"value", "ms_per_step", "pins_per_s", "ms", "round_ms", "refine_ms",
+             "graph_refine_ms", "batch_ms", "sequential_ms", "speedup_vs_sequential", "p50_ms",
+             "p99_ms", "makespan_s", "km1_final"}
+LINE_SKIP = {"phases", "per_k", "server", "copy_reference"}
+HEADLINE_KEYS = ("metric", "value", "unit", "n_gpus", "steps", "warmup", "ms_per_step",
+                 "higher_is_better", "scaling", "vs_baseline", "dtype", "data", "config",
+                 "roofline", "cpu_baseline")
+
+
+def short_numbers(x):
+    """x with its floats at six digits."""
+    if isinstance(x, float):
+        return float("%.6g" % x)
+    if isinstance(x, dict):
+        return {k: short_numbers(v) for k, v in x.items()}
+    if isinstance(x, (list, tuple)):
+        return [short_numbers(v) for v in x]
+    return x
+
+
+def leg_summary(rec):
+    """The entries of a leg's record that the printed line keeps."""
+    out = {}
+    for key, v in rec.items():
+        if key in LINE_KEYS:
+            out[key] = short_numbers(v)
+        elif key == "roofline":
+            out[key] = short_numbers({x: v[x] for x in ("bound", "frac") if x in v})
+        elif isinstance(v, dict) and key not in LINE_SKIP:
+            sub = leg_summary(v)
+            if sub:
+                out[key] = sub
+    return out
+
+
+def contract_line(rec):
+    """The printed line's record: the headline's own entries (its roofline without the
+    phases), the rest by leg_summary."""
+    out = {}
+    for key, v in rec.items():
+        if key == "roofline":
+            out[key] = {x: short_numbers(v[x]) for x in v if x not in LINE_SKIP}
+        elif key in HEADLINE_KEYS or not isinstance(v, dict):
+            out[key] = v
+        else:
+            out[key] = leg_summary(v)
+    return out
+
+
 def plain_legs(args, H, dev):
     """The plain workloads: the VLSI-like netlist (the headline), the
     sparse matrix and the tiny instance."""
@@ -1145,6 +1202,7 @@ def main():
     ap.add_argument("--calibrate-copy", type=int, default=0, metavar="MIB",
                     help="also run one plain device-to-device copy of MIB MiB (a known "
                          "byte count for scaling HBM traffic counters)")
+    ap.add_argument("--record", metavar="FILE", help="write the full record there as JSON")
     args = ap.parse_args()
     if args.steps < 1 or args.warmup < 0:
         print("bench.py needs --steps >= 1 and --warmup >= 0", file=sys.stderr)
@@ -1194,7 +1252,10 @@ def main():
         torch.cuda.empty_cache()
         print("contraction ...", file=sys.stderr, flush=True)
         out["contract"] = contract_leg(args, H, dev)
-    print(json.dumps(out), flush=True)
+    if args.record:
+        with open(args.record, "w") as f:
+            json.dump(out, f, indent=1)
+    print(json.dumps(contract_line(out)), flush=True)
 
 
 if __name__ == "__main__":

@@ -2,6 +2,7 @@
 counts of a round's phases, the roofline record and the traffic summaries'
 source-hash gate."""
 import hashlib
+import json
 import os
 import subprocess
 import sys
@@ -75,3 +76,61 @@ def test_committed_traffic_summaries_parse(profile):
         assert prefix + "_sources_sha256:" in text
         v = bench.measured_traffic(profile, prefix)
         assert v is None or v > 0
+
+
+def _full_record():
+    """A record of every leg's shape, each number with all its digits."""
+    x = 12345678901.234567
+    roof = {"kernel": "k" * 40, "bound": "hbm", "achieved": x, "peak": 8000.0, "unit": "GB/s",
+            "frac": x, "alg_bytes": x, "ms": x, "traffic": 123456789}
+    host = {"cpu_model": "c" * 20, "compiler": "g" * 45, "flags": "f" * 40}
+    cpu = {"value": x, "unit": "pins/s", "cores": 1, "kind": "oracle", "sample": "s" * 190,
+           "seconds": x, "host": host}
+    latency = {"p50_ms": x, "p99_ms": x, "round1_p50_ms": x}
+
+    def plain(ks):
+        return {"value": x, "unit": "pins/s", "ms_per_step": x, "cpu_baseline": cpu,
+                "roofline": dict(roof, phases={"select": roof}, round=roof),
+                "per_k": {k: {"records": [{"f%d" % i: 123456789 for i in range(12)}] * 10}
+                          for k in ks},
+                "round_latency": {k: latency for k in ks}, "graph_refine_ms": {k: x for k in ks},
+                "km1_final": {k: 1234567 for k in ks}, "config": "c" * 190}
+
+    times = {"refine_ms": x, "round_ms": x, "pins_per_s": x, "km1_after_rounds": [1234567] * 10}
+    run = dict(latency, value=x, unit="pins/s", makespan_s=x, server={"steps": 1234567})
+    rec = {"metric": bench.METRIC, "value": x, "unit": "pins/s", "n_gpus": 1, "steps": 20,
+           "warmup": 5, "ms_per_step": x, "higher_is_better": True, "scaling": "weak",
+           "vs_baseline": None, "dtype": "int32", "data": "synthetic",
+           "config": {"workload": "w" * 200, "n": 4000000, "k": [16], "eps": 0.03},
+           "roofline": dict(roof, phases={"select": roof}, round=roof, copy_reference=roof),
+           "cpu_baseline": cpu, "vlsi": plain(["k16"]), "sparse_matrix": plain(["k8", "k64"]),
+           "tiny": plain(["k2"]),
+           "batched": {"value": x, "batch_ms": x, "sequential_ms": x, "round_latency": latency,
+                       "speedup_vs_sequential": x, "schedule_tuned": [{"a": 1}] * 20,
+                       "cpu_baseline": cpu},
+           "served": {"open_loop": {"served": run, "plain": run},
+                      "burst": {"served": run, "plain": run}}}
+    for leg, other in (("monotone", "monotone"), ("cached", "cached")):
+        rec[leg] = {k: {"plain": times, other: times, "roofline": roof, "cpu_baseline": cpu}
+                    for k in ("k8", "k64")}
+    rec["rebalance"] = {k: dict(times, ms=x, roofline=roof, cpu_baseline=cpu)
+                        for k in ("k8", "k64")}
+    rec["contract"] = dict(times, ms=x, roofline=roof, cpu_baseline=cpu)
+    return rec
+
+
+def test_printed_line_is_short():
+    """The whole line has to be seen by who reads only the last few thousand
+    characters of the output, the progress lines (about 1,200) among them."""
+    rec = _full_record()
+    assert len(json.dumps(rec)) > 20000
+    line = bench.contract_line(rec)
+    assert len(json.dumps(line)) < 6000
+    for key in bench.HEADLINE_KEYS:
+        if key != "roofline":
+            assert line[key] == rec[key]
+    for key in ("kernel", "bound", "unit", "peak", "traffic"):
+        assert line["roofline"][key] == rec["roofline"][key]
+    assert set(line) == set(rec)
+    assert line["served"]["burst"]["plain"]["p99_ms"] == 12345700000.0
+    assert line["sparse_matrix"]["graph_refine_ms"] == {"k8": 12345700000.0, "k64": 12345700000.0}
