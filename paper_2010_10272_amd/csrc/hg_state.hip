@@ -8,6 +8,8 @@
 // each lane builds its net's bitsets from its counters, and the rows leave as
 // whole lines.  No global atomics touch Phi, so the result is deterministic by
 // construction.
+#include <climits>
+
 #include "hg_count.h"
 #include "hg_device.h"
 #include "hg_internal.h"
@@ -103,7 +105,8 @@ __global__ __launch_bounds__(kBlock) void k_pincounts(Launch L) {
 // The same where nets are long on average (group_counts): kGroupLanes lanes a net,
 // eight nets a wavefront, 32-bit counters.  A net's pins are consecutive, so no
 // place has to look for its net, and few registers keep many wavefronts in flight;
-// short nets would leave most lanes idle.
+// short nets would leave most lanes idle.  The Phi rows pass the caches by (400,000 nets
+// of 100, k = 64: 100 -> 76 us).
 // Unit: kGroupUnit consecutive nets.
 constexpr int kGroupLanes = 8;
 constexpr int kGroupNets = kWave / kGroupLanes;
@@ -174,7 +177,7 @@ __global__ __launch_bounds__(kBlock) void k_pincounts_groups(Launch L) {
         if (i < k) {
           x = (int)cnt[r * ks + i];
           cnt[r * ks + i] = 0;             // for the next nets
-          global_out(D.phi)[phi_row + i] = x;
+          __builtin_nontemporal_store(x, global_out(D.phi) + phi_row + i);
         }
         set_words<WK>(N, h, __ballot(x != 0), __ballot(x == 1), lane == owner);
       }
@@ -339,17 +342,16 @@ static unsigned grid_cap(long long items, int per_block, int cap) {
   return (unsigned)b;
 }
 
-// Lane groups for up to 64 blocks and nets of more than 255 pins on average, or of 64
-// where the nets are too few to fill the chip, 64 a wavefront; but not for a few
-// thousand nets, which then get a wavefront each.  n = 100,000, us, k_pincounts and
-// k_pincounts_groups: 100,000 nets of 300, k = 8 86 / 52, k = 64 109 / 73; 30,000 of
-// 100, k = 8 14.4 / 11.2, k = 64 19.5 / 14.3; but 300,000 of 100, k = 64 121 / 124,
-// k = 200 144 / 248; 150,000 of 64, k = 8 33 / 40; 2,100 of 300 9.6 / 12.3.
-// A batch gives a workgroup 256 nets whatever their length: there from 64 pins on
-// (16 members of 200 nets of 300, k = 8, 93 / 38).
+// Lane groups for up to 64 blocks and nets of 64 pins and more on average; but not for
+// a few thousand nets, which then get a wavefront each.  Us, k_pincounts and lane
+// groups, n = 131,072, whole calls: 100,000 nets of 200 from one window k = 8 57 / 38,
+// k = 64 56 / 41, from anywhere 83 / 82, 94 / 95; 600,000 of 64 k = 8 97 / 79, k = 64
+// 85 / 81; n = 100,000, kernels: 100,000 of 300 k = 8 86 / 52, k = 64 109 / 73; but
+// 300,000 of 100 k = 200 144 / 248; 2,100 of 300 k = 8 9.6 / 12.3.
+// A batch gives a workgroup 256 nets whatever their length (16 members of 200 nets of
+// 300, k = 8, 93 / 38).
 static bool group_counts(int k, long long m, long long P, bool batch) {
-  if (batch) return k <= 64 && P >= 64 * m;
-  return k <= 64 && m >= 4096 && (P > 255 * m || (P >= 64 * m && m < (1 << 16)));
+  return k <= 64 && P >= 64 * m && (batch || m >= 4096);
 }
 
 int pincount_unit(int k, long long m, long long P, bool batch) {
@@ -379,7 +381,10 @@ void single_count_plan(const InstDesc& d, CountPlan& plan) {
   const Launch L = single_launch(d);
   PlanLaunch pc;
   pc.kernel = (void*)pincount_kernel(d.k, d.m, d.P, false);
-  pc.grid = grid_cap(d.m, pincount_unit(d.k, d.m, d.P, false), kStateGrid);
+  // lane groups: a unit a workgroup, however many (a second turn of a few units of
+  // 131,072 + i nets cost 40%: 160,000 of 200, k = 8, 70 -> 51 us)
+  pc.grid = grid_cap(d.m, pincount_unit(d.k, d.m, d.P, false),
+                     group_counts(d.k, d.m, d.P, false) ? INT_MAX : kStateGrid);
   pc.lds = pincount_lds(d.k, d.m, d.P, false);
   pc.L = L;
   plan.pincounts.push_back(pc);

@@ -189,3 +189,39 @@ def test_time_of_long_nets(H, sizes, what):
         ms.append(_best_ms(counts if what == "counts" else rounds))
     # a tenth of a millisecond: steps of one net are a chain
     assert ms[0] < 2 * ms[1] + 0.1, ms
+
+
+@pytest.mark.parametrize("k", [3, 64])
+def test_counts_of_more_medium_nets_than_resident(H, k):
+    """More workgroups of lane groups than reside at once, the last one with one net."""
+    import torch
+    n, m, size = 1 << 15, 4096 * 32 + 1, 64
+    rng = np.random.default_rng(k)
+    pins = (rng.integers(0, n, m)[:, None] + np.arange(size) * 3) % n
+    part = rng.integers(0, k, n).astype(np.int32)
+    g = H.hg_load_csr(n, np.arange(m + 1, dtype=np.int64) * size,
+                      pins.reshape(-1).astype(np.int32), k_max=k)
+    st = H.State(g, k, part)
+    H.hg_compute_pincounts(g, st)
+    phi = np.bincount((np.arange(m)[:, None] * k + part[pins]).reshape(-1), minlength=m * k)
+    assert np.array_equal(st.phi.cpu().numpy().reshape(-1), phi)
+    assert int(st.km1.item()) == int((phi.reshape(m, k) > 0).sum()) - m
+    H.hg_sync_status(g)
+
+
+# The same pins in nets of 300, which lane groups have counted all along, and a fifth.
+# (With 64 nets a wavefront nets of 200 took half as long again, 160,000 in two turns a
+# third.)
+@pytest.mark.parametrize("size,m", [(200, 100_000), (200, 160_000)])
+@pytest.mark.parametrize("k", [8, 64])
+def test_time_of_medium_nets(H, size, m, k):
+    n, ms = 1 << 17, []
+    for s in (size, 300):
+        nets = m * size // s
+        rng = np.random.default_rng(1)
+        pins = (rng.integers(0, n, nets)[:, None] + np.arange(s)) % n
+        g = H.hg_load_csr(n, np.arange(nets + 1, dtype=np.int64) * s,
+                          pins.reshape(-1).astype(np.int32), k_max=k)
+        st = H.State(g, k, np.random.default_rng(2).integers(0, k, n).astype(np.int32))
+        ms.append(_best_ms(lambda: [H.hg_compute_pincounts(g, st) for _ in range(10)]))
+    assert ms[0] < 1.2 * ms[1], ms
