@@ -88,16 +88,17 @@ struct Threshold {
 
 // Rounds of one small graph leave out two launches that have next to nothing to
 // do: every tile-sum workgroup finds the thresholds of all k blocks itself, every
-// approve workgroup scans their tile sums.  One wavefront covers kBriefTiles tile
-// sums in one step (131,072 vertices); past 16 blocks the scans cost more than
-// the launches.  Five rounds, us, before and now: n = 1,000 k = 2 166 -> 150,
-// n = 16,000 k = 8 213 -> 200, n = 131,072 k = 2 240 -> 226, k = 16 301 -> 294; but
-// n = 60,000 k = 32 305 -> 314, k = 64 285 -> 331.  Heavy vertices need the separate
-// threshold (k_overflow_resolve).
+// approve workgroup scans their tile sums (one wavefront covers kBriefTiles in one
+// step).  Both grow with n and k, the launches do not.  Refinements of five rounds,
+// us, with the launches and without: n = 1,000 k = 2 158 / 137, k = 16 173 / 163;
+// n = 65,536 k = 2 173 / 162, k = 16 188 / 186; n = 98,304 k = 2 180 / 179, k = 8
+// 192 / 188, k = 16 197 / 201; but n = 131,072 k = 2 190 / 189, k = 8 200 / 207,
+// k = 16 206 / 221.  Heavy vertices need the separate threshold (k_overflow_resolve).
 constexpr int kBriefTiles = 256;
-constexpr int kBriefMaxK = 16;
+constexpr int kBriefMaxN = 98304, kBriefMaxK = 16;
+static_assert(kBriefMaxN <= kBriefTiles * kTile, "one step");
 inline bool brief_rounds(int n, int k, int heavy_count) {
-  return n <= kBriefTiles * kTile && k <= kBriefMaxK && heavy_count == 0;
+  return n <= kBriefMaxN && k <= kBriefMaxK && heavy_count == 0;
 }
 
 // Facts gathered at load time (device side, copied to the host once).

@@ -34,3 +34,9 @@ def test_brief_rounds_equal_batched_rounds(H, n, k, unit, eps):
         got.append(_snapshot(mb))
     for a, b in zip(*got):
         assert np.array_equal(a, b)
+
+
+@pytest.mark.parametrize("n", [98304, 98305])
+@pytest.mark.parametrize("k", [2, 16])
+def test_largest_brief_rounds_equal_batched_rounds(H, n, k):
+    test_brief_rounds_equal_batched_rounds(H, n, k, False, 0.01)
