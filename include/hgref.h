@@ -171,7 +171,8 @@ int64_t hg_max_block_weight(hg_graph g, int32_t k, double eps);
  *   netstate  uint32[m*hg_net_words(k)]  OUT: per-net record (see above)
  *   block_w   int64[k]        OUT: c(V_i)
  *   km1_out   int64[1] or NULL OUT: sum_e (lambda(e) - 1) w(e)
- * Each net is counted by one wavefront, so no atomics touch Phi. */
+ * Each net is counted by some lanes of one wavefront, one wavefront or (long nets) one
+ * workgroup in LDS, so the values never depend on timing. */
 hg_status hg_compute_pincounts(hg_graph g, int32_t k, const int32_t* part, int32_t* phi,
                                uint32_t* netstate, int64_t* block_w, int64_t* km1_out,
                                void* stream);
@@ -356,8 +357,8 @@ typedef struct {
   int32_t select_chunks;     /* 256-vertex chunks per select workgroup, 1..64    */
   int32_t finalize_chunks;   /* 256-net blocks per finalize workgroup, 1..64     */
   int32_t count_chunks;      /* 256-net chunks per pin-count workgroup, 1..64    */
-  int32_t net_lanes;         /* 0, 4, 8, 16 or 32; has no effect any more (the
-                                finalize takes a lane per net for every k)       */
+  int32_t net_lanes;         /* 0, 4, 8, 16 or 32: checked, but without effect since
+                                the sweeps choose a net's lanes by k and net sizes */
 } hg_schedule;
 
 /* Size classes, by vertex count n: [0, 2^13), [2^13, 2^16), [2^16, 2^19),

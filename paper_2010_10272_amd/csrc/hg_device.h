@@ -100,8 +100,7 @@ __device__ __forceinline__ int lanes_below(unsigned long long mask, int add) {
                                         __builtin_amdgcn_mbcnt_lo((unsigned)mask, (unsigned)add));
 }
 
-// Maximum over the wave, of values that may be negative: lanes that receive
-// nothing in a step keep their own.
+// Maximum over the wave, in every lane.
 template <typename T>
 __device__ __forceinline__ T wave_max(T v) {
 #pragma unroll

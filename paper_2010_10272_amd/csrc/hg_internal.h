@@ -298,8 +298,8 @@ struct WsLayout {
 
 WsLayout ws_layout(int n, int m, long long P, int k_max);
 
-// Touched-net flags: one byte per net, padded to whole finalize chunks of
-// 1024 nets so that the sweep reads them four at a time without bounds tests.
+// Touched-net flags: one byte per net, zero past m up to whole chunks of
+// 1024 nets, so that the sweep reads its chunks of 256 without bounds tests.
 inline size_t touched_bytes(int m) { return (((size_t)m + 1023) / 1024) * 1024; }
 
 // 32-bit words per block bitset in a net record: ceil(k/32) rounded up to a

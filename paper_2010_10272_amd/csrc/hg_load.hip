@@ -245,10 +245,10 @@ static SortPass first_load_pass(hg_graph_s* g) {
 // its tile is one LDS atomic, and the workgroups of the second split reserve
 // their output by one global atomic per bucket and tile.  Rows are sets
 // sorted by net id, so nothing depends on the order of arrival.
-// Measured (kernels of one load): netlist 4M cells, 56.5M pins 1420 -> 690 us
-// (count 64, coarse split 198, fine split 209, rows 142; the 2.1 GB they move
-// take 410 us at a large copy's 5.1 TB/s), matrix 1M x 1M, 10M pins 287 ->
-// 158 us.
+// Measured (all kernels of one load, radix passes and now): netlist 4M cells, 56.5M
+// pins 1420 -> 695 us (count 78, coarse split 199, fine split 207, rows 132, checks
+// and facts 70; the 2.1 GB they move take 410 us at a large copy's 5.1 TB/s), matrix
+// 1M x 1M, 10M pins 287 -> 152 us.
 
 constexpr int kPartBlock = 1024;                       // threads of the split kernels
 constexpr int kPartPer = kPartTile / kPartBlock;       // pins per thread and tile

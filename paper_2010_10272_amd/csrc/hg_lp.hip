@@ -906,7 +906,7 @@ __device__ __forceinline__ void brief_tiles(const InstDesc& D, int* s_g, int* s_
   }
 }
 
-// Unit: one tile of kTile vertices.  BRIEF: a brief round (InstDesc::brief).
+// Unit: one tile of kTile vertices.  BRIEF: a brief round (RoundPlan::brief).
 template <bool BRIEF>
 __global__ __launch_bounds__(kBlock) void k_tilesum(Launch L) {
   __shared__ unsigned long long s_sum[HG_MAX_K];

@@ -500,7 +500,8 @@ __global__ void k_copy_best(const long long* best, int* best_len, long long* bes
 
 // ------------------------------------------------------------ rebalancing
 // One synchronous rebalancing round (section "Rebalancing"): vertices of
-// overloaded blocks pick their best feasible target from a gain cache; a
+// overloaded blocks pick their best feasible target, light ones by the select's
+// counters, heavy ones from penalty rows filled for them alone; a
 // stable sort orders the candidates by (gain desc, id asc), a second stable
 // pass groups them by source block, and a segmented scan proposes, per
 // source, the shortest prefix whose weight reaches the block's excess; the
@@ -508,7 +509,7 @@ __global__ void k_copy_best(const long long* best, int* best_len, long long* bes
 // prefix per target that fits under L_max, and applied.
 
 struct Rb {
-  const int* cache;            // gain cache of the round-start partition
+  const int* cache;            // penalty rows of the heavy vertices of overloaded blocks
   long long* excess;           // [k]: c(V_i) - L_max
   int* cnt_src;                // [k + 1]: candidates per source (sentinel k last)
   int* cnt_tgt;                // [k + 1]: proposals per target

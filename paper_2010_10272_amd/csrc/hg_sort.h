@@ -47,9 +47,9 @@ struct SortPass {
   // Marks mode (the first pass of a monotone round's move order and of a rebalancing
   // round's): item i is vertex i, present only where marks[i] != 0, with key
   // top - gain(cand[i]) and value i.  Gains are at most top; the rebalancer's may be
-  // negative, down to -top, so its keys reach 2 * top.  The scatter clears the marks it reads and workgroup 0
-  // stores the number of present items in *count_out.  key_in / val_in are
-  // not read.
+  // negative, down to -top, so its keys reach 2 * top.  The scatter clears the marks
+  // it reads and workgroup 0 stores the number of present items in *count_out.
+  // key_in / val_in are not read.
   unsigned char* marks = nullptr;
   const long long* cand = nullptr;
   unsigned top = 0;
@@ -92,7 +92,7 @@ __device__ __forceinline__ void sort_load(const SortPass& P, int n, long long ba
 #pragma unroll
     for (int r = 0; r < PER; ++r) {
       live[r] = mk[r] != 0;
-      key[r] = P.top - (unsigned)(int)(x[r] >> 32);   // the gain, at most top
+      key[r] = P.top - (unsigned)(int)(x[r] >> 32);   // 0 .. 2 * top
       if (want_val) val[r] = (int)sort_item<PER>(base, r);
     }
     return;

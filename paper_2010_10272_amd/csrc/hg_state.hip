@@ -6,7 +6,8 @@
 // net.  Here a wavefront owns 64 consecutive nets at a time: their pins are one
 // run of the pin array, counted 64 at a time into byte counters in LDS; then
 // each lane builds its net's bitsets from its counters, and the rows leave as
-// whole lines.  No global atomics touch Phi, so the result is deterministic by
+// whole lines.  Nets of 64 pins and more on average get eight lanes each, nets of
+// more than kWaveNet pins a workgroup.  No global atomics touch Phi, so the result is deterministic by
 // construction.
 #include <climits>
 
@@ -44,9 +45,8 @@ __device__ __forceinline__ WorkItem contiguous_units(long long units) {
 // slots each) left two thirds of the gather slots empty on nets of ten pins and
 // half the lanes idle; here every lane has a pin.  (Four consecutive pins per
 // lane need a third fewer operations, but their gathers touch more lines at a
-// time: netlist 370 -> 404 us.)  Per call, before and now: netlist 56.5M pins,
-// k = 16 523 -> 348 us (gathers 135 of them, Phi stores 65), matrix 10M pins
-// k = 8 82 -> 43, k = 64 128 -> 74.
+// time: netlist 370 -> 404 us.)  Per launch, lane groups and now: netlist 56.5M pins,
+// k = 16 523 -> 305 us, matrix 10M pins k = 8 82 -> 38, k = 64 128 -> 62.
 template <int WK>
 __global__ __launch_bounds__(kBlock) void k_pincounts(Launch L) {
   extern __shared__ unsigned s_count[];   // count_words per wavefront
