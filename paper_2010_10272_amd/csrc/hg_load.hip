@@ -246,9 +246,9 @@ static SortPass first_load_pass(hg_graph_s* g) {
 // their output by one global atomic per bucket and tile.  Rows are sets
 // sorted by net id, so nothing depends on the order of arrival.
 // Measured (all kernels of one load, radix passes and now): netlist 4M cells, 56.5M
-// pins 1420 -> 695 us (count 78, coarse split 199, fine split 207, rows 132, checks
-// and facts 70; the 2.1 GB they move take 410 us at a large copy's 5.1 TB/s), matrix
-// 1M x 1M, 10M pins 287 -> 152 us.
+// pins 1420 -> 590 to 695 us (count 64 to 78, coarse split 155 to 199, fine split 169
+// to 207, rows 130, checks and facts 70; the 2.1 GB they move take 410 us at a large
+// copy's 5.1 TB/s), matrix 1M x 1M, 10M pins 287 -> 152 us.
 
 constexpr int kPartBlock = 1024;                       // threads of the split kernels
 constexpr int kPartPer = kPartTile / kPartBlock;       // pins per thread and tile

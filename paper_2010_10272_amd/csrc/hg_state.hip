@@ -46,7 +46,8 @@ __device__ __forceinline__ WorkItem contiguous_units(long long units) {
 // half the lanes idle; here every lane has a pin.  (Four consecutive pins per
 // lane need a third fewer operations, but their gathers touch more lines at a
 // time: netlist 370 -> 404 us.)  Per launch, lane groups and now: netlist 56.5M pins,
-// k = 16 523 -> 305 us, matrix 10M pins k = 8 82 -> 38, k = 64 128 -> 62.
+// k = 16 523 -> 306 us, matrix 10M pins k = 8 82 -> 43 (38 repeated, 51 after other
+// work), k = 64 128 -> 71 (61, 90).
 template <int WK>
 __global__ __launch_bounds__(kBlock) void k_pincounts(Launch L) {
   extern __shared__ unsigned s_count[];   // count_words per wavefront
