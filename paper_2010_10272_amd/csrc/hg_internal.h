@@ -89,16 +89,18 @@ struct Threshold {
 // Rounds of one small graph leave out two launches that have next to nothing to
 // do: every tile-sum workgroup finds the thresholds of all k blocks itself, every
 // approve workgroup scans their tile sums (one wavefront covers kBriefTiles in one
-// step).  Both grow with n and k, the launches do not.  Refinements of five rounds,
-// us, with the launches and without: n = 1,000 k = 2 158 / 137, k = 16 173 / 163;
-// n = 65,536 k = 2 173 / 162, k = 16 188 / 186; n = 98,304 k = 2 180 / 179, k = 8
-// 192 / 188, k = 16 197 / 201; but n = 131,072 k = 2 190 / 189, k = 8 200 / 207,
-// k = 16 206 / 221.  Heavy vertices need the separate threshold (k_overflow_resolve).
+// step).  Both grow with n and k, the launches do not.  Five rounds, us, with the
+// launches and without: a recorded refinement of n = 65,536 k = 2 180 / 167, k = 16 194
+// / 191; n = 98,304 k = 8 199 / 194, k = 16 205 / 207; n = 131,072 k = 2 199 / 197,
+// k = 8 210 / 212, but k = 16 214 / 226; single rounds, which the host launches,
+// n = 131,072 k = 2 237 / 223, k = 8 243 / 237, k = 16 247 / 248.  Heavy vertices need
+// the separate threshold (k_overflow_resolve).
 constexpr int kBriefTiles = 256;
-constexpr int kBriefMaxN = 98304, kBriefMaxK = 16;
-static_assert(kBriefMaxN <= kBriefTiles * kTile, "one step");
+constexpr int kBriefMaxK = 16;
+inline int brief_max_n(int k) { return k <= 8 ? 131072 : k <= kBriefMaxK ? 98304 : 0; }
+static_assert(131072 <= kBriefTiles * kTile, "one step");
 inline bool brief_rounds(int n, int k, int heavy_count) {
-  return n <= kBriefMaxN && k <= kBriefMaxK && heavy_count == 0;
+  return n <= brief_max_n(k) && heavy_count == 0;
 }
 
 // Facts gathered at load time (device side, copied to the host once).

@@ -40,3 +40,9 @@ def test_brief_rounds_equal_batched_rounds(H, n, k, unit, eps):
 @pytest.mark.parametrize("k", [2, 16])
 def test_largest_brief_rounds_equal_batched_rounds(H, n, k):
     test_brief_rounds_equal_batched_rounds(H, n, k, False, 0.01)
+
+
+@pytest.mark.parametrize("n", [131072, 131073])
+@pytest.mark.parametrize("k", [8, 9])
+def test_edge_of_block_counts_equals_batched_rounds(H, n, k):
+    test_brief_rounds_equal_batched_rounds(H, n, k, True, 0.01)
