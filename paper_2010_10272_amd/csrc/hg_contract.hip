@@ -60,7 +60,7 @@ struct Ct {
   int* big_count;        // [1]
   int* nsize;            // [m]: pins after deduplication
   unsigned long long* fp;// [m]
-  int unit;              // nets per wavefront and turn (ct_unit)
+  int unit, emit_unit;   // nets per wavefront and turn: sorting, writing (ct_unit)
   int key_bits;          // 8 bits per sorting pass
   unsigned* nkey[2];     // [m]
   int* nval[2];          // [m]
@@ -138,7 +138,7 @@ __device__ __forceinline__ void ct_net_done(const Ct& C, long long e, int size,
 
 // Consecutive nets per wavefront and turn: 64, fewer where that leaves the chip idle
 // and each still has 512 pins.  (Contraction of 10,000 nets of 128 pins, us, 64 a
-// wavefront 532, so 147; 30,000 of 100 414, 171; 2,000 of 1,500 557, 221.)
+// wavefront 532, so 148; 30,000 of 100 414, 172; 2,000 of 1,500 557, 200.)
 int ct_unit(long long m, long long P) {
   int nets = kWave;
   while (nets > 1 && m < 8192LL * nets && nets / 2 * P >= 512 * m) nets >>= 1;
@@ -155,7 +155,9 @@ int ct_unit(long long m, long long P) {
 //      place, so the places left empty are the duplicates'.
 //   3. lane = place: the distinct pins leave side by side; prefix sums give
 //      sizes and fingerprints.
-// Long nets are listed for k_ct_big_nets, 64 at a time (one atomic each).
+// Long nets are listed for k_ct_big_nets, 64 at a time, the last ones of a workgroup
+// together (one atomic each: one per wavefront, at 12 ns, took 59 us for 10,000 nets of
+// 256, two a wavefront).
 // What bounds it: the comparisons (a pin's net has 27 pins on average on the
 // sparse matrix, whose nets have 10) and the gathers of the map.  Workgroups that
 // went through a tile of 1,024 pins together, with a dozen barriers, binary
@@ -165,8 +167,8 @@ constexpr int kCtCap = 832;          // LDS places of a wavefront
 constexpr int kCtFlight = 4;
 constexpr int kCtGrid = 2048;        // persistent workgroups
 constexpr int kCtBigGrid = 1024;     // as many as reside (a little over kNetLdsCap words each:
-                                     // four a compute unit; 1280 left 256 for a second
-                                     // turn: 10,000 nets of 300 382 us, 322 so)
+                                     // four a compute unit; with 1280, 256 had to wait for a
+                                     // turn of their own)
 constexpr int kCtLongEmit = 2048;    // longer nets leave by a workgroup each
 
 struct alignas(16) CtLds {             // val is read four at a time
@@ -191,6 +193,7 @@ __device__ __forceinline__ void ct_flush_big(const Ct& C, CtLds& M, int count) {
 
 __global__ __launch_bounds__(kBlock) void k_ct_small_nets(Ct C) {
   __shared__ CtLds s_lds[kBlock / kWave];
+  __shared__ int s_big[kBlock / kWave], s_at;
   const int lane = lane_id(), wv = threadIdx.x / kWave;
   CtLds& M = s_lds[wv];
   constexpr int kEmpty = -1, kAbove = 0x7fffffff;
@@ -319,7 +322,19 @@ __global__ __launch_bounds__(kBlock) void k_ct_small_nets(Ct C) {
       wave_lds_sync();
     }
   }
-  if (big) ct_flush_big(C, M, big);
+  if (lane == 0) s_big[wv] = big;
+  __syncthreads();
+  if (threadIdx.x == 0) {
+    int all = 0;
+    for (int w = 0; w < kBlock / kWave; ++w) {
+      const int n = s_big[w];
+      s_big[w] = all;
+      all += n;
+    }
+    s_at = all ? (int)atomicAdd((unsigned*)C.big_count, (unsigned)all) : 0;
+  }
+  __syncthreads();
+  if (lane < big) C.big[s_at + s_big[wv] + lane] = M.big[lane];
 }
 
 // One workgroup per listed net (workgroups stride over the list).  Up to kBlock
@@ -479,8 +494,8 @@ __global__ __launch_bounds__(kBlock) void k_ct_emit(Ct C) {
   const int lane = lane_id(), wv = threadIdx.x / kWave;
   unsigned char* flag = s_flag[wv];
   for (int i = lane; i < kCtFlight * kWave; i += kWave) flag[i] = 0;
-  const long long e = ((long long)blockIdx.x * (kBlock / kWave) + wv) * C.unit + lane;
-  const bool kept = lane < C.unit && e < C.m && C.rep[e] == e;
+  const long long e = ((long long)blockIdx.x * (kBlock / kWave) + wv) * C.emit_unit + lane;
+  const bool kept = lane < C.emit_unit && e < C.m && C.rep[e] == e;
   long long pos = 0;
   int len = 0;
   if (kept) {
@@ -659,8 +674,11 @@ static hipError_t launch_contract(hg_graph_s* g, const int* cluster, int* map, i
   hipLaunchKernelGGL(k_ct_vweights, dim3(blocks_of(n)), dim3(kBlock), 0, s, C);
 
   // 3-4. per net: mapped, sorted, deduplicated pins, size, fingerprint
-  C.unit = ct_unit(m, g->P);
+  const long long small_pins = (long long)kSmallNet * m;   // at most: longer nets are listed
+  C.unit = ct_unit(m, g->P < small_pins ? g->P : small_pins);
+  C.emit_unit = ct_unit(m, g->P);
   const unsigned units = (unsigned)units_of(m, C.unit * (kBlock / kWave));
+  const unsigned emits = (unsigned)units_of(m, C.emit_unit * (kBlock / kWave));
   const unsigned sg = units < kCtGrid ? units : kCtGrid;
   hipLaunchKernelGGL(k_ct_small_nets, dim3(sg), dim3(kBlock), 0, s, C);
   hipLaunchKernelGGL(k_ct_big_nets, dim3(kCtBigGrid), dim3(kBlock), 0, s, C);
@@ -689,7 +707,7 @@ static hipError_t launch_contract(hg_graph_s* g, const int* cluster, int* map, i
   // 6. coarse net CSR in representative order
   exclusive_scan(KeptF{C.rep}, m, C.nid, &sizes[1], B, s);
   exclusive_scan(KeptSizeF{C.rep, C.nsize}, m, C.npos, &sizes[2], B, s);
-  hipLaunchKernelGGL(k_ct_emit, dim3(units), dim3(kBlock), 0, s, C);
+  hipLaunchKernelGGL(k_ct_emit, dim3(emits), dim3(kBlock), 0, s, C);
   if (g->info.max_net_size > kCtLongEmit)
     hipLaunchKernelGGL(k_ct_emit_long, dim3(kCtBigGrid), dim3(kBlock), 0, s, C);
   hipLaunchKernelGGL(k_ct_close, dim3(1), dim3(kWave), 0, s, C);

@@ -82,3 +82,35 @@ def test_time_of_longer_nets(H, size, m):
             best = min(best, ev[0].elapsed_time(ev[1]))
         ms.append(best)
     assert ms[0] < 1.5 * ms[1], ms
+
+
+@pytest.mark.parametrize("m,sizes", [(1, [129]), (5, [130, 200]), (257, [129]),
+                                     (4099, [129, 3, 140]), (8200, [131])])
+def test_edges_of_listed_nets(H, m, sizes):
+    """Long nets only, or nearly so: few of them a wavefront, listed by workgroups."""
+    test_edges_of_long_nets_and_units(H, m, sizes)
+
+
+def test_time_of_listed_nets(H):
+    """10,000 nets of 256 pins, a workgroup each, in half as much again as nets of 128:
+    twice the pins, in a call half of which is launches.  (Listed by an atomic per
+    wavefront of four nets they took 1.7 times as long.)"""
+    import torch
+    n, m, ms = 100_000, 10_000, []
+    for size in (256, 128):
+        rng = np.random.default_rng(size)
+        pins = (rng.integers(0, n, m)[:, None] + 331 * np.arange(size)[None, :]) % n
+        g = H.hg_load_csr(n, size * np.arange(m + 1, dtype=np.int64),
+                          pins.astype(np.int32).ravel(), k_max=2)
+        out, ws = H.Coarse(g), H.contract_workspace(g)
+        cl = torch.arange(n, device="cuda", dtype=torch.int32) // 2 * 2
+        best = float("inf")
+        for _ in range(8):
+            ev = [torch.cuda.Event(enable_timing=True) for _ in range(2)]
+            ev[0].record()
+            H.hg_contract(g, cl, out, ws)
+            ev[1].record()
+            ev[1].synchronize()
+            best = min(best, ev[0].elapsed_time(ev[1]))
+        ms.append(best)
+    assert ms[0] < 1.5 * ms[1], ms
