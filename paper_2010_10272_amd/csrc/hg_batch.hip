@@ -118,12 +118,12 @@ size_t table_bound(const std::vector<BatchMember>& mem, const std::vector<int>& 
       items += tiles;                                                // tile sums
       items += tiles + x.k;                                          // approve
       items += ceil_div(g->m, kFinalChunk);                          // finalize
-      items += long_pieces((int)g->info.long_count);                      // of long nets
+      items += long_pieces((int)g->info.long_count);                 // of long nets
       items += 1;                                                    // per member
     }
     if (counts) {
       items += ceil_div(g->m, kBlock);                               // pin counts
-      items += long_pieces((int)g->info.long_count);                      // of long nets
+      items += long_pieces((int)g->info.long_count);                 // of long nets
       items += ceil_div(g->n, kBwChunk);                             // block weights
       items += 1;                                                    // per member
     }
